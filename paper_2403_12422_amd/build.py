@@ -1,14 +1,16 @@
-"""Compile the HIP sources of this package into ``libjetfire.so`` (gfx950 only)."""
+"""Compile the HIP sources of this package into ``libjetfire.so`` (gfx950 only), and the Python extension that calls it."""
 import concurrent.futures
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libjetfire.so")
+EXT = os.path.join(HERE, "_native.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC_FLAGS = [
@@ -30,9 +32,27 @@ def _run(cmd, verbose):
     # the host pass warns that it does not know the packed-fp32 feature; that line is noise
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("build step failed: " + cmd[0] + "\n" + out)
     if verbose and out.strip():
         print(out)
+
+
+def _extension_commands():
+    """The host-only CPython extension (csrc/jf_python.cpp): compiled by the host compiler against torch's headers, linked
+    to the library beside it: the compile and the link command."""
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    inc, lib = os.path.join(root, "include"), os.path.join(root, "lib")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    obj = os.path.join(OBJ_DIR, "jf_python.o")
+    compile_ = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-I", INCLUDE, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"), "-Wall",
+           "-c", os.path.join(CSRC, "jf_python.cpp"), "-o", obj]
+    link = [os.environ.get("CXX", "g++"), "-shared", "-fPIC", obj, "-o", EXT, "-L", HERE, "-ljetfire", "-L", lib, "-lc10",
+           "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    return compile_, link
 
 
 def build(verbose: bool = False, jobs: int = 0) -> str:
@@ -48,9 +68,12 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
             obj = os.path.join(OBJ_DIR, os.path.basename(src)[:-4] + ".o")
             objs.append(obj)
             futures.append(pool.submit(_run, [hipcc, *HIPCC_FLAGS, "-I", INCLUDE, "-I", CSRC, "-c", src, "-o", obj], verbose))
+        ext_compile, ext_link = _extension_commands()
+        futures.append(pool.submit(_run, ext_compile, verbose))
         for f in futures:
             f.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
+    _run(ext_link, verbose)
     return LIB
 
 
