@@ -73,8 +73,6 @@ struct TileLayout {
   static constexpr int bytes(int nw) { return ((kSlots + 64 * nw - 1) / (64 * nw)) * (64 * nw) * 16; }
 };
 
-typedef __attribute__((address_space(3))) void* lds_ptr;
-typedef const __attribute__((address_space(1))) void* gbl_ptr;
 typedef __attribute__((address_space(3))) v2i* lds_v2i;
 typedef __attribute__((address_space(3))) v4i* lds_v4i;
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -116,36 +114,6 @@ struct FragAddr {
     }
   }
 };
-
-// One direct-to-LDS load of 16 bytes per lane: lane l's bytes from ubase + voff go to LDS address lds + 16*l.
-// Written out because the compiler only selects the 64-bit per-lane address form for the builtin; the form with
-// a scalar base and a 32-bit vector offset needs no address arithmetic on the vector ALU.  M0 carries the LDS
-// address and needs one wait state before the load reads it.  The load counts in vmcnt like any other; the
-// callers wait for it with s_waitcnt before the stage barrier.
-// Every direct-to-LDS load of the kernel goes through these two helpers, so the compiler itself never uses M0.
-__device__ __forceinline__ uint32_t lds_address(const int8_t* lds_tile, int lds_byte) {
-  // the tile's LDS address is taken before the byte offset is added: a cast of the sum would carry a null check
-  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr)(lds_tile) + (uint32_t)lds_byte);
-}
-__device__ __forceinline__ void load_lds_16(const int8_t* ubase, uint32_t voff, const int8_t* lds_tile, int lds_byte) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(voff), "s"(ubase), "s"(lds_address(lds_tile, lds_byte))
-               : "memory", "m0");
-}
-// the same with a full 64-bit address per lane (the clamped last stage of a K that is not a multiple of the stage)
-__device__ __forceinline__ void load_lds_16_vaddr(const int8_t* vaddr, const int8_t* lds_tile, int lds_byte) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(vaddr), "s"(lds_address(lds_tile, lds_byte))
-               : "memory", "m0");
-}
-// A pointer that is the same for all lanes, moved to scalar registers for good.
-__device__ __forceinline__ const int8_t* uniform_pointer(const int8_t* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const int8_t*)(((uint64_t)hi << 32) | lo);
-}
 
 // Global byte offset of the chunk that belongs in LDS slot `slot_idx` of a stage starting at K offset k0.
 // Out-of-range rows / columns / K are clamped to valid addresses: what they deliver only reaches

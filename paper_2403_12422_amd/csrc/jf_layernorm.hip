@@ -1,29 +1,17 @@
 // INT8-in / INT8-out LayerNorm, forward and backward (App. A).
 //
-// Each pass is a small kernel that only leaves sums (row statistics forward; row means and dgamma | dbeta partial rows
-// backward) followed by an element-wise operator on tiles: the 32 x 128 strips of jf_rowops.hpp at block size 32, workgroups
-// of B rows x 128 columns at block sizes 64 and 128.  No workgroup holds a row in registers, so rows may be of any width.
+// Rows of at most 2048 columns at block size 32 go through jf_layernorm_rows.hip.  Otherwise each pass is a small kernel
+// that only leaves sums (row statistics forward; row means and dgamma | dbeta partial rows backward) followed by an
+// element-wise operator on tiles: the 32 x 128 strips of jf_rowops.hpp at block size 32, workgroups of B rows x 128
+// columns at block sizes 64 and 128.  No workgroup holds a row in registers, so rows may be of any width.
 // Row sums of the forward pass come from exact integer dot products of the codes (v_dot4), scaled per block -- the
 // row-partials scheme of App. A applied to the INT8 input itself -- or from the partials that the preceding Add wrote.
 #include <algorithm>
 #include <mutex>
 
-#include "jf_rowops.hpp"
+#include "jf_layernorm.hpp"
 
 namespace jf {
-
-// ------------------------------------------------------------------------------------------------
-// exact sums of the 16 codes of a chunk and of their squares
-__device__ __forceinline__ void chunk_moments(const uint4& p, int& s1, int& s2) {
-  s1 = __builtin_amdgcn_sdot4((int)p.x, 0x01010101, 0, false);
-  s1 = __builtin_amdgcn_sdot4((int)p.y, 0x01010101, s1, false);
-  s1 = __builtin_amdgcn_sdot4((int)p.z, 0x01010101, s1, false);
-  s1 = __builtin_amdgcn_sdot4((int)p.w, 0x01010101, s1, false);
-  s2 = __builtin_amdgcn_sdot4((int)p.x, (int)p.x, 0, false);
-  s2 = __builtin_amdgcn_sdot4((int)p.y, (int)p.y, s2, false);
-  s2 = __builtin_amdgcn_sdot4((int)p.z, (int)p.z, s2, false);
-  s2 = __builtin_amdgcn_sdot4((int)p.w, (int)p.w, s2, false);
-}
 
 // ------------------------------------------------------------------------------------------------
 // Where whole rows are needed a workgroup owns 32 of them (at every block size: a block row is one, two or four such
@@ -480,6 +468,13 @@ static int32_t layernorm_fwd(const int8_t* X, const float* SX, const float* row_
   if (!gamma || !beta || !mean || !rstd) return JF_ERR_NULL;
   if (!aligned16(gamma) || !aligned16(beta) || !aligned4(mean) || !aligned4(rstd)) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  if (layernorm_rows_fits(C, block)) {   // one pass over the operands
+    LayerNormRows a{};
+    a.X = X; a.SX = SX; a.row_mean = row_mean; a.row_sumsq = row_sumsq; a.gamma = gamma; a.beta = beta; a.eps = eps;
+    a.rows = (int)N; a.cols = (int)C; a.Y = Y; a.SY = SY; a.mean = mean; a.rstd = rstd;
+    launch_layernorm_rows(a, st);
+    return launch_status();
+  }
   if (row_mean != nullptr) {
     const int waves = (int)std::min<int64_t>(16, std::max<int64_t>(4, C / block / 4));
     hipLaunchKernelGGL(row_stats_from_partials_kernel, dim3((unsigned)((N + 63) / 64)), dim3(64 * waves), 0, st, row_mean, row_sumsq,
@@ -527,7 +522,17 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
                                     int32_t block, int8_t* dX, float* SdX, float* dgamma, float* dbeta, float* partials,
                                     hipStream_t st) {
   using namespace jf;
-  const int nparts = (int)ln_bwd_partial_rows(N);
+  int nparts = (int)ln_bwd_partial_rows(N);
+  if (layernorm_rows_fits(C, block)) {   // one pass over the operands
+    LayerNormBwdRows a{};
+    a.G = dY; a.SG = SdY; a.X = X; a.SX = SX; a.gamma = gamma; a.mean = mean; a.rstd = rstd; a.rows = (int)N; a.cols = (int)C;
+    a.dX = dX; a.SdX = SdX; a.partials = partials;
+    nparts = launch_layernorm_bwd_rows(a, st);
+    const int32_t rc = launch_status();
+    if (rc != JF_OK) return rc;
+    hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((2 * C + 63) / 64)), dim3(1024), 0, st, partials, nparts, (int)(2 * C), dgamma, dbeta);
+    return launch_status();
+  }
   // the workspace holds the partial rows, then the two row means of every row (per range of 2048 columns)
   float* row_means = partials + (size_t)nparts * 2 * (size_t)C;
   const int ranges = (int)((C + 2047) / 2048);

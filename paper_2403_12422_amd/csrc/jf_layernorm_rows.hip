@@ -1,0 +1,477 @@
+// LayerNorm at block size 32 in one pass over the operands (App. A): each code is read once and written once.
+//
+// Bound by HBM: 2 bytes per element forward, 3 backward.  What a row needs as a whole (its moments; backward, the two row
+// means) makes an operator on tiles read its operands twice; here a workgroup owns 32 whole rows, one wave per strip of
+// 32 x 128 (Strip32's lane mapping), so the strip's codes stay in registers while the row sums go over the waves through
+// LDS.  What made that slow before was that a workgroup in its arithmetic had nothing in flight.  Now workgroups are
+// persistent and a wave requests the strip of its NEXT row group with direct-to-LDS loads as soon as it has moved the
+// current one from LDS to registers: 4 KB (8 KB backward) per wave are in flight through all of the arithmetic, without
+// registers to land in.
+//
+// Order of a wave's memory operations, per row group: codes LDS -> registers; request the next group into the same LDS;
+// sums, workgroup barrier, results; wait for ALL its loads; only then store the results.  The wait therefore never
+// includes the stores just made (loads and stores count in one counter and may finish out of order), only those of the
+// previous group, which are long done.
+//
+// 1 M x 768: forward 446 -> 313 us (5.2 TB/s), backward 784 -> 560 us (4.3 TB/s; the vector ALU issues in 92 % of the
+// cycles: 20 instructions per element) against the two-kernel scheme of jf_layernorm.hip, which
+// stays for block sizes 64 and 128 and for rows of more than 16 strips, which a compute unit's registers (128 per lane:
+// 16 waves) do not hold.
+#include <algorithm>
+
+#include "jf_layernorm.hpp"
+
+namespace jf {
+
+// s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8
+__device__ __forceinline__ void wait_all_loads() {
+  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds() {
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
+  asm volatile("" ::: "memory");
+}
+// LDS writes of all waves before, LDS reads after; global loads stay in flight (unlike __syncthreads)
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
+  asm volatile("s_barrier" ::: "memory");
+}
+// a wave's own LDS writes before its own reads
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <class T>
+__device__ __forceinline__ void store_global(int8_t* uniform_base, uint32_t off, T v) {
+  typedef __attribute__((address_space(1))) int8_t* gbl_ptr;
+  *(__attribute__((address_space(1))) T*)((gbl_ptr)uniform_base + off) = v;
+}
+
+// Signed codes of one packed dword as floats (a byte-select conversion each).
+__device__ __forceinline__ void unpack4(uint32_t w, float (&c)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) c[k] = (float)(int)(int8_t)(w >> (8 * k));
+}
+__device__ __forceinline__ uint32_t dword_of(const uint4& v, int d) { return d == 0 ? v.x : (d == 1 ? v.y : (d == 2 ? v.z : v.w)); }
+
+// A wave's place: workgroups hold `teams` teams of `strips` waves; a team owns a group of 32 rows.
+struct RowWave {
+  int lane, ch, rsub, wave, waves, team, strip;
+  int c0, col;   // first column of the strip, of the lane's chunks (lanes outside the matrix: the strip's first chunk)
+  bool ok;       // the lane's chunks lie inside the matrix
+  __device__ __forceinline__ RowWave(int cols, int strips) {
+    lane = threadIdx.x & 63;
+    ch = lane & 7;
+    rsub = lane >> 3;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    waves = blockDim.x >> 6;
+    team = wave / strips;
+    strip = wave - team * strips;
+    c0 = strip * 128;
+    ok = c0 + 16 * ch < cols;
+    col = ok ? c0 + 16 * ch : c0;
+  }
+};
+
+// LDS of a forward wave: codes, block scales, row partials of the Add, gamma, beta, the rows' mean and rstd
+constexpr int kFwdScale = 4096, kFwdPart = kFwdScale + 256, kFwdGamma = kFwdPart + 1024, kFwdBeta = kFwdGamma + 512,
+              kFwdStat = kFwdBeta + 512, kFwdWaveBytes = kFwdStat + 256;
+constexpr int kFwdRowBytes = 2 * 32 * 16;   // per wave: two copies (alternate row groups) of a sum pair for each of 32 rows
+
+template <bool PARTIALS>
+__global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRows a) {
+  extern __shared__ __align__(16) int8_t smem[];
+  const RowWave t(a.cols, a.strips);
+  double* const s_row = reinterpret_cast<double*>(smem);                       // [copy][wave][row][sum]
+  int8_t* const own = smem + t.waves * kFwdRowBytes + t.wave * kFwdWaveBytes;
+  const int groups = a.rows / 32, lc = a.cols / 32;
+  const uint32_t off = (uint32_t)(t.rsub * a.cols + t.col), off_scale = (uint32_t)(t.col / 32) * 4;
+
+  auto request = [&](int g) __attribute__((always_inline)) {
+    const int8_t* const x = uniform_pointer(a.X + (int64_t)g * 32 * a.cols);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) load_lds_16(x + (int64_t)p * 8 * a.cols, off, own, 1024 * p);
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)g * lc)), off_scale, own, kFwdScale);
+    if (PARTIALS) {   // the strip's four block columns x 32 rows of both partials
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int64_t o = (int64_t)min(4 * t.strip + 2 * i + (t.lane >> 5), lc - 1) * a.rows + g * 32 + (t.lane & 31);
+        load_lds_4_vaddr(a.row_mean + o, own, kFwdPart + 256 * i);
+        load_lds_4_vaddr(a.row_sumsq + o, own, kFwdPart + 512 + 256 * i);
+      }
+    }
+  };
+
+  int first = blockIdx.x * a.teams;                    // first row group of the workgroup's teams
+  const int stride = gridDim.x * a.teams;
+  request(min(first + t.team, groups - 1));
+  float* const s_gamma = reinterpret_cast<float*>(own + kFwdGamma);
+  float* const s_beta = reinterpret_cast<float*>(own + kFwdBeta);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = t.c0 + t.lane + 64 * i;
+    s_gamma[t.lane + 64 * i] = c < a.cols ? a.gamma[c] : 0.0f;
+    s_beta[t.lane + 64 * i] = c < a.cols ? a.beta[c] : 0.0f;
+  }
+  wait_all_loads();
+  wave_lds_fence();
+
+  int copy = 0;
+  for (; first < groups; first += stride, copy ^= 1) {
+    const int g = first + t.team;                      // past the last group: a repeat of it that stores nothing
+    uint4 px[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) px[p] = *reinterpret_cast<const uint4*>(own + 1024 * p + 16 * t.lane);
+    const float sx = *reinterpret_cast<const float*>(own + kFwdScale + 4 * t.lane);
+    double* const row = s_row + ((copy * t.waves + t.wave) * 32) * 2;
+    if (PARTIALS) {
+      const float* part = reinterpret_cast<const float*>(own + kFwdPart) + 128 * (t.lane >> 5) + (t.lane & 31);
+      double v = 0.0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v += 4 * t.strip + j < lc ? (double)part[32 * j] : 0.0;
+      row[2 * (t.lane & 31) + (t.lane >> 5)] = v;
+    }
+    wait_lds();                                        // the strip is in registers: its LDS may be filled again
+    if (first + stride < groups) request(min(g + stride, groups - 1));
+    if (!PARTIALS) {
+      // exact integer moments of the chunk, of the block's two chunks, then in double over the strip's four blocks
+      const double sd = t.ok ? (double)sx : 0.0, sd2 = sd * sd;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        int s1, s2;
+        chunk_moments(px[p], s1, s2);
+        s1 += lane_xor_i32<0>(s1);
+        s2 += lane_xor_i32<0>(s2);
+        double s = sd * (double)s1, q = sd2 * (double)s2;
+        s += lane_xor_f64<1>(s);
+        q += lane_xor_f64<1>(q);
+        s += lane_xor_f64<2>(s);
+        q += lane_xor_f64<2>(q);
+        if (t.ch == 0) *reinterpret_cast<double2*>(row + 2 * (t.rsub + 8 * p)) = make_double2(s, q);
+      }
+    }
+    lds_barrier();
+    // Every wave finishes the sums of its team's 32 rows: lanes 0..31 the first sum of row lane, lanes 32..63 the second
+    {
+      const double* v = s_row + ((copy * t.waves + t.team * a.strips) * 32 + (t.lane & 31)) * 2 + (t.lane >> 5);
+      double sum = 0.0;
+      for (int w = 0; w < a.strips; ++w) sum += v[64 * w];
+      const double other = lane_xor_f64<5>(sum);
+      const double mud = (t.lane < 32 ? sum : other) * (PARTIALS ? a.inv_blocks : a.inv_cols);
+      const float var = fmaxf((float)((t.lane < 32 ? other : sum) * a.inv_cols - mud * mud), 0.0f);
+      const float ve = var + a.eps;
+      float rs = __builtin_amdgcn_rsqf(ve);            // refined by one Newton step (relative error about 1e-7)
+      rs = rs * __builtin_fmaf(-0.5f * ve * rs, rs, 1.5f);
+      if (t.lane < 32) reinterpret_cast<float2*>(own + kFwdStat)[t.lane] = make_float2((float)mud, rs);
+      wave_lds_fence();
+      if (t.strip == 0 && t.lane < 32 && g < groups) {
+        // (stores: counted with the loads, hence before the wait below, not before the next group's)
+        a.mean[g * 32 + t.lane] = (float)mud;
+        a.rstd[g * 32 + t.lane] = rs;
+      }
+    }
+    float k1[4], kb[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const float2 st = reinterpret_cast<const float2*>(own + kFwdStat)[t.rsub + 8 * p];
+      k1[p] = sx * st.y;
+      kb[p] = __builtin_fmaf(-128.0f, k1[p], -st.x * st.y);
+    }
+    float y[4][16];
+    float m = 0.0f;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {                      // four columns at a time: gamma and beta come out of LDS
+      const float4 gm = *reinterpret_cast<const float4*>(s_gamma + 16 * t.ch + 4 * d), bt = *reinterpret_cast<const float4*>(s_beta + 16 * t.ch + 4 * d);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const uint32_t w = dword_of(px[p], d) ^ 0x80808080u;   // code + 128 per byte
+        y[p][4 * d + 0] = __builtin_fmaf(__builtin_fmaf((float)(w & 0xffu), k1[p], kb[p]), gm.x, bt.x);
+        y[p][4 * d + 1] = __builtin_fmaf(__builtin_fmaf((float)((w >> 8) & 0xffu), k1[p], kb[p]), gm.y, bt.y);
+        y[p][4 * d + 2] = __builtin_fmaf(__builtin_fmaf((float)((w >> 16) & 0xffu), k1[p], kb[p]), gm.z, bt.z);
+        y[p][4 * d + 3] = __builtin_fmaf(__builtin_fmaf((float)(w >> 24), k1[p], kb[p]), gm.w, bt.w);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) m = amax16(m, y[p]);
+    float scale;
+    double inv;
+    strip32_block_scale(m, scale, inv);
+    uint4 o[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      o[p] = quantize16(y[p], inv);
+      asm volatile("" : "+v"(o[p].x), "+v"(o[p].y), "+v"(o[p].z), "+v"(o[p].w));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wait_all_loads();
+    if (t.ok && g < groups) {
+      // uniform base + 32-bit lane offset, like the loads: no 64-bit lane addresses to keep
+      int8_t* const out = uniform_pointer(a.Y + (int64_t)g * 32 * a.cols);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) store_global(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
+      if ((t.lane & 57) == 0) store_global(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)), off_scale, scale);
+    }
+  }
+}
+
+// LDS of a backward wave: codes of x and of g, their block scales, mean and rstd of the 32 rows, gamma, the two row means
+constexpr int kBwdG = 4096, kBwdScaleX = 8192, kBwdScaleG = kBwdScaleX + 256, kBwdMean = kBwdScaleG + 256, kBwdRstd = kBwdMean + 128,
+              kBwdGamma = kBwdRstd + 128, kBwdMeans = kBwdGamma + 512, kBwdWaveBytes = kBwdMeans + 256;
+constexpr int kBwdRowBytes = 2 * 32 * 8;
+
+// dx = rstd (ghat - mean_C(ghat) - xhat mean_C(ghat xhat)) with ghat = g gamma, xhat = (x - mean) rstd; the column sums
+// of g xhat and g stay in registers over all row groups and end as one partial row of dgamma | dbeta per workgroup.
+__global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNormBwdRows a) {
+  extern __shared__ __align__(16) int8_t smem[];
+  const RowWave t(a.cols, a.strips);
+  float* const s_row = reinterpret_cast<float*>(smem);                         // [copy][wave][row][sum]
+  int8_t* const own = smem + t.waves * kBwdRowBytes + t.wave * kBwdWaveBytes;
+  const int groups = a.rows / 32, lc = a.cols / 32;
+  const uint32_t off = (uint32_t)(t.rsub * a.cols + t.col), off_scale = (uint32_t)(t.col / 32) * 4;
+
+  auto request = [&](int g) __attribute__((always_inline)) {
+    const int8_t* const x = uniform_pointer(a.X + (int64_t)g * 32 * a.cols);
+    const int8_t* const gr = uniform_pointer(a.G + (int64_t)g * 32 * a.cols);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      load_lds_16(x + (int64_t)p * 8 * a.cols, off, own, 1024 * p);
+      load_lds_16(gr + (int64_t)p * 8 * a.cols, off, own, kBwdG + 1024 * p);
+    }
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)g * lc)), off_scale, own, kBwdScaleX);
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SG + (int64_t)g * lc)), off_scale, own, kBwdScaleG);
+    if (t.lane < 32) {   // 32 floats each
+      load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.mean + g * 32)), (uint32_t)t.lane * 4, own, kBwdMean);
+      load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.rstd + g * 32)), (uint32_t)t.lane * 4, own, kBwdRstd);
+    }
+  };
+
+  int first = blockIdx.x * a.teams;
+  const int stride = gridDim.x * a.teams;
+  request(min(first + t.team, groups - 1));
+  float* const s_gamma = reinterpret_cast<float*>(own + kBwdGamma);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = t.c0 + t.lane + 64 * i;
+    s_gamma[t.lane + 64 * i] = c < a.cols ? a.gamma[c] : 0.0f;
+  }
+  wait_all_loads();
+  wave_lds_fence();
+
+  float cgs[16], cbs[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) cgs[e] = cbs[e] = 0.0f;
+  int copy = 0;
+  for (; first < groups; first += stride, copy ^= 1) {
+    const int g = first + t.team;                      // past the last group: a repeat of it that adds and stores nothing
+    uint4 px[4], pg[4];
+    float mu[4], rs[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      px[p] = *reinterpret_cast<const uint4*>(own + 1024 * p + 16 * t.lane);
+      pg[p] = *reinterpret_cast<const uint4*>(own + kBwdG + 1024 * p + 16 * t.lane);
+      mu[p] = reinterpret_cast<const float*>(own + kBwdMean)[t.rsub + 8 * p];
+      rs[p] = reinterpret_cast<const float*>(own + kBwdRstd)[t.rsub + 8 * p];
+    }
+    const float sx = *reinterpret_cast<const float*>(own + kBwdScaleX + 4 * t.lane);
+    float sg = *reinterpret_cast<const float*>(own + kBwdScaleG + 4 * t.lane);
+    wait_lds();                                        // the strips are in registers: their LDS may be filled again
+    if (first + stride < groups) request(min(g + stride, groups - 1));
+    sg = t.ok && g < groups ? sg : 0.0f;               // what lies outside adds nothing to the sums
+    float kx[4], cx[4], m1[4], m2[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      kx[p] = sx * rs[p];
+      cx[p] = -mu[p] * rs[p];                          // xhat = code kx + cx
+      m1[p] = m2[p] = 0.0f;
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const float4 gm4 = *reinterpret_cast<const float4*>(s_gamma + 16 * t.ch + 4 * d);
+      const float gm[4] = {gm4.x, gm4.y, gm4.z, gm4.w};
+      // g in units of its block scale, which goes onto the sums of the four rows instead of onto every element
+      float tg[4], tb[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        float x[4], gr[4];
+        unpack4(dword_of(px[p], d), x);
+        unpack4(dword_of(pg[p], d), gr);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float xh = __builtin_fmaf(x[e], kx[p], cx[p]), gh = gr[e] * gm[e];
+          // in place (left to itself the compiler keeps the operands of many deferred updates alive instead)
+          asm volatile("v_add_f32 %0, %0, %1" : "+v"(m1[p]) : "v"(gh));
+          asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(m2[p]) : "v"(gh), "v"(xh));
+          tg[e] = p == 0 ? gr[e] * xh : __builtin_fmaf(gr[e], xh, tg[e]);
+          if (p == 0) tb[e] = gr[e];
+          else asm volatile("v_add_f32 %0, %0, %1" : "+v"(tb[e]) : "v"(gr[e]));
+        }
+        __builtin_amdgcn_sched_barrier(0);             // interleaved passes would keep their unpacked values live together
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(cgs[4 * d + e]) : "v"(sg), "v"(tg[e]));
+        asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(cbs[4 * d + e]) : "v"(sg), "v"(tb[e]));
+      }
+    }
+    float* const row = s_row + ((copy * t.waves + t.wave) * 32) * 2;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      m1[p] = wave_group_sum<7>(m1[p] * sg);
+      m2[p] = wave_group_sum<7>(m2[p] * sg);
+      if (t.ch == 0) *reinterpret_cast<float2*>(row + 2 * (t.rsub + 8 * p)) = make_float2(m1[p], m2[p]);
+    }
+    lds_barrier();
+    {
+      const float* v = s_row + ((copy * t.waves + t.team * a.strips) * 32 + (t.lane & 31)) * 2 + (t.lane >> 5);
+      float sum = 0.0f;
+      for (int w = 0; w < a.strips; ++w) sum += v[64 * w];
+      reinterpret_cast<float*>(own + kBwdMeans)[2 * (t.lane & 31) + (t.lane >> 5)] = sum * a.inv_cols;
+      wave_lds_fence();
+    }
+    // the codes are unpacked again below: 128 floats kept from above would not fit the registers
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      asm volatile("" : "+v"(px[p].x), "+v"(px[p].y), "+v"(px[p].z), "+v"(px[p].w));
+      asm volatile("" : "+v"(pg[p].x), "+v"(pg[p].y), "+v"(pg[p].z), "+v"(pg[p].w));
+    }
+    // dx = g_code (rstd sg gamma) + x_code kxm + krow
+    float kxm[4], krow[4], rsg[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const float2 q = reinterpret_cast<const float2*>(own + kBwdMeans)[t.rsub + 8 * p];
+      kxm[p] = -rs[p] * q.y * kx[p];
+      krow[p] = -rs[p] * __builtin_fmaf(cx[p], q.y, q.x);
+      rsg[p] = rs[p] * sg;
+    }
+    float y[4][16];
+    float m = 0.0f;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const float4 gm4 = *reinterpret_cast<const float4*>(s_gamma + 16 * t.ch + 4 * d);
+      const float gm[4] = {gm4.x, gm4.y, gm4.z, gm4.w};
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        float x[4], gr[4];
+        unpack4(dword_of(px[p], d), x);
+        unpack4(dword_of(pg[p], d), gr);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[p][4 * d + e] = __builtin_fmaf(x[e], kxm[p], __builtin_fmaf(gr[e], rsg[p] * gm[e], krow[p]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) m = amax16(m, y[p]);
+    float scale;
+    double inv;
+    strip32_block_scale(m, scale, inv);
+    uint4 o[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      o[p] = quantize16(y[p], inv);
+      asm volatile("" : "+v"(o[p].x), "+v"(o[p].y), "+v"(o[p].z), "+v"(o[p].w));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wait_all_loads();
+    if (t.ok && g < groups) {
+      // uniform base + 32-bit lane offset, like the loads: no 64-bit lane addresses to keep
+      int8_t* const out = uniform_pointer(a.dX + (int64_t)g * 32 * a.cols);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) store_global(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
+      if ((t.lane & 57) == 0) store_global(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)), off_scale, scale);
+    }
+  }
+
+  // column sums over the 8 row lanes of the wave, then over the teams through LDS, in a fixed order
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    cgs[e] = wave_group_sum<56>(cgs[e]);
+    cbs[e] = wave_group_sum<56>(cbs[e]);
+  }
+  if (a.teams > 1) {
+    float* const mine = reinterpret_cast<float*>(own);   // all requests have landed and nobody else uses this wave's part
+    if (t.rsub == 0) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        reinterpret_cast<float4*>(mine + 16 * t.ch)[d] = make_float4(cgs[4 * d], cgs[4 * d + 1], cgs[4 * d + 2], cgs[4 * d + 3]);
+        reinterpret_cast<float4*>(mine + 128 + 16 * t.ch)[d] = make_float4(cbs[4 * d], cbs[4 * d + 1], cbs[4 * d + 2], cbs[4 * d + 3]);
+      }
+    }
+    lds_barrier();
+    if (t.team == 0) {
+      for (int k = 1; k < a.teams; ++k) {
+        const float* other = reinterpret_cast<const float*>(own + k * a.strips * kBwdWaveBytes);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          cgs[e] += other[16 * t.ch + e];
+          cbs[e] += other[128 + 16 * t.ch + e];
+        }
+      }
+    }
+  }
+  if (t.team == 0 && t.ok && t.rsub == 0) {
+    float* dst = a.partials + (int64_t)blockIdx.x * 2 * a.cols + t.col;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      *reinterpret_cast<float4*>(dst + 4 * d) = make_float4(cgs[4 * d], cgs[4 * d + 1], cgs[4 * d + 2], cgs[4 * d + 3]);
+      *reinterpret_cast<float4*>(dst + a.cols + 4 * d) = make_float4(cbs[4 * d], cbs[4 * d + 1], cbs[4 * d + 2], cbs[4 * d + 3]);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------ host
+// A launch needs more LDS than a kernel gets by default; the limit is raised once per process (for every device).
+template <class Kernel>
+static bool allow_lds(Kernel kernel, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+}
+
+// Teams per workgroup, one workgroup per compute unit.  The waves of a workgroup are dealt to the four SIMDs in turn, so
+// that the fullest SIMD sets the pace: the count that does most row groups per wave of that SIMD (six strips: two teams, 3
+// waves on every SIMD, instead of two workgroups of one team, which leave 2, 3, 3 and 4: 622 -> 571 us backward at 1 M x
+// 768), of equal ones the larger; fewer while there are compute units without a workgroup.
+static int choose_teams(int strips, int groups) {
+  int best = 1;
+  for (int n = 2; n * strips <= 16; ++n)
+    if ((n * strips + 3) / 4 * best <= (best * strips + 3) / 4 * n) best = n;
+  return std::max(1, std::min(best, (groups + 255) / 256));
+}
+
+bool layernorm_rows_fits(int64_t C, int32_t block) { return block == 32 && C <= 16 * 128; }
+
+void launch_layernorm_rows(LayerNormRows a, hipStream_t st) {
+  const int groups = a.rows / 32;
+  a.strips = (a.cols + 127) / 128;
+  a.teams = choose_teams(a.strips, groups);
+  a.inv_cols = 1.0 / (double)a.cols;
+  a.inv_blocks = 1.0 / (double)(a.cols / 32);
+  const int waves = a.strips * a.teams, grid = std::min((groups + a.teams - 1) / a.teams, 256);
+  const size_t lds = (size_t)waves * (kFwdRowBytes + kFwdWaveBytes);
+  if (a.row_mean) {
+    static const bool ok = allow_lds(layernorm_rows_kernel<true>, 16 * (kFwdRowBytes + kFwdWaveBytes));
+    (void)ok;
+    hipLaunchKernelGGL(layernorm_rows_kernel<true>, dim3(grid), dim3(64 * waves), lds, st, a);
+  } else {
+    static const bool ok = allow_lds(layernorm_rows_kernel<false>, 16 * (kFwdRowBytes + kFwdWaveBytes));
+    (void)ok;
+    hipLaunchKernelGGL(layernorm_rows_kernel<false>, dim3(grid), dim3(64 * waves), lds, st, a);
+  }
+}
+
+int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st) {
+  const int groups = a.rows / 32;
+  a.strips = (a.cols + 127) / 128;
+  a.teams = choose_teams(a.strips, groups);
+  a.inv_cols = 1.0f / (float)a.cols;
+  const int waves = a.strips * a.teams, grid = std::min((groups + a.teams - 1) / a.teams, 256);
+  static_assert(16 * (kBwdRowBytes + kBwdWaveBytes) <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
+  static const bool ok = allow_lds(layernorm_bwd_rows_kernel, 16 * (kBwdRowBytes + kBwdWaveBytes));
+  (void)ok;
+  hipLaunchKernelGGL(layernorm_bwd_rows_kernel, dim3(grid), dim3(64 * waves), (size_t)waves * (kBwdRowBytes + kBwdWaveBytes), st, a);
+  return grid;
+}
+
+}  // namespace jf
