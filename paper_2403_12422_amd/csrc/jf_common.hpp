@@ -168,6 +168,20 @@ __device__ __forceinline__ T* uniform_pointer(T* p) {
   return (T*)(((uint64_t)hi << 32) | lo);
 }
 
+// Results are stored non-temporal.  Each XCD's L2 is private, so whatever a kernel leaves dirty in it has to be written
+// back before the next kernel may start; streamed, the lines go out while the kernel still runs.  The reader is another
+// kernel, i.e. mostly another XCD, and finds them in the memory-side cache either way.  Takes 0.9-1.2 us off every kernel of
+// 10-60 MB (Add at 8192 x 1280 8.7 -> 7.4 us, GELU at 4096 x 3072 9.2 -> 8.1 us), 1-3 % off those of 1-2 GB.
+template <class T>
+__device__ __forceinline__ void store_out(void* p, T v) { __builtin_nontemporal_store(v, static_cast<T*>(p)); }
+__device__ __forceinline__ void store_out(void* p, const uint4& v) {
+  store_out(p, v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w});
+}
+__device__ __forceinline__ void store_out(void* p, const float4& v) {
+  typedef float v4f __attribute__((ext_vector_type(4)));
+  store_out(p, v4f{v.x, v.y, v.z, v.w});
+}
+
 // Eq. 1 scale of a block from its max-abs: one IEEE FP32 division; 0 for an all-zero block.  `inv` is the
 // reciprocal of the scale in double precision (0 for an all-zero block, so that every code becomes 0): the
 // hardware estimate refined by two Newton steps, relative error below 2^-50.  The double reciprocal exists for

@@ -181,11 +181,11 @@ __global__ void __launch_bounds__(256) gelu_kernel(const int8_t* __restrict__ X,
     double inv;
     block_scale(m, scale, inv);
     if (!col_ok[j]) continue;
-    if (wave == 0 && rsub == 0 && (col[j] % B) == 0) SY[(int64_t)bi * lc + col[j] / B] = scale;
+    if (wave == 0 && rsub == 0 && (col[j] % B) == 0) store_out(&SY[(int64_t)bi * lc + col[j] / B], scale);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int row = r0 + 8 * p + rsub;
-      *reinterpret_cast<uint4*>(Y + (int64_t)row * cols + col[j]) = quantize16(y[j][p], inv);
+      store_out(Y + (int64_t)row * cols + col[j], quantize16(y[j][p], inv));
     }
   }
 }
@@ -271,9 +271,9 @@ __global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict
   float scale;
   double inv;
   block_scale(m, scale, inv);
-  if (lane == 0) SY[(int64_t)bi * lc + bj] = scale;
+  if (lane == 0) store_out(&SY[(int64_t)bi * lc + bj], scale);
 #pragma unroll
-  for (int p = 0; p < P; ++p) *reinterpret_cast<uint4*>(Y + base + (int64_t)p * RPP * cols) = quantize16(y[p], inv);
+  for (int p = 0; p < P; ++p) store_out(Y + base + (int64_t)p * RPP * cols, quantize16(y[p], inv));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -320,8 +320,8 @@ __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1,
         ps = wave_group_sum<CH>(ps);
         pq = wave_group_sum<CH>(pq);
         if ((ch & CH) == 0) {
-          row_mean[(int64_t)(col / B) * rows + row] = ps * (1.0f / (float)B);   // block-column-major, see jf_add_q
-          row_sumsq[(int64_t)(col / B) * rows + row] = pq;
+          store_out(&row_mean[(int64_t)(col / B) * rows + row], ps * (1.0f / (float)B));   // block-column-major, see jf_add_q
+          store_out(&row_sumsq[(int64_t)(col / B) * rows + row], pq);
         }
       }
     }
@@ -334,11 +334,11 @@ __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1,
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) SY[(int64_t)bi * lc + col / B] = scale;
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_out(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
-    *reinterpret_cast<uint4*>(Y + (int64_t)row * cols + col) = quantize16(y[p], inv);
+    store_out(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
   }
 }
 
@@ -385,11 +385,11 @@ __global__ void __launch_bounds__(256) dropout_kernel(const int8_t* __restrict__
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) SY[(int64_t)bi * lc + col / B] = scale;
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_out(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
-    *reinterpret_cast<uint4*>(Y + (int64_t)row * cols + col) = quantize16(y[p], inv);
+    store_out(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
   }
 }
 
@@ -453,9 +453,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) gelu_strip32_kernel(const in
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) SY[t.block_index()] = scale;
+  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) *reinterpret_cast<uint4*>(Y + t.base + p * pass) = quantize16(y[p], inv);
+  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // Add (App. A) at block size 32, optionally with the row partials of App. A's LayerNorm paragraph (PARTIALS).
@@ -497,8 +497,8 @@ __global__ void __launch_bounds__(64 * kStripWaves) add_strip32_kernel(const int
       if (t.ok && (t.ch & 1) == 0) {
         // block-column-major: the 32 rows of the strip are one 128-byte line per block column
         const int64_t o = (int64_t)(t.col / 32) * rows + (t.bi * 32 + t.rsub + 8 * p);
-        row_mean[o] = ps * (1.0f / 32.0f);
-        row_sumsq[o] = pq;
+        store_out(&row_mean[o], ps * (1.0f / 32.0f));
+        store_out(&row_sumsq[o], pq);
       }
     }
   }
@@ -506,9 +506,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) add_strip32_kernel(const int
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) SY[t.block_index()] = scale;
+  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) *reinterpret_cast<uint4*>(Y + t.base + p * pass) = quantize16(y[p], inv);
+  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // The four keep bits of one packed dword of codes -> 0xff / 0x00 per byte: the multiplication puts bit j of the
@@ -557,9 +557,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) dropout_strip32_kernel(const
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) SY[t.block_index()] = scale;
+  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) *reinterpret_cast<uint4*>(Y + t.base + p * pass) = quantize16(y[p], inv);
+  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // ------------------------------------------------------------------------------------------------ host

@@ -575,14 +575,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
       if (g.Of) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
-          *reinterpret_cast<float4*>(g.Of + (int64_t)m * g.Nn + nb + 8 * q4) =
-              make_float4(acc[a][b][4 * q4], acc[a][b][4 * q4 + 1], acc[a][b][4 * q4 + 2], acc[a][b][4 * q4 + 3]);
+          store_out(g.Of + (int64_t)m * g.Nn + nb + 8 * q4,
+                    make_float4(acc[a][b][4 * q4], acc[a][b][4 * q4 + 1], acc[a][b][4 * q4 + 2], acc[a][b][4 * q4 + 3]));
       }
       if (g.Oq) {
         float scale;
         double inv;
         block_scale(amax[a][b], scale, inv);
-        if (lane == 0 && (mrow0 % B) == 0 && (ncol0 % B) == 0) g.Os[(int64_t)(mrow0 / B) * ln + ncol0 / B] = scale;
+        if (lane == 0 && (mrow0 % B) == 0 && (ncol0 % B) == 0) store_out(&g.Os[(int64_t)(mrow0 / B) * ln + ncol0 / B], scale);
         // Codes go to LDS first, laid out as the TM x TN byte tile with its 16-byte chunks XOR-swizzled by the
         // row, so that the tile can be written to memory as whole rows.
         const int row = 32 * (wm0 + a) + (lane & 31);
@@ -606,7 +606,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
       const int row = id / CPRO, c = id % CPRO;
       if (m0 + row < g.M && n0 + 16 * c < g.Nn) {
         const uint4 v = *reinterpret_cast<const uint4*>(code_row(row) + 16 * (c ^ (row & (CPRO - 1))));
-        *reinterpret_cast<uint4*>(g.Oq + (int64_t)(m0 + row) * g.Nn + n0 + 16 * c) = v;
+        store_out(g.Oq + (int64_t)(m0 + row) * g.Nn + n0 + 16 * c, v);
       }
     }
   }

@@ -254,9 +254,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_bwd_apply_strip32_
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) SdX[t.block_index()] = scale;
+  if ((t.lane & 57) == 0) store_out(&SdX[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) *reinterpret_cast<uint4*>(dX + t.base + p * pass) = quantize16(y[p], inv);
+  for (int p = 0; p < 4; ++p) store_out(dX + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // Row statistics of LayerNorm from the row partials that the preceding Add wrote (App. A, LayerNorm paragraph):
@@ -333,9 +333,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_apply_strip32_kern
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) SY[t.block_index()] = scale;
+  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) *reinterpret_cast<uint4*>(Y + t.base + p * pass) = quantize16(y[p], inv);
+  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // The same two element-wise operators at block sizes 64 and 128: one workgroup of four waves owns B rows x 128 columns
@@ -407,11 +407,11 @@ __global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __res
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) SY[(int64_t)bi * lc + col / B] = scale;
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_out(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
-    *reinterpret_cast<uint4*>(Y + (int64_t)row * cols + col) = quantize16(y[p], inv);
+    store_out(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
   }
 }
 

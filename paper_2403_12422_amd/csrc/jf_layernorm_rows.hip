@@ -46,9 +46,9 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 template <class T>
-__device__ __forceinline__ void store_global(int8_t* uniform_base, uint32_t off, T v) {
+__device__ __forceinline__ void store_out_at(int8_t* uniform_base, uint32_t off, T v) {
   typedef __attribute__((address_space(1))) int8_t* gbl_ptr;
-  *(__attribute__((address_space(1))) T*)((gbl_ptr)uniform_base + off) = v;
+  __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T*)((gbl_ptr)uniform_base + off));   // see store_out
 }
 
 // Signed codes of one packed dword as floats (a byte-select conversion each).
@@ -212,8 +212,8 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
       // uniform base + 32-bit lane offset, like the loads: no 64-bit lane addresses to keep
       int8_t* const out = uniform_pointer(a.Y + (int64_t)g * 32 * a.cols);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) store_global(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_global(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)), off_scale, scale);
+      for (int p = 0; p < 4; ++p) store_out_at(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
+      if ((t.lane & 57) == 0) store_out_at(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)), off_scale, scale);
     }
   }
 }
@@ -380,8 +380,8 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
       // uniform base + 32-bit lane offset, like the loads: no 64-bit lane addresses to keep
       int8_t* const out = uniform_pointer(a.dX + (int64_t)g * 32 * a.cols);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) store_global(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_global(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)), off_scale, scale);
+      for (int p = 0; p < 4; ++p) store_out_at(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
+      if ((t.lane & 57) == 0) store_out_at(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)), off_scale, scale);
     }
   }
 

@@ -77,14 +77,14 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
   // one lane per block writes the scale: the top-left 32-granule of the block
   if ((lane & 39) == 0 && col_ok && r0 < rows && (r0 % B) == 0 && ((c0 + 32 * (c4 >> 3)) % B) == 0) {
     const int bi = r0 / B, bj = (c0 + 32 * (c4 >> 3)) / B;
-    s[(int64_t)bi * lc + bj] = scale;
-    if (TRANSPOSED_COPY) sT[(int64_t)bj * lr + bi] = scale;
+    store_out(&s[(int64_t)bi * lc + bj], scale);
+    if (TRANSPOSED_COPY) store_out(&sT[(int64_t)bj * lr + bi], scale);
   }
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = r0 + 2 * i + rh;
     const uint32_t packed = quantize4(v[i][0], v[i][1], v[i][2], v[i][3], inv);
-    if (col_ok && row < rows) *reinterpret_cast<uint32_t*>(q + (int64_t)row * ldq + col) = packed;
+    if (col_ok && row < rows) store_out(q + (int64_t)row * ldq + col, packed);
     if (TRANSPOSED_COPY) *reinterpret_cast<uint32_t*>(&s_codes[(wave * 32 + 2 * i + rh) * 132 + 4 * c4]) = packed;
   }
   if (TRANSPOSED_COPY) {
@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
           for (int b = 0; b < 4; ++b) acc |= (uint32_t)s_codes[(16 * ch + 4 * d + b) * 132 + tc] << (8 * b);
           w[d] = acc;
         }
-        *reinterpret_cast<uint4*>(qT + (int64_t)gc * ldqT + gr) = make_uint4(w[0], w[1], w[2], w[3]);
+        store_out(qT + (int64_t)gc * ldqT + gr, make_uint4(w[0], w[1], w[2], w[3]));
       }
     }
   }
@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restric
     if constexpr (sizeof(T) == 4) {
 #pragma unroll
       for (int d = 0; d < 4; ++d)
-        *reinterpret_cast<float4*>(dst + 4 * d) = make_float4(v[4 * d], v[4 * d + 1], v[4 * d + 2], v[4 * d + 3]);
+        store_out(dst + 4 * d, make_float4(v[4 * d], v[4 * d + 1], v[4 * d + 2], v[4 * d + 3]));
     } else {
       typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 #pragma unroll
@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restric
         h8 h;
 #pragma unroll
         for (int b = 0; b < 8; ++b) h[b] = (_Float16)v[8 * d + b];
-        *reinterpret_cast<h8*>(dst + 8 * d) = h;
+        store_out(dst + 8 * d, h);
       }
     }
   }
