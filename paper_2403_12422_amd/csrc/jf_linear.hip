@@ -1,32 +1,47 @@
 // Per-block INT8 linear layer (Sec. 5, Alg. 1): C entry points of forward, dgrad, wgrad and the INT32-partial
-// test hook.  The kernel lives in jf_gemm_kernel.hpp and is instantiated per product and block size in
-// jf_gemm_<product>_b<block>.hip.
-#include "jf_gemm_kernel.hpp"
+// test hook.  The kernels live in jf_gemm_kernel.hpp and jf_gemm_fine.hpp and are instantiated per product and block size
+// in jf_gemm_<product>_b<block>.hip; jf_gemm_shapes.hpp picks among them.
+#include <atomic>
+
+#include "jf_gemm_shapes.hpp"
 
 namespace jf {
 
-void launch_gemm_fwd_b32(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_fwd_b64(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_fwd_b128(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_dgrad_b32(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_dgrad_b64(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_dgrad_b128(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_wgrad_b32(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_wgrad_b64(const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_wgrad_b128(const GemmArgs& a, bool dump, hipStream_t st);
-bool launch_gemm_bwd_pair_b32(const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
+static std::atomic<int> g_forced_shape{0};   // test hook, see jf_debug_set_gemm_shape: 0 unless a test sets it
 
-std::atomic<int> g_forced_shape{0};
+void launch_gemm_fwd_b32(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_fwd_b64(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_fwd_b128(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_dgrad_b32(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_dgrad_b64(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_dgrad_b128(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_wgrad_b32(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_wgrad_b64(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_wgrad_b128(int shape, const GemmArgs& a, bool dump, hipStream_t st);
+void launch_gemm_bwd_pair_b32(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
+void launch_gemm_bwd_pair_b64(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
+void launch_gemm_bwd_pair_b128(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
+
+// Input and weight gradient in one launch, if that is the faster way; false: nothing launched.
+static bool launch_bwd_pair(int block, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st) {
+  const int pair = choose_pair(block, dgrad, wgrad, g_forced_shape.load(std::memory_order_relaxed));
+  if (pair == 0) return false;
+  if (block == 32) launch_gemm_bwd_pair_b32(pair, dgrad, wgrad, st);
+  else if (block == 64) launch_gemm_bwd_pair_b64(pair, dgrad, wgrad, st);
+  else launch_gemm_bwd_pair_b128(pair, dgrad, wgrad, st);
+  return true;
+}
 
 // which: 0 forward, 1 dgrad, 2 wgrad
 static void launch_gemm(int which, int block, const GemmArgs& a, bool dump, hipStream_t st) {
-  typedef void (*launcher)(const GemmArgs&, bool, hipStream_t);
+  typedef void (*launcher)(int, const GemmArgs&, bool, hipStream_t);
   static const launcher table[3][3] = {
       {launch_gemm_fwd_b32, launch_gemm_fwd_b64, launch_gemm_fwd_b128},
       {launch_gemm_dgrad_b32, launch_gemm_dgrad_b64, launch_gemm_dgrad_b128},
       {launch_gemm_wgrad_b32, launch_gemm_wgrad_b64, launch_gemm_wgrad_b128},
   };
-  table[which][block == 32 ? 0 : (block == 64 ? 1 : 2)](a, dump, st);
+  const int shape = choose_shape(block, a, g_forced_shape.load(std::memory_order_relaxed));
+  table[which][block == 32 ? 0 : (block == 64 ? 1 : 2)](shape, a, dump, st);
 }
 
 static int32_t check_linear(const void* p0, const void* p1, const void* p2, const void* p3, int64_t N, int64_t C,
@@ -127,7 +142,7 @@ extern "C" int32_t jf_linear_bwd(const int8_t* dY, const float* SdY, const int8_
   GemmArgs gw = make_args(2, dY, SdY, X, SX, N, C, D, block);
   gw.Oq = dW; gw.Os = SdW; gw.Of = dW_f32;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (block != 32 || !launch_gemm_bwd_pair_b32(gd, gw, st)) {   // shapes that fill the chip on their own: two launches
+  if (!launch_bwd_pair(block, gd, gw, st)) {
     launch_gemm(1, block, gd, false, st);
     rc = launch_status();
     if (rc != JF_OK) return rc;
@@ -155,7 +170,7 @@ extern "C" int32_t jf_debug_linear_partials(int32_t which, const int8_t* A, cons
 }
 
 extern "C" int32_t jf_debug_set_gemm_shape(int32_t shape) {
-  if (shape != 0 && shape != 1 && shape != 4 && shape != 6 && shape != 7 && shape != 8) return JF_ERR_SHAPE;
+  if (shape != 0 && shape != 1 && shape != 4 && shape != 6 && shape != 7 && shape != 8 && shape != 10 && (shape < 21 || shape > 25)) return JF_ERR_SHAPE;
   jf::g_forced_shape.store(shape, std::memory_order_relaxed);
   return JF_OK;
 }
