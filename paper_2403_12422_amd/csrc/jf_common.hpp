@@ -168,19 +168,28 @@ __device__ __forceinline__ T* uniform_pointer(T* p) {
   return (T*)(((uint64_t)hi << 32) | lo);
 }
 
-// Results are stored non-temporal.  Each XCD's L2 is private, so whatever a kernel leaves dirty in it has to be written
-// back before the next kernel may start; streamed, the lines go out while the kernel still runs.  The reader is another
-// kernel, i.e. mostly another XCD, and finds them in the memory-side cache either way.  Takes 0.9-1.2 us off every kernel of
-// 10-60 MB (Add at 8192 x 1280 8.7 -> 7.4 us, GELU at 4096 x 3072 9.2 -> 8.1 us), 1-3 % off those of 1-2 GB.
+// Results are written through (sc1: agent scope).  Each XCD's L2 is private, so whatever a kernel leaves dirty in it has to
+// be written back before the next kernel may start, 1-2 us after a kernel of 10-60 MB; written through, the lines go out
+// while the kernel still runs and stay readable in L2 and in the memory-side cache.  Non-temporal stores do the first but
+// not the second, which costs the next kernel of a small step more than it saves (MLP step 1152 x 4352 -> 896 at block 128:
+// write-back 104, non-temporal 123, write-through 102 us; 4096 x 768 -> 3072: 138, 132, 132; residual path 8192 x 1280: 56,
+// 54, 52; GELU 4096 x 3072: 17.1, 15.1, 14.2).  A large result has to be stored in
+// whole lines per wave, because a line written through in pieces goes to memory piece by piece (the FP16 hand-over at
+// 8192 x 5120 in 16-byte pieces: 87 instead of 71 us); store_part is for what cannot be.
+// (Written out because no builtin takes the scope bit for 16 bytes.  A 16-byte store reads its data one wait state late:
+// the s_nop keeps the next vector instruction from overwriting it, which the compiler does for its own stores.)
 template <class T>
-__device__ __forceinline__ void store_out(void* p, T v) { __builtin_nontemporal_store(v, static_cast<T*>(p)); }
+__device__ __forceinline__ void store_out(void* p, T v) {
+  static_assert(sizeof(T) == 16 || sizeof(T) == 8 || sizeof(T) == 4, "one store instruction");
+  if constexpr (sizeof(T) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+  else if constexpr (sizeof(T) == 8) asm volatile("global_store_dwordx2 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+  else asm volatile("global_store_dword %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+}
 __device__ __forceinline__ void store_out(void* p, const uint4& v) {
   store_out(p, v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w});
 }
-__device__ __forceinline__ void store_out(void* p, const float4& v) {
-  typedef float v4f __attribute__((ext_vector_type(4)));
-  store_out(p, v4f{v.x, v.y, v.z, v.w});
-}
+template <class T>
+__device__ __forceinline__ void store_part(void* p, T v) { *static_cast<T*>(p) = v; }
 
 // Eq. 1 scale of a block from its max-abs: one IEEE FP32 division; 0 for an all-zero block.  `inv` is the
 // reciprocal of the scale in double precision (0 for an all-zero block, so that every code becomes 0): the

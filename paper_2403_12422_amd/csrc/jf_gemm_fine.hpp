@@ -173,7 +173,7 @@ __device__ __forceinline__ void gemm_fine_tile(const GemmArgs& g, const int tile
   // ---- epilogue: max-abs of the block, Eq. 1, codes through LDS so that they are stored as whole rows of the tile.
   // Lane l holds columns 4 * (l / 16) .. + 3 of row l % 16 of the quarter.
   const int row = 16 * wm + (lane & 15), col = 16 * wn + 4 * (lane >> 4);
-  if (g.Of) store_out(g.Of + (int64_t)(m0 + row) * g.Nn + n0 + col, make_float4(acc[0], acc[1], acc[2], acc[3]));
+  if (g.Of) store_part(g.Of + (int64_t)(m0 + row) * g.Nn + n0 + col, make_float4(acc[0], acc[1], acc[2], acc[3]));
   if (!g.Oq) return;
   float amax = fmaxf(fmaxf(fabsf(acc[0]), fabsf(acc[1])), fmaxf(fabsf(acc[2]), fabsf(acc[3])));
   amax = wave_group_max<63>(amax);

@@ -546,7 +546,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
       if (g.Of) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
-          store_out(g.Of + (int64_t)m * g.Nn + nb + 8 * q4,
+          store_part(g.Of + (int64_t)m * g.Nn + nb + 8 * q4,
                     make_float4(acc[a][b][4 * q4], acc[a][b][4 * q4 + 1], acc[a][b][4 * q4 + 2], acc[a][b][4 * q4 + 3]));
       }
       if (g.Oq) {

@@ -45,10 +45,9 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <class T>
-__device__ __forceinline__ void store_out_at(int8_t* uniform_base, uint32_t off, T v) {
-  typedef __attribute__((address_space(1))) int8_t* gbl_ptr;
-  __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T*)((gbl_ptr)uniform_base + off));   // see store_out
+// 16 bytes per lane at a scalar base and a 32-bit lane offset, written through (see store_out)
+__device__ __forceinline__ void store_out_at(int8_t* uniform_base, uint32_t off, v4i v) {
+  asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" : : "v"(off), "v"(v), "s"(uniform_base) : "memory");
 }
 
 // Signed codes of one packed dword as floats (a byte-select conversion each).
@@ -213,7 +212,7 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
       int8_t* const out = uniform_pointer(a.Y + (int64_t)g * 32 * a.cols);
 #pragma unroll
       for (int p = 0; p < 4; ++p) store_out_at(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_out_at(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)), off_scale, scale);
+      if ((t.lane & 57) == 0) store_out(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)) + off_scale, scale);
     }
   }
 }
@@ -381,7 +380,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
       int8_t* const out = uniform_pointer(a.dX + (int64_t)g * 32 * a.cols);
 #pragma unroll
       for (int p = 0; p < 4; ++p) store_out_at(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_out_at(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)), off_scale, scale);
+      if ((t.lane & 57) == 0) store_out(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)) + off_scale, scale);
     }
   }
 
