@@ -2,29 +2,22 @@
 //
 // HBM-bound: 4 (or 2) bytes in, 1 byte out per element.  One workgroup of four
 // waves owns a 128 x 128 tile; wave w owns the 32-row strip w of it.  Inside a
-// strip a lane holds 4 consecutive columns of 16 rows, so each row of the strip
-// is read as one 512-byte (FP32) run and written as one 128-byte run of codes.
+// strip a lane holds 16 bytes (4 FP32 or 8 FP16 columns) of 16 or 8 rows, so each row
+// of the strip is read as one run of 512 or 256 bytes and written as one 128-byte line of codes.
 #include "jf_common.hpp"
 
 namespace jf {
 
-template <typename T>
-struct Load4;
-template <>
-struct Load4<float> {
-  static __device__ __forceinline__ void run(const float* p, float (&v)[4]) {
-    float4 t = *reinterpret_cast<const float4*>(p);
-    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-  }
-};
-template <>
-struct Load4<_Float16> {
-  static __device__ __forceinline__ void run(const _Float16* p, float (&v)[4]) {
-    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-    h4 t = *reinterpret_cast<const h4*>(p);
-    v[0] = (float)t[0]; v[1] = (float)t[1]; v[2] = (float)t[2]; v[3] = (float)t[3];
-  }
-};
+__device__ __forceinline__ void load_vec(const float* p, float (&v)[4]) {
+  float4 t = *reinterpret_cast<const float4*>(p);
+  v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+}
+__device__ __forceinline__ void load_vec(const _Float16* p, float (&v)[8]) {
+  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  h8 t = *reinterpret_cast<const h8*>(p);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = (float)t[i];
+}
 
 // B = quantization block; the tile is 128 x 128 and 256 threads (WPW = 4 waves per workgroup), or, for small
 // tensors at B = 32 where the waves do not depend on each other, one 32 x 128 strip and one wave (WPW = 1), which
@@ -40,29 +33,36 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
   static_assert(WPW == 4 || (WPW == 1 && B == 32 && !TRANSPOSED_COPY), "single-wave workgroups: independent waves only");
   const int r0 = (wg.y * WPW + wave) * 32;             // first row of this wave's strip
   const int c0 = wg.x * 128;
-  const int c4 = lane & 31, rh = lane >> 5;
-  const int col = c0 + 4 * c4;
-  const bool col_ok = col < cols;                      // cols % 32 == 0: whole 8-lane groups are in or out
+  constexpr int VEC = 16 / sizeof(T), LPR = 128 / VEC, RPI = 64 / LPR, NI = 32 / RPI;   // columns per lane, lanes per row, rows at once
+  const int cl = lane % LPR, rh = lane / LPR;
+  const int col = c0 + VEC * cl, cg = cl / (32 / VEC); // first column; 32-column group of the tile
+  const bool col_ok = col < cols;                      // cols % 32 == 0: the lanes of a group are in or out together
 
-  float v[16][4];
+  float v[NI][VEC];
   float amax = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int row = r0 + 2 * i + rh;
+  for (int i = 0; i < NI; ++i) {
+    const int row = r0 + RPI * i + rh;
     if (col_ok && row < rows) {
-      Load4<T>::run(x + (int64_t)row * ldx + col, v[i]);
+      load_vec(x + (int64_t)row * ldx + col, v[i]);
     } else {
-      v[i][0] = v[i][1] = v[i][2] = v[i][3] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) v[i][k] = 0.0f;
     }
-    amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[i][0]), fabsf(v[i][1])), fmaxf(fabsf(v[i][2]), fabsf(v[i][3]))));
   }
-  // lanes sharing a 32-column group: same c4 / 8, any c4 % 8, any rh
-  amax = wave_group_max<1 | 2 | 4 | 32>(amax);
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) amax = fmaxf(amax, fabsf(v[i][k]));
+  // lanes sharing a 32-column group: the lanes of the group in a row, and those of the rows read at once
+  constexpr int GROUP_MASK = (32 / VEC - 1) | (63 & ~(LPR - 1));
+  const bool group_first = (lane & GROUP_MASK) == 0;
+  amax = wave_group_max<GROUP_MASK>(amax);
   if (B > 32) {  // at B = 32 a block lies inside one wave's strip: no exchange, the waves run independently
-    if ((lane & 39) == 0) s_amax[wave][c4 >> 3] = amax;
+    if (group_first) s_amax[wave][cg] = amax;
     __syncthreads();
     constexpr int G = B / 32;  // 32-granules per block side
-    const int w0 = (wave / G) * G, g0 = ((c4 >> 3) / G) * G;
+    const int w0 = (wave / G) * G, g0 = (cg / G) * G;
     amax = 0.0f;
 #pragma unroll
     for (int a = 0; a < G; ++a)
@@ -75,17 +75,26 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
 
   const int lr = rows / B, lc = cols / B;
   // one lane per block writes the scale: the top-left 32-granule of the block
-  if ((lane & 39) == 0 && col_ok && r0 < rows && (r0 % B) == 0 && ((c0 + 32 * (c4 >> 3)) % B) == 0) {
-    const int bi = r0 / B, bj = (c0 + 32 * (c4 >> 3)) / B;
+  if (group_first && col_ok && r0 < rows && (r0 % B) == 0 && ((c0 + 32 * cg) % B) == 0) {
+    const int bi = r0 / B, bj = (c0 + 32 * cg) / B;
     store_out(&s[(int64_t)bi * lc + bj], scale);
     if (TRANSPOSED_COPY) store_out(&sT[(int64_t)bj * lr + bi], scale);
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int row = r0 + 2 * i + rh;
-    const uint32_t packed = quantize4(v[i][0], v[i][1], v[i][2], v[i][3], inv);
-    if (col_ok && row < rows) store_out(q + (int64_t)row * ldq + col, packed);
-    if (TRANSPOSED_COPY) *reinterpret_cast<uint32_t*>(&s_codes[(wave * 32 + 2 * i + rh) * 132 + 4 * c4]) = packed;
+  for (int i = 0; i < NI; ++i) {
+    const int row = r0 + RPI * i + rh;
+    uint32_t packed[VEC / 4];
+#pragma unroll
+    for (int k = 0; k < VEC / 4; ++k)
+      packed[k] = quantize4(v[i][4 * k], v[i][4 * k + 1], v[i][4 * k + 2], v[i][4 * k + 3], inv);
+    if (col_ok && row < rows) {
+      if constexpr (VEC == 4) store_out(q + (int64_t)row * ldq + col, packed[0]);
+      else store_out(q + (int64_t)row * ldq + col, v2i{(int)packed[0], (int)packed[1]});
+    }
+    if (TRANSPOSED_COPY) {
+#pragma unroll
+      for (int k = 0; k < VEC / 4; ++k) *reinterpret_cast<uint32_t*>(&s_codes[(wave * 32 + RPI * i + rh) * 132 + VEC * cl + 4 * k]) = packed[k];
+    }
   }
   if (TRANSPOSED_COPY) {
     __syncthreads();
@@ -102,7 +111,7 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
           for (int b = 0; b < 4; ++b) acc |= (uint32_t)s_codes[(16 * ch + 4 * d + b) * 132 + tc] << (8 * b);
           w[d] = acc;
         }
-        store_out(qT + (int64_t)gc * ldqT + gr, make_uint4(w[0], w[1], w[2], w[3]));
+        store_part(qT + (int64_t)gc * ldqT + gr, make_uint4(w[0], w[1], w[2], w[3]));
       }
     }
   }
@@ -134,37 +143,47 @@ static void dispatch_quantize(int block, const T* x, int64_t ldx, int rows, int 
 }
 
 // Dequantizer Q^-1 of Eq. 1: out = code * scale as FP32 or FP16 (the hand-over to a floating-point operator
-// such as the FP16 attention core of Sec. 7.1).  A thread converts 16 consecutive codes of one row.
+// such as the FP16 attention core of Sec. 7.1).  HBM-bound: 1 byte in, 2 or 4 out per element.  A thread writes 16 bytes
+// (8 FP16 or 4 FP32 values) at a time, so that a wave fills whole lines, and takes DQ_CHUNKS such chunks 256 apart, whose
+// codes and scales are requested before the first is used; rows follow each other without a gap, so that no lane idles at
+// their ends.  The quotient chunk / (chunks per row) is formed once per workgroup in 64 bits and per chunk in 32.
+static constexpr int DQ_CHUNKS = 4;
 template <typename T>
 __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restrict__ q, const float* __restrict__ s, int rows,
-                                                          int cols, int block, T* __restrict__ out, int64_t ldo) {
-  const int chunks = cols / 16;
-  const int64_t total = (int64_t)rows * chunks;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int row = (int)(i / chunks), col = 16 * (int)(i % chunks);
-    const uint4 p = *reinterpret_cast<const uint4*>(q + (int64_t)row * cols + col);
-    const float sc = s[(int64_t)(row / block) * (cols / block) + col / block];
-    const uint32_t w[4] = {p.x, p.y, p.z, p.w};
-    float v[16];
+                                                          int cols, int block_log2, T* __restrict__ out, int64_t ldo) {
+  constexpr int VEC = 16 / sizeof(T);
+  typedef typename std::conditional<VEC == 8, uint2, uint32_t>::type packed_t;
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  const uint32_t chunks = cols / VEC;
+  const int64_t first = (int64_t)blockIdx.x * (256 * DQ_CHUNKS), total = (int64_t)rows * chunks;
+  const int row0 = (int)(first / chunks);
+  const uint32_t rem = (uint32_t)(first - (int64_t)row0 * chunks);
+  const int lc = cols >> block_log2;
+  packed_t p[DQ_CHUNKS];
+  float sc[DQ_CHUNKS];
+  int row[DQ_CHUNKS], col[DQ_CHUNKS];
 #pragma unroll
-    for (int d = 0; d < 4; ++d)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) v[4 * d + b] = (float)(int8_t)(w[d] >> (8 * b)) * sc;
-    T* dst = out + (int64_t)row * ldo + col;
-    if constexpr (sizeof(T) == 4) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d)
-        store_out(dst + 4 * d, make_float4(v[4 * d], v[4 * d + 1], v[4 * d + 2], v[4 * d + 3]));
-    } else {
-      typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-#pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        h8 h;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) h[b] = (_Float16)v[8 * d + b];
-        store_out(dst + 8 * d, h);
-      }
+  for (int u = 0; u < DQ_CHUNKS; ++u) {
+    const uint32_t i = rem + u * 256 + threadIdx.x, r = i / chunks;
+    row[u] = row0 + (int)r;
+    col[u] = VEC * (int)(i - r * chunks);
+    if (first + u * 256 + threadIdx.x < total) {
+      p[u] = *reinterpret_cast<const packed_t*>(q + (int64_t)row[u] * cols + col[u]);
+      sc[u] = s[(int64_t)(row[u] >> block_log2) * lc + (col[u] >> block_log2)];
     }
+  }
+#pragma unroll
+  for (int u = 0; u < DQ_CHUNKS; ++u) {
+    if (first + u * 256 + threadIdx.x >= total) break;
+    vec_t v;
+#pragma unroll
+    for (int b = 0; b < VEC; ++b) {
+      uint32_t w;
+      if constexpr (VEC == 8) w = b < 4 ? p[u].x : p[u].y;
+      else w = p[u];
+      v[b] = (T)(byte_to_float(w, b & 3) * sc[u]);
+    }
+    store_out(out + (int64_t)row[u] * ldo + col[u], v);
   }
 }
 
@@ -179,13 +198,14 @@ extern "C" int32_t jf_dequantize_block(const int8_t* q, const float* s, int64_t 
   if (!valid_dim(rows, block) || !valid_dim(cols, block) || !valid_size(rows, cols) || ldo < cols) return JF_ERR_SHAPE;
   if (!aligned16(q) || !aligned4(s) || !aligned16(out) || (ldo % 8)) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const int64_t total = rows * (cols / 16);
-  const unsigned grid = (unsigned)((total + 255) / 256 < 8192 ? (total + 255) / 256 : 8192);
+  const int log2b = block == 32 ? 5 : (block == 64 ? 6 : 7);
+  const int64_t per_wg = 256 * DQ_CHUNKS * (out_dtype == 0 ? 4 : 8);
+  const unsigned grid = (unsigned)((rows * cols + per_wg - 1) / per_wg);
   if (out_dtype == 0)
-    hipLaunchKernelGGL((dequantize_kernel<float>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, (int)block,
+    hipLaunchKernelGGL((dequantize_kernel<float>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
                        static_cast<float*>(out), ldo);
   else
-    hipLaunchKernelGGL((dequantize_kernel<_Float16>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, (int)block,
+    hipLaunchKernelGGL((dequantize_kernel<_Float16>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
                        static_cast<_Float16*>(out), ldo);
   return launch_status();
 }
