@@ -188,6 +188,38 @@ __device__ __forceinline__ void store_out(void* p, T v) {
 __device__ __forceinline__ void store_out(void* p, const uint4& v) {
   store_out(p, v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w});
 }
+// How the operators that run at the speed of memory store a result of `rows` rows of `row_bytes` bytes: chosen by the
+// launcher, a template argument of the kernels (a branch in the kernel costs the large tensors 2-3 %).
+// Rows that are no multiple of a line share lines between waves, and a result beyond the last-level cache then pays for
+// every piece: written back from 32 MB on (GELU 199680 x 1504: 385 -> 306 us, 40000 x 1504: 64 -> 62; 16384 x 1504, 25 MB:
+// through 26.3, back 29.1).  Whole lines that no cache will hold for the reader are streamed from 64 MB on (GELU 100000 x
+// 1536: 149 -> 136 us, 262144 x 3072: 742 -> 728).
+enum StorePolicy { kStoreThrough, kStoreStream, kStoreBack };
+inline StorePolicy store_policy(int64_t rows, int64_t row_bytes) {
+  const int64_t bytes = rows * row_bytes;
+  if (row_bytes % 128) return bytes >= (32 << 20) ? kStoreBack : kStoreThrough;
+  return bytes >= (64 << 20) ? kStoreStream : kStoreThrough;
+}
+// f(integral_constant<StorePolicy, P>) for the policy of a result
+template <class F>
+inline void with_store_policy(int64_t rows, int64_t row_bytes, F&& f) {
+  const StorePolicy p = store_policy(rows, row_bytes);
+  if (p == kStoreThrough) f(std::integral_constant<StorePolicy, kStoreThrough>());
+  else if (p == kStoreStream) f(std::integral_constant<StorePolicy, kStoreStream>());
+  else f(std::integral_constant<StorePolicy, kStoreBack>());
+}
+template <StorePolicy P, class T>
+__device__ __forceinline__ void store_as(void* p, const T& v) {
+  if constexpr (P == kStoreThrough) {
+    store_out(p, v);
+  } else if constexpr (P == kStoreStream) {
+    typedef int many __attribute__((ext_vector_type(sizeof(T) / 4)));
+    typedef typename std::conditional<sizeof(T) == 4, int, many>::type vec;
+    __builtin_nontemporal_store(__builtin_bit_cast(vec, v), static_cast<vec*>(p));
+  } else {
+    *static_cast<T*>(p) = v;
+  }
+}
 template <class T>
 __device__ __forceinline__ void store_part(void* p, T v) { *static_cast<T*>(p) = v; }
 

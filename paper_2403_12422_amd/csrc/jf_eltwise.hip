@@ -73,7 +73,7 @@ __device__ __forceinline__ void gelu_build_table(float* tab, float sx, int lane)
 // quantization blocks; wave w owns rows [w*B/4, (w+1)*B/4) in B/32 passes of 8 rows, lane = (row l/8,
 // 16-byte chunk l%8) in each of the J 128-column halves, so every row segment is a full 128-byte line.
 // J = 2 (B = 64) halves the number of workgroups; the tables built per element stay the same.
-template <bool BWD, int B, int J>
+template <bool BWD, int B, int J, StorePolicy SP>
 __global__ void __launch_bounds__(256) gelu_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                     const int8_t* __restrict__ G, const float* __restrict__ SG,
                                                     int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
@@ -181,11 +181,11 @@ __global__ void __launch_bounds__(256) gelu_kernel(const int8_t* __restrict__ X,
     double inv;
     block_scale(m, scale, inv);
     if (!col_ok[j]) continue;
-    if (wave == 0 && rsub == 0 && (col[j] % B) == 0) store_out(&SY[(int64_t)bi * lc + col[j] / B], scale);
+    if (wave == 0 && rsub == 0 && (col[j] % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col[j] / B], scale);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int row = r0 + 8 * p + rsub;
-      store_out(Y + (int64_t)row * cols + col[j], quantize16(y[j][p], inv));
+      store_as<SP>(Y + (int64_t)row * cols + col[j], quantize16(y[j][p], inv));
     }
   }
 }
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(256) gelu_kernel(const int8_t* __restrict__ X,
 // run independently and one wave's table build overlaps its neighbours' loads and stores.  Lane = (row l / CPR,
 // 16-byte chunk l % CPR) with CPR = B/16 chunks per block row, in B*CPR/64 passes; the four waves of a workgroup
 // read neighbouring 32- or 64-byte pieces of the same memory lines.
-template <bool BWD, int B>
+template <bool BWD, int B, StorePolicy SP>
 __global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                          const int8_t* __restrict__ G, const float* __restrict__ SG,
                                                          int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
@@ -271,16 +271,16 @@ __global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict
   float scale;
   double inv;
   block_scale(m, scale, inv);
-  if (lane == 0) store_out(&SY[(int64_t)bi * lc + bj], scale);
+  if (lane == 0) store_as<SP>(&SY[(int64_t)bi * lc + bj], scale);
 #pragma unroll
-  for (int p = 0; p < P; ++p) store_out(Y + base + (int64_t)p * RPP * cols, quantize16(y[p], inv));
+  for (int p = 0; p < P; ++p) store_as<SP>(Y + base + (int64_t)p * RPP * cols, quantize16(y[p], inv));
 }
 
 // ------------------------------------------------------------------------------------------------
 // Add (App. A): y = x1 + x2 on the dequantized operands, re-quantized per block (Alg. 2), and optionally
 // the row partials that App. A's LayerNorm paragraph attaches to this operator: for every row and block
 // column, the mean and the sum of squares of y over the block's B columns (stored block-column-major).  Same tiling as GELU.
-template <int B>
+template <int B, StorePolicy SP>
 __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1, const float* __restrict__ S1,
                                                    const int8_t* __restrict__ X2, const float* __restrict__ S2, int rows,
                                                    int cols, int8_t* __restrict__ Y, float* __restrict__ SY,
@@ -320,8 +320,8 @@ __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1,
         ps = wave_group_sum<CH>(ps);
         pq = wave_group_sum<CH>(pq);
         if ((ch & CH) == 0) {
-          store_out(&row_mean[(int64_t)(col / B) * rows + row], ps * (1.0f / (float)B));   // block-column-major, see jf_add_q
-          store_out(&row_sumsq[(int64_t)(col / B) * rows + row], pq);
+          store_as<SP>(&row_mean[(int64_t)(col / B) * rows + row], ps * (1.0f / (float)B));   // block-column-major, see jf_add_q
+          store_as<SP>(&row_sumsq[(int64_t)(col / B) * rows + row], pq);
         }
       }
     }
@@ -334,11 +334,11 @@ __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1,
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) store_out(&SY[(int64_t)bi * lc + col / B], scale);
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
-    store_out(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
+    store_as<SP>(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
   }
 }
 
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1,
 // Dropout (App. A): y = x o m / (1 - p) on the dequantized input, re-quantized per block; the keep mask m is
 // an input, packed 8 columns per byte (bit c % 8 of byte c / 8 of a row).  The backward pass is the same
 // operator on the upstream gradient.  Same tiling as GELU; a lane's 16 columns are two mask bytes.
-template <int B>
+template <int B, StorePolicy SP>
 __global__ void __launch_bounds__(256) dropout_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                        const uint8_t* __restrict__ mask, float keep_scale, int rows,
                                                        int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
@@ -385,16 +385,16 @@ __global__ void __launch_bounds__(256) dropout_kernel(const int8_t* __restrict__
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) store_out(&SY[(int64_t)bi * lc + col / B], scale);
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
-    store_out(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
+    store_as<SP>(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
   }
 }
 
 // ------------------------------------------------------------------------------------------------
-template <bool BWD>
+template <bool BWD, StorePolicy SP>
 __global__ void __launch_bounds__(64 * kStripWaves) gelu_strip32_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                           const int8_t* __restrict__ G, const float* __restrict__ SG,
                                                           int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
@@ -453,13 +453,13 @@ __global__ void __launch_bounds__(64 * kStripWaves) gelu_strip32_kernel(const in
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // Add (App. A) at block size 32, optionally with the row partials of App. A's LayerNorm paragraph (PARTIALS).
-template <bool PARTIALS>
+template <bool PARTIALS, StorePolicy SP>
 __global__ void __launch_bounds__(64 * kStripWaves) add_strip32_kernel(const int8_t* __restrict__ X1, const float* __restrict__ S1,
                                                          const int8_t* __restrict__ X2, const float* __restrict__ S2,
                                                          int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY,
@@ -497,8 +497,8 @@ __global__ void __launch_bounds__(64 * kStripWaves) add_strip32_kernel(const int
       if (t.ok && (t.ch & 1) == 0) {
         // block-column-major: the 32 rows of the strip are one 128-byte line per block column
         const int64_t o = (int64_t)(t.col / 32) * rows + (t.bi * 32 + t.rsub + 8 * p);
-        store_out(&row_mean[o], ps * (1.0f / 32.0f));
-        store_out(&row_sumsq[o], pq);
+        store_as<SP>(&row_mean[o], ps * (1.0f / 32.0f));
+        store_as<SP>(&row_sumsq[o], pq);
       }
     }
   }
@@ -506,9 +506,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) add_strip32_kernel(const int
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // The four keep bits of one packed dword of codes -> 0xff / 0x00 per byte: the multiplication puts bit j of the
@@ -522,6 +522,7 @@ __device__ __forceinline__ uint32_t keep_bytes(uint32_t nibble) {
 
 // Dropout (App. A) at block size 32: dropped codes are cleared in the packed dwords (a code of 0 dequantizes to
 // exactly 0), so the mask costs a few integer instructions per four elements and none per element.
+template <StorePolicy SP>
 __global__ void __launch_bounds__(64 * kStripWaves) dropout_strip32_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                              const uint8_t* __restrict__ mask, float keep_scale, int rows,
                                                              int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
@@ -557,24 +558,12 @@ __global__ void __launch_bounds__(64 * kStripWaves) dropout_strip32_kernel(const
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // ------------------------------------------------------------------------------------------------ host
-template <bool BWD, int B>
-static void launch_gelu_wave(const int8_t* X, const float* SX, const int8_t* G, const float* SG, int rows, int cols,
-                             int8_t* Y, float* SY, hipStream_t st) {
-  hipLaunchKernelGGL((gelu_wave_kernel<BWD, B>), dim3(tile_grid((cols / B + 3) / 4, rows / B)), dim3(256), 0, st, X, SX, G, SG,
-                     rows, cols, Y, SY);
-}
-template <bool BWD, int B, int J>
-static void launch_gelu_cfg(const int8_t* X, const float* SX, const int8_t* G, const float* SG, int rows, int cols,
-                            int8_t* Y, float* SY, hipStream_t st) {
-  hipLaunchKernelGGL((gelu_kernel<BWD, B, J>), dim3(tile_grid((cols + 128 * J - 1) / (128 * J), rows / B)), dim3(256), 0, st,
-                     X, SX, G, SG, rows, cols, Y, SY);
-}
 template <bool BWD>
 static void launch_gelu(int block, const int8_t* X, const float* SX, const int8_t* G, const float* SG, int rows,
                         int cols, int8_t* Y, float* SY, hipStream_t st) {
@@ -583,14 +572,18 @@ static void launch_gelu(int block, const int8_t* X, const float* SX, const int8_
   // bandwidth once the data comes from HBM: crossover near 100 M elements), beyond that one block per workgroup
   // column, in workgroups of 256 columns.  At B = 128 a lane already holds four 8-row passes of a 128-column workgroup.
   const int64_t n = (int64_t)rows * cols;
-  if (block == 128) launch_gelu_cfg<BWD, 128, 1>(X, SX, G, SG, rows, cols, Y, SY, st);
-  else if (block == 64) {
-    if (n <= (int64_t(64) << 20)) launch_gelu_wave<BWD, 64>(X, SX, G, SG, rows, cols, Y, SY, st);
-    else launch_gelu_cfg<BWD, 64, 2>(X, SX, G, SG, rows, cols, Y, SY, st);
-  } else {
-    hipLaunchKernelGGL((gelu_strip32_kernel<BWD>), strip_grid(rows, cols), dim3(64 * kStripWaves), 0, st, X, SX, G, SG,
-                       rows, cols, Y, SY);
-  }
+  with_store_policy(rows, cols, [&](auto sp) {
+    constexpr StorePolicy SP = decltype(sp)::value;
+    const auto tiles = [&](int width) { return dim3(tile_grid((cols + width - 1) / width, rows / block)); };
+    if (block == 128)
+      hipLaunchKernelGGL((gelu_kernel<BWD, 128, 1, SP>), tiles(128), dim3(256), 0, st, X, SX, G, SG, rows, cols, Y, SY);
+    else if (block == 64 && n <= (int64_t(64) << 20))
+      hipLaunchKernelGGL((gelu_wave_kernel<BWD, 64, SP>), tiles(4 * 64), dim3(256), 0, st, X, SX, G, SG, rows, cols, Y, SY);
+    else if (block == 64)
+      hipLaunchKernelGGL((gelu_kernel<BWD, 64, 2, SP>), tiles(256), dim3(256), 0, st, X, SX, G, SG, rows, cols, Y, SY);
+    else
+      hipLaunchKernelGGL((gelu_strip32_kernel<BWD, SP>), strip_grid(rows, cols), dim3(64 * kStripWaves), 0, st, X, SX, G, SG, rows, cols, Y, SY);
+  });
 }
 
 }  // namespace jf
@@ -627,11 +620,14 @@ extern "C" int32_t jf_dropout_q(const int8_t* X, const float* SX, const uint8_t*
   const dim3 grid(tile_grid((C + 127) / 128, N / block));
   const float keep_scale = (float)(1.0 / (1.0 - (double)p));
   const int rows = (int)N, cols = (int)C;
-  if (block == 32)
-    hipLaunchKernelGGL(dropout_strip32_kernel, strip_grid(N, C), dim3(64 * kStripWaves), 0, st, X, SX, mask_bits,
-                       keep_scale, rows, cols, Y, SY);
-  else if (block == 64) hipLaunchKernelGGL((dropout_kernel<64>), grid, dim3(256), 0, st, X, SX, mask_bits, keep_scale, rows, cols, Y, SY);
-  else hipLaunchKernelGGL((dropout_kernel<128>), grid, dim3(256), 0, st, X, SX, mask_bits, keep_scale, rows, cols, Y, SY);
+  with_store_policy(N, C, [&](auto sp) {
+    constexpr StorePolicy SP = decltype(sp)::value;
+    if (block == 32)
+      hipLaunchKernelGGL((dropout_strip32_kernel<SP>), strip_grid(N, C), dim3(64 * kStripWaves), 0, st, X, SX, mask_bits,
+                         keep_scale, rows, cols, Y, SY);
+    else if (block == 64) hipLaunchKernelGGL((dropout_kernel<64, SP>), grid, dim3(256), 0, st, X, SX, mask_bits, keep_scale, rows, cols, Y, SY);
+    else hipLaunchKernelGGL((dropout_kernel<128, SP>), grid, dim3(256), 0, st, X, SX, mask_bits, keep_scale, rows, cols, Y, SY);
+  });
   return launch_status();
 }
 
@@ -646,11 +642,14 @@ extern "C" int32_t jf_add_q(const int8_t* X1, const float* S1, const int8_t* X2,
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const dim3 grid(tile_grid((C + 127) / 128, N / block));
   const int rows = (int)N, cols = (int)C;
-  if (block == 32) {
-    const dim3 strips = strip_grid(N, C);
-    if (row_mean) hipLaunchKernelGGL((add_strip32_kernel<true>), strips, dim3(64 * kStripWaves), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
-    else hipLaunchKernelGGL((add_strip32_kernel<false>), strips, dim3(64 * kStripWaves), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
-  } else if (block == 64) hipLaunchKernelGGL((add_kernel<64>), grid, dim3(256), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
-  else hipLaunchKernelGGL((add_kernel<128>), grid, dim3(256), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
+  with_store_policy(N, C, [&](auto sp) {
+    constexpr StorePolicy SP = decltype(sp)::value;
+    if (block == 32) {
+      const dim3 strips = strip_grid(N, C);
+      if (row_mean) hipLaunchKernelGGL((add_strip32_kernel<true, SP>), strips, dim3(64 * kStripWaves), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
+      else hipLaunchKernelGGL((add_strip32_kernel<false, SP>), strips, dim3(64 * kStripWaves), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
+    } else if (block == 64) hipLaunchKernelGGL((add_kernel<64, SP>), grid, dim3(256), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
+    else hipLaunchKernelGGL((add_kernel<128, SP>), grid, dim3(256), 0, st, X1, S1, X2, S2, rows, cols, Y, SY, row_mean, row_sumsq);
+  });
   return launch_status();
 }

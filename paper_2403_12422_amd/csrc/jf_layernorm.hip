@@ -205,6 +205,7 @@ __global__ void __launch_bounds__(64 * WMAX) __attribute__((amdgpu_waves_per_eu(
 // that the first kernel left (one share per range of 2048 columns): dx = ug a_c + ux b + d with per-row
 // b = -rstd q2 sx rstd and d, and per-column a_c = rstd sg gamma_c (u = code + 128), then Eq. 1.  Rows may be of any
 // width.
+template <StorePolicy SP>
 __global__ void __launch_bounds__(64 * kStripWaves) layernorm_bwd_apply_strip32_kernel(
     const int8_t* __restrict__ G, const float* __restrict__ SG, const int8_t* __restrict__ X, const float* __restrict__ SX,
     const float* __restrict__ gamma, const float* __restrict__ mean_in, const float* __restrict__ rstd_in,
@@ -254,9 +255,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_bwd_apply_strip32_
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_out(&SdX[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_as<SP>(&SdX[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_out(dX + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < 4; ++p) store_as<SP>(dX + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // Row statistics of LayerNorm from the row partials that the preceding Add wrote (App. A, LayerNorm paragraph):
@@ -298,6 +299,7 @@ __global__ void __launch_bounds__(1024) row_stats_from_partials_kernel(const flo
 // LayerNorm at block size 32 from given row statistics (App. A: the operator is handed the row mean and rstd):
 // y = (x - mean) rstd gamma + beta on 32 x 128 strips, one wave each, like the other element-wise operators --
 // no workgroup needs a whole row, so rows may be of any width.
+template <StorePolicy SP>
 __global__ void __launch_bounds__(64 * kStripWaves) layernorm_apply_strip32_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                                      const float* __restrict__ gamma, const float* __restrict__ beta,
                                                                      const float* __restrict__ mean_in, const float* __restrict__ rstd_in,
@@ -333,9 +335,9 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_apply_strip32_kern
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_out(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_out(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // The same two element-wise operators at block sizes 64 and 128: one workgroup of four waves owns B rows x 128 columns
@@ -343,7 +345,7 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_apply_strip32_kern
 // strips (lane = (row l / 8, 16-byte chunk l % 8): full 128-byte lines); the block max-abs goes over the lanes of a
 // block column inside a wave and over the four waves through LDS.  MODE 0: y = (x - mean) rstd gamma + beta (forward),
 // MODE 1: dx from the row means of the sums kernel (backward).
-template <int B, int MODE>
+template <int B, int MODE, StorePolicy SP>
 __global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __restrict__ G, const float* __restrict__ SG,
                                                               const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                               const float* __restrict__ gamma, const float* __restrict__ beta,
@@ -407,11 +409,11 @@ __global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __res
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) store_out(&SY[(int64_t)bi * lc + col / B], scale);
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
-    store_out(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
+    store_as<SP>(Y + (int64_t)row * cols + col, quantize16(y[p], inv));
   }
 }
 
@@ -488,15 +490,18 @@ static int32_t layernorm_fwd(const int8_t* X, const float* SX, const float* row_
   if (rc != JF_OK) return rc;
   const dim3 tiles(tile_grid((C + 127) / 128, N / block));
   const float* none = nullptr;
-  if (block == 32)
-    hipLaunchKernelGGL(layernorm_apply_strip32_kernel, strip_grid(N, C), dim3(64 * kStripWaves), 0, st, X, SX, gamma, beta, mean,
-                       rstd, (int)N, (int)C, Y, SY);
-  else if (block == 64)
-    hipLaunchKernelGGL((layernorm_tile_kernel<64, 0>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, none, X, SX, gamma, beta,
-                       (const float*)mean, (const float*)rstd, none, 1, (int)N, (int)C, Y, SY);
-  else
-    hipLaunchKernelGGL((layernorm_tile_kernel<128, 0>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, none, X, SX, gamma, beta,
-                       (const float*)mean, (const float*)rstd, none, 1, (int)N, (int)C, Y, SY);
+  with_store_policy(N, C, [&](auto sp) {
+    constexpr StorePolicy SP = decltype(sp)::value;
+    if (block == 32)
+      hipLaunchKernelGGL((layernorm_apply_strip32_kernel<SP>), strip_grid(N, C), dim3(64 * kStripWaves), 0, st, X, SX, gamma, beta, mean,
+                         rstd, (int)N, (int)C, Y, SY);
+    else if (block == 64)
+      hipLaunchKernelGGL((layernorm_tile_kernel<64, 0, SP>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, none, X, SX, gamma, beta,
+                         (const float*)mean, (const float*)rstd, none, 1, (int)N, (int)C, Y, SY);
+    else
+      hipLaunchKernelGGL((layernorm_tile_kernel<128, 0, SP>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, none, X, SX, gamma, beta,
+                         (const float*)mean, (const float*)rstd, none, 1, (int)N, (int)C, Y, SY);
+  });
   return launch_status();
 }
 
@@ -542,15 +547,18 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
   if (rc1 != JF_OK) return rc1;
   const dim3 tiles(tile_grid((C + 127) / 128, N / block));
   const float* none = nullptr;
-  if (block == 32)
-    hipLaunchKernelGGL(layernorm_bwd_apply_strip32_kernel, strip_grid(N, C), dim3(64 * kStripWaves), 0, st, dY, SdY, X, SX, gamma,
-                       mean, rstd, row_means, ranges, (int)N, (int)C, dX, SdX);
-  else if (block == 64)
-    hipLaunchKernelGGL((layernorm_tile_kernel<64, 1>), tiles, dim3(256), 0, st, dY, SdY, X, SX, gamma, none, mean, rstd,
-                       (const float*)row_means, ranges, (int)N, (int)C, dX, SdX);
-  else
-    hipLaunchKernelGGL((layernorm_tile_kernel<128, 1>), tiles, dim3(256), 0, st, dY, SdY, X, SX, gamma, none, mean, rstd,
-                       (const float*)row_means, ranges, (int)N, (int)C, dX, SdX);
+  with_store_policy(N, C, [&](auto sp) {
+    constexpr StorePolicy SP = decltype(sp)::value;
+    if (block == 32)
+      hipLaunchKernelGGL((layernorm_bwd_apply_strip32_kernel<SP>), strip_grid(N, C), dim3(64 * kStripWaves), 0, st, dY, SdY, X, SX, gamma,
+                         mean, rstd, row_means, ranges, (int)N, (int)C, dX, SdX);
+    else if (block == 64)
+      hipLaunchKernelGGL((layernorm_tile_kernel<64, 1, SP>), tiles, dim3(256), 0, st, dY, SdY, X, SX, gamma, none, mean, rstd,
+                         (const float*)row_means, ranges, (int)N, (int)C, dX, SdX);
+    else
+      hipLaunchKernelGGL((layernorm_tile_kernel<128, 1, SP>), tiles, dim3(256), 0, st, dY, SdY, X, SX, gamma, none, mean, rstd,
+                         (const float*)row_means, ranges, (int)N, (int)C, dX, SdX);
+  });
   const int32_t rc = launch_status();
   if (rc != JF_OK) return rc;
   hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((2 * C + 63) / 64)), dim3(1024), 0, st, partials, nparts, (int)(2 * C), dgamma, dbeta);

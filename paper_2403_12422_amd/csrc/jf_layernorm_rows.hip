@@ -45,9 +45,15 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// 16 bytes per lane at a scalar base and a 32-bit lane offset, written through (see store_out)
-__device__ __forceinline__ void store_out_at(int8_t* uniform_base, uint32_t off, v4i v) {
-  asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" : : "v"(off), "v"(v), "s"(uniform_base) : "memory");
+// 16 bytes per lane at a scalar base and a 32-bit lane offset (see store_out, store_as)
+template <StorePolicy SP>
+__device__ __forceinline__ void store_as_at(int8_t* uniform_base, uint32_t off, v4i v) {
+  typedef __attribute__((address_space(1))) int8_t* gbl_ptr;
+  typedef __attribute__((address_space(1))) v4i* gbl_v4i;
+  const gbl_v4i p = (gbl_v4i)((gbl_ptr)uniform_base + off);
+  if constexpr (SP == kStoreThrough) asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" : : "v"(off), "v"(v), "s"(uniform_base) : "memory");
+  else if constexpr (SP == kStoreStream) __builtin_nontemporal_store(v, p);
+  else *p = v;
 }
 
 // Signed codes of one packed dword as floats (a byte-select conversion each).
@@ -81,7 +87,7 @@ constexpr int kFwdScale = 4096, kFwdPart = kFwdScale + 256, kFwdGamma = kFwdPart
               kFwdStat = kFwdBeta + 512, kFwdWaveBytes = kFwdStat + 256;
 constexpr int kFwdRowBytes = 2 * 32 * 16;   // per wave: two copies (alternate row groups) of a sum pair for each of 32 rows
 
-template <bool PARTIALS>
+template <bool PARTIALS, StorePolicy SP>
 __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRows a) {
   extern __shared__ __align__(16) int8_t smem[];
   const RowWave t(a.cols, a.strips);
@@ -211,8 +217,8 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
       // uniform base + 32-bit lane offset, like the loads: no 64-bit lane addresses to keep
       int8_t* const out = uniform_pointer(a.Y + (int64_t)g * 32 * a.cols);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) store_out_at(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_out(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)) + off_scale, scale);
+      for (int p = 0; p < 4; ++p) store_as_at<SP>(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
+      if ((t.lane & 57) == 0) store_as<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)) + off_scale, scale);
     }
   }
 }
@@ -224,6 +230,7 @@ constexpr int kBwdRowBytes = 2 * 32 * 8;
 
 // dx = rstd (ghat - mean_C(ghat) - xhat mean_C(ghat xhat)) with ghat = g gamma, xhat = (x - mean) rstd; the column sums
 // of g xhat and g stay in registers over all row groups and end as one partial row of dgamma | dbeta per workgroup.
+template <StorePolicy SP>
 __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNormBwdRows a) {
   extern __shared__ __align__(16) int8_t smem[];
   const RowWave t(a.cols, a.strips);
@@ -379,8 +386,8 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
       // uniform base + 32-bit lane offset, like the loads: no 64-bit lane addresses to keep
       int8_t* const out = uniform_pointer(a.dX + (int64_t)g * 32 * a.cols);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) store_out_at(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_out(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)) + off_scale, scale);
+      for (int p = 0; p < 4; ++p) store_as_at<SP>(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
+      if ((t.lane & 57) == 0) store_as<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)) + off_scale, scale);
     }
   }
 
@@ -422,10 +429,12 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
 }
 
 // ------------------------------------------------------------------------------------------------ host
-// A launch needs more LDS than a kernel gets by default; the limit is raised once per process (for every device).
-template <class Kernel>
-static bool allow_lds(Kernel kernel, size_t bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+// A launch needs more LDS than a kernel gets by default; the limit is raised once per kernel and process (for every device).
+template <auto KERNEL, class Args>
+static void launch_rows(size_t wave_bytes, int grid, int waves, const Args& a, hipStream_t st) {
+  static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(16 * wave_bytes));
+  (void)raised;   // a limit that could not be raised is reported by the launch
+  hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(64 * waves), waves * wave_bytes, st, a);
 }
 
 // Teams per workgroup, one workgroup per compute unit.  The waves of a workgroup are dealt to the four SIMDs in turn, so
@@ -448,16 +457,10 @@ void launch_layernorm_rows(LayerNormRows a, hipStream_t st) {
   a.inv_cols = 1.0 / (double)a.cols;
   a.inv_blocks = 1.0 / (double)(a.cols / 32);
   const int waves = a.strips * a.teams, grid = std::min((groups + a.teams - 1) / a.teams, 256);
-  const size_t lds = (size_t)waves * (kFwdRowBytes + kFwdWaveBytes);
-  if (a.row_mean) {
-    static const bool ok = allow_lds(layernorm_rows_kernel<true>, 16 * (kFwdRowBytes + kFwdWaveBytes));
-    (void)ok;
-    hipLaunchKernelGGL(layernorm_rows_kernel<true>, dim3(grid), dim3(64 * waves), lds, st, a);
-  } else {
-    static const bool ok = allow_lds(layernorm_rows_kernel<false>, 16 * (kFwdRowBytes + kFwdWaveBytes));
-    (void)ok;
-    hipLaunchKernelGGL(layernorm_rows_kernel<false>, dim3(grid), dim3(64 * waves), lds, st, a);
-  }
+  with_store_policy(a.rows, a.cols, [&](auto sp) {
+    if (a.row_mean) launch_rows<layernorm_rows_kernel<true, decltype(sp)::value>>(kFwdRowBytes + kFwdWaveBytes, grid, waves, a, st);
+    else launch_rows<layernorm_rows_kernel<false, decltype(sp)::value>>(kFwdRowBytes + kFwdWaveBytes, grid, waves, a, st);
+  });
 }
 
 int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st) {
@@ -467,9 +470,9 @@ int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st) {
   a.inv_cols = 1.0f / (float)a.cols;
   const int waves = a.strips * a.teams, grid = std::min((groups + a.teams - 1) / a.teams, 256);
   static_assert(16 * (kBwdRowBytes + kBwdWaveBytes) <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
-  static const bool ok = allow_lds(layernorm_bwd_rows_kernel, 16 * (kBwdRowBytes + kBwdWaveBytes));
-  (void)ok;
-  hipLaunchKernelGGL(layernorm_bwd_rows_kernel, dim3(grid), dim3(64 * waves), (size_t)waves * (kBwdRowBytes + kBwdWaveBytes), st, a);
+  with_store_policy(a.rows, a.cols, [&](auto sp) {
+    launch_rows<layernorm_bwd_rows_kernel<decltype(sp)::value>>(kBwdRowBytes + kBwdWaveBytes, grid, waves, a, st);
+  });
   return grid;
 }
 

@@ -22,7 +22,7 @@ __device__ __forceinline__ void load_vec(const _Float16* p, float (&v)[8]) {
 // B = quantization block; the tile is 128 x 128 and 256 threads (WPW = 4 waves per workgroup), or, for small
 // tensors at B = 32 where the waves do not depend on each other, one 32 x 128 strip and one wave (WPW = 1), which
 // spreads a tensor of a few hundred tiles over all compute units.
-template <typename T, int B, bool TRANSPOSED_COPY, int WPW = 4>
+template <typename T, int B, bool TRANSPOSED_COPY, int WPW, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict__ x, int64_t ldx, int rows, int cols,
                                                         int8_t* __restrict__ q, int64_t ldq, float* __restrict__ s,
                                                         int8_t* __restrict__ qT, int64_t ldqT, float* __restrict__ sT) {
@@ -77,8 +77,8 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
   // one lane per block writes the scale: the top-left 32-granule of the block
   if (group_first && col_ok && r0 < rows && (r0 % B) == 0 && ((c0 + 32 * cg) % B) == 0) {
     const int bi = r0 / B, bj = (c0 + 32 * cg) / B;
-    store_out(&s[(int64_t)bi * lc + bj], scale);
-    if (TRANSPOSED_COPY) store_out(&sT[(int64_t)bj * lr + bi], scale);
+    store_as<SP>(&s[(int64_t)bi * lc + bj], scale);
+    if (TRANSPOSED_COPY) store_as<SP>(&sT[(int64_t)bj * lr + bi], scale);
   }
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -88,8 +88,8 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
     for (int k = 0; k < VEC / 4; ++k)
       packed[k] = quantize4(v[i][4 * k], v[i][4 * k + 1], v[i][4 * k + 2], v[i][4 * k + 3], inv);
     if (col_ok && row < rows) {
-      if constexpr (VEC == 4) store_out(q + (int64_t)row * ldq + col, packed[0]);
-      else store_out(q + (int64_t)row * ldq + col, v2i{(int)packed[0], (int)packed[1]});
+      if constexpr (VEC == 4) store_as<SP>(q + (int64_t)row * ldq + col, packed[0]);
+      else store_as<SP>(q + (int64_t)row * ldq + col, v2i{(int)packed[0], (int)packed[1]});
     }
     if (TRANSPOSED_COPY) {
 #pragma unroll
@@ -120,18 +120,22 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
 template <typename T, int B>
 static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t* q, int64_t ldq, float* s, int8_t* qT,
                             int64_t ldqT, float* sT, hipStream_t st) {
-  dim3 grid(tile_grid((cols + 127) / 128, (rows + 127) / 128));
-  if constexpr (B == 32) {
-    if (!qT && grid.x < 512) {  // fewer than two workgroups per compute unit: one wave per workgroup instead
-      hipLaunchKernelGGL((quantize_kernel<T, B, false, 1>), dim3(tile_grid((cols + 127) / 128, rows / 32)), dim3(64), 0, st, x,
-                         ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
+  const dim3 grid(tile_grid((cols + 127) / 128, (rows + 127) / 128));
+  with_store_policy(rows, ldq, [&](auto sp) {
+    constexpr StorePolicy SP = decltype(sp)::value;
+    if (qT) {
+      hipLaunchKernelGGL((quantize_kernel<T, B, true, 4, SP>), grid, dim3(256), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
       return;
     }
-  }
-  if (qT)
-    hipLaunchKernelGGL((quantize_kernel<T, B, true>), grid, dim3(256), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
-  else
-    hipLaunchKernelGGL((quantize_kernel<T, B, false>), grid, dim3(256), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
+    if constexpr (B == 32 && SP == kStoreThrough) {
+      if (grid.x < 512) {  // fewer than two workgroups per compute unit: one wave per workgroup instead
+        hipLaunchKernelGGL((quantize_kernel<T, B, false, 1, SP>), dim3(tile_grid((cols + 127) / 128, rows / 32)), dim3(64), 0, st, x,
+                           ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((quantize_kernel<T, B, false, 4, SP>), grid, dim3(256), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
+  });
 }
 
 template <typename T>
@@ -148,7 +152,7 @@ static void dispatch_quantize(int block, const T* x, int64_t ldx, int rows, int 
 // codes and scales are requested before the first is used; rows follow each other without a gap, so that no lane idles at
 // their ends.  The quotient chunk / (chunks per row) is formed once per workgroup in 64 bits and per chunk in 32.
 static constexpr int DQ_CHUNKS = 4;
-template <typename T>
+template <typename T, StorePolicy SP>
 __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restrict__ q, const float* __restrict__ s, int rows,
                                                           int cols, int block_log2, T* __restrict__ out, int64_t ldo) {
   constexpr int VEC = 16 / sizeof(T);
@@ -183,7 +187,7 @@ __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restric
       else w = p[u];
       v[b] = (T)(byte_to_float(w, b & 3) * sc[u]);
     }
-    store_out(out + (int64_t)row[u] * ldo + col[u], v);
+    store_as<SP>(out + (int64_t)row[u] * ldo + col[u], v);
   }
 }
 
@@ -201,12 +205,15 @@ extern "C" int32_t jf_dequantize_block(const int8_t* q, const float* s, int64_t 
   const int log2b = block == 32 ? 5 : (block == 64 ? 6 : 7);
   const int64_t per_wg = 256 * DQ_CHUNKS * (out_dtype == 0 ? 4 : 8);
   const unsigned grid = (unsigned)((rows * cols + per_wg - 1) / per_wg);
-  if (out_dtype == 0)
-    hipLaunchKernelGGL((dequantize_kernel<float>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
-                       static_cast<float*>(out), ldo);
-  else
-    hipLaunchKernelGGL((dequantize_kernel<_Float16>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
-                       static_cast<_Float16*>(out), ldo);
+  with_store_policy(rows, ldo * (out_dtype == 0 ? 4 : 2), [&](auto sp) {
+    constexpr StorePolicy SP = decltype(sp)::value;
+    if (out_dtype == 0)
+      hipLaunchKernelGGL((dequantize_kernel<float, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
+                         static_cast<float*>(out), ldo);
+    else
+      hipLaunchKernelGGL((dequantize_kernel<_Float16, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
+                         static_cast<_Float16*>(out), ldo);
+  });
   return launch_status();
 }
 
