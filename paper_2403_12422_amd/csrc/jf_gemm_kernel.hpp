@@ -245,13 +245,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   const int8_t* baseA = uniform_pointer(g.A + originA);
   const int8_t* baseB = uniform_pointer(g.Bm + originB);
   const int64_t kstrideA = AK ? 1 : g.lda, kstrideB = BK ? 1 : g.ldb;
-  // Issue the direct-to-LDS loads of the next stage into ring slot `slot`.  There is no separate code for the end of the
+  // Issue the direct-to-LDS loads of the next stage into ring slot `slot`, one at a time.  There is no separate code for the end of the
   // loop: past the last stage every lane loads the same valid address, so that the counts of outstanding loads never
   // change.  (The straight-line tails this replaces made the kernels 3-4 times as long, and code that runs once is
   // fetched once: 64 KB of it cost a product of 12 stages 2 us.)
+  constexpr int LOADS = CA + CB;   // vector-memory instructions per wave and stage
   int next = 0;
-  auto issue = [&](int slot) __attribute__((always_inline)) {
-    if (next >= nstages - 1) {
+  auto issue_load = [&](int slot, int n) __attribute__((always_inline)) {   // load n of stage `next`
+    if (n == 0 && next >= nstages - 1) {
       if (next == nstages - 1) {
         baseA -= (int64_t)(overlap * B) * kstrideA;
         baseB -= (int64_t)(overlap * B) * kstrideB;
@@ -265,13 +266,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
       }
     }
     const int byte = slot * STAGE_BYTES + 1024 * wave;
-#pragma unroll
-    for (int i = 0; i < CA; ++i) load_lds_16(baseA, offA[i], s_ring, byte + 1024 * i * NW);
-#pragma unroll
-    for (int i = 0; i < CB; ++i) load_lds_16(baseB, offB[i], s_ring, byte + A_BYTES + 1024 * i * NW);
-    baseA += KC * kstrideA;
-    baseB += KC * kstrideB;
-    ++next;
+    if (n < CA) load_lds_16(baseA, offA[n], s_ring, byte + 1024 * n * NW);
+    else load_lds_16(baseB, offB[n - CA], s_ring, byte + A_BYTES + 1024 * (n - CA) * NW);
+    if (n + 1 == LOADS) {
+      baseA += KC * kstrideA;
+      baseB += KC * kstrideB;
+      ++next;
+    }
   };
 
   FragAddr<TM, AK, KC, WM> addrA;
@@ -303,7 +304,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   // Stage loop over the ring of NBUF LDS buffers: while stage t is computed, stages t+1 .. t+NBUF-1 are in flight,
   // which covers the L2 latency even when a stage is only two K steps long.  The loop is unrolled NBUF times so that every
   // LDS address is a compile-time immediate and the accumulators stay in the same registers.
-  constexpr int LOADS = CA + CB;   // vector-memory instructions per wave and stage
   static_assert(LOADS * (NBUF - 1) <= 63, "vmcnt immediate");
   // Wait for this wave's own loads of all but the youngest `stages` stages and for its LDS reads, then meet the other
   // waves.  A bare s_barrier is used instead of __syncthreads(): the fence of the latter makes the compiler drain
@@ -369,11 +369,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   // read all at once after the barrier they hold up the vector ALU, which they share register ports with.
   //   STEPWISE (B = 32, several sub-blocks per wave): the fragments of one K step are read while the units of the K step
   //     before are folded; two register sets, one per K step of the stage.  The barrier stands before the last K step.
+  //   ONE_SET (2x2 sub-blocks at B = 64, where two sets do not fit three waves per SIMD): those of the next stage into
+  //     the registers that come out of use, beside the last two units.  The barrier stands before them.
   //   otherwise: those of one stage while the stage before is folded; two sets, one per stage.  The barrier comes first.
   static_assert(SPS % KPB == 0 && (NKB * NTILE) % 2 == 0, "a stage leaves the tile rotation where it found it");
   constexpr int NT = NKB * NTILE;   // units per stage
   constexpr bool STEPWISE = GemmPipeline<B, WM, WN>::STEPWISE, ONE_SET = GemmPipeline<B, WM, WN>::ONE_SET;
   static_assert(!STEPWISE || (KPB == 1 && SPS % 2 == 0), "the register sets alternate");
+  static_assert(!ONE_SET || (WM == 2 && WN == 2 && NT == 4), "the order in which fragments come out of use");
   constexpr int SETS = STEPWISE || !ONE_SET ? 2 : 1, STEPS = STEPWISE ? 1 : SPS;   // register sets, K steps in each
   v16i vi[2];
   v4i fa[SETS][STEPS][WM], fb[SETS][STEPS][WN];
@@ -413,52 +416,62 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   auto run_stage = [&](int t, auto u_tag) __attribute__((always_inline)) {
     constexpr int u = decltype(u_tag)::value, slot = u % NBUF, nslot = (u + 1) % NBUF;
     constexpr int set = ONE_SET ? 0 : u & 1, nset = ONE_SET ? 0 : set ^ 1;
+    constexpr int SYNC = STEPWISE ? (SPS - 1) * NTILE : ONE_SET ? NT - 2 : 0;   // the unit before which the waves meet
+    constexpr bool SPREAD_LOADS = B == 128;
     static_for<0, NT>([&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value, kb = i / NTILE, q = i % NTILE;
       v16i &cur = vi[i & 1], &nxt = vi[(i & 1) ^ 1];
-      if constexpr (i == (STEPWISE ? (SPS - 1) * NTILE : ONE_SET ? NT - 1 : 0)) {
-        wait_stage(std::integral_constant<int, NBUF - 2>());
-        issue(slot);                       // the stage NBUF ahead, into the slot this one has left
-      }
+      if constexpr (i == SYNC) wait_stage(std::integral_constant<int, NBUF - 2>());
+      // The loads of the stage NBUF ahead, into the slot that this one has left: all at once, or, from the eight waves of
+      // a compute unit's only workgroup, one after another over the units -- requested together they wait for each other
+      // there, and the MFMAs behind them with them (8192 x 4096 -> 8192 at B = 128 320 -> 312 us; the other shapes, whose
+      // workgroups are out of step, lose 1-5 % by it).
+      auto loads = [&](auto js_tag) __attribute__((always_inline)) {
+        constexpr int p0 = SYNC * KPB, P = SPREAD_LOADS ? NT * KPB - p0 : 1, at = i * KPB + decltype(js_tag)::value - p0;
+        static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) {
+          if constexpr (decltype(n)::value * P / LOADS == at) issue_load(slot, decltype(n)::value);
+        });
+      };
+      if constexpr (!SPREAD_LOADS) loads(std::integral_constant<int, 0>());
       const float s = scale;
       scale = scale_of(first + u * NKB, i + 1);
-      if constexpr (ONE_SET && i + 1 == NT) {
-        static_for<0, SPS * READS>([&](auto n) __attribute__((always_inline)) {
-          read_frag(nslot, 0, decltype(n)::value / READS, decltype(n)::value % READS);
-        });
-        static_for<0, KPB>([&](auto js) __attribute__((always_inline)) { fold_or_dump(t, i, cur, s, js); });
+      static_for<0, KPB>([&](auto js_tag) __attribute__((always_inline)) {
+        constexpr int js = decltype(js_tag)::value;
+        if constexpr (i + 1 < NT) chain_step(set, i + 1, js, nxt);
+        else chain_step(nset, 0, js, nxt);
         __builtin_amdgcn_sched_barrier(0);
-        static_for<0, KPB>([&](auto js) __attribute__((always_inline)) { chain_step(0, 0, decltype(js)::value, nxt); });
-      } else {
-        static_for<0, KPB>([&](auto js_tag) __attribute__((always_inline)) {
-          constexpr int js = decltype(js_tag)::value;
-          if constexpr (i + 1 < NT) chain_step(set, i + 1, js, nxt);
-          else chain_step(nset, 0, js, nxt);
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (STEPWISE) {   // the next K step's reads: all but the last unit of this one share them
-            constexpr int U = NTILE - 1;
-            static_for<0, READS>([&](auto n_tag) __attribute__((always_inline)) {
-              constexpr int n = decltype(n_tag)::value;
-              if constexpr (n * U / READS == q) read_frag(kb + 1 < SPS ? slot : nslot, (kb + 1) % 2, (kb + 1) % SPS, n);
-            });
-          } else if constexpr (!ONE_SET) {   // the next stage's reads, over all but the last unit and the MFMAs of their chains
-            constexpr int P = (NT - 1) * KPB, R = SPS * READS;
-            static_for<0, R>([&](auto n_tag) __attribute__((always_inline)) {
-              constexpr int n = decltype(n_tag)::value;
-              if constexpr (n * P / R == i * KPB + js) read_frag(nslot, nset, n / READS, n % READS);
-            });
-          }
-          fold_or_dump(t, i, cur, s, js_tag);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      }
+        if constexpr (STEPWISE) {   // the next K step's reads: all but the last unit of this one share them
+          constexpr int U = NTILE - 1;
+          static_for<0, READS>([&](auto n_tag) __attribute__((always_inline)) {
+            constexpr int n = decltype(n_tag)::value;
+            if constexpr (n * U / READS == q) read_frag(kb + 1 < SPS ? slot : nslot, (kb + 1) % 2, (kb + 1) % SPS, n);
+          });
+        } else if constexpr (ONE_SET) {
+          // the next stage's, as this one's come out of use: those of sub-block 0 beside the last unit but one, the
+          // rest, which the chain issued in that unit has read, beside the last
+          static_for<0, SPS>([&](auto j_tag) __attribute__((always_inline)) {
+            constexpr int j = decltype(j_tag)::value;
+            if constexpr (j % KPB == js && i == NT - 2) read_frag(nslot, 0, j, 0), read_frag(nslot, 0, j, WM);
+            if constexpr (j % KPB == js && i == NT - 1) read_frag(nslot, 0, j, 1), read_frag(nslot, 0, j, WM + 1);
+          });
+        } else {   // the next stage's reads, over all but the last unit and the MFMAs of their chains
+          constexpr int P = (NT - 1) * KPB, R = SPS * READS;
+          static_for<0, R>([&](auto n_tag) __attribute__((always_inline)) {
+            constexpr int n = decltype(n_tag)::value;
+            if constexpr (n * P / R == i * KPB + js) read_frag(nslot, nset, n / READS, n % READS);
+          });
+        }
+        if constexpr (SPREAD_LOADS) loads(js_tag);
+        fold_or_dump(t, i, cur, s, js_tag);
+        __builtin_amdgcn_sched_barrier(0);
+      });
     });
   };
 
   static_assert(NBUF >= 3, "two stages in flight beside the one in use");
   issue_scales(0);
 #pragma unroll 1
-  for (int t = 0; t < NBUF; ++t) issue(t);
+  for (int t = 0; t < NBUF; ++t) static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { issue_load(t, decltype(n)::value); });
   wait_stage(std::integral_constant<int, NBUF - 1>());
   read_scales(0);
   if (nkb > SEG) issue_scales(1);
