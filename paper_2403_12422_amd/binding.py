@@ -115,75 +115,75 @@ def jf_quantize_block(x, block=32, transposed_copy=False, out=None):
 
     `out` (here and in every function below) is an optional tuple of preallocated output tensors, in the
     order they are returned; without it the outputs are allocated with torch."""
-    return _native().quantize(x, block, transposed_copy, out)
+    return (_ext or _native()).quantize(x, block, transposed_copy, out)
 
 
 def jf_dequantize_block(q, s, block=32, dtype=torch.float32, out=None):
     """(codes, scales) -> float32 or float16 tensor of code * scale."""
     if dtype not in (torch.float32, torch.float16):
         raise JetfireError(7, "output must be float32 or float16")
-    return _native().dequantize(q, s, block, dtype == torch.float16, out)
+    return (_ext or _native()).dequantize(q, s, block, dtype == torch.float16, out)
 
 
 def jf_linear_fwd(X, SX, W, SW, block=32, want_f32=False, out=None):
     """Y = X W^T.  X (N,C) int8, W (D,C) int8 -> (Y int8 (N,D), SY, Y_f32 or None)."""
-    return _native().linear_fwd(X, SX, W, SW, block, want_f32, out)
+    return (_ext or _native()).linear_fwd(X, SX, W, SW, block, want_f32, out)
 
 
 def jf_linear_dgrad(dY, SdY, W, SW, block=32, want_f32=False, out=None):
     """dX = dY W.  dY (N,D) int8, W (D,C) int8 -> (dX int8 (N,C), SdX, dX_f32 or None)."""
-    return _native().linear_dgrad(dY, SdY, W, SW, block, want_f32, out)
+    return (_ext or _native()).linear_dgrad(dY, SdY, W, SW, block, want_f32, out)
 
 
 def jf_linear_wgrad(dY, SdY, X, SX, block=32, want_q=True, want_f32=False, out=None):
     """dW = dY^T X.  dY (N,D) int8, X (N,C) int8 -> (dW int8 (D,C) or None, SdW or None, dW_f32 or None)."""
-    return _native().linear_wgrad(dY, SdY, X, SX, block, want_q, want_f32, out)
+    return (_ext or _native()).linear_wgrad(dY, SdY, X, SX, block, want_q, want_f32, out)
 
 
 def jf_linear_bwd(dY, SdY, W, SW, X, SX, block=32, want_f32=False, out=None):
     """Both backward products in one call: returns ((dX, SdX, dX_f32 or None), (dW, SdW, dW_f32 or None)); `out` is the
     same pair of triples, preallocated."""
-    return _native().linear_bwd(dY, SdY, W, SW, X, SX, block, want_f32, out)
+    return (_ext or _native()).linear_bwd(dY, SdY, W, SW, X, SX, block, want_f32, out)
 
 
 def jf_gelu_q(X, SX, block=32, out=None):
-    return _native().gelu(X, SX, block, out)
+    return (_ext or _native()).gelu(X, SX, block, out)
 
 
 def jf_gelu_q_bwd(dY, SdY, X, SX, block=32, out=None):
-    return _native().gelu_bwd(dY, SdY, X, SX, block, out)
+    return (_ext or _native()).gelu_bwd(dY, SdY, X, SX, block, out)
 
 
 def jf_layernorm_q(X, SX, gamma, beta, eps=1e-5, block=32, out=None):
-    return _native().layernorm(X, SX, None, None, gamma, beta, eps, block, out)
+    return (_ext or _native()).layernorm(X, SX, None, None, gamma, beta, eps, block, out)
 
 
 def jf_layernorm_q_partials(X, SX, row_mean, row_sumsq, gamma, beta, eps=1e-5, block=32, out=None):
     """LayerNorm whose row statistics come from the row partials written by jf_add_q."""
     if row_mean is None or row_sumsq is None:
         raise JetfireError(1, "row_mean and row_sumsq are required")
-    return _native().layernorm(X, SX, row_mean, row_sumsq, gamma, beta, eps, block, out)
+    return (_ext or _native()).layernorm(X, SX, row_mean, row_sumsq, gamma, beta, eps, block, out)
 
 
 def jf_dropout_q(X, SX, mask_bits, p, block=32, out=None):
     """Y = Q(X * m / (1 - p)); mask_bits (N, C/8) uint8, bit c % 8 of byte c // 8 of a row is column c's keep bit."""
-    return _native().dropout(X, SX, mask_bits, p, block, out)
+    return (_ext or _native()).dropout(X, SX, mask_bits, p, block, out)
 
 
 def jf_add_q(X1, S1, X2, S2, block=32, want_partials=False, out=None):
     """Y = Q(X1 + X2); with want_partials also the row partials (mean, sum of squares) of the sum, stored block column by
     block column: two (C/block, N) tensors."""
-    return _native().add(X1, S1, X2, S2, block, want_partials, out)
+    return (_ext or _native()).add(X1, S1, X2, S2, block, want_partials, out)
 
 
 def jf_layernorm_q_bwd(dY, SdY, X, SX, gamma, mean, rstd, block=32, workspace=None, out=None):
-    return _native().layernorm_bwd(dY, SdY, X, SX, gamma, mean, rstd, block, workspace, out, False)
+    return (_ext or _native()).layernorm_bwd(dY, SdY, X, SX, gamma, mean, rstd, block, workspace, out, False)
 
 
 def jf_layernorm_q_bwd_static(dY, SdY, X, SX, gamma, mean, rstd, out, block=32):
     """jf_layernorm_q_bwd without a workspace: the library's static device scratch holds the partial sums, and
     nothing is allocated -- `out` = (dX, SdX, dgamma, dbeta), preallocated, is therefore required."""
-    return _native().layernorm_bwd(dY, SdY, X, SX, gamma, mean, rstd, block, None, out, True)
+    return (_ext or _native()).layernorm_bwd(dY, SdY, X, SX, gamma, mean, rstd, block, None, out, True)
 
 
 def jf_debug_linear_partials(which, A, Bm, N, C, D, block, kb):
