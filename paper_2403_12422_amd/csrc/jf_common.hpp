@@ -49,8 +49,8 @@ inline bool valid_size(int64_t rows, int64_t cols) { return rows * cols <= (int6
 struct TileIndex {
   int x, y;  // column group, row group
 };
-__device__ __forceinline__ TileIndex tile_of_workgroup(int column_groups) {
-  const unsigned i = blockIdx.x;
+__device__ __forceinline__ TileIndex tile_of_workgroup(int column_groups, unsigned first = 0) {   // first: workgroups before the tiles
+  const unsigned i = blockIdx.x - first;
   TileIndex t;
   t.x = (int)(i % (unsigned)column_groups);
   t.y = (int)(i / (unsigned)column_groups);

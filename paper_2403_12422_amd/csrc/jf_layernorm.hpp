@@ -34,13 +34,14 @@ struct LayerNormBwdRows {
   const float *SX, *gamma, *mean, *rstd;
   int rows, cols;
   int8_t* dX;
-  float *SdX, *partials;
-  int strips, teams;
+  float *SdX, *partials, *dgamma, *dbeta;
+  int strips, teams, row_wgs;     // row_wgs: workgroups that own rows; those behind them own columns
   float inv_cols;
 };
 
 // Whether the one-pass kernels take rows of C columns at this block size, and their launches.  The backward one returns
-// the number of partial rows of dgamma | dbeta that it leaves in `partials` (at most 256 and at most rows / 32).
+// the number of partial rows of dgamma | dbeta that it leaves in `partials` (at most 256 and at most rows / 32), or 0 if it
+// has written dgamma and dbeta themselves.
 bool layernorm_rows_fits(int64_t C, int32_t block);
 void launch_layernorm_rows(LayerNormRows a, hipStream_t st);
 int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st);

@@ -228,11 +228,63 @@ constexpr int kBwdG = 4096, kBwdScaleX = 8192, kBwdScaleG = kBwdScaleX + 256, kB
               kBwdGamma = kBwdRstd + 128, kBwdMeans = kBwdGamma + 512, kBwdWaveBytes = kBwdMeans + 256;
 constexpr int kBwdRowBytes = 2 * 32 * 8;
 
+// dgamma and dbeta of one block column straight from g and x: a lane owns 16 columns of row l % 32 of its wave's row groups.
+// The column sums need nothing of the row pass, only its operands a second time, which for a short tensor come out of L2:
+// up to 2048 rows this saves the launch that adds the partial rows (512 x 544: 16.2 -> 13.3 us forward and backward), and
+// the row pass 8 of its 20 instructions per element.  Beyond that, or with few waves in a workgroup (2048 x 160: two), the
+// workgroups of the few block columns take longer than the row pass.
+__device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, int group, float* s_sum) {
+  const int lane = threadIdx.x & 63, row = lane & 31, waves = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = group * 32 + 16 * (lane >> 5), lc = a.cols / 32;
+  float sgx[16], sgb[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) sgx[e] = sgb[e] = 0.0f;
+  for (int g = wave; g < a.rows / 32; g += waves) {
+    const int64_t at = (int64_t)(g * 32 + row) * a.cols + col;
+    const uint4 px = *reinterpret_cast<const uint4*>(a.X + at), pg = *reinterpret_cast<const uint4*>(a.G + at);
+    const float rs = a.rstd[g * 32 + row], sg = a.SG[(int64_t)g * lc + group];
+    const float kx = a.SX[(int64_t)g * lc + group] * rs, cx = -a.mean[g * 32 + row] * rs;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      float x[4], gr[4];
+      unpack4(dword_of(px, d), x);
+      unpack4(dword_of(pg, d), gr);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float gv = gr[e] * sg;
+        sgx[4 * d + e] = __builtin_fmaf(gv, __builtin_fmaf(x[e], kx, cx), sgx[4 * d + e]);
+        sgb[4 * d + e] += gv;
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    sgx[e] = wave_group_sum<31>(sgx[e]);
+    sgb[e] = wave_group_sum<31>(sgb[e]);
+    if (row == 0) {
+      s_sum[64 * wave + 16 * (lane >> 5) + e] = sgx[e];
+      s_sum[64 * wave + 32 + 16 * (lane >> 5) + e] = sgb[e];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {   // the waves in order
+    float v = 0.0f;
+    for (int w = 0; w < waves; ++w) v += s_sum[64 * w + lane];
+    (lane < 32 ? a.dgamma : a.dbeta)[group * 32 + row] = v;
+  }
+}
+
 // dx = rstd (ghat - mean_C(ghat) - xhat mean_C(ghat xhat)) with ghat = g gamma, xhat = (x - mean) rstd; the column sums
 // of g xhat and g stay in registers over all row groups and end as one partial row of dgamma | dbeta per workgroup.
-template <StorePolicy SP>
+// COLUMNS_APART: the column sums are left to workgroups of their own behind the row_wgs that own rows (column_sums_direct).
+template <StorePolicy SP, bool COLUMNS_APART>
 __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNormBwdRows a) {
   extern __shared__ __align__(16) int8_t smem[];
+  if (COLUMNS_APART && (int)blockIdx.x >= a.row_wgs) {
+    column_sums_direct(a, blockIdx.x - a.row_wgs, reinterpret_cast<float*>(smem));
+    return;
+  }
   const RowWave t(a.cols, a.strips);
   float* const s_row = reinterpret_cast<float*>(smem);                         // [copy][wave][row][sum]
   int8_t* const own = smem + t.waves * kBwdRowBytes + t.wave * kBwdWaveBytes;
@@ -256,7 +308,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
   };
 
   int first = blockIdx.x * a.teams;
-  const int stride = gridDim.x * a.teams;
+  const int stride = (COLUMNS_APART ? a.row_wgs : (int)gridDim.x) * a.teams;
   request(min(first + t.team, groups - 1));
   float* const s_gamma = reinterpret_cast<float*>(own + kBwdGamma);
 #pragma unroll
@@ -311,6 +363,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
           // in place (left to itself the compiler keeps the operands of many deferred updates alive instead)
           asm volatile("v_add_f32 %0, %0, %1" : "+v"(m1[p]) : "v"(gh));
           asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(m2[p]) : "v"(gh), "v"(xh));
+          if (COLUMNS_APART) continue;
           tg[e] = p == 0 ? gr[e] * xh : __builtin_fmaf(gr[e], xh, tg[e]);
           if (p == 0) tb[e] = gr[e];
           else asm volatile("v_add_f32 %0, %0, %1" : "+v"(tb[e]) : "v"(gr[e]));
@@ -318,7 +371,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
         __builtin_amdgcn_sched_barrier(0);             // interleaved passes would keep their unpacked values live together
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < 4 && !COLUMNS_APART; ++e) {
         asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(cgs[4 * d + e]) : "v"(sg), "v"(tg[e]));
         asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(cbs[4 * d + e]) : "v"(sg), "v"(tb[e]));
       }
@@ -391,6 +444,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
     }
   }
 
+  if (COLUMNS_APART) return;
   // column sums over the 8 row lanes of the wave, then over the teams through LDS, in a fixed order
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
@@ -468,12 +522,21 @@ int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st) {
   a.strips = (a.cols + 127) / 128;
   a.teams = choose_teams(a.strips, groups);
   a.inv_cols = 1.0f / (float)a.cols;
-  const int waves = a.strips * a.teams, grid = std::min((groups + a.teams - 1) / a.teams, 256);
+  const int waves = a.strips * a.teams;
+  a.row_wgs = std::min((groups + a.teams - 1) / a.teams, 256);
   static_assert(16 * (kBwdRowBytes + kBwdWaveBytes) <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
+  const bool apart = a.rows <= 2048 && groups <= 12 * waves;   // at most 12 row groups for a wave of the column workgroups
   with_store_policy(a.rows, a.cols, [&](auto sp) {
-    launch_rows<layernorm_bwd_rows_kernel<decltype(sp)::value>>(kBwdRowBytes + kBwdWaveBytes, grid, waves, a, st);
+    constexpr StorePolicy SP = decltype(sp)::value;
+    if constexpr (SP == kStoreThrough) {   // (2048 rows are always stored through)
+      if (apart) {
+        launch_rows<layernorm_bwd_rows_kernel<SP, true>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs + a.cols / 32, waves, a, st);
+        return;
+      }
+    }
+    launch_rows<layernorm_bwd_rows_kernel<SP, false>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs, waves, a, st);
   });
-  return grid;
+  return apart ? 0 : a.row_wgs;
 }
 
 }  // namespace jf

@@ -61,13 +61,13 @@ struct Strip32 {
                     // reductions only with each other (whole blocks are in or out), and store nothing.
   int lane, wave;   // lane of the wave, wave of the workgroup (a workgroup holds kStripWaves neighbouring strips)
   bool inside;      // the wave's strip exists (the last workgroup may hold fewer)
-  __device__ __forceinline__ Strip32(int rows, int cols) {
+  __device__ __forceinline__ Strip32(int rows, int cols, unsigned first = 0) {   // first: workgroups before the strips
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     ch = lane & 7;
     rsub = lane >> 3;
     const unsigned groups = (unsigned)((cols + 127) / 128), strips = groups * (unsigned)(rows / 32);
-    const unsigned id = blockIdx.x * (blockDim.x >> 6) + wave;   // strips are numbered column group fastest
+    const unsigned id = (blockIdx.x - first) * (blockDim.x >> 6) + wave;   // strips are numbered column group fastest
     inside = id < strips;
     const unsigned sid = inside ? id : strips - 1;
     c0 = (int)(sid % groups) * 128;
