@@ -176,14 +176,17 @@ __device__ __forceinline__ T* uniform_pointer(T* p) {
 // 54, 52; GELU 4096 x 3072: 17.1, 15.1, 14.2).  A large result has to be stored in
 // whole lines per wave, because a line written through in pieces goes to memory piece by piece (the FP16 hand-over at
 // 8192 x 5120 in 16-byte pieces: 87 instead of 71 us); store_part is for what cannot be.
-// (Written out because no builtin takes the scope bit for 16 bytes.  A 16-byte store reads its data one wait state late:
-// the s_nop keeps the next vector instruction from overwriting it, which the compiler does for its own stores.)
+// (Stores the compiler knows: it has to keep the two wait states between a 16-byte store and the next write of its data.)
 template <class T>
 __device__ __forceinline__ void store_out(void* p, T v) {
   static_assert(sizeof(T) == 16 || sizeof(T) == 8 || sizeof(T) == 4, "one store instruction");
-  if constexpr (sizeof(T) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
-  else if constexpr (sizeof(T) == 8) asm volatile("global_store_dwordx2 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
-  else asm volatile("global_store_dword %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  if constexpr (sizeof(T) == 16)
+    __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) v4u*)p, __builtin_bit_cast(v4u, v), "agent");
+  else if constexpr (sizeof(T) == 8)
+    __hip_atomic_store((__attribute__((address_space(1))) unsigned long long*)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    __hip_atomic_store((__attribute__((address_space(1))) unsigned*)p, __builtin_bit_cast(unsigned, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void store_out(void* p, const uint4& v) {
   store_out(p, v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w});
@@ -215,7 +218,7 @@ __device__ __forceinline__ void store_as(void* p, const T& v) {
   } else if constexpr (P == kStoreStream) {
     typedef int many __attribute__((ext_vector_type(sizeof(T) / 4)));
     typedef typename std::conditional<sizeof(T) == 4, int, many>::type vec;
-    __builtin_nontemporal_store(__builtin_bit_cast(vec, v), static_cast<vec*>(p));
+    __builtin_nontemporal_store(__builtin_bit_cast(vec, v), (__attribute__((address_space(1))) vec*)p);
   } else {
     *static_cast<T*>(p) = v;
   }

@@ -147,24 +147,23 @@ __device__ __forceinline__ void fold(float (&acc)[N], const V& v, float t) {
 }
 
 // Compile-time shape of one kernel instance: tile, stage and LDS ring.
-// DEEP: a stage of 128 K bytes where the shape's default is 64.
-template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DEEP>
+template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK>
 struct GemmShape {
   static constexpr int NW = WGM * WGN;
   static constexpr int TM = 32 * WM * WGM, TN = 32 * WN * WGN;
-  // K bytes per stage: 128 when a stage has to hold a whole B = 128 block, for the workgroups of more than
-  // four waves of fewer than four sub-blocks each (one workgroup per compute unit, whose barriers are the most
-  // expensive), and for the one-sub-block waves at B = 64 (a stage must hold an even number of sub-block x
-  // K-block units); 64 otherwise, which lets three workgroups with a ring of three stages share the LDS of a
-  // compute unit.
-  static constexpr int KC = (DEEP || B == 128 || (WGM * WGN > 4 && WM * WN < 4) || (B == 64 && WM * WN == 1)) ? 128 : 64;
+  // K bytes per stage: 128 when a stage has to hold a whole B = 128 block, and for the waves of one sub-block, which
+  // spend the most instructions per MFMA on the stage itself (at B = 64 a stage must also hold an even number of sub-block
+  // x K-block units); 64 otherwise, which lets three workgroups with a ring of three stages share the LDS of a compute unit.
+  static constexpr int KC = (B == 128 || WM * WN == 1) ? 128 : 64;
   typedef TileLayout<TM, AK, KC> LA;
   typedef TileLayout<TN, BK, KC> LB;
   static constexpr int A_BYTES = LA::bytes(NW), B_BYTES = LB::bytes(NW);
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  // Stages in the LDS ring: one being read, the rest in flight.  Tiles that leave a compute unit to a single
-  // workgroup (more than four waves, B > 32) take a ring of four if that fits the LDS, the others a ring of three.
-  static constexpr int NBUF = (B > 32 && NW > 4 && 4 * STAGE_BYTES <= 156 * 1024) ? 4 : 3;
+  // Stages in the LDS ring: one being read, the rest in flight.  Two for the waves of one sub-block at B = 32: with four
+  // workgroups per compute unit a stage lasts long enough (2048^3 on 64x64 tiles 22.5 -> 20.1 us against three stages of 64
+  // bytes, 23.0 against three of 128, which leave room for three workgroups).  Tiles that leave a compute unit to a single
+  // workgroup (more than four waves, B > 32) take four if that fits the LDS, the others three.
+  static constexpr int NBUF = (B == 32 && WM * WN == 1) ? 2 : (B > 32 && NW > 4 && 4 * STAGE_BYTES <= 156 * 1024) ? 4 : 3;
   static_assert(NBUF * STAGE_BYTES <= 156 * 1024, "the ring must fit the LDS of a compute unit");
   static constexpr int RING_BYTES = NBUF * STAGE_BYTES;
   // Block scales: two segments of 64 K blocks for every block row and block column of the tile, behind the ring.
@@ -177,16 +176,16 @@ struct GemmShape {
 // per SIMD).
 template <int B, int WM, int WN>
 struct GemmPipeline {
-  static constexpr bool STEPWISE = B == 32 && WM * WN > 1, ONE_SET = B == 64 && WM * WN > 1;
+  static constexpr bool STEPWISE = B == 32, ONE_SET = B == 64 && WM * WN > 1;
 };
 
 // One output tile: K loop and epilogue.  `tile_index` of `ntiles` is this workgroup's position in the launch (or in
 // its part of a launch that holds two products); s_ring is the workgroup's LDS ring of NBUF stages with the scales behind
 // it, s_amax its max-abs exchange area, both owned by the calling kernel.
-template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DUMP, bool DEEP>
+template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DUMP>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_index, const int ntiles, int8_t* const s_ring,
                                           float (*const s_amax)[8]) {
-  typedef GemmShape<B, WM, WN, WGM, WGN, AK, BK, DEEP> Shape;
+  typedef GemmShape<B, WM, WN, WGM, WGN, AK, BK> Shape;
   constexpr int NW = Shape::NW;
   constexpr int TM = Shape::TM, TN = Shape::TN;
   constexpr int KPB = B / 32;  // MFMA K steps per quantization block
@@ -367,8 +366,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   // Two INT32 tiles rotate: the chain of the next unit is issued before the fold of the current one.
   // Fragments are read from LDS ahead of the chain that takes them and spread over the folds, one or two reads per unit:
   // read all at once after the barrier they hold up the vector ALU, which they share register ports with.
-  //   STEPWISE (B = 32, several sub-blocks per wave): the fragments of one K step are read while the units of the K step
-  //     before are folded; two register sets, one per K step of the stage.  The barrier stands before the last K step.
+  //   STEPWISE (B = 32): the fragments of one K step are read while the units of the K step before are folded (two steps
+  //     before, where a step is a single unit); two register sets used by turns.  The barrier stands before the last step(s).
   //   ONE_SET (2x2 sub-blocks at B = 64, where two sets do not fit three waves per SIMD): those of the next stage into
   //     the registers that come out of use, beside the last two units.  The barrier stands before them.
   //   otherwise: those of one stage while the stage before is folded; two sets, one per stage.  The barrier comes first.
@@ -378,6 +377,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   static_assert(!STEPWISE || (KPB == 1 && SPS % 2 == 0), "the register sets alternate");
   static_assert(!ONE_SET || (WM == 2 && WN == 2 && NT == 4), "the order in which fragments come out of use");
   constexpr int SETS = STEPWISE || !ONE_SET ? 2 : 1, STEPS = STEPWISE ? 1 : SPS;   // register sets, K steps in each
+  constexpr int AHEAD = NTILE == 1 ? 2 : 1;   // STEPWISE: K steps between a read and the step beside which it stands
   v16i vi[2];
   v4i fa[SETS][STEPS][WM], fb[SETS][STEPS][WN];
   constexpr int READS = WM + WN;
@@ -416,7 +416,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   auto run_stage = [&](int t, auto u_tag) __attribute__((always_inline)) {
     constexpr int u = decltype(u_tag)::value, slot = u % NBUF, nslot = (u + 1) % NBUF;
     constexpr int set = ONE_SET ? 0 : u & 1, nset = ONE_SET ? 0 : set ^ 1;
-    constexpr int SYNC = STEPWISE ? (SPS - 1) * NTILE : ONE_SET ? NT - 2 : 0;   // the unit before which the waves meet
+    constexpr int SYNC = STEPWISE ? (SPS - AHEAD) * NTILE : ONE_SET ? NT - 2 : 0;   // the unit before which the waves meet
     constexpr bool SPREAD_LOADS = B == 128;
     static_for<0, NT>([&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value, kb = i / NTILE, q = i % NTILE;
@@ -440,7 +440,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
         if constexpr (i + 1 < NT) chain_step(set, i + 1, js, nxt);
         else chain_step(nset, 0, js, nxt);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (STEPWISE) {   // the next K step's reads: all but the last unit of this one share them
+        if constexpr (STEPWISE && AHEAD == 2) {   // the K step after next, into the registers of this one
+          static_for<0, READS>([&](auto n_tag) __attribute__((always_inline)) {
+            read_frag(kb + 2 < SPS ? slot : nslot, kb % 2, (kb + 2) % SPS, decltype(n_tag)::value);
+          });
+        } else if constexpr (STEPWISE) {   // the next K step's reads: all but the last unit of this one share them
           constexpr int U = NTILE - 1;
           static_for<0, READS>([&](auto n_tag) __attribute__((always_inline)) {
             constexpr int n = decltype(n_tag)::value;
@@ -468,15 +472,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
     });
   };
 
-  static_assert(NBUF >= 3, "two stages in flight beside the one in use");
+  static_assert(NBUF >= 2, "a stage in flight beside the one in use");
   issue_scales(0);
 #pragma unroll 1
   for (int t = 0; t < NBUF; ++t) static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { issue_load(t, decltype(n)::value); });
   wait_stage(std::integral_constant<int, NBUF - 1>());
   read_scales(0);
   if (nkb > SEG) issue_scales(1);
-  static_for<0, STEPS * READS>([&](auto n) __attribute__((always_inline)) {
-    read_frag(0, 0, decltype(n)::value / READS, decltype(n)::value % READS);
+  static_for<0, (STEPWISE ? AHEAD : STEPS) * READS>([&](auto n) __attribute__((always_inline)) {
+    constexpr int j = decltype(n)::value / READS;
+    read_frag(0, STEPWISE ? j : 0, j, decltype(n)::value % READS);
   });
   static_for<0, KPB>([&](auto js) __attribute__((always_inline)) { chain_step(0, 0, decltype(js)::value, vi[0]); });
   scale = scale_of(0, 0);
@@ -597,15 +602,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
 }
 
 // A product's tile function with its compile-time shape, for the kernels below.
-template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DEEP = false, bool DUMP = false>
+template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DUMP = false>
 struct GemmInstance {
-  typedef GemmShape<B, WM, WN, WGM, WGN, AK, BK, DEEP> Shape;
+  typedef GemmShape<B, WM, WN, WGM, WGN, AK, BK> Shape;
   // Resident waves per SIMD the register allocation has to allow.  Four waves: 3 for the 128x128 tile and for the 64x64
-  // tiles with a stage of 128 K bytes (three workgroups share the LDS of a compute unit), else 4.  Eight waves: 4 for the
-  // 256x128 tile at B = 32 (two workgroups per compute unit), else 2 (one).
-  static constexpr int WMIN = Shape::NW == 8 ? (B == 32 ? 4 : 2) : (WM * WN == 4 || Shape::KC == 128) ? 3 : 4;
+  // tile at B = 64 (three workgroups share the LDS of a compute unit), else 4.  Eight waves: 4 for the 256x128 tile at
+  // B = 32 (two workgroups per compute unit), else 2 (one).
+  static constexpr int WMIN = Shape::NW == 8 ? (B == 32 ? 4 : 2) : (WM * WN == 4 || B == 64) ? 3 : 4;
   static __device__ __forceinline__ void run(const GemmArgs& g, int tile_index, int ntiles, int8_t* s_ring, float (*s_amax)[8]) {
-    gemm_tile<B, WM, WN, WGM, WGN, AK, BK, DUMP, DEEP>(g, tile_index, ntiles, s_ring, s_amax);
+    gemm_tile<B, WM, WN, WGM, WGN, AK, BK, DUMP>(g, tile_index, ntiles, s_ring, s_amax);
   }
 };
 
@@ -666,18 +671,17 @@ struct FineInstance;   // jf_gemm_fine.hpp
 template <int B, bool AK, bool BK, bool DUMP>
 static void launch_shape(int shape, const GemmArgs& a, hipStream_t st) {
   if constexpr (B == 128) {
-    if (shape == 6) launch_one<GemmInstance<B, 2, 2, 4, 2, AK, BK, false, DUMP>>(a, st);
-    else launch_one<GemmInstance<B, 2, 1, 2, 4, AK, BK, false, DUMP>>(a, st);
+    if (shape == 6) launch_one<GemmInstance<B, 2, 2, 4, 2, AK, BK, DUMP>>(a, st);
+    else launch_one<GemmInstance<B, 2, 1, 2, 4, AK, BK, DUMP>>(a, st);
   } else {
-    if (shape == 1) launch_one<GemmInstance<B, 2, 2, 2, 2, AK, BK, false, DUMP>>(a, st);
+    if (shape == 1) launch_one<GemmInstance<B, 2, 2, 2, 2, AK, BK, DUMP>>(a, st);
     else if constexpr (B == 32) {
-      if (shape == 6) launch_one<GemmInstance<B, 2, 2, 4, 2, AK, BK, false, DUMP>>(a, st);
-      else if (shape == 8) launch_one<GemmInstance<B, 2, 1, 2, 2, AK, BK, false, DUMP>>(a, st);
-      else if (shape == 7) launch_one<GemmInstance<B, 1, 1, 2, 2, AK, BK, true, DUMP>>(a, st);
-      else if (DUMP || shape == 4) launch_one<GemmInstance<B, 1, 1, 2, 2, AK, BK, false, DUMP>>(a, st);
+      if (shape == 6) launch_one<GemmInstance<B, 2, 2, 4, 2, AK, BK, DUMP>>(a, st);
+      else if (shape == 8) launch_one<GemmInstance<B, 2, 1, 2, 2, AK, BK, DUMP>>(a, st);
+      else if (DUMP || shape == 4) launch_one<GemmInstance<B, 1, 1, 2, 2, AK, BK, DUMP>>(a, st);
       else launch_one<FineInstance<AK, BK>>(a, st);
     } else {
-      launch_one<GemmInstance<B, 1, 1, 2, 2, AK, BK, false, DUMP>>(a, st);
+      launch_one<GemmInstance<B, 1, 1, 2, 2, AK, BK, DUMP>>(a, st);
     }
   }
 }

@@ -9,14 +9,13 @@
 //   6   256x128: eight waves of 2x2 sub-blocks; two workgroups per compute unit at B = 32, one at B = 128 (not at B = 64).
 //       A quarter less operand traffic per MFMA than 128x128, and at B = 32 four waves per SIMD instead of three:
 //       8192^3 991 -> 964 us
-//   7   64x64 with a stage of 128 instead of 64 K bytes: half the barriers, three workgroups per compute unit (B = 32)
 //   8   128x64: four waves of 2x1 sub-blocks, four workgroups per compute unit (B = 32)
 //   10  32x32: four waves of 16x16 outputs, jf_gemm_fine.hpp (B = 32)
 // A model of the busiest SIMD predicts the time of each and the least is taken.  Its constants are least-squares fits to the
 // measured times of 276 products (92 layers drawn over the logarithm of their sizes, 128 .. 16384 tokens, 128 .. 8192
 // features; all three products) and 184 backward passes: rms error 4-8 % for one shape (22 % for shape 10), and the shape
-// taken is on average within 1.5 % (B = 32), 0.4 % (64) and 0.1 % (128) of the best one in each case; for the choice
-// between one and two launches of the backward products within 1.7 %, 0.3 % and 0.2 %.
+// taken is on average within 0.8 % (B = 32), 0.4 % (64) and 0.1 % (128) of the best one in each case; for the choice
+// between one and two launches of the backward products within 1.9 %, 0.1 % and 0.2 %.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -42,13 +41,13 @@ struct ShapeModel {
 };
 
 static constexpr ShapeModel kShapes32[] = {
-    {6, 256, 128, 2, 8, 2.53, 53.6, 62.1, 0.73, 0.537}, {1, 128, 128, 3, 4, 3.69, 59.8, 88.3, 0.67, 0.478},
-    {8, 128, 64, 4, 2, 3.51, 68.3, 105.9, 0.67, 0.490}, {4, 64, 64, 4, 1, 3.46, 82.9, 121.3, 1.20, 0.429},
-    {7, 64, 64, 3, 1, 3.36, 76.9, 102.8, 0.92, 0.802},  {10, 32, 32, 4, 0.25, 3.84, 174.5, 223.5, 1.10, 1.263}};
-static constexpr ShapeModel kShapes64[] = {{1, 128, 128, 3, 4, 3.36, 43.5, 61.9, 0.54, 0.421},
-                                           {4, 64, 64, 3, 1, 3.29, 64.5, 75.6, 0.64, 0.769}};
-static constexpr ShapeModel kShapes128[] = {{6, 256, 128, 1, 8, -0.19, 33.2, 28.5, 0.38, 0.860},
-                                            {1, 128, 128, 1, 4, 2.23, 38.7, 33.6, 0.68, 0.808}};
+    {6, 256, 128, 2, 8, 2.32, 53.2, 61.5, 0.75, 0.512}, {1, 128, 128, 3, 4, 3.11, 59.2, 87.6, 0.67, 0.480},
+    {8, 128, 64, 4, 2, 2.99, 67.9, 105.1, 0.64, 0.496}, {4, 64, 64, 4, 1, 2.99, 75.3, 120.7, 1.14, 0.650},
+    {10, 32, 32, 4, 0.25, 3.29, 172.4, 211.7, 1.06, 1.475}};
+static constexpr ShapeModel kShapes64[] = {{1, 128, 128, 3, 4, 2.91, 42.1, 57.6, 0.47, 0.449},
+                                           {4, 64, 64, 3, 1, 2.72, 63.3, 72.0, 0.67, 0.823}};
+static constexpr ShapeModel kShapes128[] = {{6, 256, 128, 1, 8, -1.04, 30.1, 25.9, 0.42, 0.924},
+                                            {1, 128, 128, 1, 4, 1.49, 34.7, 31.0, 0.81, 0.881}};
 
 // Both backward products in one launch: input gradient on shape `dgrad`, weight gradient on shape `wgrad`.  The compute
 // units share the work of both, W = their average (more by 0.6 of what the rounding to whole workgroups adds while all are
@@ -58,11 +57,11 @@ struct PairModel {
   int pair, dgrad, wgrad;   // `pair` as in jf_debug_set_gemm_shape
   double fixed_us, work, longest;
 };
-static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.56, 0.961, 0.191},  {22, 8, 8, 3.69, 1.002, 0.136},
-                                         {23, 4, 4, 3.75, 1.127, -0.062}, {24, 10, 4, 3.98, 0.982, 0.416},
-                                         {25, 4, 10, 3.98, 1.306, 0.167}};
-static constexpr PairModel kPairs64[] = {{21, 1, 1, 3.36, 1.026, 0.097}, {22, 4, 4, 4.11, 0.986, 0.450}};
-static constexpr PairModel kPairs128[] = {{21, 6, 6, -0.26, 1.013, 0.372}, {22, 1, 1, 2.23, 1.090, 0.107}};
+static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.19, 0.922, 0.244}, {22, 8, 8, 3.20, 0.993, 0.148},
+                                         {23, 4, 4, 2.90, 1.044, 0.291}, {24, 10, 4, 3.01, 0.997, 0.423},
+                                         {25, 4, 10, 2.81, 1.302, 0.196}};
+static constexpr PairModel kPairs64[] = {{21, 1, 1, 2.65, 0.972, 0.221}, {22, 4, 4, 2.97, 0.994, 0.352}};
+static constexpr PairModel kPairs128[] = {{21, 6, 6, -1.18, 1.040, 0.336}, {22, 1, 1, 1.45, 1.114, 0.117}};
 
 struct ShapeTable {
   const ShapeModel* shapes;

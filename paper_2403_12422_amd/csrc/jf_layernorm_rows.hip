@@ -50,10 +50,11 @@ template <StorePolicy SP>
 __device__ __forceinline__ void store_as_at(int8_t* uniform_base, uint32_t off, v4i v) {
   typedef __attribute__((address_space(1))) int8_t* gbl_ptr;
   typedef __attribute__((address_space(1))) v4i* gbl_v4i;
-  const gbl_v4i p = (gbl_v4i)((gbl_ptr)uniform_base + off);
-  if constexpr (SP == kStoreThrough) asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" : : "v"(off), "v"(v), "s"(uniform_base) : "memory");
-  else if constexpr (SP == kStoreStream) __builtin_nontemporal_store(v, p);
-  else *p = v;
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  const gbl_ptr p = (gbl_ptr)uniform_base + off;
+  if constexpr (SP == kStoreThrough) __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) v4u*)p, __builtin_bit_cast(v4u, v), "agent");
+  else if constexpr (SP == kStoreStream) __builtin_nontemporal_store(v, (gbl_v4i)p);
+  else *(gbl_v4i)p = v;
 }
 
 // Signed codes of one packed dword as floats (a byte-select conversion each).
