@@ -13,9 +13,9 @@
 //   10  32x32: four waves of 16x16 outputs, jf_gemm_fine.hpp (B = 32)
 // A model of the busiest SIMD predicts the time of each and the least is taken.  Its constants are least-squares fits to the
 // measured times of 276 products (92 layers drawn over the logarithm of their sizes, 128 .. 16384 tokens, 128 .. 8192
-// features; all three products) and 184 backward passes: rms error 4-8 % for one shape (22 % for shape 10), and the shape
-// taken is on average within 0.8 % (B = 32), 0.4 % (64) and 0.1 % (128) of the best one in each case; for the choice
-// between one and two launches of the backward products within 1.9 %, 0.1 % and 0.2 %.
+// features; all three products) and 184 backward passes: rms error 4-9 % for one shape, and the shape taken is on
+// average within 0.8 % (B = 32), 0.3 % (64) and 0.1 % (128) of the best one in each case; for the choice between one and
+// two launches of the backward products within 1.3 %, 0.1 % and 0.2 %.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -27,27 +27,36 @@ namespace jf {
 // A workgroup puts `sub` 32x32 sub-blocks on every SIMD of its compute unit; with T tiles the busiest unit holds
 // ceil(T / 256) workgroups while all are resident at once, T / 256 + tail beyond that.  A sub-block costs `ns` per 32 K on
 // a SIMD shared by several workgroups, `ns_alone` on one that holds a single one (which cannot overlap its own MFMA, fold
-// and waits), and `epilogue_us` besides; fixed_us is the launch and the latency of the first stage.
+// and waits) in the forward product, `dgrad` and `wgrad` times that in the others, whose operands are read transposed, and
+// `epilogue_us` besides; fixed_us is the launch and the latency of the first stage.
+enum Product { kForward, kDgrad, kWgrad };
 struct ShapeModel {
   int shape, tm, tn, resident;
-  double sub, fixed_us, ns, ns_alone, tail, epilogue_us;
+  double sub, fixed_us, ns, ns_alone, tail, epilogue_us, dgrad, wgrad;
 
   double tiles(const GemmArgs& a) const { return (double)((a.M + tm - 1) / tm) * ((a.Nn + tn - 1) / tn); }
-  double tile_us(const GemmArgs& a, double rate) const { return sub * (a.K / 32 * rate * 1e-3 + epilogue_us); }
-  double product_us(const GemmArgs& a) const {
+  double tile_us(Product p, const GemmArgs& a, bool alone) const {
+    const double rate = (alone ? ns_alone : ns) * (p == kForward ? 1.0 : p == kDgrad ? dgrad : wgrad);
+    return sub * (a.K / 32 * rate * 1e-3 + epilogue_us);
+  }
+  double product_us(Product p, const GemmArgs& a) const {
     const double t = tiles(a), busiest = t <= 256.0 * resident ? std::ceil(t / 256.0) : t / 256.0 + tail;
-    return fixed_us + busiest * tile_us(a, busiest <= 1.0 ? ns_alone : ns);
+    return fixed_us + busiest * tile_us(p, a, busiest <= 1.0);
   }
 };
 
 static constexpr ShapeModel kShapes32[] = {
-    {6, 256, 128, 2, 8, 2.32, 53.2, 61.5, 0.75, 0.512}, {1, 128, 128, 3, 4, 3.11, 59.2, 87.6, 0.67, 0.480},
-    {8, 128, 64, 4, 2, 2.99, 67.9, 105.1, 0.64, 0.496}, {4, 64, 64, 4, 1, 2.99, 75.3, 120.7, 1.14, 0.650},
-    {10, 32, 32, 4, 0.25, 3.29, 172.4, 211.7, 1.06, 1.475}};
-static constexpr ShapeModel kShapes64[] = {{1, 128, 128, 3, 4, 2.91, 42.1, 57.6, 0.47, 0.449},
-                                           {4, 64, 64, 3, 1, 2.72, 63.3, 72.0, 0.67, 0.823}};
-static constexpr ShapeModel kShapes128[] = {{6, 256, 128, 1, 8, -1.04, 30.1, 25.9, 0.42, 0.924},
-                                            {1, 128, 128, 1, 4, 1.49, 34.7, 31.0, 0.81, 0.881}};
+    {6, 256, 128, 2, 8, 2.25, 51.8, 60.0, 0.78, 0.524, 1.028, 1.039},
+    {1, 128, 128, 3, 4, 3.11, 58.8, 87.2, 0.68, 0.480, 1.021, 0.995},
+    {8, 128, 64, 4, 2, 2.98, 66.8, 103.3, 0.65, 0.501, 1.026, 1.020},
+    {4, 64, 64, 4, 1, 2.95, 68.5, 109.1, 1.03, 0.703, 1.074, 1.206},
+    {10, 32, 32, 4, 0.25, 3.26, 110.0, 125.5, 0.72, 1.798, 1.511, 2.205}};
+static constexpr ShapeModel kShapes64[] = {
+    {1, 128, 128, 3, 4, 2.82, 42.2, 58.5, 0.51, 0.464, 0.967, 1.001},
+    {4, 64, 64, 3, 1, 2.71, 58.3, 66.0, 0.59, 0.827, 1.055, 1.237}};
+static constexpr ShapeModel kShapes128[] = {
+    {6, 256, 128, 1, 8, -1.22, 29.8, 25.3, 0.38, 0.945, 1.014, 1.070},
+    {1, 128, 128, 1, 4, 1.44, 34.2, 30.7, 0.79, 0.890, 1.001, 1.046}};
 
 // Both backward products in one launch: input gradient on shape `dgrad`, weight gradient on shape `wgrad`.  The compute
 // units share the work of both, W = their average (more by 0.6 of what the rounding to whole workgroups adds while all are
@@ -57,11 +66,10 @@ struct PairModel {
   int pair, dgrad, wgrad;   // `pair` as in jf_debug_set_gemm_shape
   double fixed_us, work, longest;
 };
-static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.19, 0.922, 0.244}, {22, 8, 8, 3.20, 0.993, 0.148},
-                                         {23, 4, 4, 2.90, 1.044, 0.291}, {24, 10, 4, 3.01, 0.997, 0.423},
-                                         {25, 4, 10, 2.81, 1.302, 0.196}};
-static constexpr PairModel kPairs64[] = {{21, 1, 1, 2.65, 0.972, 0.221}, {22, 4, 4, 2.97, 0.994, 0.352}};
-static constexpr PairModel kPairs128[] = {{21, 6, 6, -1.18, 1.040, 0.336}, {22, 1, 1, 1.45, 1.114, 0.117}};
+static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.14, 0.922, 0.243}, {22, 8, 8, 3.15, 0.986, 0.148}, {23, 4, 4, 2.69, 0.998, 0.310},
+                                         {24, 10, 4, 2.91, 0.974, 0.378}, {25, 4, 10, 2.64, 1.032, 0.217}};
+static constexpr PairModel kPairs64[] = {{21, 1, 1, 2.71, 0.983, 0.204}, {22, 4, 4, 2.93, 0.945, 0.385}};
+static constexpr PairModel kPairs128[] = {{21, 6, 6, -1.43, 1.014, 0.324}, {22, 1, 1, 1.41, 1.106, 0.115}};
 
 struct ShapeTable {
   const ShapeModel* shapes;
@@ -72,18 +80,24 @@ struct ShapeTable {
       if (shapes[i].shape == shape) return shapes + i;
     return nullptr;
   }
-  const ShapeModel& best(const GemmArgs& a) const {
-    const ShapeModel* b = shapes;
-    for (int i = 1; i < nshapes; ++i)
-      if (shapes[i].product_us(a) < b->product_us(a)) b = shapes + i;
-    return *b;
+  struct Choice {
+    int shape;
+    double us;
+  };
+  Choice best(Product p, const GemmArgs& a) const {
+    Choice c = {shapes[0].shape, shapes[0].product_us(p, a)};
+    for (int i = 1; i < nshapes; ++i) {
+      const double us = shapes[i].product_us(p, a);
+      if (us < c.us) c = {shapes[i].shape, us};
+    }
+    return c;
   }
   double pair_us(const PairModel& p, const GemmArgs& d, const GemmArgs& w) const {
     const ShapeModel &sd = *find(p.dgrad), &sw = *find(p.wgrad);
     const double td = sd.tiles(d), tw = sw.tiles(w), per_cu = (td + tw) / 256.0;
-    const double alone = std::max(sd.tile_us(d, sd.ns_alone), sw.tile_us(w, sw.ns_alone));
+    const double alone = std::max(sd.tile_us(kDgrad, d, true), sw.tile_us(kWgrad, w, true));
     if (per_cu <= 1.0) return p.fixed_us + alone;
-    double work = (td * sd.tile_us(d, sd.ns) + tw * sw.tile_us(w, sw.ns)) / 256.0;
+    double work = (td * sd.tile_us(kDgrad, d, false) + tw * sw.tile_us(kWgrad, w, false)) / 256.0;
     if (per_cu <= std::min(sd.resident, sw.resident)) work *= 1.0 + 0.6 * (std::ceil(per_cu) / per_cu - 1.0);
     return p.fixed_us + std::max(alone, p.work * work + p.longest * alone);
   }
@@ -95,14 +109,14 @@ static inline ShapeTable shape_table(int block) {
 }
 
 // Shape of one product; `forced` (test hook) if that is a shape of this block size.
-static int choose_shape(int block, const GemmArgs& a, int forced) {
+static int choose_shape(int block, Product p, const GemmArgs& a, int forced) {
   const ShapeTable t = shape_table(block);
-  return t.find(forced) ? forced : t.best(a).shape;
+  return t.find(forced) ? forced : t.best(p, a).shape;
 }
 // Pair of the backward products, 0 for two launches.
 static int choose_pair(int block, const GemmArgs& dgrad, const GemmArgs& wgrad, int forced) {
   const ShapeTable t = shape_table(block);
-  double least = t.best(dgrad).product_us(dgrad) + t.best(wgrad).product_us(wgrad);
+  double least = t.best(kDgrad, dgrad).us + t.best(kWgrad, wgrad).us;
   int pair = 0;
   for (int i = 0; i < t.npairs; ++i) {
     if (t.pairs[i].pair == forced) return forced;

@@ -40,7 +40,7 @@ static void launch_gemm(int which, int block, const GemmArgs& a, bool dump, hipS
       {launch_gemm_dgrad_b32, launch_gemm_dgrad_b64, launch_gemm_dgrad_b128},
       {launch_gemm_wgrad_b32, launch_gemm_wgrad_b64, launch_gemm_wgrad_b128},
   };
-  const int shape = choose_shape(block, a, g_forced_shape.load(std::memory_order_relaxed));
+  const int shape = choose_shape(block, (Product)which, a, g_forced_shape.load(std::memory_order_relaxed));
   table[which][block == 32 ? 0 : (block == 64 ? 1 : 2)](shape, a, dump, st);
 }
 
