@@ -280,6 +280,12 @@ __global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict
 // Add (App. A): y = x1 + x2 on the dequantized operands, re-quantized per block (Alg. 2), and optionally
 // the row partials that App. A's LayerNorm paragraph attaches to this operator: for every row and block
 // column, the mean and the sum of squares of y over the block's B columns (stored block-column-major).  Same tiling as GELU.
+// The row partials are 8 bytes per row and block column, a quarter of the codes at B = 32, and a wave has a line of them in
+// pieces: 32 bytes of each block column per pass of 8 rows.  They are written back whatever the codes' policy, so that L2
+// puts the pieces together; streamed or written through every piece goes to memory by itself (with partials streamed,
+// through, back; codes streamed: 1048576 x 768 653, 543, 472 us, 98304 x 768 61, 55, 46; 262144 x 3072 at block 64 588, 551,
+// 494, at block 128 511, 502, 482; codes through: 65536 x 768 through 39.5, back 35.0 us, 8192 x 1280 10.8, 9.0, 4096 x 3072
+// 12.1, 10.6, 512 x 768 3.5, 3.4).
 template <int B, StorePolicy SP>
 __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1, const float* __restrict__ S1,
                                                    const int8_t* __restrict__ X2, const float* __restrict__ S2, int rows,
@@ -320,8 +326,8 @@ __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1,
         ps = wave_group_sum<CH>(ps);
         pq = wave_group_sum<CH>(pq);
         if ((ch & CH) == 0) {
-          store_as<SP>(&row_mean[(int64_t)(col / B) * rows + row], ps * (1.0f / (float)B));   // block-column-major, see jf_add_q
-          store_as<SP>(&row_sumsq[(int64_t)(col / B) * rows + row], pq);
+          store_part(&row_mean[(int64_t)(col / B) * rows + row], ps * (1.0f / (float)B));   // block-column-major, see jf_add_q
+          store_part(&row_sumsq[(int64_t)(col / B) * rows + row], pq);
         }
       }
     }
@@ -497,8 +503,8 @@ __global__ void __launch_bounds__(64 * kStripWaves) add_strip32_kernel(const int
       if (t.ok && (t.ch & 1) == 0) {
         // block-column-major: the 32 rows of the strip are one 128-byte line per block column
         const int64_t o = (int64_t)(t.col / 32) * rows + (t.bi * 32 + t.rsub + 8 * p);
-        store_as<SP>(&row_mean[o], ps * (1.0f / 32.0f));
-        store_as<SP>(&row_sumsq[o], pq);
+        store_part(&row_mean[o], ps * (1.0f / 32.0f));
+        store_part(&row_sumsq[o], pq);
       }
     }
   }

@@ -1,0 +1,46 @@
+"""Operators whose results are stored in another way from some size on: a large tensor against the same rows in calls that
+are too small for that (every block is computed by itself, so all results are equal bit for bit; run with -m gpu)."""
+import pytest
+import torch
+
+import paper_2403_12422_amd as jf
+from test_gpu_parity import say
+
+pytestmark = pytest.mark.gpu
+# just past 64 MB in whole lines, just past 32 MB in rows that share lines; small calls of 128 rows and of 1/8
+SIZES = [(32, 87424, 768), (64, 87424, 768), (128, 87424, 768), (32, 42112, 800), (64, 40448, 832)]
+
+
+def _tensor(g, n, c, block):
+    return (torch.randint(-127, 128, (n, c), dtype=torch.int8, device="cuda", generator=g),
+            0.01 + torch.rand((n // block, c // block), device="cuda", generator=g))
+
+
+@pytest.mark.parametrize("block,N,C", SIZES)
+def test_large_results_equal_those_of_small_calls(block, N, C):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + C + block)
+    (X, SX), (Z, SZ) = _tensor(g, N, C, block), _tensor(g, N, C, block)
+    mask = torch.randint(0, 256, (N, C // 8), dtype=torch.uint8, device="cuda", generator=g)
+    x32 = torch.randn((N, C), device="cuda", generator=g)
+    ops = {
+        "add": lambda r, b: jf.jf_add_q(X[r], SX[b], Z[r], SZ[b], block),
+        "add with row partials": lambda r, b: jf.jf_add_q(X[r], SX[b], Z[r], SZ[b], block, want_partials=True),
+        "gelu": lambda r, b: jf.jf_gelu_q(X[r], SX[b], block),
+        "gelu backward": lambda r, b: jf.jf_gelu_q_bwd(Z[r], SZ[b], X[r], SX[b], block),
+        "dropout": lambda r, b: jf.jf_dropout_q(X[r], SX[b], mask[r], 0.25, block),
+        "quantize FP32": lambda r, b: jf.jf_quantize_block(x32[r], block),
+        "quantize FP16": lambda r, b: jf.jf_quantize_block(x32[r].half(), block),
+    }
+    whole = slice(None)
+    parts = [(0, 128), (128, N // 8 // 128 * 128), (N - 128, N)]
+    for name, op in ops.items():
+        say(f"{name} block={block} {N} x {C}")
+        got = op(whole, whole)
+        for first, last in parts:
+            rows, brows = slice(first, last), slice(first // block, last // block)
+            want = op(rows, brows)
+            assert torch.equal(got[0][rows], want[0]), name
+            assert torch.equal(got[1][brows], want[1]), name
+            for a, b in zip(got[2:], want[2:]):   # row partials: block column by block column
+                assert torch.equal(a[:, rows], b), name
