@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(256) gelu_kernel(const int8_t* __restrict__ X,
     double inv;
     block_scale(m, scale, inv);
     if (!col_ok[j]) continue;
-    if (wave == 0 && rsub == 0 && (col[j] % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col[j] / B], scale);
+    if (wave == 0 && rsub == 0 && (col[j] % B) == 0) store_scale<SP>(&SY[(int64_t)bi * lc + col[j] / B], scale);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int row = r0 + 8 * p + rsub;
@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict
   float scale;
   double inv;
   block_scale(m, scale, inv);
-  if (lane == 0) store_as<SP>(&SY[(int64_t)bi * lc + bj], scale);
+  if (lane == 0) store_scale<SP>(&SY[(int64_t)bi * lc + bj], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) store_as<SP>(Y + base + (int64_t)p * RPP * cols, quantize16(y[p], inv));
 }
@@ -340,7 +340,7 @@ __global__ void __launch_bounds__(256) add_kernel(const int8_t* __restrict__ X1,
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col / B], scale);
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_scale<SP>(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
@@ -391,7 +391,7 @@ __global__ void __launch_bounds__(256) dropout_kernel(const int8_t* __restrict__
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col / B], scale);
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_scale<SP>(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;
@@ -459,7 +459,7 @@ __global__ void __launch_bounds__(64 * kStripWaves) gelu_strip32_kernel(const in
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
   for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
@@ -512,7 +512,7 @@ __global__ void __launch_bounds__(64 * kStripWaves) add_strip32_kernel(const int
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
   for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
@@ -564,7 +564,7 @@ __global__ void __launch_bounds__(64 * kStripWaves) dropout_strip32_kernel(const
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
   for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }

@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_bwd_apply_strip32_
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_as<SP>(&SdX[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_scale<SP>(&SdX[t.block_index()], scale);
 #pragma unroll
   for (int p = 0; p < 4; ++p) store_as<SP>(dX + t.base + p * pass, quantize16(y[p], inv));
 }
@@ -385,7 +385,7 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_apply_strip32_kern
   double inv;
   strip32_block_scale(m, scale, inv);
   if (!t.ok) return;
-  if ((t.lane & 57) == 0) store_as<SP>(&SY[t.block_index()], scale);
+  if ((t.lane & 57) == 0) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
   for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
@@ -465,7 +465,7 @@ __global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __res
   double inv;
   block_scale(m, scale, inv);
   if (!col_ok) return;
-  if (wave == 0 && rsub == 0 && (col % B) == 0) store_as<SP>(&SY[(int64_t)bi * lc + col / B], scale);
+  if (wave == 0 && rsub == 0 && (col % B) == 0) store_scale<SP>(&SY[(int64_t)bi * lc + col / B], scale);
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const int row = r0 + 8 * p + rsub;

@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
       int8_t* const out = uniform_pointer(a.Y + (int64_t)g * 32 * a.cols);
 #pragma unroll
       for (int p = 0; p < 4; ++p) store_as_at<SP>(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_as<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)) + off_scale, scale);
+      if ((t.lane & 57) == 0) store_scale<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)) + off_scale, scale);
     }
   }
 }
@@ -441,7 +441,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
       int8_t* const out = uniform_pointer(a.dX + (int64_t)g * 32 * a.cols);
 #pragma unroll
       for (int p = 0; p < 4; ++p) store_as_at<SP>(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_as<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)) + off_scale, scale);
+      if ((t.lane & 57) == 0) store_scale<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)) + off_scale, scale);
     }
   }
 

@@ -77,8 +77,8 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
   // one lane per block writes the scale: the top-left 32-granule of the block
   if (group_first && col_ok && r0 < rows && (r0 % B) == 0 && ((c0 + 32 * cg) % B) == 0) {
     const int bi = r0 / B, bj = (c0 + 32 * cg) / B;
-    store_as<SP>(&s[(int64_t)bi * lc + bj], scale);
-    if (TRANSPOSED_COPY) store_as<SP>(&sT[(int64_t)bj * lr + bi], scale);
+    store_scale<SP>(&s[(int64_t)bi * lc + bj], scale);
+    if (TRANSPOSED_COPY) store_scale<SP>(&sT[(int64_t)bj * lr + bi], scale);
   }
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
