@@ -30,6 +30,14 @@
  *    throws or aborts.  On JF_ERR_LAUNCH, jf_last_hip_error() returns the HIP
  *    error code of the failed call.  Nothing is launched when an error other
  *    than JF_ERR_LAUNCH is returned.
+ *  - Outputs may share memory with inputs where this says so, and only as the
+ *    very buffer of an operand of the same size: the codes (and, with them or
+ *    by themselves, the scales) that GELU, Add, Dropout and LayerNorm write,
+ *    forward and backward, over those of any of their operands; LayerNorm
+ *    backward's dgamma or dbeta over gamma.  (LayerNorm backward adds its
+ *    column sums in another, equally fixed, order there.)  Any other overlap
+ *    of an output with an input, another output or ws gives unspecified
+ *    results.
  *  - Inputs are assumed finite; NaN/Inf inputs and codes of -128 give
  *    unspecified results (never out-of-bounds accesses).
  *

@@ -43,6 +43,22 @@ inline bool valid_dim(int64_t d, int32_t block) { return d > 0 && d <= (int64_t(
 // A tensor holds at most 2^40 elements (far beyond any device memory): keeps every workgroup count inside 32 bits.
 inline bool valid_size(int64_t rows, int64_t cols) { return rows * cols <= (int64_t(1) << 40); }
 
+// Memory that a call reads or writes (p may be null: nothing).  Where an output shares memory with an input, kernels that
+// read and write side by side must not take the place of kernels that followed each other.
+struct MemRange {
+  const void* p;
+  int64_t bytes;
+};
+template <int N, int M>
+inline bool any_overlap(const MemRange (&a)[N], const MemRange (&b)[M]) {
+  for (const MemRange& x : a)
+    for (const MemRange& y : b) {
+      const uintptr_t px = reinterpret_cast<uintptr_t>(x.p), py = reinterpret_cast<uintptr_t>(y.p);
+      if (px && py && px < py + (uintptr_t)y.bytes && py < px + (uintptr_t)x.bytes) return true;
+    }
+  return false;
+}
+
 // -------------------------------------------------------------- device side
 // The kernels that tile a matrix in two dimensions are launched as a one-dimensional grid, column group fastest:
 // the y and z dimensions of a grid stop at 65535, which a tensor of 2^24 rows exceeds.

@@ -552,16 +552,24 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
                                     hipStream_t st) {
   using namespace jf;
   int nparts = (int)ln_bwd_partial_rows(N);
+  // In place (dX over dY or X, dgamma over gamma) the column sums are taken in a kernel behind the one that writes dX:
+  // where they come from workgroups beside it, those read what dX replaces, or replace what dX is formed from.
+  const int64_t grid_bytes = N / block * (C / block) * 4;
+  const MemRange in[] = {{dY, N * C}, {SdY, grid_bytes}, {X, N * C}, {SX, grid_bytes}, {gamma, 4 * C}, {mean, 4 * N}, {rstd, 4 * N}};
+  const MemRange out[] = {{dX, N * C}, {SdX, grid_bytes}}, sums[] = {{dgamma, 4 * C}, {dbeta, 4 * C}};
+  const bool sums_in_place = any_overlap(sums, in);
+  const auto launch_colsum = [&]() {
+    hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((2 * C + 63) / 64)), dim3(1024), 0, st, partials, nparts, (int)(2 * C), dgamma, dbeta);
+    return launch_status();
+  };
   if (layernorm_rows_fits(C, block)) {   // one pass over the operands
     LayerNormBwdRows a{};
     a.G = dY; a.SG = SdY; a.X = X; a.SX = SX; a.gamma = gamma; a.mean = mean; a.rstd = rstd; a.rows = (int)N; a.cols = (int)C;
     a.dX = dX; a.SdX = SdX; a.partials = partials;
     a.dgamma = dgamma; a.dbeta = dbeta;
-    nparts = launch_layernorm_bwd_rows(a, st);
+    nparts = launch_layernorm_bwd_rows(a, sums_in_place || any_overlap(out, in), st);
     const int32_t rc = launch_status();
-    if (rc != JF_OK || nparts == 0) return rc;
-    hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((2 * C + 63) / 64)), dim3(1024), 0, st, partials, nparts, (int)(2 * C), dgamma, dbeta);
-    return launch_status();
+    return rc != JF_OK || nparts == 0 ? rc : launch_colsum();
   }
   // the workspace holds the partial rows, then the two row means of every row (per range of 2048 columns)
   float* row_means = partials + (size_t)nparts * 2 * (size_t)C;
@@ -570,7 +578,7 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
                      row_means, partials);
   const int32_t rc1 = launch_status();
   if (rc1 != JF_OK) return rc1;
-  const ColumnSums cs = {partials, dgamma, dbeta, nparts, (int)((2 * C + 63) / 64)};
+  const ColumnSums cs = {partials, dgamma, dbeta, nparts, sums_in_place ? 0 : (int)((2 * C + 63) / 64)};
   const dim3 tiles(cs.groups + tile_grid((C + 127) / 128, N / block)), strips(cs.groups + strip_grid(N, C).x);
   const float* none = nullptr;
   with_store_policy(N, C, [&](auto sp) {
@@ -585,7 +593,8 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
       hipLaunchKernelGGL((layernorm_tile_kernel<128, 1, SP>), tiles, dim3(256), 0, st, dY, SdY, X, SX, gamma, none, mean, rstd,
                          (const float*)row_means, ranges, (int)N, (int)C, dX, SdX, cs);
   });
-  return launch_status();
+  const int32_t rc2 = launch_status();
+  return rc2 != JF_OK || !sums_in_place ? rc2 : launch_colsum();
 }
 
 static int32_t layernorm_bwd_check(const int8_t* dY, const float* SdY, const int8_t* X, const float* SX,

@@ -41,9 +41,9 @@ struct LayerNormBwdRows {
 
 // Whether the one-pass kernels take rows of C columns at this block size, and their launches.  The backward one returns
 // the number of partial rows of dgamma | dbeta that it leaves in `partials` (at most 256 and at most rows / 32), or 0 if it
-// has written dgamma and dbeta themselves.
+// has written dgamma and dbeta themselves, which it does not do where an output shares memory with an input (in_place).
 bool layernorm_rows_fits(int64_t C, int32_t block);
 void launch_layernorm_rows(LayerNormRows a, hipStream_t st);
-int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st);
+int launch_layernorm_bwd_rows(LayerNormBwdRows a, bool in_place, hipStream_t st);
 
 }  // namespace jf

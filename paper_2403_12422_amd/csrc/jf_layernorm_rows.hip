@@ -518,7 +518,7 @@ void launch_layernorm_rows(LayerNormRows a, hipStream_t st) {
   });
 }
 
-int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st) {
+int launch_layernorm_bwd_rows(LayerNormBwdRows a, bool in_place, hipStream_t st) {
   const int groups = a.rows / 32;
   a.strips = (a.cols + 127) / 128;
   a.teams = choose_teams(a.strips, groups);
@@ -526,7 +526,7 @@ int launch_layernorm_bwd_rows(LayerNormBwdRows a, hipStream_t st) {
   const int waves = a.strips * a.teams;
   a.row_wgs = std::min((groups + a.teams - 1) / a.teams, 256);
   static_assert(16 * (kBwdRowBytes + kBwdWaveBytes) <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
-  const bool apart = a.rows <= 2048 && groups <= 12 * waves;   // at most 12 row groups for a wave of the column workgroups
+  const bool apart = !in_place && a.rows <= 2048 && groups <= 12 * waves;   // at most 12 row groups for a wave of the column workgroups
   with_store_policy(a.rows, a.cols, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
     if constexpr (SP == kStoreThrough) {   // (2048 rows are always stored through)
