@@ -34,10 +34,11 @@
  *    very buffer of an operand of the same size: the codes (and, with them or
  *    by themselves, the scales) that GELU, Add, Dropout and LayerNorm write,
  *    forward and backward, over those of any of their operands; LayerNorm
- *    backward's dgamma or dbeta over gamma.  (LayerNorm backward adds its
- *    column sums in another, equally fixed, order there.)  Any other overlap
- *    of an output with an input, another output or ws gives unspecified
- *    results.
+ *    backward's dgamma or dbeta over gamma; jf_linear_bwd's dW and SdW over W
+ *    and SW.  (LayerNorm backward adds its column sums in another, equally
+ *    fixed, order there; jf_linear_bwd launches its products one by one.)  Any
+ *    other overlap of an output with an input, another output or ws gives
+ *    unspecified results.
  *  - Inputs are assumed finite; NaN/Inf inputs and codes of -128 give
  *    unspecified results (never out-of-bounds accesses).
  *
@@ -148,9 +149,8 @@ int32_t jf_linear_wgrad(const int8_t* dY, const float* SdY, const int8_t* X, con
  * Both backward products of a layer in one call (Sec. 4): dX = dY W exactly
  * as jf_linear_dgrad and dW = dY^T X exactly as jf_linear_wgrad, same
  * arguments, same results bit for bit.  The two products need the same dY
- * and nothing of each other; for layers whose products are too small to fill
- * the chip one by one (block 32, outputs of a few hundred 64 x 64 tiles) they
- * run as ONE kernel launch, otherwise as two.
+ * and nothing of each other, so they run as ONE kernel launch where a model of
+ * the launch says that this is faster, otherwise as two.
  */
 int32_t jf_linear_bwd(const int8_t* dY, const float* SdY, const int8_t* W, const float* SW, const int8_t* X,
                       const float* SX, int64_t N, int64_t C, int64_t D, int32_t block, int8_t* dX, float* SdX,

@@ -142,7 +142,10 @@ extern "C" int32_t jf_linear_bwd(const int8_t* dY, const float* SdY, const int8_
   GemmArgs gw = make_args(2, dY, SdY, X, SX, N, C, D, block);
   gw.Oq = dW; gw.Os = SdW; gw.Of = dW_f32;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (!launch_bwd_pair(block, gd, gw, st)) {
+  // dW over W: the input gradient has to have read W before the weight gradient replaces it
+  const MemRange weights[] = {{W, D * C}, {SW, D / block * (C / block) * 4}};
+  const MemRange grads[] = {{dW, D * C}, {SdW, D / block * (C / block) * 4}, {dW_f32, D * C * 4}};
+  if (any_overlap(grads, weights) || !launch_bwd_pair(block, gd, gw, st)) {
     launch_gemm(1, block, gd, false, st);
     rc = launch_status();
     if (rc != JF_OK) return rc;

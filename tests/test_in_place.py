@@ -100,3 +100,25 @@ def test_layernorm_backward(block, N, C):
         dX, SdX, dg, db = jf.jf_layernorm_q_bwd(*t.values(), block, out=tuple(out))
         _same((dX, SdX), want[:2])
         assert_layernorm_param_grads_close(host(dg), host(db), o[2], o[3], oracle.dequantize(G, SG, block), xh, over)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("block", [32, 64, 128])
+@pytest.mark.parametrize("blocks", [(3, 5, 2), (8, 8, 8), (37, 5, 3)])
+def test_weight_gradient_over_the_weights(block, blocks):
+    N, C, D = (block * b for b in blocks)
+    g = workloads.rng(9500 + N)
+    quantized = lambda r, c, std: tuple(map(dev, oracle.quantize_block(workloads.gaussian(g, r, c, std), block)))
+    X, W, dY = quantized(N, C, 1.0), quantized(D, C, 0.02), quantized(N, D, 1e-3)
+    want = jf.jf_linear_dgrad(*dY, *W, block), jf.jf_linear_wgrad(*dY, *X, block)
+    try:
+        for shape in (0, 21, 22):   # automatic, and both products asked for in one launch
+            say(f"weight gradient over the weights block={block} {N} x {C} -> {D}, shape {shape}")
+            jf.jf_debug_set_gemm_shape(shape)
+            Wc = tuple(t.clone() for t in W)
+            dX = torch.empty((N, C), dtype=torch.int8, device="cuda"), torch.empty((N // block, C // block), device="cuda")
+            got = jf.jf_linear_bwd(*dY, *Wc, *X, block, out=((*dX, None), (*Wc, None)))
+            _same(got[0][:2], want[0][:2])
+            _same(got[1][:2], want[1][:2])
+    finally:
+        jf.jf_debug_set_gemm_shape(0)
