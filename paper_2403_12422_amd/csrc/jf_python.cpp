@@ -113,19 +113,29 @@ Ref owned(PyObject* o) {
 }
 Ref same(PyObject* o) { Py_INCREF(o); return Ref(o); }
 Ref none() { return same(Py_None); }
-// An output from torch's caching allocator.  On the current device, where a tensor of that device exists already, the
-// generic constructor does: empty_cuda's lazy initialisation and device guards take 0.17 of its 0.51 us.
-c10::DeviceIndex g_device = -1;   // the current device, read at the start of every call (under the interpreter lock)
-Ref empty(std::initializer_list<int64_t> size, at::ScalarType dtype, const at::Tensor& like) {
-  const at::IntArrayRef s(size.begin(), size.size());
-  const bool here = like.device().index() == g_device;
-  static at::Allocator* const allocator = c10::hip::HIPCachingAllocatorMasqueradingAsCUDA::get();   // torch's for its "cuda" devices
-  return owned(THPVariable_Wrap(at::Tensor(
-      here ? at::detail::empty_generic(s, allocator, c10::DispatchKeySet(c10::DispatchKey::CUDA), dtype, std::nullopt)
-           : at::detail::empty_cuda(s, dtype, like.device(), std::nullopt))));
-}
-Ref empty_codes(int64_t r, int64_t c, const at::Tensor& like) { return empty({r, c}, at::kChar, like); }
-Ref empty_grid(int64_t r, int64_t c, int64_t b, const at::Tensor& like) { return empty({r / b, c / b}, at::kFloat, like); }
+// New outputs on the device of `like`, from torch's caching allocator.  On the current device, where a tensor of that device
+// exists already, the generic constructor does: empty_cuda's lazy initialisation and device guards take 0.17 of its 0.51 us.
+// Which device is current belongs to the calling thread and is read for each call.
+class Outputs {
+  const at::Tensor& like;
+  bool here;
+
+ public:
+  explicit Outputs(const at::Tensor& t) : like(t) {
+    c10::DeviceIndex device = -1;
+    here = c10::hip::GetDevice(&device) == hipSuccess && t.device().index() == device;
+  }
+  Ref tensor(std::initializer_list<int64_t> size, at::ScalarType dtype) const {
+    const at::IntArrayRef s(size.begin(), size.size());
+    if (!here) return owned(THPVariable_Wrap(at::Tensor(at::detail::empty_cuda(s, dtype, like.device(), std::nullopt))));
+    at::Allocator* const allocator = c10::hip::HIPCachingAllocatorMasqueradingAsCUDA::get();   // torch's for its "cuda" devices
+    return owned(THPVariable_Wrap(
+        at::Tensor(at::detail::empty_generic(s, allocator, c10::DispatchKeySet(c10::DispatchKey::CUDA), dtype, std::nullopt))));
+  }
+  Ref floats(std::initializer_list<int64_t> size) const { return tensor(size, at::kFloat); }
+  Ref codes(int64_t r, int64_t c) const { return tensor({r, c}, at::kChar); }
+  Ref grid(int64_t r, int64_t c, int64_t b) const { return floats({r / b, c / b}); }
+};
 
 // The caller's preallocated outputs: item i of a sequence that must hold `n` items (n < 0: at least -n).
 struct Given {
@@ -184,9 +194,10 @@ PyObject* quantize(PyObject* const* a, Py_ssize_t n) {
     q = out[0], s = out[1];
     qT = (transposed ? out[2] : none()), sT = (transposed ? out[3] : none());
   } else {
-    q = empty_codes(rows, cols, x), s = empty_grid(rows, cols, b, x);
-    qT = (transposed ? empty_codes(cols, rows, x) : none());
-    sT = (transposed ? empty_grid(cols, rows, b, x) : none());
+    const Outputs make(x);
+    q = make.codes(rows, cols), s = make.grid(rows, cols, b);
+    qT = (transposed ? make.codes(cols, rows) : none());
+    sT = (transposed ? make.grid(cols, rows, b) : none());
   }
   const void* px = x.const_data_ptr();
   int8_t *pq = pointer<int8_t>(q.p), *pqT = pointer<int8_t>(qT.p);
@@ -202,7 +213,7 @@ PyObject* dequantize(PyObject* const* a, Py_ssize_t n) {
   const int32_t b = (int32_t)integer(a[2]);
   const bool half = flag(a[3]);
   const int64_t rows = q.size(0), cols = q.size(1);
-  Ref out = a[4] != Py_None ? same(a[4]) : empty({rows, cols}, half ? at::kHalf : at::kFloat, q);
+  Ref out = a[4] != Py_None ? same(a[4]) : Outputs(q).tensor({rows, cols}, half ? at::kHalf : at::kFloat);
   void* po = pointer<void>(out.p);
   launch([&](void* st) { return jf_dequantize_block(in<int8_t>(q), in<float>(s), rows, cols, b, po, half ? 1 : 0, cols, st); });
   return out.release();
@@ -218,9 +229,10 @@ PyObject* linear(linear_fn fn, const at::Tensor& p, const at::Tensor& sp, const 
     const Given out(given, 3);
     q = out[0], s = out[1], f = out[2];
   } else {
-    q = (want_q ? empty_codes(rows, cols, p) : none());
-    s = (want_q ? empty_grid(rows, cols, b, p) : none());
-    f = (want_f32 ? empty({rows, cols}, at::kFloat, p) : none());
+    const Outputs make(p);
+    q = (want_q ? make.codes(rows, cols) : none());
+    s = (want_q ? make.grid(rows, cols, b) : none());
+    f = (want_f32 ? make.floats({rows, cols}) : none());
   }
   int8_t* pq = pointer<int8_t>(q.p);
   float *ps = pointer<float>(s.p), *pf = pointer<float>(f.p);
@@ -271,11 +283,12 @@ PyObject* linear_bwd(PyObject* const* a, Py_ssize_t n) {
       for (int j = 0; j < 3; ++j) o[3 * i + j] = half[j];
     }
   } else {
+    const Outputs make(dY);
     const int64_t rows[2] = {N, D};
     for (int i = 0; i < 2; ++i) {
-      o[3 * i] = empty_codes(rows[i], C, dY);
-      o[3 * i + 1] = empty_grid(rows[i], C, b, dY);
-      o[3 * i + 2] = (want_f32 ? empty({rows[i], C}, at::kFloat, dY) : none());
+      o[3 * i] = make.codes(rows[i], C);
+      o[3 * i + 1] = make.grid(rows[i], C, b);
+      o[3 * i + 2] = (want_f32 ? make.floats({rows[i], C}) : none());
     }
   }
   int8_t *dX = pointer<int8_t>(o[0].p), *dW = pointer<int8_t>(o[3].p);
@@ -299,7 +312,8 @@ PyObject* gelu(PyObject* const* a, Py_ssize_t n) {
     const Given out(a[3], 2);
     Y = out[0], SY = out[1];
   } else {
-    Y = empty_codes(N, C, X), SY = empty({SX.size(0), SX.size(1)}, at::kFloat, X);
+    const Outputs make(X);
+    Y = make.codes(N, C), SY = make.floats({SX.size(0), SX.size(1)});
   }
   int8_t* y = pointer<int8_t>(Y.p);
   float* sy = pointer<float>(SY.p);
@@ -319,7 +333,8 @@ PyObject* gelu_bwd(PyObject* const* a, Py_ssize_t n) {
     const Given out(a[5], 2);
     dX = out[0], SdX = out[1];
   } else {
-    dX = empty_codes(N, C, X), SdX = empty({SX.size(0), SX.size(1)}, at::kFloat, X);
+    const Outputs make(X);
+    dX = make.codes(N, C), SdX = make.floats({SX.size(0), SX.size(1)});
   }
   int8_t* y = pointer<int8_t>(dX.p);
   float* sy = pointer<float>(SdX.p);
@@ -347,8 +362,9 @@ PyObject* layernorm(PyObject* const* a, Py_ssize_t n) {
     const Given out(a[8], 4);
     Y = out[0], SY = out[1], mean = out[2], rstd = out[3];
   } else {
-    Y = empty_codes(N, C, X), SY = empty({SX.size(0), SX.size(1)}, at::kFloat, X);
-    mean = empty({N}, at::kFloat, X), rstd = empty({N}, at::kFloat, X);
+    const Outputs make(X);
+    Y = make.codes(N, C), SY = make.floats({SX.size(0), SX.size(1)});
+    mean = make.floats({N}), rstd = make.floats({N});
   }
   int8_t* y = pointer<int8_t>(Y.p);
   float *sy = pointer<float>(SY.p), *mu = pointer<float>(mean.p), *rs = pointer<float>(rstd.p);
@@ -372,7 +388,8 @@ PyObject* dropout(PyObject* const* a, Py_ssize_t n) {
     const Given out(a[5], 2);
     Y = out[0], SY = out[1];
   } else {
-    Y = empty_codes(N, C, X), SY = empty({SX.size(0), SX.size(1)}, at::kFloat, X);
+    const Outputs make(X);
+    Y = make.codes(N, C), SY = make.floats({SX.size(0), SX.size(1)});
   }
   int8_t* y = pointer<int8_t>(Y.p);
   float* sy = pointer<float>(SY.p);
@@ -394,9 +411,10 @@ PyObject* add(PyObject* const* a, Py_ssize_t n) {
     Y = out[0], SY = out[1];
     rm = (partials ? out[2] : none()), rq = (partials ? out[3] : none());
   } else {
-    Y = empty_codes(N, C, X1), SY = empty({S1.size(0), S1.size(1)}, at::kFloat, X1);
-    rm = (partials ? empty({C / b, N}, at::kFloat, X1) : none());
-    rq = (partials ? empty({C / b, N}, at::kFloat, X1) : none());
+    const Outputs make(X1);
+    Y = make.codes(N, C), SY = make.floats({S1.size(0), S1.size(1)});
+    rm = (partials ? make.floats({C / b, N}) : none());
+    rq = (partials ? make.floats({C / b, N}) : none());
   }
   int8_t* y = pointer<int8_t>(Y.p);
   float *sy = pointer<float>(SY.p), *m = pointer<float>(rm.p), *q = pointer<float>(rq.p);
@@ -419,7 +437,7 @@ PyObject* layernorm_bwd(PyObject* const* a, Py_ssize_t n) {
       ws = same(a[8]);
     } else {
       const int64_t need = (int64_t)jf_workspace_bytes(JF_OP_LAYERNORM_BWD, N, C, 0, b);
-      ws = empty({need > 16 ? need : 16}, at::kByte, X);
+      ws = Outputs(X).tensor({need > 16 ? need : 16}, at::kByte);
     }
   }
   Ref dX, SdX, dg, db;
@@ -428,8 +446,9 @@ PyObject* layernorm_bwd(PyObject* const* a, Py_ssize_t n) {
     dX = out[0], SdX = out[1], dg = out[2], db = out[3];
     if (fixed) codes(dX.p), grid(SdX.p), vector(dg.p), vector(db.p);
   } else {
-    dX = empty_codes(N, C, X), SdX = empty({SX.size(0), SX.size(1)}, at::kFloat, X);
-    dg = empty({C}, at::kFloat, X), db = empty({C}, at::kFloat, X);
+    const Outputs make(X);
+    dX = make.codes(N, C), SdX = make.floats({SX.size(0), SX.size(1)});
+    dg = make.floats({C}), db = make.floats({C});
   }
   int8_t* y = pointer<int8_t>(dX.p);
   float *sy = pointer<float>(SdX.p), *g = pointer<float>(dg.p), *e = pointer<float>(db.p);
@@ -455,7 +474,6 @@ PyObject* init(PyObject* const* a, Py_ssize_t n) {
 template <PyObject* (*F)(PyObject* const*, Py_ssize_t)>
 PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  if (c10::hip::GetDevice(&g_device) != hipSuccess) g_device = -1;   // no GPU: the operands' checks say so
   return F(args, n);
   END_HANDLE_TH_ERRORS
 }

@@ -11,6 +11,8 @@ ALLOWED = {
     # the scratch of jf_layernorm_q_bwd_static and its address per device, the test hook for tile shapes, the error code of
     # each thread; a constant table of functions
     build.LIB: ("scratch", "g_scratch_ptr", "g_scratch_mutex", "g_forced_shape", "g_last_hip_error", "launch_gemm.*table"),
+    # the exception class and the module's own tables
+    build.EXT: ("g_error", "g_methods", "g_module"),
 }
 
 
