@@ -12,6 +12,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libjetfire.so")
+_EXT_PATH = os.path.join(_HERE, "_native.so")
 _lib = None
 _ext = None
 
@@ -75,6 +76,9 @@ def _native():
     global _ext
     if _ext is None:
         load_library()
+        if not os.path.exists(_EXT_PATH):
+            raise JetfireError(-1, f"{_EXT_PATH} is missing: run `python -m paper_2403_12422_amd.build` with the headers of this "
+                                   "Python and torch installed; without it only load_library() works, the C ABI itself")
         ext = importlib.import_module(__package__ + "._native")
         ext.init(JetfireError)
         _ext = ext
