@@ -200,5 +200,6 @@ def jf_debug_linear_partials(which, A, Bm, N, C, D, block, kb):
 
 
 def jf_debug_set_gemm_shape(shape):
-    """Test hook: 0 automatic, 1 128x128, 4 64x64, 6 256x128, 7 64x64 with a deep stage, 8 128x64."""
+    """Test hook: 0 automatic, 1 128x128, 4 64x64, 6 256x128, 8 128x64, 10 32x32, 21..25 pairs of shapes for both backward
+    products in one launch, as far as the block size has them (include/jetfire.h); else the choice stays automatic."""
     _check(load_library().jf_debug_set_gemm_shape(shape))

@@ -156,14 +156,7 @@ __device__ __forceinline__ void load_lds_16(const int8_t* ubase, uint32_t voff, 
                : "v"(voff), "s"(ubase), "s"(lds_address(lds_tile, lds_byte))
                : "memory", "m0");
 }
-// the same with a full 64-bit address per lane (the clamped last stage of a K that is not a multiple of the stage)
-__device__ __forceinline__ void load_lds_16_vaddr(const int8_t* vaddr, const int8_t* lds_tile, int lds_byte) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(vaddr), "s"(lds_address(lds_tile, lds_byte))
-               : "memory", "m0");
-}
-// the same with 4 bytes per lane (lane l's to LDS address lds + 4*l), in both address forms
+// the same with 4 bytes per lane (lane l's to LDS address lds + 4*l), in that form and with a full 64-bit address per lane
 __device__ __forceinline__ void load_lds_4(const void* ubase, uint32_t voff, const int8_t* lds_tile, int lds_byte) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :

@@ -73,8 +73,6 @@ struct TileLayout {
 
 typedef __attribute__((address_space(3))) v2i* lds_v2i;
 typedef __attribute__((address_space(3))) v4i* lds_v4i;
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) v4f* lds_v4f;
 
 // Per-lane LDS byte offsets of an operand's MFMA fragments inside a stage buffer.  Everything that
 // does not depend on the lane is a compile-time immediate added at the read, so the main loop spends

@@ -67,8 +67,7 @@ static GemmArgs make_args(int which, const int8_t* a, const float* sa, const int
                           int64_t C, int64_t D, int32_t block) {
   GemmArgs g{};
   g.A = a; g.SA = sa; g.Bm = b; g.SB = sb;
-  const int LN = (int)(N / block), LC = (int)(C / block), LD = (int)(D / block);
-  (void)LN;
+  const int LC = (int)(C / block), LD = (int)(D / block);
   if (which == 0) {         // Y = X W^T : A = X (N x C) K-major, Bm = W (D x C) K-major
     g.M = (int)N; g.Nn = (int)D; g.K = (int)C; g.lda = C; g.ldb = C;
     g.sa_p = LC; g.sa_k = 1; g.sb_p = LC; g.sb_k = 1;
@@ -172,6 +171,7 @@ extern "C" int32_t jf_debug_linear_partials(int32_t which, const int8_t* A, cons
   return launch_status();
 }
 
+// (7 was a 64x64 tile with longer stages, which shape 4 has now; it is still accepted and leaves the choice automatic)
 extern "C" int32_t jf_debug_set_gemm_shape(int32_t shape) {
   if (shape != 0 && shape != 1 && shape != 4 && shape != 6 && shape != 7 && shape != 8 && shape != 10 && (shape < 21 || shape > 25)) return JF_ERR_SHAPE;
   jf::g_forced_shape.store(shape, std::memory_order_relaxed);
