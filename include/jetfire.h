@@ -175,7 +175,7 @@ int32_t jf_gelu_q_bwd(const int8_t* dY, const float* SdY, const int8_t* X, const
  * are those of the dequantized input; y = (x - mean) * rstd * gamma + beta.
  * gamma, beta: FP32 [C] (Sec. 7.1 keeps them in floating point).
  * Outputs: Y codes + SY, and mean[N], rstd[N] (FP32, saved for backward).
- * Rows may be of any width (no workgroup holds a whole row).
+ * Rows may be of any width.
  */
 int32_t jf_layernorm_q(const int8_t* X, const float* SX, const float* gamma, const float* beta, float eps, int64_t N,
                        int64_t C, int32_t block, int8_t* Y, float* SY, float* mean, float* rstd, void* stream);

@@ -203,9 +203,19 @@ __device__ __forceinline__ void store_out(void* p, const uint4& v) {
 // How the operators that run at the speed of memory store a result of `rows` rows of `row_bytes` bytes: chosen by the
 // launcher, a template argument of the kernels (a branch in the kernel costs the large tensors 2-3 %).
 // Rows that are no multiple of a line share lines between waves, and a result beyond the last-level cache then pays for
-// every piece: written back from 32 MB on (GELU 199680 x 1504: 385 -> 306 us, 40000 x 1504: 64 -> 62; 16384 x 1504, 25 MB:
-// through 26.3, back 29.1).  Whole lines that no cache will hold for the reader are streamed from 64 MB on (GELU 100000 x
-// 1536: 149 -> 136 us, 262144 x 3072: 742 -> 728).
+// every piece: written back from 32 MB on.  Whole lines that no cache will hold for the reader are streamed from 64 MB on.
+// Through / stream / back, block 32, operands from memory (us):
+//   1048576 x 768, whole lines   Add 451 / 433 / 452, GELU backward 451 / 436 / 452, Dropout 301 / 286 / 304, LayerNorm 310 /
+//                                311 / 315, FP16 quantizer 412 / 402 / 429, FP16 dequantizer 407 / 392 / 411
+//   98304 x 768, whole lines     Add 42.5 / 41.0 / 42.6, GELU 29.2 / 28.5 / 30.4, LayerNorm 34.2 / 31.3 / 34.9, backward 60.2 / 58.0 /
+//                                62.0, FP32 quantizer 70.1 / 66.6 / 69.5, FP16 dequantizer 39.6 / 37.4 / 40.5
+//   199680 x 1504, shared lines  Add 223 / 184 / 180, GELU 161 / 139 / 121, LayerNorm 174 / 154 / 126, backward 254 / 229 / 215,
+//                                quantizers and dequantizer equal within 3 %
+//   16384 x 1280, whole lines    GELU 9.9 / 10.2 / 11.5, LayerNorm 12.2 / 12.9 / 14.1, FP16 quantizer 10.8 / 11.6 / 12.6
+// (Between the bounds, 37 to 68 MB, streaming is 5-15 % faster still for an operator by itself -- LayerNorm 65536 x 768
+// 25.3 / 22.2 / 25.5, 24576 x 1504 21.8 / 19.8 / 20.8 -- but takes the result out of the cache that its reader finds it in.)
+// The products always write through: their results make up too little of their time for the rule to matter (forward 32768 x
+// 768 -> 3104, 101 MB of shared lines, 181 / 182 / 184; 16384 x 4096 -> 4096 485 / 483 / 487).
 enum StorePolicy { kStoreThrough, kStoreStream, kStoreBack };
 inline StorePolicy store_policy(int64_t rows, int64_t row_bytes) {
   const int64_t bytes = rows * row_bytes;

@@ -158,8 +158,9 @@ struct GemmShape {
   static constexpr int A_BYTES = LA::bytes(NW), B_BYTES = LB::bytes(NW);
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   // Stages in the LDS ring: one being read, the rest in flight.  Two for the waves of one sub-block at B = 32: with four
-  // workgroups per compute unit a stage lasts long enough (2048^3 on 64x64 tiles 22.5 -> 20.1 us against three stages of 64
-  // bytes, 23.0 against three of 128, which leave room for three workgroups).  Tiles that leave a compute unit to a single
+  // workgroups per compute unit a stage lasts long enough (2048^3, forward / dgrad / wgrad: 22.0 / 20.9 / 22.7 us
+  // against 23.5 / 22.2 / 22.7 with three stages of 64 bytes; 4096 x 768 -> 3072 27.2 / 23.3 / 29.8 against 29.4 / 25.8 / 30.0;
+  // three stages of 128 bytes leave room for three workgroups and are slower).  Tiles that leave a compute unit to a single
   // workgroup (more than four waves, B > 32) take four if that fits the LDS, the others three.
   static constexpr int NBUF = (B == 32 && WM * WN == 1) ? 2 : (B > 32 && NW > 4 && 4 * STAGE_BYTES <= 156 * 1024) ? 4 : 3;
   static_assert(NBUF * STAGE_BYTES <= 156 * 1024, "the ring must fit the LDS of a compute unit");
