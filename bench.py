@@ -585,21 +585,24 @@ def main():
         del xl, sxl, gl, sgl, yl, syl, ml, rl, wsl, xq, oq, osq
         torch.cuda.empty_cache()
 
-    # HBM traffic of the GEMM kernels and the ceilings of the fold: measured offline (rocprofv3 --pmc resp. the
-    # micro-benchmarks), summarised into JSON files under profiles/ by microbench/summarize_profiles.py
+    # HBM traffic of the GEMM kernels and the ceiling of the fold are not measured in this run: rocprofv3 --pmc resp. the
+    # micro-benchmarks, summarised into JSON files under profiles/ by microbench/summarize_profiles.py.  The traffic counts
+    # only if it was recorded on the kernels as they are; the ceiling is the machine's and does not depend on them.
+    from paper_2403_12422_amd.build import source_digest
+
     def profile_json(name):
         path = os.path.join(ROOT, "profiles", name)
         return json.load(open(path)) if os.path.exists(path) else None
 
     traffic = None
     tj = profile_json("bench_config2_hbm_traffic.json")
-    if (N, C, D, B) == (4096, 768, 3072, 32) and tj:
+    if (N, C, D, B) == (4096, 768, 3072, 32) and tj and tj.get("kernel_sources") == source_digest():
         traffic = tj.get("gemm_bytes_per_step_launches")
     fold = profile_json("microbench_fold_ceilings.json")
     ceiling = None
     if fold and str(B) in fold.get("bare_fold_TOPS", {}):
         ceiling = {"bare_TOPS": fold["bare_fold_TOPS"][str(B)],
-                   "with_k_loop_overheads_TOPS": fold.get("with_k_loop_overheads_TOPS", {}).get(str(B)),
+                   "measured": "by micro-benchmarks on another occasion",
                    "frac_of_bare": round(achieved / fold["bare_fold_TOPS"][str(B)], 4),
                    "source": fold.get("source")}
 
@@ -641,8 +644,9 @@ def main():
             "unit_note": "INT8 multiply-accumulate counted as 2 ops (TOP/s)",
             "frac": round(achieved / INT8_MFMA_PEAK_TOPS, 4),
             "traffic": traffic,
-            "traffic_note": "HBM bytes of the two GEMM launches of a step, rocprofv3 FETCH_SIZE + WRITE_SIZE scaled by a 256 MiB "
-                            "copy; algorithmic bytes are 3 x 18.1e6",
+            "traffic_note": "HBM bytes of the two GEMM launches of a step, from profiles/bench_config2_hbm_traffic.json (recorded on these "
+                            "kernel sources; null where they have changed since), not of this run: rocprofv3 FETCH_SIZE + "
+                            "WRITE_SIZE scaled by a 256 MiB copy; algorithmic bytes are 3 x 18.1e6",
             "avg_launch_ms": round(step_gemm_ms / 2, 5),
             "launch_ms": {k: r4(v) for k, v in gemm_loops.items()},
             "launch_ms_note": f"per launch, from 5 x {args.gemm_loop_launches} back-to-back launches between HIP events on the launch stream; "

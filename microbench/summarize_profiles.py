@@ -15,6 +15,8 @@ import re
 import sys
 
 R = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, R)
+from paper_2403_12422_amd.build import source_digest  # noqa: E402
 RAW_NAME = sys.argv[1].rstrip("/") if len(sys.argv) > 1 else sys.exit(__doc__)
 RAW = os.path.join(R, RAW_NAME)
 OUT = os.path.join(R, "profiles")
@@ -23,6 +25,14 @@ PROLOGUE = "(run on the MI355X machine from /tmp with TMPDIR=/tmp; paths relative to
 
 def short(name, n=120):
     return re.sub(r"^void ", "", name)[:n]
+
+
+def product(name):
+    """fwd, dgrad, wgrad or pair of a GEMM kernel, from its operands' layouts (A K-major, B K-major)."""
+    if "gemm_pair_kernel" in name:
+        return "pair"
+    flags = tuple(re.findall(r"true|false", name)[:2])
+    return {("true", "true"): "fwd", ("true", "false"): "dgrad", ("false", "false"): "wgrad"}.get(flags, "other")
 
 
 def have(*paths):
@@ -64,8 +74,8 @@ def bench_kernel_trace():
         per.setdefault(r["Kernel_Name"], []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
     out = ["rocprofv3 kernel-trace summary of the default benchmark (config 2: tokens 4096, in 768, out 3072, block 32)",
            "command " + PROLOGUE + ":", "  " + cmd,
-           "220 steps (20 warm-up + 200 timed; two GEMM launches each: gemm_kernel<32, 2, 2, 2, 2, true, true, ..> = forward product on",
-           "128x128 tiles, gemm_pair_kernel = input gradient + weight gradient in one grid of 64x64 tiles), then the dedicated timing",
+           "220 steps (20 warm-up + 200 timed; two GEMM launches each: gemm_kernel with both operands K-major (true, true) = forward",
+           "product, gemm_pair_kernel = input gradient + weight gradient in one grid), then the dedicated timing",
            "loops of bench.py (5 x 100 back-to-back launches of the forward product, the pair, dgrad alone, wgrad alone), then the",
            "per-op loops of the memory-bound kernels at the configured shape.", ""] + table + [""]
     ops = 2.0 * 4096 * 768 * 3072
@@ -78,8 +88,8 @@ def bench_kernel_trace():
         a, b, c = sum(d) / len(d), (sum(d[:n_step]) / n_step if n_step else float("nan")), sum(d[-500:]) / len(d[-500:])
         out.append(f"{a:14.2f} {b:10.2f} {c:10.2f} {len(d):6d}  {short(name, 100)}")
         summary[name] = (a, b, c)
-    fwd = [v for k, v in summary.items() if "gemm_kernel<32, 2, 2, 2, 2, true, true" in k]
-    pair = [v for k, v in summary.items() if "gemm_pair_kernel" in k]
+    fwd = [v for k, v in summary.items() if product(k) == "fwd"]
+    pair = [v for k, v in summary.items() if product(k) == "pair"]
     if fwd and pair:
         for label, i in (("all launches", 0), ("launches inside the steps", 1), ("launches of the timing loops", 2)):
             t = fwd[0][i] + pair[0][i]
@@ -117,10 +127,10 @@ def bench_hbm_traffic():
            f"calibration: a plain 256 MiB device-to-device copy (torch copy_, kernel __amd_rocclr_copyBuffer) reads FETCH_SIZE = {cf:.0f}",
            f"and WRITE_SIZE = {cw:.0f} for 262144 KiB each way -> scale factors {sf:.3f} (fetch) and {sw:.3f} (write) KiB per count",
            "", f"{'kernel':44s} {'fetch KiB':>10} {'write KiB':>12} {'total MB':>10}  algorithmic MB"]
-    ent = [("gemm forward (gemm_kernel 128x128)", lambda k: "gemm_kernel<32, 2, 2, 2, 2, true, true" in k, 18.2),
-           ("gemm dgrad + wgrad (gemm_pair_kernel)", lambda k: "gemm_pair_kernel" in k, 36.3),
-           ("gemm dgrad alone (64x64, deep stage)", lambda k: "gemm_kernel<32, 1, 1, 2, 2, true, false" in k, 18.2),
-           ("gemm wgrad alone (64x64)", lambda k: "gemm_kernel<32, 1, 1, 2, 2, false, false" in k, 18.2)]
+    ent = [("gemm forward", lambda k: "gemm" in k and product(k) == "fwd", 18.2),
+           ("gemm dgrad + wgrad (gemm_pair_kernel)", lambda k: "gemm" in k and product(k) == "pair", 36.3),
+           ("gemm dgrad alone", lambda k: "gemm" in k and product(k) == "dgrad", 18.2),
+           ("gemm wgrad alone", lambda k: "gemm" in k and product(k) == "wgrad", 18.2)]
     per = {}
     for name, pat, alg in ent:
         f, w = avg(fe, pat) * sf, avg(wr, pat) * sw
@@ -131,14 +141,13 @@ def bench_hbm_traffic():
             "The excess on the read side is re-reading by the eight XCDs: each XCD's L2 pulls its own copy of the operand band it",
             "works on from the Infinity Cache / HBM (FETCH_SIZE counts L2 misses, many of which hit the Infinity Cache).", ""]
     others = [("quantize (mean over X, W, dH)", "quantize_kernel"), ("gelu fwd", "gelu_strip32_kernel<false"), ("gelu bwd", "gelu_strip32_kernel<true"),
-              ("layernorm fwd: row statistics", "layernorm_row_stats_kernel"), ("layernorm fwd: normalise (strips)", "layernorm_apply_strip32_kernel"),
-              ("layernorm bwd: sums", "layernorm_bwd_sums_kernel"), ("layernorm bwd: dx (strips)", "layernorm_bwd_apply_strip32_kernel"),
+              ("layernorm fwd (one pass)", "layernorm_rows_kernel"), ("layernorm bwd (one pass)", "layernorm_bwd_rows_kernel"),
               ("colsum (dgamma, dbeta)", "colsum_kernel")]
     for name, key in others:
         f, w = avg(fe, lambda k: key in k) * sf, avg(wr, lambda k: key in k) * sw
         out.append(f"{name:44s} {f:10.0f} {w:12.0f} {(f + w) * 1024 / 1e6:10.1f}")
     write("bench_config2_hbm_traffic.txt", out)
-    json.dump({"workload": "config 2 (tokens 4096, in 768, out 3072, block 32)", "gemm_bytes_per_step_launches": int(step),
+    json.dump({"workload": "config 2 (tokens 4096, in 768, out 3072, block 32)", "kernel_sources": source_digest(), "gemm_bytes_per_step_launches": int(step),
                "per_kernel_bytes": {k: int(v) for k, v in per.items()}, "source": "profiles/bench_config2_hbm_traffic.txt"},
               open(os.path.join(OUT, "bench_config2_hbm_traffic.json"), "w"), indent=1)
     print("wrote profiles/bench_config2_hbm_traffic.json")
@@ -171,7 +180,7 @@ def hbm_sized_trace():
            "command " + PROLOGUE + ":",
            f"  rocprofv3 --kernel-trace --output-format csv -d {RAW_NAME}/prof_hbm -o hbm -- python3 bench.py --no-cpu-baseline --no-extra-configs --steps 5 --warmup 2 --gemm-loop-launches 2",
            "Only launches of at least 100 us are listed (the same kernels also run on the configured shapes).  GB/s = algorithmic bytes",
-           "of the operator (as in bench.py) / the kernel's average duration; LayerNorm forward and backward are two resp. three kernels.", "",
+           "of the operator (as in bench.py) / the kernel's average duration; LayerNorm forward is one kernel, backward two (the second adds the column sums).", "",
            f"{'avg us':>10} {'min us':>10} {'calls':>6} {'grid':>10}  kernel"]
     for (name, grid), d in sorted(per.items(), key=lambda kv: -sum(kv[1]) / len(kv[1])):
         if sum(d) / len(d) >= 100.0:
@@ -221,7 +230,7 @@ def gemm_pmc():
                        f"{(a('SQ_INSTS_VALU') - a('SQ_INSTS_MFMA')) / a('SQ_INSTS_MFMA'):9.1f} {a('SQ_LDS_IDX_ACTIVE') / a('SQ_BUSY_CU_CYCLES'):8.3f} "
                        f"{a('TCC_MISS_sum') / a('TCC_REQ_sum'):8.3f} {a('TCC_REQ_sum') / 1e6:9.2f} {a('SQ_WAIT_INST_ANY') / a('SQ_WAVE_CYCLES'):6.3f}")
         out.append("")
-    out += ["Template arguments: block, sub-blocks per wave (rows, columns), waves per workgroup (rows, columns), A K-major, B K-major, ...",
+    out += ["Template arguments: block, sub-blocks per wave (rows, columns), waves per workgroup (rows, columns), A K-major, B K-major, test hook.",
             "Reading: at block 32 and 64 the vector ALU is the saturated pipe and the matrix cores are busy a fraction of the time that",
             "follows from the fold's instruction count per MFMA (Sec. 5.3): the dequantize fold bounds the kernel, not the MFMA rate."]
     write("gemm_pmc_mfma_valu_utilisation.txt", out)
@@ -239,28 +248,23 @@ def microbench():
             "  that no MFMA writes; '1 mfma + 16 cvt + 16 fmac' / '+ 8 cvt + 8 fmac' / '+ 4 cvt + 4 fmac' are block size 32 / 64 / 128;",
             "  'MFMA rate' = 65536 ops x 1024 SIMDs / that time.  fold_chain_rate: the same mixes with the real data flow (the fold reads the",
             "  tile the previous MFMA chain wrote, tiles in VGPRs).  kloop_overheads: the block-32 pattern of fold_chain_rate plus, one kind at a",
-            "  time, the other instructions of the real K loop (variant 1: one ds_read_b128 per unit; 2: + stage barrier; 3: + direct-to-LDS",
+            "  time, the other instructions of a K loop (variant 1: one ds_read_b128 per unit; 2: + stage barrier; 3: + direct-to-LDS",
             "  loads with 64-bit lane addresses; 4: + scalar scale loads and their product; 5: loads with scalar base + 32-bit lane offset,",
-            "  the form the GEMM kernel uses; 6: 5 with a stage's eight fragment reads issued at once).  kloop_model: the whole K loop",
-            "  written the naive way for the tile shapes and block sizes in use ('KC' = K bytes per stage).  l2_bandwidth: bytes per",
+            "  the form the GEMM kernel uses; 6: 5 with a stage's eight fragment reads issued at once).  kloop_model: a whole K loop",
+            "  written the naive way for a set of tile shapes and block sizes ('KC' = K bytes per stage).  Both take their scales by scalar",
+            "  loads and a stage's fragments together; the GEMM kernel does neither (scales by lane reads, fragments spread over the",
+            "  units) and is faster than the model at block 32 and 128, so it is no bound.  l2_bandwidth: bytes per",
             "  second into the compute units.  quantizer_issue_rate: issue cost per element of the Eq. 1 rounding variants and of the other",
             "  instructions of the memory-bound kernels.  transposed_operands: the weight gradient with its operands transposed inside the",
             "  kernel against the same product from pre-transposed copies, and what writing those copies costs the quantizer.", ""]
     write("microbench_machine_limits.txt", head + text)
-    bare, loop = {}, {}
+    bare = {}
     for l in text:
         m = re.match(r"block\s+(\d+) \(chain of \d\), tiles in VGPRs, (\d) waves/SIMD:\s+[\d.]+ ns per MFMA ->\s+(\d+) TOP/s", l)
         if m:
             bare[m.group(1)] = max(bare.get(m.group(1), 0.0), float(m.group(3)))
-        m = re.match(r"variant 5, (\d) waves/SIMD:\s+[\d.]+ ns per MFMA\+fold ->\s+(\d+) TOP/s", l)
-        if m:
-            loop["32"] = max(loop.get("32", 0.0), float(m.group(2)))
-        m = re.match(r"B=(\d+)\s+\S+, \d waves\s+full loop \d waves/SIMD:\s+[\d.]+ ns per MFMA ->\s+(\d+) TOP/s", l)
-        if m and m.group(1) != "32":
-            loop[m.group(1)] = max(loop.get(m.group(1), 0.0), float(m.group(2)))
-    json.dump({"bare_fold_TOPS": bare, "with_k_loop_overheads_TOPS": loop, "peak_TOPS": 5000.0,
-               "note": "best over 2-4 waves per SIMD; bare = MFMA chain + fold with no memory traffic (fold_chain_rate), with overheads = "
-                       "plus fragment reads, stage barrier, direct-to-LDS loads, scale loads (kloop_overheads variant 5 at block 32, kloop_model at 64 / 128)",
+    json.dump({"bare_fold_TOPS": bare, "peak_TOPS": 5000.0,
+               "note": "best over 2-4 waves per SIMD; MFMA chain + fold with no memory traffic (fold_chain_rate)",
                "source": "profiles/microbench_machine_limits.txt"}, open(os.path.join(OUT, "microbench_fold_ceilings.json"), "w"), indent=1)
     print("wrote profiles/microbench_fold_ceilings.json")
 

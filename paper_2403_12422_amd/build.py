@@ -6,7 +6,9 @@ library is built all the same (``python -m paper_2403_12422_amd.build --library-
 """
 import concurrent.futures
 import glob
+import hashlib
 import os
+import re
 import subprocess
 import sys
 import sysconfig
@@ -28,6 +30,16 @@ HIPCC_FLAGS = [
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+
+
+def source_digest() -> str:
+    """Digest of the device sources without their comments: tells whether a recorded profile is of the present kernels."""
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.h*"))):      # .hip and .hpp
+        with open(path) as f:
+            code = [re.sub(r"\s+", " ", line.split("//")[0]).strip() for line in f]
+        h.update("\n".join([os.path.basename(path)] + [line for line in code if line]).encode())
+    return h.hexdigest()[:16]
 
 
 def _run(cmd, verbose):
