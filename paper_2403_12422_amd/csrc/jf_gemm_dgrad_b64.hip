@@ -1,4 +1,4 @@
 // gemm_kernel instances of the dgrad product at block size 64 (a translation unit of its own for build time).
-#include "jf_gemm_kernel.hpp"
+#include "jf_gemm_wide.hpp"
 
 JF_GEMM_INSTANCE(launch_gemm_dgrad_b64, 64, true, false)

@@ -664,11 +664,16 @@ static void launch_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t st) 
 
 template <bool AK, bool BK>
 struct FineInstance;   // jf_gemm_fine.hpp
+template <int B, bool AK, bool BK>
+static void launch_wide(const GemmArgs& a, hipStream_t st);   // jf_gemm_wide.hpp
 
 // Launches the product on tile shape `shape`, numbered and chosen as jf_gemm_shapes.hpp says.  One translation unit per
 // (product, block size) instantiates this, so that the kernels compile in parallel.  AK / BK: operand A / Bm is K-major.
 template <int B, bool AK, bool BK, bool DUMP>
 static void launch_shape(int shape, const GemmArgs& a, hipStream_t st) {
+  if constexpr (B > 32 && !DUMP) {
+    if (shape == 11) return launch_wide<B, AK, BK>(a, st);
+  }
   if constexpr (B == 128) {
     if (shape == 6) launch_one<GemmInstance<B, 2, 2, 4, 2, AK, BK, DUMP>>(a, st);
     else launch_one<GemmInstance<B, 2, 1, 2, 4, AK, BK, DUMP>>(a, st);

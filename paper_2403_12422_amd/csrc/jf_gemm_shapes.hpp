@@ -11,11 +11,14 @@
 //       8192^3 alone, forward / dgrad / wgrad: 990 / 965 / 951 us on 128x128, 943 / 940 / 933 us on 256x128
 //   8   128x64: four waves of 2x1 sub-blocks, four workgroups per compute unit (B = 32)
 //   10  32x32: four waves of 16x16 outputs, jf_gemm_fine.hpp (B = 32)
+//   11  256x256: eight waves of 2x4 sub-blocks in persistent workgroups, one per compute unit, jf_gemm_wide.hpp (B = 64, 128)
 // A model of the busiest SIMD predicts the time of each and the least is taken.  Its constants are least-squares fits to the
 // measured times of 276 products (92 layers drawn over the logarithm of their sizes, 128 .. 16384 tokens, 128 .. 8192
 // features; all three products) and 184 backward passes: rms error 4-9 % for one shape, and the shape taken is on
-// average within 0.8 % (B = 32), 0.3 % (64) and 0.1 % (128) of the best one in each case; for the choice between one and
-// two launches of the backward products within 1.3 %, 0.1 % and 0.2 %.
+// average within 0.8 % (B = 32) of the best one in each case; for the choice between one and two launches of the backward
+// products within 1.3 %.  With shape 11, whose constants and those of the pairs at B = 128 are fitted to 540 products and 180
+// backward passes per block size: 0.5 % (B = 64) and 0.2 % (128), pairs 0.2 % and 0.8 %.  Over the same layers shape 11 is taken
+// for 11 % (B = 64) and 44 % (128) of the products and gains 0.9 % and 7.0 % on the average of all.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -29,6 +32,7 @@ namespace jf {
 // a SIMD shared by several workgroups, `ns_alone` on one that holds a single one (which cannot overlap its own MFMA, fold
 // and waits) in the forward product, `dgrad` and `wgrad` times that in the others, whose operands are read transposed, and
 // `epilogue_us` besides; fixed_us is the launch and the latency of the first stage.
+static constexpr int kPersistent = 1 << 24;   // as many as the largest output has
 enum Product { kForward, kDgrad, kWgrad };
 struct ShapeModel {
   int shape, tm, tn, resident;
@@ -40,6 +44,7 @@ struct ShapeModel {
     return sub * (a.K / 32 * rate * 1e-3 + epilogue_us);
   }
   double product_us(Product p, const GemmArgs& a) const {
+    // (a persistent workgroup takes whole tiles by turns, however many there are: `resident` is kPersistent there)
     const double t = tiles(a), busiest = t <= 256.0 * resident ? std::ceil(t / 256.0) : t / 256.0 + tail;
     return fixed_us + busiest * tile_us(p, a, busiest <= 1.0);
   }
@@ -53,10 +58,12 @@ static constexpr ShapeModel kShapes32[] = {
     {10, 32, 32, 4, 0.25, 3.26, 110.0, 125.5, 0.72, 1.798, 1.511, 2.205}};
 static constexpr ShapeModel kShapes64[] = {
     {1, 128, 128, 3, 4, 2.82, 42.2, 58.5, 0.51, 0.464, 0.967, 1.001},
-    {4, 64, 64, 3, 1, 2.71, 58.3, 66.0, 0.59, 0.827, 1.055, 1.237}};
+    {4, 64, 64, 3, 1, 2.71, 58.3, 66.0, 0.59, 0.827, 1.055, 1.237},
+    {11, 256, 256, kPersistent, 16, 0.0, 41.3, 38.4, 0.0, 0.490, 0.995, 0.990}};
 static constexpr ShapeModel kShapes128[] = {
     {6, 256, 128, 1, 8, -1.22, 29.8, 25.3, 0.38, 0.945, 1.014, 1.070},
-    {1, 128, 128, 1, 4, 1.44, 34.2, 30.7, 0.79, 0.890, 1.001, 1.046}};
+    {1, 128, 128, 1, 4, 1.44, 34.2, 30.7, 0.79, 0.890, 1.001, 1.046},
+    {11, 256, 256, kPersistent, 16, 0.0, 25.1, 21.8, 0.0, 0.474, 0.993, 1.015}};
 
 // Both backward products in one launch: input gradient on shape `dgrad`, weight gradient on shape `wgrad`.  The compute
 // units share the work of both, W = their average (more by 0.6 of what the rounding to whole workgroups adds while all are
@@ -68,8 +75,9 @@ struct PairModel {
 };
 static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.14, 0.922, 0.243}, {22, 8, 8, 3.15, 0.986, 0.148}, {23, 4, 4, 2.69, 0.998, 0.310},
                                          {24, 10, 4, 2.91, 0.974, 0.378}, {25, 4, 10, 2.64, 1.032, 0.217}};
-static constexpr PairModel kPairs64[] = {{21, 1, 1, 2.71, 0.983, 0.204}, {22, 4, 4, 2.93, 0.945, 0.385}};
-static constexpr PairModel kPairs128[] = {{21, 6, 6, -1.43, 1.014, 0.324}, {22, 1, 1, 1.41, 1.106, 0.115}};
+// Pair 26 is one list of tiles dealt to persistent workgroups: time = work * (the longest workgroup's tiles).
+static constexpr PairModel kPairs64[] = {{21, 1, 1, 2.71, 0.983, 0.204}, {22, 4, 4, 2.93, 0.945, 0.385}, {26, 11, 11, 0.0, 0.973, 0.0}};
+static constexpr PairModel kPairs128[] = {{21, 6, 6, -1.50, 0.910, 0.310}, {22, 1, 1, 1.46, 1.090, 0.118}, {26, 11, 11, 0.0, 1.011, 0.0}};
 
 struct ShapeTable {
   const ShapeModel* shapes;
@@ -94,6 +102,19 @@ struct ShapeTable {
   }
   double pair_us(const PairModel& p, const GemmArgs& d, const GemmArgs& w) const {
     const ShapeModel &sd = *find(p.dgrad), &sw = *find(p.wgrad);
+    if (sd.resident == kPersistent) {
+      // as gemm_wide_pair_kernel deals them; the workgroup with most tiles is the first of either product
+      const bool second_first = w.K > d.K;
+      const int64_t td = (int64_t)sd.tiles(d), tw = (int64_t)sw.tiles(w), t1 = second_first ? tw : td, t2 = second_first ? td : tw;
+      const double us_d = sd.tile_us(kDgrad, d, false), us_w = sw.tile_us(kWgrad, w, false);
+      const int64_t split = (t1 + 7) & ~int64_t(7), n = std::min<int64_t>(256, split + t2);
+      double busiest = 0.0;
+      for (const int64_t i : {int64_t(0), split % n}) {
+        const int64_t n1 = i < t1 ? (t1 - i + n - 1) / n : 0, j = (n - split % n + i) % n, n2 = j < t2 ? (t2 - j + n - 1) / n : 0;
+        busiest = std::max(busiest, n1 * (second_first ? us_w : us_d) + n2 * (second_first ? us_d : us_w));
+      }
+      return p.fixed_us + p.work * busiest;
+    }
     const double td = sd.tiles(d), tw = sw.tiles(w), per_cu = (td + tw) / 256.0;
     const double alone = std::max(sd.tile_us(kDgrad, d, true), sw.tile_us(kWgrad, w, true));
     if (per_cu <= 1.0) return p.fixed_us + alone;

@@ -173,7 +173,7 @@ extern "C" int32_t jf_debug_linear_partials(int32_t which, const int8_t* A, cons
 
 // (7 was a 64x64 tile with longer stages, which shape 4 has now; it is still accepted and leaves the choice automatic)
 extern "C" int32_t jf_debug_set_gemm_shape(int32_t shape) {
-  if (shape != 0 && shape != 1 && shape != 4 && shape != 6 && shape != 7 && shape != 8 && shape != 10 && (shape < 21 || shape > 25)) return JF_ERR_SHAPE;
+  if (shape != 0 && shape != 1 && shape != 4 && shape != 6 && shape != 7 && shape != 8 && shape != 10 && shape != 11 && (shape < 21 || shape > 26)) return JF_ERR_SHAPE;
   jf::g_forced_shape.store(shape, std::memory_order_relaxed);
   return JF_OK;
 }
