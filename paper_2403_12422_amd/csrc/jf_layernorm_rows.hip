@@ -13,8 +13,8 @@
 // includes the stores just made (loads and stores count in one counter and may finish out of order), only those of the
 // previous group, which are long done.
 //
-// 1 M x 768: forward 446 -> 313 us (5.2 TB/s), backward 784 -> 560 us (4.3 TB/s; the vector ALU issues in 92 % of the
-// cycles: 20 instructions per element) against the two-kernel scheme of jf_layernorm.hip, which
+// 1 M x 768: forward 446 -> 313 us (5.2 TB/s), backward 784 -> 484 us (5.0 TB/s; vector ALU and memory both near their
+// limits: 19 instructions per element) against the two-kernel scheme of jf_layernorm.hip, which
 // stays for block sizes 64 and 128 and for rows of more than 16 strips, which a compute unit's registers (128 per lane:
 // 16 waves) do not hold.
 #include <algorithm>
@@ -63,6 +63,21 @@ __device__ __forceinline__ void unpack4(uint32_t w, float (&c)[4]) {
   for (int k = 0; k < 4; ++k) c[k] = (float)(int)(int8_t)(w >> (8 * k));
 }
 __device__ __forceinline__ uint32_t dword_of(const uint4& v, int d) { return d == 0 ? v.x : (d == 1 ? v.y : (d == 2 ? v.z : v.w)); }
+
+// v[0] + v[64] + v[128] + ... of the `strips` waves of a team, in that order, four LDS reads in flight at a time (one after
+// the other they are one LDS latency per strip, beside which nothing runs where a workgroup has a single row group).
+template <class T>
+__device__ __forceinline__ T sum_over_strips(const T* v, int strips) {
+  T sum = 0;
+  for (int w = 0; w < strips; w += 4) {
+    T q[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = v[64 * min(w + j, strips - 1)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sum += w + j < strips ? q[j] : (T)0;
+  }
+  return sum;
+}
 
 // A wave's place: workgroups hold `teams` teams of `strips` waves; a team owns a group of 32 rows.
 struct RowWave {
@@ -164,8 +179,7 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
     // Every wave finishes the sums of its team's 32 rows: lanes 0..31 the first sum of row lane, lanes 32..63 the second
     {
       const double* v = s_row + ((copy * t.waves + t.team * a.strips) * 32 + (t.lane & 31)) * 2 + (t.lane >> 5);
-      double sum = 0.0;
-      for (int w = 0; w < a.strips; ++w) sum += v[64 * w];
+      const double sum = sum_over_strips(v, a.strips);
       const double other = lane_xor_f64<5>(sum);
       const double mud = (t.lane < 32 ? sum : other) * (PARTIALS ? a.inv_blocks : a.inv_cols);
       const float var = fmaxf((float)((t.lane < 32 ? other : sum) * a.inv_cols - mud * mud), 0.0f);
@@ -276,11 +290,34 @@ __device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, in
   }
 }
 
+// Sums over the 8 row lanes of a wave (lane bits 3, 4, 5, in that order) of 16 + 16 values.  The half-row swaps of two values
+// and one addition reduce both: 80 instructions where 32 butterflies take 320, at the end of a workgroup with nothing beside it
+// (with two rows of ghat kept: 8192 x 1280 17.2 -> 15.0 us, 4096 x 768 11.5 -> 10.1, 1056 x 800 7.1 -> 6.5).  Lane (bits 4, 5) ends with values 4 j + bit 4 + 2 (bit 5), j = 0 .. 7, of {a, b}.
+__device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float (&b)[16], float (&out)[8]) {
+  const auto half = [](float x, float y, auto swap) __attribute__((always_inline)) {
+    const auto p = swap(__builtin_bit_cast(int, x), __builtin_bit_cast(int, y));
+    return __builtin_bit_cast(float, (int)p[0]) + __builtin_bit_cast(float, (int)p[1]);
+  };
+  const auto swap16 = [](int x, int y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); };
+  const auto swap32 = [](int x, int y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); };
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = wave_group_sum<8>(j < 4 ? a[4 * j + k] : b[4 * (j - 4) + k]);
+    out[j] = half(half(v[0], v[1], swap16), half(v[2], v[3], swap16), swap32);
+  }
+}
+
 // dx = rstd (ghat - mean_C(ghat) - xhat mean_C(ghat xhat)) with ghat = g gamma, xhat = (x - mean) rstd; the column sums
 // of g xhat and g stay in registers over all row groups and end as one partial row of dgamma | dbeta per workgroup.
 // COLUMNS_APART: the column sums are left to workgroups of their own behind the row_wgs that own rows (column_sums_direct).
-template <StorePolicy SP, bool COLUMNS_APART>
-__global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNormBwdRows a) {
+// KEPT: of how many of a lane's four rows ghat stays in registers between the two passes over the strip, 16 each, instead of
+// being formed again (two instructions per element).  Workgroups of at most 12 waves, three on a SIMD, have 168 registers: room
+// for two rows beside the column sums, for all four without them; 16 waves have none.  More than fits goes to scratch
+// memory, whose loads also wait for the strips in flight (1 M x 768 with three rows 513 us, two 484, one 515, none 535).
+template <StorePolicy SP, bool COLUMNS_APART, int KEPT>
+__global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(const LayerNormBwdRows a) {
   extern __shared__ __align__(16) int8_t smem[];
   if (COLUMNS_APART && (int)blockIdx.x >= a.row_wgs) {
     column_sums_direct(a, blockIdx.x - a.row_wgs, reinterpret_cast<float*>(smem));
@@ -341,6 +378,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
     if (first + stride < groups) request(min(g + stride, groups - 1));
     sg = t.ok && g < groups ? sg : 0.0f;               // what lies outside adds nothing to the sums
     float kx[4], cx[4], m1[4], m2[4];
+    float y[4][16];                                    // dx; with KEEP ghat in units of g's block scale before
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       kx[p] = sx * rs[p];
@@ -361,6 +399,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float xh = __builtin_fmaf(x[e], kx[p], cx[p]), gh = gr[e] * gm[e];
+          if (p < KEPT) y[p][4 * d + e] = gh;
           // in place (left to itself the compiler keeps the operands of many deferred updates alive instead)
           asm volatile("v_add_f32 %0, %0, %1" : "+v"(m1[p]) : "v"(gh));
           asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(m2[p]) : "v"(gh), "v"(xh));
@@ -387,18 +426,16 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
     lds_barrier();
     {
       const float* v = s_row + ((copy * t.waves + t.team * a.strips) * 32 + (t.lane & 31)) * 2 + (t.lane >> 5);
-      float sum = 0.0f;
-      for (int w = 0; w < a.strips; ++w) sum += v[64 * w];
-      reinterpret_cast<float*>(own + kBwdMeans)[2 * (t.lane & 31) + (t.lane >> 5)] = sum * a.inv_cols;
+      reinterpret_cast<float*>(own + kBwdMeans)[2 * (t.lane & 31) + (t.lane >> 5)] = sum_over_strips(v, a.strips) * a.inv_cols;
       wave_lds_fence();
     }
-    // the codes are unpacked again below: 128 floats kept from above would not fit the registers
+    // the codes are unpacked again below: 128 floats kept from above would not fit the registers of three waves per SIMD
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       asm volatile("" : "+v"(px[p].x), "+v"(px[p].y), "+v"(px[p].z), "+v"(px[p].w));
       asm volatile("" : "+v"(pg[p].x), "+v"(pg[p].y), "+v"(pg[p].z), "+v"(pg[p].w));
     }
-    // dx = g_code (rstd sg gamma) + x_code kxm + krow
+    // dx = (g_code gamma) (rstd sg) + x_code kxm + krow
     float kxm[4], krow[4], rsg[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -407,19 +444,22 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
       krow[p] = -rs[p] * __builtin_fmaf(cx[p], q.y, q.x);
       rsg[p] = rs[p] * sg;
     }
-    float y[4][16];
     float m = 0.0f;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      const float4 gm4 = *reinterpret_cast<const float4*>(s_gamma + 16 * t.ch + 4 * d);
-      const float gm[4] = {gm4.x, gm4.y, gm4.z, gm4.w};
+      float gm[4];
+      if constexpr (KEPT < 4) {
+        const float4 gm4 = *reinterpret_cast<const float4*>(s_gamma + 16 * t.ch + 4 * d);
+        gm[0] = gm4.x, gm[1] = gm4.y, gm[2] = gm4.z, gm[3] = gm4.w;
+      }
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
         float x[4], gr[4];
         unpack4(dword_of(px[p], d), x);
-        unpack4(dword_of(pg[p], d), gr);
+        if (p >= KEPT) unpack4(dword_of(pg[p], d), gr);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[p][4 * d + e] = __builtin_fmaf(x[e], kxm[p], __builtin_fmaf(gr[e], rsg[p] * gm[e], krow[p]));
+        for (int e = 0; e < 4; ++e)
+          y[p][4 * d + e] = __builtin_fmaf(x[e], kxm[p], __builtin_fmaf(p < KEPT ? y[p][4 * d + e] : gr[e] * gm[e], rsg[p], krow[p]));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -447,39 +487,27 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_rows_kernel(const LayerNor
 
   if (COLUMNS_APART) return;
   // column sums over the 8 row lanes of the wave, then over the teams through LDS, in a fixed order
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    cgs[e] = wave_group_sum<56>(cgs[e]);
-    cbs[e] = wave_group_sum<56>(cbs[e]);
-  }
+  float sums[8];
+  reduce_rows32(cgs, cbs, sums);
+  // lane: sum j of column 16 ch + 4 (j % 4) + its place among the four lanes 16 apart; dgamma for j < 4, dbeta beyond
+  const int place = 16 * t.ch + (((t.lane >> 4) & 1) | ((t.lane >> 5) << 1));
   if (a.teams > 1) {
     float* const mine = reinterpret_cast<float*>(own);   // all requests have landed and nobody else uses this wave's part
-    if (t.rsub == 0) {
 #pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        reinterpret_cast<float4*>(mine + 16 * t.ch)[d] = make_float4(cgs[4 * d], cgs[4 * d + 1], cgs[4 * d + 2], cgs[4 * d + 3]);
-        reinterpret_cast<float4*>(mine + 128 + 16 * t.ch)[d] = make_float4(cbs[4 * d], cbs[4 * d + 1], cbs[4 * d + 2], cbs[4 * d + 3]);
-      }
-    }
+    for (int j = 0; j < 8; ++j) mine[128 * (j / 4) + 4 * (j % 4) + place] = sums[j];   // (twice, by lanes 8 apart)
     lds_barrier();
     if (t.team == 0) {
       for (int k = 1; k < a.teams; ++k) {
         const float* other = reinterpret_cast<const float*>(own + k * a.strips * kBwdWaveBytes);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          cgs[e] += other[16 * t.ch + e];
-          cbs[e] += other[128 + 16 * t.ch + e];
-        }
+        for (int j = 0; j < 8; ++j) sums[j] += other[128 * (j / 4) + 4 * (j % 4) + place];
       }
     }
   }
-  if (t.team == 0 && t.ok && t.rsub == 0) {
-    float* dst = a.partials + (int64_t)blockIdx.x * 2 * a.cols + t.col;
+  if (t.team == 0 && t.ok && (t.lane & 8) == 0) {
+    float* dst = a.partials + (int64_t)blockIdx.x * 2 * a.cols + t.c0 + place;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      *reinterpret_cast<float4*>(dst + 4 * d) = make_float4(cgs[4 * d], cgs[4 * d + 1], cgs[4 * d + 2], cgs[4 * d + 3]);
-      *reinterpret_cast<float4*>(dst + a.cols + 4 * d) = make_float4(cbs[4 * d], cbs[4 * d + 1], cbs[4 * d + 2], cbs[4 * d + 3]);
-    }
+    for (int j = 0; j < 8; ++j) dst[(j / 4) * a.cols + 4 * (j % 4)] = sums[j];
   }
 }
 
@@ -532,11 +560,13 @@ int launch_layernorm_bwd_rows(LayerNormBwdRows a, bool in_place, hipStream_t st)
     constexpr StorePolicy SP = decltype(sp)::value;
     if constexpr (SP == kStoreThrough) {   // (2048 rows are always stored through)
       if (apart) {
-        launch_rows<layernorm_bwd_rows_kernel<SP, true>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs + a.cols / 32, waves, a, st);
+        if (waves <= 12) launch_rows<layernorm_bwd_rows_kernel<SP, true, 4>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs + a.cols / 32, waves, a, st);
+        else launch_rows<layernorm_bwd_rows_kernel<SP, true, 0>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs + a.cols / 32, waves, a, st);
         return;
       }
     }
-    launch_rows<layernorm_bwd_rows_kernel<SP, false>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs, waves, a, st);
+    if (waves <= 12) launch_rows<layernorm_bwd_rows_kernel<SP, false, 2>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs, waves, a, st);
+    else launch_rows<layernorm_bwd_rows_kernel<SP, false, 0>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs, waves, a, st);
   });
   return apart ? 0 : a.row_wgs;
 }
