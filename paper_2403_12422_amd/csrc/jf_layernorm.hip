@@ -1,6 +1,7 @@
 // INT8-in / INT8-out LayerNorm, forward and backward (App. A).
 //
-// Rows of at most 2048 columns at block size 32 go through jf_layernorm_rows.hip.  Otherwise each pass is a small kernel
+// Rows of at most 2048 / 1024 / 512 columns at block size 32 / 64 / 128 go through jf_layernorm_rows.hpp where there are enough
+// of them (layernorm_rows_fits).  Otherwise each pass is a small kernel
 // that only leaves sums (row statistics forward; row means and dgamma | dbeta partial rows backward) followed by an
 // element-wise operator on tiles: the 32 x 128 strips of jf_rowops.hpp at block size 32, workgroups of B rows x 128
 // columns at block sizes 64 and 128.  No workgroup holds a row in registers, so rows may be of any width.
@@ -494,11 +495,11 @@ static int32_t layernorm_fwd(const int8_t* X, const float* SX, const float* row_
   if (!gamma || !beta || !mean || !rstd) return JF_ERR_NULL;
   if (!aligned16(gamma) || !aligned16(beta) || !aligned4(mean) || !aligned4(rstd)) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (layernorm_rows_fits(C, block)) {   // one pass over the operands
+  if (layernorm_rows_fits(N, C, block, false)) {   // one pass over the operands
     LayerNormRows a{};
     a.X = X; a.SX = SX; a.row_mean = row_mean; a.row_sumsq = row_sumsq; a.gamma = gamma; a.beta = beta; a.eps = eps;
     a.rows = (int)N; a.cols = (int)C; a.Y = Y; a.SY = SY; a.mean = mean; a.rstd = rstd;
-    launch_layernorm_rows(a, st);
+    (block == 32 ? launch_layernorm_rows_b32 : block == 64 ? launch_layernorm_rows_b64 : launch_layernorm_rows_b128)(a, st);
     return launch_status();
   }
   if (row_mean != nullptr) {
@@ -562,12 +563,13 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
     hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((2 * C + 63) / 64)), dim3(1024), 0, st, partials, nparts, (int)(2 * C), dgamma, dbeta);
     return launch_status();
   };
-  if (layernorm_rows_fits(C, block)) {   // one pass over the operands
+  if (layernorm_rows_fits(N, C, block, true)) {   // one pass over the operands
     LayerNormBwdRows a{};
     a.G = dY; a.SG = SdY; a.X = X; a.SX = SX; a.gamma = gamma; a.mean = mean; a.rstd = rstd; a.rows = (int)N; a.cols = (int)C;
     a.dX = dX; a.SdX = SdX; a.partials = partials;
     a.dgamma = dgamma; a.dbeta = dbeta;
-    nparts = launch_layernorm_bwd_rows(a, sums_in_place || any_overlap(out, in), st);
+    nparts = (block == 32 ? launch_layernorm_bwd_rows_b32 : block == 64 ? launch_layernorm_bwd_rows_b64 : launch_layernorm_bwd_rows_b128)(
+        a, sums_in_place || any_overlap(out, in), st);
     const int32_t rc = launch_status();
     return rc != JF_OK || nparts == 0 ? rc : launch_colsum();
   }

@@ -1,9 +1,10 @@
-// LayerNorm at block size 32 in one pass over the operands (App. A): each code is read once and written once.
+// LayerNorm in one pass over the operands (App. A): each code is read once and written once.
 //
 // Bound by HBM: 2 bytes per element forward, 3 backward.  What a row needs as a whole (its moments; backward, the two row
 // means) makes an operator on tiles read its operands twice; here a workgroup owns 32 whole rows, one wave per strip of
 // 32 x 128 (Strip32's lane mapping), so the strip's codes stay in registers while the row sums go over the waves through
-// LDS.  What made that slow before was that a workgroup in its arithmetic had nothing in flight.  Now workgroups are
+// LDS.  At block sizes 64 and 128 two or four such teams of waves own the row groups of a block row and exchange the block
+// max-abs as well.  What made that slow before was that a workgroup in its arithmetic had nothing in flight.  Now workgroups are
 // persistent and a wave requests the strip of its NEXT row group with direct-to-LDS loads as soon as it has moved the
 // current one from LDS to registers: 4 KB (8 KB backward) per wave are in flight through all of the arithmetic, without
 // registers to land in.
@@ -14,9 +15,9 @@
 // previous group, which are long done.
 //
 // 1 M x 768: forward 446 -> 313 us (5.2 TB/s), backward 784 -> 484 us (5.0 TB/s; vector ALU and memory both near their
-// limits: 19 instructions per element) against the two-kernel scheme of jf_layernorm.hip, which
-// stays for block sizes 64 and 128 and for rows of more than 16 strips, which a compute unit's registers (128 per lane:
-// 16 waves) do not hold.
+// limits: 19 instructions per element) against the two-kernel scheme of jf_layernorm.hip, which stays for rows of which a
+// compute unit's registers (128 per lane: 16 waves) do not hold a block row.
+#pragma once
 #include <algorithm>
 
 #include "jf_layernorm.hpp"
@@ -96,31 +97,53 @@ struct RowWave {
     ok = c0 + 16 * ch < cols;
     col = ok ? c0 + 16 * ch : c0;
   }
+  // first lane of a block, in the first of the teams that share it
+  template <int B>
+  __device__ __forceinline__ bool owns_scale() const { return (lane & (56 | (B / 16 - 1))) == 0 && (B == 32 || team % (B / 32) == 0); }
 };
+
+// Max-abs of the lane's block: over the lanes of a block column, then over the teams of a block row through LDS, by way of
+// `at` in each wave's own part (`parts`, `part_bytes` each), which its owner has read and writes again behind the next
+// barrier at the earliest.
+template <int B>
+__device__ __forceinline__ float block_row_max(float m, const RowWave& t, int strips, int8_t* parts, int part_bytes, int at) {
+  m = wave_group_max<56 | (B / 16 - 1)>(m);
+  if constexpr (B > 32) {
+    constexpr int BT = B / 32;
+    const auto slot = [&](int wave) { return reinterpret_cast<float*>(parts + wave * part_bytes + at) + t.ch / (B / 16); };
+    wave_lds_fence();
+    if ((t.lane & (56 | (B / 16 - 1))) == 0) *slot(t.wave) = m;
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < BT; ++k) m = fmaxf(m, *slot((t.team / BT * BT + k) * strips + t.strip));
+  }
+  return m;
+}
 
 // LDS of a forward wave: codes, block scales, row partials of the Add, gamma, beta, the rows' mean and rstd
 constexpr int kFwdScale = 4096, kFwdPart = kFwdScale + 256, kFwdGamma = kFwdPart + 1024, kFwdBeta = kFwdGamma + 512,
               kFwdStat = kFwdBeta + 512, kFwdWaveBytes = kFwdStat + 256;
 constexpr int kFwdRowBytes = 2 * 32 * 16;   // per wave: two copies (alternate row groups) of a sum pair for each of 32 rows
 
-template <bool PARTIALS, StorePolicy SP>
+template <int B, bool PARTIALS, StorePolicy SP>
 __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRows a) {
   extern __shared__ __align__(16) int8_t smem[];
   const RowWave t(a.cols, a.strips);
   double* const s_row = reinterpret_cast<double*>(smem);                       // [copy][wave][row][sum]
   int8_t* const own = smem + t.waves * kFwdRowBytes + t.wave * kFwdWaveBytes;
-  const int groups = a.rows / 32, lc = a.cols / 32;
-  const uint32_t off = (uint32_t)(t.rsub * a.cols + t.col), off_scale = (uint32_t)(t.col / 32) * 4;
+  constexpr int BT = B / 32, NBC = 128 / B;            // teams of a block row, block columns of a strip
+  const int groups = a.rows / 32, lc = a.cols / B;
+  const uint32_t off = (uint32_t)(t.rsub * a.cols + t.col), off_scale = (uint32_t)(t.col / B) * 4;
 
   auto request = [&](int g) __attribute__((always_inline)) {
     const int8_t* const x = uniform_pointer(a.X + (int64_t)g * 32 * a.cols);
 #pragma unroll
     for (int p = 0; p < 4; ++p) load_lds_16(x + (int64_t)p * 8 * a.cols, off, own, 1024 * p);
-    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)g * lc)), off_scale, own, kFwdScale);
-    if (PARTIALS) {   // the strip's four block columns x 32 rows of both partials
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)(g / BT) * lc)), off_scale, own, kFwdScale);
+    if (PARTIALS) {   // the strip's block columns x 32 rows of both partials
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int64_t o = (int64_t)min(4 * t.strip + 2 * i + (t.lane >> 5), lc - 1) * a.rows + g * 32 + (t.lane & 31);
+      for (int i = 0; i < (NBC + 1) / 2; ++i) {
+        const int64_t o = (int64_t)min(NBC * t.strip + 2 * i + (t.lane >> 5), lc - 1) * a.rows + g * 32 + (t.lane & 31);
         load_lds_4_vaddr(a.row_mean + o, own, kFwdPart + 256 * i);
         load_lds_4_vaddr(a.row_sumsq + o, own, kFwdPart + 512 + 256 * i);
       }
@@ -153,7 +176,7 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
       const float* part = reinterpret_cast<const float*>(own + kFwdPart) + 128 * (t.lane >> 5) + (t.lane & 31);
       double v = 0.0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v += 4 * t.strip + j < lc ? (double)part[32 * j] : 0.0;
+      for (int j = 0; j < NBC; ++j) v += NBC * t.strip + j < lc ? (double)part[32 * j] : 0.0;
       row[2 * (t.lane & 31) + (t.lane >> 5)] = v;
     }
     wait_lds();                                        // the strip is in registers: its LDS may be filled again
@@ -217,9 +240,10 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
     }
 #pragma unroll
     for (int p = 0; p < 4; ++p) m = amax16(m, y[p]);
+    m = block_row_max<B>(m, t, a.strips, smem + t.waves * kFwdRowBytes, kFwdWaveBytes, kFwdStat);
     float scale;
     double inv;
-    strip32_block_scale(m, scale, inv);
+    block_scale(m, scale, inv);
     uint4 o[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -233,7 +257,7 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
       int8_t* const out = uniform_pointer(a.Y + (int64_t)g * 32 * a.cols);
 #pragma unroll
       for (int p = 0; p < 4; ++p) store_as_at<SP>(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_scale<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)g * lc)) + off_scale, scale);
+      if (t.owns_scale<B>()) store_scale<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SY + (int64_t)(g / BT) * lc)) + off_scale, scale);
     }
   }
 }
@@ -248,18 +272,20 @@ constexpr int kBwdRowBytes = 2 * 32 * 8;
 // up to 2048 rows this saves the launch that adds the partial rows (512 x 544: 16.2 -> 13.3 us forward and backward), and
 // the row pass 8 of its 20 instructions per element.  Beyond that, or with few waves in a workgroup (2048 x 160: two), the
 // workgroups of the few block columns take longer than the row pass.
+template <int B>
 __device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, int group, float* s_sum) {
   const int lane = threadIdx.x & 63, row = lane & 31, waves = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int col = group * 32 + 16 * (lane >> 5), lc = a.cols / 32;
+  const int col = group * 32 + 16 * (lane >> 5), lc = a.cols / B;
   float sgx[16], sgb[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) sgx[e] = sgb[e] = 0.0f;
   for (int g = wave; g < a.rows / 32; g += waves) {
     const int64_t at = (int64_t)(g * 32 + row) * a.cols + col;
     const uint4 px = *reinterpret_cast<const uint4*>(a.X + at), pg = *reinterpret_cast<const uint4*>(a.G + at);
-    const float rs = a.rstd[g * 32 + row], sg = a.SG[(int64_t)g * lc + group];
-    const float kx = a.SX[(int64_t)g * lc + group] * rs, cx = -a.mean[g * 32 + row] * rs;
+    const int64_t block = (int64_t)(g / (B / 32)) * lc + group / (B / 32);
+    const float rs = a.rstd[g * 32 + row], sg = a.SG[block];
+    const float kx = a.SX[block] * rs, cx = -a.mean[g * 32 + row] * rs;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
       float x[4], gr[4];
@@ -316,18 +342,19 @@ __device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float 
 // being formed again (two instructions per element).  Workgroups of at most 12 waves, three on a SIMD, have 168 registers: room
 // for two rows beside the column sums, for all four without them; 16 waves have none.  More than fits goes to scratch
 // memory, whose loads also wait for the strips in flight (1 M x 768 with three rows 513 us, two 484, one 515, none 535).
-template <StorePolicy SP, bool COLUMNS_APART, int KEPT>
+template <int B, StorePolicy SP, bool COLUMNS_APART, int KEPT>
 __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(const LayerNormBwdRows a) {
   extern __shared__ __align__(16) int8_t smem[];
   if (COLUMNS_APART && (int)blockIdx.x >= a.row_wgs) {
-    column_sums_direct(a, blockIdx.x - a.row_wgs, reinterpret_cast<float*>(smem));
+    column_sums_direct<B>(a, blockIdx.x - a.row_wgs, reinterpret_cast<float*>(smem));
     return;
   }
   const RowWave t(a.cols, a.strips);
   float* const s_row = reinterpret_cast<float*>(smem);                         // [copy][wave][row][sum]
   int8_t* const own = smem + t.waves * kBwdRowBytes + t.wave * kBwdWaveBytes;
-  const int groups = a.rows / 32, lc = a.cols / 32;
-  const uint32_t off = (uint32_t)(t.rsub * a.cols + t.col), off_scale = (uint32_t)(t.col / 32) * 4;
+  constexpr int BT = B / 32, NBC = 128 / B;            // teams of a block row, block columns of a strip
+  const int groups = a.rows / 32, lc = a.cols / B;
+  const uint32_t off = (uint32_t)(t.rsub * a.cols + t.col), off_scale = (uint32_t)(t.col / B) * 4;
 
   auto request = [&](int g) __attribute__((always_inline)) {
     const int8_t* const x = uniform_pointer(a.X + (int64_t)g * 32 * a.cols);
@@ -337,8 +364,8 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
       load_lds_16(x + (int64_t)p * 8 * a.cols, off, own, 1024 * p);
       load_lds_16(gr + (int64_t)p * 8 * a.cols, off, own, kBwdG + 1024 * p);
     }
-    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)g * lc)), off_scale, own, kBwdScaleX);
-    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SG + (int64_t)g * lc)), off_scale, own, kBwdScaleG);
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)(g / BT) * lc)), off_scale, own, kBwdScaleX);
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SG + (int64_t)(g / BT) * lc)), off_scale, own, kBwdScaleG);
     if (t.lane < 32) {   // 32 floats each
       load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.mean + g * 32)), (uint32_t)t.lane * 4, own, kBwdMean);
       load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.rstd + g * 32)), (uint32_t)t.lane * 4, own, kBwdRstd);
@@ -465,9 +492,10 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
     }
 #pragma unroll
     for (int p = 0; p < 4; ++p) m = amax16(m, y[p]);
+    m = block_row_max<B>(m, t, a.strips, smem + t.waves * kBwdRowBytes, kBwdWaveBytes, kBwdMeans);
     float scale;
     double inv;
-    strip32_block_scale(m, scale, inv);
+    block_scale(m, scale, inv);
     uint4 o[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -481,7 +509,7 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
       int8_t* const out = uniform_pointer(a.dX + (int64_t)g * 32 * a.cols);
 #pragma unroll
       for (int p = 0; p < 4; ++p) store_as_at<SP>(out + (int64_t)p * 8 * a.cols, off, v4i{(int)o[p].x, (int)o[p].y, (int)o[p].z, (int)o[p].w});
-      if ((t.lane & 57) == 0) store_scale<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)g * lc)) + off_scale, scale);
+      if (t.owns_scale<B>()) store_scale<SP>(reinterpret_cast<int8_t*>(uniform_pointer(a.SdX + (int64_t)(g / BT) * lc)) + off_scale, scale);
     }
   }
 
@@ -524,51 +552,62 @@ static void launch_rows(size_t wave_bytes, int grid, int waves, const Args& a, h
 // Teams per workgroup, one workgroup per compute unit.  The waves of a workgroup are dealt to the four SIMDs in turn, so
 // that the fullest SIMD sets the pace: the count that does most row groups per wave of that SIMD (six strips: two teams, 3
 // waves on every SIMD, instead of two workgroups of one team, which leave 2, 3, 3 and 4: 622 -> 571 us backward at 1 M x
-// 768), of equal ones the larger; fewer while there are compute units without a workgroup.
-static int choose_teams(int strips, int groups) {
-  int best = 1;
-  for (int n = 2; n * strips <= 16; ++n)
+// 768), of equal ones the larger; fewer while there are compute units without a workgroup.  Whole block rows: `step` teams.
+static int choose_teams(int strips, int groups, int step) {
+  int best = step;
+  for (int n = 2 * step; n * strips <= 16; n += step)
     if ((n * strips + 3) / 4 * best <= (best * strips + 3) / 4 * n) best = n;
-  return std::max(1, std::min(best, (groups + 255) / 256));
+  return std::max(step, std::min(best, (groups / step + 255) / 256 * step));
 }
 
-bool layernorm_rows_fits(int64_t C, int32_t block) { return block == 32 && C <= 16 * 128; }
-
-void launch_layernorm_rows(LayerNormRows a, hipStream_t st) {
+template <int B>
+static void launch_layernorm_rows_b(LayerNormRows a, hipStream_t st) {
   const int groups = a.rows / 32;
   a.strips = (a.cols + 127) / 128;
-  a.teams = choose_teams(a.strips, groups);
+  a.teams = choose_teams(a.strips, groups, B / 32);
   a.inv_cols = 1.0 / (double)a.cols;
-  a.inv_blocks = 1.0 / (double)(a.cols / 32);
+  a.inv_blocks = 1.0 / (double)(a.cols / B);
   const int waves = a.strips * a.teams, grid = std::min((groups + a.teams - 1) / a.teams, 256);
   with_store_policy(a.rows, a.cols, [&](auto sp) {
-    if (a.row_mean) launch_rows<layernorm_rows_kernel<true, decltype(sp)::value>>(kFwdRowBytes + kFwdWaveBytes, grid, waves, a, st);
-    else launch_rows<layernorm_rows_kernel<false, decltype(sp)::value>>(kFwdRowBytes + kFwdWaveBytes, grid, waves, a, st);
+    if (a.row_mean) launch_rows<layernorm_rows_kernel<B, true, decltype(sp)::value>>(kFwdRowBytes + kFwdWaveBytes, grid, waves, a, st);
+    else launch_rows<layernorm_rows_kernel<B, false, decltype(sp)::value>>(kFwdRowBytes + kFwdWaveBytes, grid, waves, a, st);
   });
 }
 
-int launch_layernorm_bwd_rows(LayerNormBwdRows a, bool in_place, hipStream_t st) {
+template <int B>
+static int launch_layernorm_bwd_rows_b(LayerNormBwdRows a, bool in_place, hipStream_t st) {
   const int groups = a.rows / 32;
   a.strips = (a.cols + 127) / 128;
-  a.teams = choose_teams(a.strips, groups);
+  a.teams = choose_teams(a.strips, groups, B / 32);
   a.inv_cols = 1.0f / (float)a.cols;
   const int waves = a.strips * a.teams;
   a.row_wgs = std::min((groups + a.teams - 1) / a.teams, 256);
   static_assert(16 * (kBwdRowBytes + kBwdWaveBytes) <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
   const bool apart = !in_place && a.rows <= 2048 && groups <= 12 * waves;   // at most 12 row groups for a wave of the column workgroups
+  constexpr size_t BYTES = kBwdRowBytes + kBwdWaveBytes;
   with_store_policy(a.rows, a.cols, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
     if constexpr (SP == kStoreThrough) {   // (2048 rows are always stored through)
       if (apart) {
-        if (waves <= 12) launch_rows<layernorm_bwd_rows_kernel<SP, true, 4>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs + a.cols / 32, waves, a, st);
-        else launch_rows<layernorm_bwd_rows_kernel<SP, true, 0>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs + a.cols / 32, waves, a, st);
+        const int grid = a.row_wgs + a.cols / 32;
+        if (waves <= 12) launch_rows<layernorm_bwd_rows_kernel<B, SP, true, 4>>(BYTES, grid, waves, a, st);
+        else launch_rows<layernorm_bwd_rows_kernel<B, SP, true, 0>>(BYTES, grid, waves, a, st);
         return;
       }
     }
-    if (waves <= 12) launch_rows<layernorm_bwd_rows_kernel<SP, false, 2>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs, waves, a, st);
-    else launch_rows<layernorm_bwd_rows_kernel<SP, false, 0>>(kBwdRowBytes + kBwdWaveBytes, a.row_wgs, waves, a, st);
+    if (waves <= 12) launch_rows<layernorm_bwd_rows_kernel<B, SP, false, 2>>(BYTES, a.row_wgs, waves, a, st);
+    else launch_rows<layernorm_bwd_rows_kernel<B, SP, false, 0>>(BYTES, a.row_wgs, waves, a, st);
   });
   return apart ? 0 : a.row_wgs;
 }
+
+// One translation unit per block size instantiates the launches, so that the kernels compile in parallel.
+#define JF_LAYERNORM_ROWS_INSTANCE(B)                                                                            \
+  namespace jf {                                                                                                 \
+  void launch_layernorm_rows_b##B(const LayerNormRows& a, hipStream_t st) { launch_layernorm_rows_b<B>(a, st); } \
+  int launch_layernorm_bwd_rows_b##B(const LayerNormBwdRows& a, bool in_place, hipStream_t st) {                 \
+    return launch_layernorm_bwd_rows_b<B>(a, in_place, st);                                                      \
+  }                                                                                                              \
+  }
 
 }  // namespace jf
