@@ -140,7 +140,7 @@ def bench_hbm_traffic():
     out += ["", f"the two GEMM launches of a step: {step / 1e6:.1f} MB (algorithmic 3 x 18.1 = 54.4 MB).",
             "The excess on the read side is re-reading by the eight XCDs: each XCD's L2 pulls its own copy of the operand band it",
             "works on from the Infinity Cache / HBM (FETCH_SIZE counts L2 misses, many of which hit the Infinity Cache).", ""]
-    others = [("quantize (mean over X, W, dH)", "quantize_kernel"), ("gelu fwd", "gelu_strip32_kernel<false"), ("gelu bwd", "gelu_strip32_kernel<true"),
+    others = [("quantize (mean over X, W, dH)", "quantize_kernel"), ("gelu fwd", "gelu_kernel<false, 32"), ("gelu bwd", "gelu_kernel<true, 32"),
               ("layernorm fwd (one pass)", "layernorm_rows_kernel"), ("layernorm bwd (one pass)", "layernorm_bwd_rows_kernel"),
               ("colsum (dgamma, dbeta)", "colsum_kernel")]
     for name, key in others:

@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __res
       m = amax16(m, y[p]);
     }
   }
-  m = strip_block_max<B>(m);
+  m = wave_group_max<56 | (B / 16 - 1)>(m);
   // s_amax[wave][32-column group]; the in-wave reduction already covered the whole block width
   if ((lane & 57) == 0) s_amax[wave][ch >> 1] = m;
   __syncthreads();

@@ -1,13 +1,9 @@
 // Helpers shared by the INT8-in / INT8-out operators (Sec. 6, Alg. 2, App. A): unpacking and Eq. 1 for 16 codes at a
-// time, the lane mapping of the block-32 strip kernels, and host-side argument checks.
+// time, the lane mapping of the strip kernels, and host-side argument checks.
 #pragma once
 #include "jf_common.hpp"
 
 namespace jf {
-
-__device__ __forceinline__ float amax4(float m, float a, float b, float c, float d) {
-  return fmaxf(fmaxf(m, fmaxf(fabsf(a), fabsf(b))), fmaxf(fabsf(c), fabsf(d)));
-}
 
 __device__ __forceinline__ uint4 quantize16(const float (&y)[16], double inv) {
   uint4 o;
@@ -31,55 +27,56 @@ __device__ __forceinline__ void unpack16_biased(const uint4& p, float (&u)[16]) 
   }
 }
 
-// Reduce over the lanes of a wave that share a quantization-block column in the (8 rows x 8 chunks)
-// strip mapping: all 8 row lanes (bits 3..5) and the B/16 (<= 8) chunk lanes of the block (low bits).
-template <int B>
-__device__ __forceinline__ float strip_block_max(float m) {
-  constexpr int CH = B >= 128 ? 7 : (B == 64 ? 3 : 1);
-  return wave_group_max<56 | CH>(m);
-}
-
 // ------------------------------------------------------------------------------------------------
-// Block size 32: the element-wise operators as one WAVE per workgroup.  A wave owns a strip of 32 rows x 128
-// columns -- four quantization blocks side by side.  Lane l = (rsub = l / 8, ch = l % 8) holds the 16-byte chunk ch
-// of rows rsub, rsub + 8, rsub + 16, rsub + 24 of the strip: every load or store instruction of the wave moves
-// eight full 128-byte lines, a lane holds 64 elements of ONE block (columns 32 (ch / 2) .. + 31), so the block's
-// max-abs is a local maximum followed by four cross-lane steps, and nothing is exchanged between waves: no LDS
-// traffic (but the GELU tables), no barrier.  Per element the kernels spend what Alg. 2 needs (unpack, the
-// operator, max-abs, Eq. 1) and little else; the per-lane overhead is paid once per 64 elements.
-// Strips (waves) per workgroup: four neighbouring strips of the same rows, so that 512 contiguous bytes of every row
-// are requested close together in time (on 0.8 GB tensors of 3072 columns 5.4-5.7 TB/s instead of 4.4-5.0 with one
-// strip per workgroup).  The waves of a workgroup share nothing and never meet at a barrier.
+// The element-wise operators on strips.  A wave owns a strip of 32 rows x 128 columns.  Lane l = (rsub = l / 8, ch = l % 8)
+// holds the 16-byte chunk ch of rows rsub, rsub + 8, rsub + 16, rsub + 24 of the strip: every load or store instruction of
+// the wave moves eight full 128-byte lines, and a lane's 64 elements belong to ONE quantization block.  At block size 32 the
+// strip is four blocks side by side: their max-abs is a local maximum followed by four cross-lane steps, and nothing is
+// exchanged between waves, no barrier.  At block sizes 64 and 128 two or four waves of a workgroup stand one above the other
+// and exchange it through LDS.  Per element the kernels spend what Alg. 2 needs (unpack, the operator, max-abs, Eq. 1) and
+// little else; the per-lane overhead is paid once per 64 elements.
+// Waves per workgroup: at block size 32 four neighbouring strips of the same rows, so that 512 contiguous bytes of every row
+// are requested close together in time (on 0.8 GB tensors of 3072 columns 5.4-5.7 TB/s instead of 4.4-5.0 with one strip per
+// workgroup); two by two at 64 and one above the other at 128, and twice as wide for results that go to memory (262144 x
+// 3072, four and eight waves: Add at 64 449 and 424 us, at 128 495 and 447, Dropout 323 and 301, 368 and 318; 8192 x 1280 Add
+// 6.7 and 7.2, GELU backward at 128 7.7 and 8.7).
 constexpr int kStripWaves = 4;
-struct Strip32 {
+constexpr int strip_waves(int block, StorePolicy sp) { return block == 32 || sp == kStoreThrough ? 4 : 8; }
+template <int B, int WAVES = kStripWaves>
+struct Strip {
+  static constexpr int BT = B / 32;   // waves that share a block
   int ch, rsub;     // chunk column and row of the lane inside an 8-row pass
-  int bi, lc;       // block row of the strip, block columns of the matrix
+  int bi, lc;       // 32-row group of the strip, block columns of the matrix
   int c0, col;      // first column of the strip, first column of the lane's chunks
   bool ok;          // the lane's chunks lie inside the matrix (cols % 32 == 0: a block is all in or all out)
   int64_t base;     // element offset of the lane's chunk in pass 0; pass p adds 8 p cols.  Lanes outside the matrix
                     // point at the strip's first chunk instead: they load like the others (no branch), share their
                     // reductions only with each other (whole blocks are in or out), and store nothing.
-  int lane, wave;   // lane of the wave, wave of the workgroup (a workgroup holds kStripWaves neighbouring strips)
-  bool inside;      // the wave's strip exists (the last workgroup may hold fewer)
-  __device__ __forceinline__ Strip32(int rows, int cols, unsigned first = 0) {   // first: workgroups before the strips
+  int lane, wave;   // lane of the wave, wave of the workgroup
+  bool inside;      // the wave's strip exists (the last workgroup may hold fewer; the others repeat the last strip)
+  __device__ __forceinline__ Strip(int rows, int cols, unsigned first = 0) {   // first: workgroups before the strips
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     ch = lane & 7;
     rsub = lane >> 3;
-    const unsigned groups = (unsigned)((cols + 127) / 128), strips = groups * (unsigned)(rows / 32);
-    const unsigned id = (blockIdx.x - first) * (blockDim.x >> 6) + wave;   // strips are numbered column group fastest
+    const unsigned groups = (unsigned)((cols + 127) / 128), strips = groups * (unsigned)(rows / B);
+    const unsigned id = (blockIdx.x - first) * (WAVES / BT) + wave / BT;   // numbered column group fastest
     inside = id < strips;
     const unsigned sid = inside ? id : strips - 1;
     c0 = (int)(sid % groups) * 128;
-    bi = (int)(sid / groups);
-    lc = cols / 32;
+    bi = (int)(sid / groups) * BT + wave % BT;
+    lc = cols / B;
     col = c0 + 16 * ch;
     ok = col < cols;
     base = (int64_t)(bi * 32 + rsub) * cols + (ok ? col : c0);
+    ok = ok && inside;
   }
-  // index of the lane's block in a scale grid (clamped like base)
-  __device__ __forceinline__ int64_t block_index() const { return (int64_t)bi * lc + (ok ? col : c0) / 32; }
+  // index of the lane's block in a scale grid (clamped like base), and whether the lane is the one to store its scale
+  __device__ __forceinline__ int64_t block_index() const { return (int64_t)(bi / BT) * lc + (col < lc * B ? col : c0) / B; }
+  __device__ __forceinline__ bool owns_scale() const { return (lane & (56 | (B / 16 - 1))) == 0 && (BT == 1 || wave % BT == 0); }
 };
+
+typedef Strip<32> Strip32;
 
 // max-abs of 16 values folded into m: eight v_max3_f32 with absolute-value modifiers (the compiler's fmaxf
 // quiets each operand with an extra instruction first)
@@ -89,11 +86,21 @@ __device__ __forceinline__ float amax16(float m, const float (&y)[16]) {
   return m;
 }
 
-// Block max-abs over the 16 lanes of a strip that share a block column (same ch / 2), then Eq. 1's scale.
-__device__ __forceinline__ void strip32_block_scale(float m, float& scale, double& inv) {
-  m = wave_group_max<56 | 1>(m);
+// Block max-abs, over the lanes of a strip that share a block column and over the waves that share the block through `exchange`
+// (two values per wave), then Eq. 1's scale.  At block sizes 64 and 128 every wave of the workgroup has to get here.
+template <int B, int WAVES>
+__device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES>& t, float (*exchange)[2], float& scale, double& inv) {
+  m = wave_group_max<56 | (B / 16 - 1)>(m);
+  if constexpr (B > 32) {
+    if ((t.lane & (56 | (B / 16 - 1))) == 0) exchange[t.wave][t.ch / (B / 16)] = m;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < t.BT; ++k) m = fmaxf(m, exchange[t.wave / t.BT * t.BT + k][t.ch / (B / 16)]);
+  }
   block_scale(m, scale, inv);
 }
+// at block size 32: the 16 lanes of a strip that share a block column (same ch / 2)
+__device__ __forceinline__ void strip32_block_scale(float m, float& scale, double& inv) { block_scale(wave_group_max<56 | 1>(m), scale, inv); }
 
 __device__ __forceinline__ void load16f(const float* p, float (&v)[16]) {
 #pragma unroll
@@ -104,10 +111,28 @@ __device__ __forceinline__ void load16f(const float* p, float (&v)[16]) {
 }
 
 // ------------------------------------------------------------------------------------------------ host
-// workgroups of the strip kernels: kStripWaves strips each
+// workgroups of the strip kernels: WAVES strips of 32 rows each
+template <int B = 32, int WAVES = kStripWaves>
 static inline dim3 strip_grid(int64_t rows, int64_t cols) {
-  const int64_t strips = ((cols + 127) / 128) * (rows / 32);
-  return dim3((unsigned)((strips + kStripWaves - 1) / kStripWaves));
+  const int64_t strips = ((cols + 127) / 128) * (rows / B), per_wg = WAVES * 32 / B;
+  return dim3((unsigned)((strips + per_wg - 1) / per_wg));
+}
+// f(integral_constant<int, B>) for a block size
+template <class F>
+static inline void with_block(int block, F&& f) {
+  if (block == 32) f(std::integral_constant<int, 32>());
+  else if (block == 64) f(std::integral_constant<int, 64>());
+  else f(std::integral_constant<int, 128>());
+}
+
+// f(block size, waves per workgroup, store policy) as integral constants
+template <class F>
+static void with_instance(int block, int64_t rows, int64_t cols, F&& f) {
+  with_block(block, [&](auto b) {
+    with_store_policy(rows, cols, [&](auto sp) {
+      f(b, std::integral_constant<int, strip_waves(decltype(b)::value, decltype(sp)::value)>(), sp);
+    });
+  });
 }
 
 static inline int32_t check_eltwise(const void* x, const void* sx, const void* y, const void* sy, int64_t N, int64_t C,
