@@ -1,9 +1,10 @@
 // jf_quantize_block: per-block quantizer Q of Sec. 4, Eq. 1 (FP32/FP16 -> INT8 + FP32 scale grid).
 //
-// HBM-bound: 4 (or 2) bytes in, 1 byte out per element.  One workgroup of four
-// waves owns a 128 x 128 tile; wave w owns the 32-row strip w of it.  Inside a
-// strip a lane holds 16 bytes (4 FP32 or 8 FP16 columns) of 16 or 8 rows, so each row
-// of the strip is read as one run of 512 or 256 bytes and written as one 128-byte line of codes.
+// HBM-bound: 4 (or 2) bytes in, 1 byte out per element.  A workgroup of four waves owns a 128 x 128 tile; wave w owns the
+// 32-row strip w of it.  Inside a strip a lane holds 16 bytes (4 FP32 or 8 FP16 columns) of 16 or 8 rows, so each row
+// of the strip is read as one run of 512 or 256 bytes and written as one 128-byte line of codes.  A small tensor gives a
+// compute unit a wave or two of that kind, whose 64 elements a lane are a serial chain of loads and roundings with nothing beside
+// it; there the strips are narrower (launch_quantize).
 #include "jf_common.hpp"
 
 namespace jf {
@@ -19,22 +20,22 @@ __device__ __forceinline__ void load_vec(const _Float16* p, float (&v)[8]) {
   for (int i = 0; i < 8; ++i) v[i] = (float)t[i];
 }
 
-// B = quantization block; the tile is 128 x 128 and 256 threads (WPW = 4 waves per workgroup), or, for small
-// tensors at B = 32 where the waves do not depend on each other, one 32 x 128 strip and one wave (WPW = 1), which
-// spreads a tensor of a few hundred tiles over all compute units.
-template <typename T, int B, bool TRANSPOSED_COPY, int WPW, StorePolicy SP>
-__global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict__ x, int64_t ldx, int rows, int cols,
+// B = quantization block; a workgroup's tile is WR x WC waves of 32 rows and COLS columns each.
+template <typename T, int B, bool TRANSPOSED_COPY, int WR, int WC, int COLS, StorePolicy SP>
+__global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restrict__ x, int64_t ldx, int rows, int cols,
                                                         int8_t* __restrict__ q, int64_t ldq, float* __restrict__ s,
                                                         int8_t* __restrict__ qT, int64_t ldqT, float* __restrict__ sT) {
-  __shared__ float s_amax[4][4];                       // [32-row strip][32-col group]
+  constexpr int TR = 32 * WR, TC = COLS * WC;          // the tile
+  static_assert(TR >= B || B == 32, "a block lies inside one workgroup's tile");
+  static_assert(TC >= B && (!TRANSPOSED_COPY || (TR == 128 && COLS == 128 && WC == 1)), "whole blocks; the transposed copy goes by 128 x 128");
+  __shared__ float s_amax[WR][TC / 32];                // [32-row strip][32-col group]
   __shared__ __align__(16) uint8_t s_codes[TRANSPOSED_COPY ? 128 * 132 : 16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const TileIndex wg = tile_of_workgroup((cols + 127) / 128);
-  static_assert(WPW == 4 || (WPW == 1 && B == 32 && !TRANSPOSED_COPY), "single-wave workgroups: independent waves only");
-  const int r0 = (wg.y * WPW + wave) * 32;             // first row of this wave's strip
-  const int c0 = wg.x * 128;
-  constexpr int VEC = 16 / sizeof(T), LPR = 128 / VEC, RPI = 64 / LPR, NI = 32 / RPI;   // columns per lane, lanes per row, rows at once
-  const int cl = lane % LPR, rh = lane / LPR;
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % WR, across = WC == 1 ? 0 : (threadIdx.x >> 6) / WR;
+  const TileIndex wg = tile_of_workgroup((cols + TC - 1) / TC);
+  const int r0 = (wg.y * WR + wave) * 32;              // first row of this wave's strip
+  const int c0 = wg.x * TC;
+  constexpr int VEC = 16 / sizeof(T), LPR = COLS / VEC, RPI = 64 / LPR, NI = 32 / RPI;   // columns per lane, lanes per row, rows at once
+  const int cl = lane % LPR + LPR * across, rh = lane / LPR;
   const int col = c0 + VEC * cl, cg = cl / (32 / VEC); // first column; 32-column group of the tile
   const bool col_ok = col < cols;                      // cols % 32 == 0: the lanes of a group are in or out together
 
@@ -117,24 +118,34 @@ __global__ void __launch_bounds__(64 * WPW) quantize_kernel(const T* __restrict_
   }
 }
 
+// Narrow strips, in workgroups of one block row and, at block size 128, one block: 64 columns a wave up to 256 tiles of 128 x 128
+// (one for each compute unit; FP16, half the bytes in flight a lane, up to 768), 32 columns for the smallest tensors and, in
+// FP16 at block sizes 64 and 128, up to 256 tiles.  Kernel times in us with 128, 64 and 32 columns, operands not in L2:
+//   FP32  block 32   256 x 256 3.4, 3.0, 2.8; 1056 x 800 (63 tiles) 4.1, 3.4, 3.2; 2048 x 1024 (128) 5.0, 4.0, 4.3; 4096 x 768 (192)
+//                    5.6, 5.0, 5.8; 4096 x 1536 (384) 6.3, 6.8, 7.7
+//         block 64   1024 x 768 4.2, 3.3, 3.3; 2048 x 2048 (256) 5.6, 5.4, 6.0; 4096 x 1536 8.1, 8.4, 9.0     128: 4.3, 4.0, 4.2; 5.6, 5.4, 5.9
+//   FP16  block 32   1024 x 768 5.6, 3.8, 3.3; 2048 x 2048 8.4, 6.5, 6.8; 4096 x 3072 (768) 10.7, 10.1, 15.0; 8192 x 2048 (1024) 13.3, 14.0
+//         block 64   1024 x 768 5.7, 4.0, 3.5; 2048 x 2048 7.8, 6.8, 6.3; 8192 x 1280 (640) 10.4, 10.0, 11.4     128: 5.7, 4.5, 4.3; 8.1, 6.5, 6.0
 template <typename T, int B>
 static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t* q, int64_t ldq, float* s, int8_t* qT,
                             int64_t ldqT, float* sT, hipStream_t st) {
-  const dim3 grid(tile_grid((cols + 127) / 128, (rows + 127) / 128));
+  // the kernel for tiles of WR x WC strips of COLS columns
+  const auto launch = [&](auto kernel, int WR, int WC, int COLS) {
+    const dim3 grid(tile_grid((cols + COLS * WC - 1) / (COLS * WC), (rows + 32 * WR - 1) / (32 * WR)));
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * WR * WC), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
+  };
+  constexpr bool FP16 = sizeof(T) == 2;
+  const int64_t tiles = (int64_t)((cols + 127) / 128) * ((rows + 127) / 128);
   with_store_policy(rows, ldq, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
-    if (qT) {
-      hipLaunchKernelGGL((quantize_kernel<T, B, true, 4, SP>), grid, dim3(256), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
-      return;
+    if (qT) return launch(quantize_kernel<T, B, true, 4, 1, 128, SP>, 4, 1, 128);
+    if constexpr (SP == kStoreThrough) {
+      constexpr int G = B / 32;
+      if constexpr (B == 32 || FP16)
+        if (tiles <= (B == 32 ? 64 : 256)) return launch(quantize_kernel<T, B, false, G, G, 32, SP>, G, G, 32);
+      if (tiles <= (FP16 ? 768 : 256)) return launch(quantize_kernel<T, B, false, G, (B + 63) / 64, 64, SP>, G, (B + 63) / 64, 64);
     }
-    if constexpr (B == 32 && SP == kStoreThrough) {
-      if (grid.x < 512) {  // fewer than two workgroups per compute unit: one wave per workgroup instead
-        hipLaunchKernelGGL((quantize_kernel<T, B, false, 1, SP>), dim3(tile_grid((cols + 127) / 128, rows / 32)), dim3(64), 0, st, x,
-                           ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
-        return;
-      }
-    }
-    hipLaunchKernelGGL((quantize_kernel<T, B, false, 4, SP>), grid, dim3(256), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
+    launch(quantize_kernel<T, B, false, 4, 1, 128, SP>, 4, 1, 128);
   });
 }
 
