@@ -5,7 +5,8 @@
 //   * GELU: within one quantization block the input takes at most 255 values (code * block scale), so GELU (or its
 //     derivative) is tabulated once per block in LDS and every element is a table lookup indexed by its code byte -- the
 //     dequantize step of Alg. 2 and the erf evaluation collapse into it;
-//   * one wave per strip of 32 x 128, 64 elements of one block per lane, see jf_rowops.hpp; at block size 32 no barrier.
+//   * one wave per strip of 32 x 128 (64 for small tensors), 64 (32) elements of one block per lane, see jf_rowops.hpp; at block
+//     size 32 no barrier.
 #include "jf_rowops.hpp"
 
 namespace jf {
@@ -75,18 +76,19 @@ __device__ __forceinline__ void wave_lds_order() {
 }
 
 // GELU forward and backward (BWD: dx = g GELU'(x)) on strips: a table per block and wave.
-template <bool BWD, int B, int WAVES, StorePolicy SP>
+template <bool BWD, int B, int WAVES, int COLS, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX, const int8_t* __restrict__ G,
                                                          const float* __restrict__ SG, int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
-  constexpr int NBC = 128 / B;   // blocks of a strip
+  constexpr int NBC = COLS / B;   // blocks of a strip
   __shared__ float s_tabs[WAVES][NBC][256];
   __shared__ float s_amax[WAVES][2];
-  const Strip<B, WAVES> t(rows, cols);
+  const Strip<B, WAVES, COLS> t(rows, cols);
+  constexpr int P = Strip<B, WAVES, COLS>::PASSES;
   if (B == 32 && !t.inside) return;   // a whole wave; there is no workgroup barrier
-  const int64_t pass = (int64_t)8 * cols;
-  uint4 px[4], pg[BWD ? 4 : 1];   // requested first: their latency runs beside the table build
+  const int64_t pass = (int64_t)t.ROWS * cols;
+  uint4 px[P], pg[BWD ? P : 1];   // requested first: their latency runs beside the table build
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < P; ++p) {
     px[p] = *reinterpret_cast<const uint4*>(X + t.base + p * pass);
     if (BWD) pg[p] = *reinterpret_cast<const uint4*>(G + t.base + p * pass);
   }
@@ -105,10 +107,10 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
     sg = SG[t.block_index()];
     sg128 = -128.0f * sg;
   }
-  float y[4][16];
+  float y[P][16];
   float m = 0.0f;
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < P; ++p) {
     const uint32_t w[4] = {px[p].x, px[p].y, px[p].z, px[p].w};
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
@@ -131,10 +133,10 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
   if (!t.ok) return;
   if (t.owns_scale()) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < P; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
-// The same for block size 64 and results that are written through, with one quantization block per WAVE: no workgroup
+// The same for block size 64 and results that are written through but not small, with one quantization block per WAVE: no workgroup
 // barrier and no LDS exchange between waves, so the four waves of a workgroup (four neighbouring block columns)
 // run independently and one wave's table build overlaps its neighbours' loads and stores (8192 x 1280 backward 7.3 us, on
 // strips 7.9; 4096 x 3072 8.0 and 8.7; from HBM its 64-byte row pieces cost a third of the bandwidth).  Lane = (row l / CPR,
@@ -215,27 +217,28 @@ __global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict
 // codes' policy, since a wave has whole lines of them at block sizes 64 and 128 only (streamed in pieces, 1048576 x 768 at
 // block 32 took 653 us, written through 543, back 472), and each lane stores those of another pass: two or four stores per
 // strip for eight of a few lanes each (8192 x 1280 7.6 -> 7.3 us, 1048576 x 768 469 -> 447; at block 128 7.5 -> 7.4, 468 -> 409).
-template <int B, int WAVES, bool PARTIALS, StorePolicy SP>
+template <int B, int WAVES, int COLS, bool PARTIALS, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) add_kernel(const int8_t* __restrict__ X1, const float* __restrict__ S1,
                                                               const int8_t* __restrict__ X2, const float* __restrict__ S2, int rows, int cols,
                                                               int8_t* __restrict__ Y, float* __restrict__ SY, float* __restrict__ row_mean,
                                                               float* __restrict__ row_sumsq) {
   __shared__ float s_amax[WAVES][2];
-  const Strip<B, WAVES> t(rows, cols);
+  const Strip<B, WAVES, COLS> t(rows, cols);
+  constexpr int P = Strip<B, WAVES, COLS>::PASSES;
   if (B == 32 && !t.inside) return;   // a whole wave; there is no workgroup barrier
-  const int64_t pass = (int64_t)8 * cols;
-  float y[4][16], ps[4], pq[4];
+  const int64_t pass = (int64_t)t.ROWS * cols;
+  float y[P][16], ps[P], pq[P];
   float m = 0.0f;
-  uint4 p1[4], p2[4];
+  uint4 p1[P], p2[P];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < P; ++p) {
     p1[p] = *reinterpret_cast<const uint4*>(X1 + t.base + p * pass);
     p2[p] = *reinterpret_cast<const uint4*>(X2 + t.base + p * pass);
   }
   const float s1 = S1[t.block_index()], s2 = S2[t.block_index()];
   const float k = -128.0f * (s1 + s2);  // the unpacked codes carry +128
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < P; ++p) {
     float u1[16], u2[16];
     unpack16_biased(p1[p], u1);
     unpack16_biased(p2[p], u2);
@@ -249,8 +252,8 @@ __global__ void __launch_bounds__(64 * WAVES) add_kernel(const int8_t* __restric
         ps[p] += y[p][e];
         pq[p] = __builtin_fmaf(y[p][e], y[p][e], pq[p]);
       }
-      ps[p] = wave_group_sum<B / 16 - 1>(ps[p]) * (1.0f / (float)B);
-      pq[p] = wave_group_sum<B / 16 - 1>(pq[p]);
+      ps[p] = wave_group_sum<Strip<B, WAVES, COLS>::BLOCK_CHUNK_LANES>(ps[p]) * (1.0f / (float)B);
+      pq[p] = wave_group_sum<Strip<B, WAVES, COLS>::BLOCK_CHUNK_LANES>(pq[p]);
     }
   }
   if (PARTIALS && t.ok) {
@@ -259,20 +262,23 @@ __global__ void __launch_bounds__(64 * WAVES) add_kernel(const int8_t* __restric
     float* const mean = row_mean + (int64_t)(t.col / B) * rows + t.bi * 32 + t.rsub;
     float* const sumsq = row_sumsq + (int64_t)(t.col / B) * rows + t.bi * 32 + t.rsub;
     const auto pick = [](bool second, float a, float b) { return second ? b : a; };   // (by value: of references it would be an address)
-    const int p = t.ch & 3;
-    const auto of_pass = [&](const float(&v)[4]) { return pick(p & 2, pick(p & 1, v[0], v[1]), pick(p & 1, v[2], v[3])); };
+    const int p = t.ch & (P - 1);
+    const auto of_pass = [&](const float(&v)[P]) {
+      if constexpr (P == 4) return pick(p & 2, pick(p & 1, v[0], v[1]), pick(p & 1, v[2], v[3]));
+      else return pick(p, v[0], v[P - 1]);
+    };
     if constexpr (B == 32) {
       const int odd = t.ch & 1;
 #pragma unroll
-      for (int i = 0; i < 4; i += 2) {
-        store_part(&mean[8 * (i + odd)], pick(odd, ps[i], ps[i + 1]));
-        store_part(&sumsq[8 * (i + odd)], pick(odd, pq[i], pq[i + 1]));
+      for (int i = 0; i < P; i += 2) {
+        store_part(&mean[t.ROWS * (i + odd)], pick(odd, ps[i], ps[i + 1]));
+        store_part(&sumsq[t.ROWS * (i + odd)], pick(odd, pq[i], pq[i + 1]));
       }
-    } else if constexpr (B == 64) {
+    } else if constexpr (B == 64 && P == 4) {
       store_part(&mean[8 * p], of_pass(ps));
       store_part(&sumsq[8 * p], of_pass(pq));
     } else {
-      store_part((t.ch < 4 ? mean : sumsq) + 8 * p, pick(t.ch < 4, of_pass(pq), of_pass(ps)));
+      store_part((t.ch < P ? mean : sumsq) + t.ROWS * p, pick(t.ch < P, of_pass(pq), of_pass(ps)));
     }
   }
   float scale;
@@ -281,7 +287,7 @@ __global__ void __launch_bounds__(64 * WAVES) add_kernel(const int8_t* __restric
   if (!t.ok) return;
   if (t.owns_scale()) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < P; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -341,16 +347,29 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
 }
 
 // ------------------------------------------------------------------------------------------------ host
+// Whether an operator at block size 32 or 64 takes strips of 64 columns: half the serial chain of a wave (two tables instead of
+// four) on twice the waves, against 64-byte row pieces.  Kernel times in us on operands that are not in L2, 128 -> 64 columns:
+//   GELU           256 x 256 4.0 -> 3.3, 1056 x 2080 4.8 -> 4.1, 8192 x 1280 7.2 -> 6.4, 4096 x 3072 7.4 -> 6.6, 8192 x 4096 13.8 -> 12.9,
+//                  16384 x 2880 20.4 -> 21.4; block 64 (wave kernel) 1024 x 768 4.0 -> 3.4, 8192 x 1280 6.9 -> 6.2, 8192 x 2048 7.8 -> 7.9
+//   GELU backward  1056 x 2080 5.1 -> 4.6, 8192 x 1280 8.7 -> 7.8, 8192 x 3072 14.2 -> 13.9, 8192 x 4096 16.9 -> 17.5; block 64 1024 x 768
+//                  4.5 -> 3.7, 8192 x 1280 8.0 -> 7.6, 4096 x 3072 8.7 -> 8.8
+//   Add            1056 x 800 4.0 -> 3.6, 8192 x 1280 7.1 -> 6.9, 8192 x 2048 8.9 -> 9.7; with partials 4.8 -> 4.3, 8.0 -> 7.6, 9.6 -> 11.0
+//   Dropout        has nothing but its loads and the rounding: 4096 x 768 3.5 -> 3.7, 16384 x 1280 8.4 -> 9.5; always 128.
+static bool narrow_gelu(bool backward, int block, int64_t rows, int64_t cols) {
+  return rows * cols <= (int64_t)(block == 64 ? (backward ? 10 : 12) : (backward ? 24 : 32)) << 20;
+}
+static bool narrow_add(int64_t rows, int64_t cols) { return rows * cols <= 10 << 20; }
+
 template <bool BWD>
 static void launch_gelu(int block, const int8_t* X, const float* SX, const int8_t* G, const float* SG, int rows, int cols, int8_t* Y, float* SY,
                         hipStream_t st) {
-  with_instance(block, rows, cols, [&](auto b, auto w, auto sp) {
-    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value;
+  with_instance(block, rows, cols, narrow_gelu(BWD, block, rows, cols), [&](auto b, auto w, auto c, auto sp) {
+    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, COLS = decltype(c)::value;
     constexpr StorePolicy SP = decltype(sp)::value;
-    if constexpr (B == 64 && SP == kStoreThrough)
+    if constexpr (B == 64 && SP == kStoreThrough && COLS == 128)
       hipLaunchKernelGGL((gelu_wave_kernel<BWD, SP>), dim3(tile_grid((cols + 255) / 256, rows / 64)), dim3(256), 0, st, X, SX, G, SG, rows, cols, Y, SY);
     else
-      hipLaunchKernelGGL((gelu_kernel<BWD, B, WAVES, SP>), (strip_grid<B, WAVES>(rows, cols)), dim3(64 * WAVES), 0, st, X, SX, G, SG, rows, cols, Y, SY);
+      hipLaunchKernelGGL((gelu_kernel<BWD, B, WAVES, COLS, SP>), (strip_grid<B, WAVES, COLS>(rows, cols)), dim3(64 * WAVES), 0, st, X, SX, G, SG, rows, cols, Y, SY);
   });
 }
 
@@ -403,14 +422,14 @@ extern "C" int32_t jf_add_q(const int8_t* X1, const float* S1, const int8_t* X2,
   if ((row_mean == nullptr) != (row_sumsq == nullptr)) return JF_ERR_NULL;
   if (!aligned16(X2) || !aligned4(S2) || (row_mean && (!aligned4(row_mean) || !aligned4(row_sumsq)))) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  with_instance(block, N, C, [&](auto b, auto w, auto sp) {
-    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value;
+  with_instance(block, N, C, narrow_add(N, C), [&](auto b, auto w, auto c, auto sp) {
+    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, COLS = decltype(c)::value;
     constexpr StorePolicy SP = decltype(sp)::value;
     const auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, (strip_grid<B, WAVES>(N, C)), dim3(64 * WAVES), 0, st, X1, S1, X2, S2, (int)N, (int)C, Y, SY, row_mean, row_sumsq);
+      hipLaunchKernelGGL(kernel, (strip_grid<B, WAVES, COLS>(N, C)), dim3(64 * WAVES), 0, st, X1, S1, X2, S2, (int)N, (int)C, Y, SY, row_mean, row_sumsq);
     };
-    if (row_mean) launch(add_kernel<B, WAVES, true, SP>);
-    else launch(add_kernel<B, WAVES, false, SP>);
+    if (row_mean) launch(add_kernel<B, WAVES, COLS, true, SP>);
+    else launch(add_kernel<B, WAVES, COLS, false, SP>);
   });
   return launch_status();
 }

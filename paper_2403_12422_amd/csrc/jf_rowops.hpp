@@ -35,6 +35,7 @@ __device__ __forceinline__ void unpack16_biased(const uint4& p, float (&u)[16]) 
 // exchanged between waves, no barrier.  At block sizes 64 and 128 two or four waves of a workgroup stand one above the other
 // and exchange it through LDS.  Per element the kernels spend what Alg. 2 needs (unpack, the operator, max-abs, Eq. 1) and
 // little else; the per-lane overhead is paid once per 64 elements.
+// For small tensors a strip is 64 columns wide, in two passes of 16 rows (block sizes 32 and 64).
 // Waves per workgroup: at block size 32 four neighbouring strips of the same rows, so that 512 contiguous bytes of every row
 // are requested close together in time (on 0.8 GB tensors of 3072 columns 5.4-5.7 TB/s instead of 4.4-5.0 with one strip per
 // workgroup); two by two at 64 and one above the other at 128, and twice as wide for results that go to memory (262144 x
@@ -42,9 +43,13 @@ __device__ __forceinline__ void unpack16_biased(const uint4& p, float (&u)[16]) 
 // 6.7 and 7.2, GELU backward at 128 7.7 and 8.7).
 constexpr int kStripWaves = 4;
 constexpr int strip_waves(int block, StorePolicy sp) { return block == 32 || sp == kStoreThrough ? 4 : 8; }
-template <int B, int WAVES = kStripWaves>
+template <int B, int WAVES = kStripWaves, int COLS = 128>
 struct Strip {
   static constexpr int BT = B / 32;   // waves that share a block
+  static constexpr int LANES = COLS / 16, ROWS = 64 / LANES, PASSES = 32 / ROWS;   // lanes of a row, rows of a pass
+  // lane id bits: chunk column (of 64 columns: bits 0 and 3, so that the lanes of a block of 32 share bits 0 to 2)
+  static constexpr int CHUNK_LANES = LANES == 4 ? 9 : LANES - 1, BLOCK_CHUNK_LANES = LANES == 4 && B == 64 ? 9 : B / 16 - 1;
+  static constexpr int BLOCK_LANES = (63 & ~CHUNK_LANES) | BLOCK_CHUNK_LANES;      // bits in which the lanes of a block differ
   int ch, rsub;     // chunk column and row of the lane inside an 8-row pass
   int bi, lc;       // 32-row group of the strip, block columns of the matrix
   int c0, col;      // first column of the strip, first column of the lane's chunks
@@ -57,13 +62,13 @@ struct Strip {
   __device__ __forceinline__ Strip(int rows, int cols, unsigned first = 0) {   // first: workgroups before the strips
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    ch = lane & 7;
-    rsub = lane >> 3;
-    const unsigned groups = (unsigned)((cols + 127) / 128), strips = groups * (unsigned)(rows / B);
+    ch = LANES == 4 ? (lane & 1) | ((lane >> 2) & 2) : lane & (LANES - 1);
+    rsub = LANES == 4 ? ((lane >> 1) & 3) | ((lane >> 2) & 12) : lane / LANES;
+    const unsigned groups = (unsigned)((cols + COLS - 1) / COLS), strips = groups * (unsigned)(rows / B);
     const unsigned id = (blockIdx.x - first) * (WAVES / BT) + wave / BT;   // numbered column group fastest
     inside = id < strips;
     const unsigned sid = inside ? id : strips - 1;
-    c0 = (int)(sid % groups) * 128;
+    c0 = (int)(sid % groups) * COLS;
     bi = (int)(sid / groups) * BT + wave % BT;
     lc = cols / B;
     col = c0 + 16 * ch;
@@ -73,7 +78,7 @@ struct Strip {
   }
   // index of the lane's block in a scale grid (clamped like base), and whether the lane is the one to store its scale
   __device__ __forceinline__ int64_t block_index() const { return (int64_t)(bi / BT) * lc + (col < lc * B ? col : c0) / B; }
-  __device__ __forceinline__ bool owns_scale() const { return (lane & (56 | (B / 16 - 1))) == 0 && (BT == 1 || wave % BT == 0); }
+  __device__ __forceinline__ bool owns_scale() const { return (lane & BLOCK_LANES) == 0 && (BT == 1 || wave % BT == 0); }
 };
 
 typedef Strip<32> Strip32;
@@ -88,11 +93,11 @@ __device__ __forceinline__ float amax16(float m, const float (&y)[16]) {
 
 // Block max-abs, over the lanes of a strip that share a block column and over the waves that share the block through `exchange`
 // (two values per wave), then Eq. 1's scale.  At block sizes 64 and 128 every wave of the workgroup has to get here.
-template <int B, int WAVES>
-__device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES>& t, float (*exchange)[2], float& scale, double& inv) {
-  m = wave_group_max<56 | (B / 16 - 1)>(m);
+template <int B, int WAVES, int COLS>
+__device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES, COLS>& t, float (*exchange)[2], float& scale, double& inv) {
+  m = wave_group_max<Strip<B, WAVES, COLS>::BLOCK_LANES>(m);
   if constexpr (B > 32) {
-    if ((t.lane & (56 | (B / 16 - 1))) == 0) exchange[t.wave][t.ch / (B / 16)] = m;
+    if ((t.lane & t.BLOCK_LANES) == 0) exchange[t.wave][t.ch / (B / 16)] = m;
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < t.BT; ++k) m = fmaxf(m, exchange[t.wave / t.BT * t.BT + k][t.ch / (B / 16)]);
@@ -112,9 +117,9 @@ __device__ __forceinline__ void load16f(const float* p, float (&v)[16]) {
 
 // ------------------------------------------------------------------------------------------------ host
 // workgroups of the strip kernels: WAVES strips of 32 rows each
-template <int B = 32, int WAVES = kStripWaves>
+template <int B = 32, int WAVES = kStripWaves, int COLS = 128>
 static inline dim3 strip_grid(int64_t rows, int64_t cols) {
-  const int64_t strips = ((cols + 127) / 128) * (rows / B), per_wg = WAVES * 32 / B;
+  const int64_t strips = ((cols + COLS - 1) / COLS) * (rows / B), per_wg = WAVES * 32 / B;
   return dim3((unsigned)((strips + per_wg - 1) / per_wg));
 }
 // f(integral_constant<int, B>) for a block size
@@ -132,6 +137,16 @@ static void with_instance(int block, int64_t rows, int64_t cols, F&& f) {
     with_store_policy(rows, cols, [&](auto sp) {
       f(b, std::integral_constant<int, strip_waves(decltype(b)::value, decltype(sp)::value)>(), sp);
     });
+  });
+}
+// f(block size, waves per workgroup, columns of a strip, store policy): 64 columns instead of 128 if `narrow`, at block sizes 32
+// and 64 and for results that are written through
+template <class F>
+static void with_instance(int block, int64_t rows, int64_t cols, bool narrow, F&& f) {
+  with_instance(block, rows, cols, [&](auto b, auto w, auto sp) {
+    if constexpr (decltype(b)::value <= 64 && decltype(sp)::value == kStoreThrough)
+      if (narrow) return f(b, w, std::integral_constant<int, 64>(), sp);
+    f(b, w, std::integral_constant<int, 128>(), sp);
   });
 }
 
