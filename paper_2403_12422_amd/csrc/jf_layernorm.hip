@@ -495,11 +495,13 @@ static int32_t layernorm_fwd(const int8_t* X, const float* SX, const float* row_
   if (!gamma || !beta || !mean || !rstd) return JF_ERR_NULL;
   if (!aligned16(gamma) || !aligned16(beta) || !aligned4(mean) || !aligned4(rstd)) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (layernorm_rows_fits(N, C, block, false)) {   // one pass over the operands
+  const bool whole_rows = layernorm_rows_fits(N, C, block, false);
+  if (whole_rows || (row_mean == nullptr && layernorm_wide_fits(N, C, block, false))) {   // one pass over the operands
     LayerNormRows a{};
     a.X = X; a.SX = SX; a.row_mean = row_mean; a.row_sumsq = row_sumsq; a.gamma = gamma; a.beta = beta; a.eps = eps;
     a.rows = (int)N; a.cols = (int)C; a.Y = Y; a.SY = SY; a.mean = mean; a.rstd = rstd;
-    (block == 32 ? launch_layernorm_rows_b32 : block == 64 ? launch_layernorm_rows_b64 : launch_layernorm_rows_b128)(a, st);
+    if (!whole_rows) launch_layernorm_wide(a, st);
+    else (block == 32 ? launch_layernorm_rows_b32 : block == 64 ? launch_layernorm_rows_b64 : launch_layernorm_rows_b128)(a, st);
     return launch_status();
   }
   if (row_mean != nullptr) {
@@ -563,13 +565,16 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
     hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((2 * C + 63) / 64)), dim3(1024), 0, st, partials, nparts, (int)(2 * C), dgamma, dbeta);
     return launch_status();
   };
-  if (layernorm_rows_fits(N, C, block, true)) {   // one pass over the operands
+  const bool whole_rows = layernorm_rows_fits(N, C, block, true);
+  if (whole_rows || layernorm_wide_fits(N, C, block, true)) {   // one pass over the operands
     LayerNormBwdRows a{};
     a.G = dY; a.SG = SdY; a.X = X; a.SX = SX; a.gamma = gamma; a.mean = mean; a.rstd = rstd; a.rows = (int)N; a.cols = (int)C;
     a.dX = dX; a.SdX = SdX; a.partials = partials;
     a.dgamma = dgamma; a.dbeta = dbeta;
-    nparts = (block == 32 ? launch_layernorm_bwd_rows_b32 : block == 64 ? launch_layernorm_bwd_rows_b64 : launch_layernorm_bwd_rows_b128)(
-        a, sums_in_place || any_overlap(out, in), st);
+    if (!whole_rows) nparts = launch_layernorm_bwd_wide(a, st);
+    else
+      nparts = (block == 32 ? launch_layernorm_bwd_rows_b32 : block == 64 ? launch_layernorm_bwd_rows_b64 : launch_layernorm_bwd_rows_b128)(
+          a, sums_in_place || any_overlap(out, in), st);
     const int32_t rc = launch_status();
     return rc != JF_OK || nparts == 0 ? rc : launch_colsum();
   }

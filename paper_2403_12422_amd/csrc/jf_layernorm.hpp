@@ -1,5 +1,5 @@
-// What the two LayerNorm sources share: jf_layernorm.hip (entry points; sums kernels + operators on tiles) and
-// jf_layernorm_rows.hpp (one pass over whole rows).
+// What the LayerNorm sources share: jf_layernorm.hip (entry points; sums kernels + operators on tiles), jf_layernorm_rows.hpp (one
+// pass over whole rows) and jf_layernorm_wide.hip (the same for wider rows).
 #pragma once
 #include "jf_rowops.hpp"
 
@@ -62,5 +62,25 @@ void launch_layernorm_rows_b128(const LayerNormRows& a, hipStream_t st);
 int launch_layernorm_bwd_rows_b32(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
 int launch_layernorm_bwd_rows_b64(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
 int launch_layernorm_bwd_rows_b128(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
+
+
+// Whether the kernels for wider rows (jf_layernorm_wide.hip) take a pass at block size 32, and their launches; the backward one
+// returns its number of partial rows (at most 256 and at most rows / 32).  Forward not from the row partials of an Add: those say what
+// the first of the two kernels reads the codes for.  A compute unit takes whole row groups: few of them, or a last round that is nearly
+// empty, leave too many idle.  Two kernels -> one in us:
+//   backward   4096 x 4096 (128 groups) 24.6 -> 29.5, 5120 x 2560 (160) 29.1 -> 22.2, 5120 x 4096 34.8 -> 30.6, 8192 x 4096 46.1 -> 35.3,
+//              8256 x 4096 (258) 53.5 -> 55.0, 10240 x 4096 (320) 58.6 -> 56.2, 18432 x 2560 (576) 70.1 -> 56.8, 8192 x 11008 148 -> 99;
+//              beyond kLayerNormWideCols LDS has room for the column sums of few waves only
+//   forward    4096 x 4096 12.8 -> 13.4, 5120 x 2560 11.7 -> 9.9, 8192 x 3072 15.5 -> 12.3, 8256 x 4096 22.4 -> 25.8, 9600 x 4096 (300) 25.3 -> 26.8,
+//              18432 x 2560 27.5 -> 28.6, 20480 x 4096 (640) 43.7 -> 41.3, 22528 x 3072 (704) 36.1 -> 32.3, 25600 x 2560 (800) 36.6 -> 38.9,
+//              8192 x 7168 31.6 -> 27.7, 8192 x 8192 40.1 -> 42.0
+constexpr int kLayerNormWideCols = 11264;
+inline bool layernorm_wide_fits(int64_t N, int64_t C, int32_t block, bool backward) {
+  const int64_t groups = N / 32, room = (groups + 255) / 256 * 256;   // row groups of full rounds
+  if (block != 32 || C > (backward ? kLayerNormWideCols : 7168) || groups < 160) return false;
+  return room == 256 || (backward ? 8 * groups >= 5 * room : 5 * groups >= 4 * room);
+}
+void launch_layernorm_wide(LayerNormRows a, hipStream_t st);
+int launch_layernorm_bwd_wide(LayerNormBwdRows a, hipStream_t st);
 
 }  // namespace jf
