@@ -34,8 +34,8 @@ struct RowStrips {
     nstrips = blockDim.x >> 6;
     block = block_size;
     lc = cols / block;
-    // rows wider than 16 strips are shared by the workgroups blockIdx.y = 0, 1, ...: 2048 columns each
-    const int c0 = (blockIdx.y * 16 + wave) * 128, c = c0 + 16 * ch;
+    // rows wider than 16 strips (2048 columns) are shared evenly by the workgroups blockIdx.y = 0, 1, ...
+    const int c0 = (blockIdx.y * nstrips + wave) * 128, c = c0 + 16 * ch;
     ok = c < cols;
     col = ok ? c : min(c0, cols - 32);   // lanes outside the matrix point at a valid chunk instead, see Strip32
   }
@@ -111,94 +111,135 @@ __global__ void __launch_bounds__(1024) layernorm_row_stats_kernel(const int8_t*
 // compute unit with a single workgroup and nothing to overlap its memory latency with.)
 //
 // First kernel: the workgroup of strip waves described above walks over the row blocks blockIdx.x, blockIdx.x +
-// gridDim.x, ... (four waves per SIMD: another workgroup's loads run beside this one's arithmetic).  The row sums go
-// over the chunk lanes, then over the strips through LDS (two copies used by alternate row blocks: one barrier per block); the running column sums of
+// gridDim.x, ..., one 32 x 128 strip of each in a wave.  Ten instructions per element (the block scale of g goes onto sums, not
+// onto elements; in place of fifteen, with the column reduction of jf_layernorm.hpp and even column ranges: 4096 x 2560 at block 32,
+// whole pass, 19.5 -> 16.6 us, 4096 x 4096 at 64 22.6 -> 21.3, 2048 x 1024 at 128 11.1 -> 10.2).  The row sums go over the chunk lanes, then over the strips through LDS (two copies used by alternate row blocks: one barrier per block); the running column sums of
 // g xhat and g stay in registers over all row blocks -- a lane always holds the same 16 columns -- and are added
 // over the 8 row lanes of the wave at the end (every wave owns its own 128 columns of the partial row).  All orders
 // are fixed: results are bit-stable from run to run.
-template <int WMAX>
-__global__ void __launch_bounds__(64 * WMAX) __attribute__((amdgpu_waves_per_eu(4))) layernorm_bwd_sums_kernel(
+// LDS of a wave: codes of x and of g, their block scales, mean and rstd of the 32 rows
+constexpr int kSumsG = 4096, kSumsScaleX = 8192, kSumsScaleG = kSumsScaleX + 256, kSumsMean = kSumsScaleG + 256, kSumsRstd = kSumsMean + 128,
+              kSumsWaveBytes = kSumsRstd + 128, kSumsRowBytes = 2 * 32 * 8;
+template <bool AHEAD>
+__global__ void __launch_bounds__(1024) layernorm_bwd_sums_kernel(
     const int8_t* __restrict__ G, const float* __restrict__ SG, const int8_t* __restrict__ X, const float* __restrict__ SX,
     const float* __restrict__ gamma, const float* __restrict__ mean_in, const float* __restrict__ rstd_in, int rows,
     int cols, int block, float* __restrict__ row_means, float* __restrict__ partials) {
-  __shared__ float s_row[2][WMAX][32][2];   // [row block parity][strip][row]: sums of ghat and of ghat xhat
+  extern __shared__ __align__(16) int8_t smem[];
   const RowStrips t(cols, block);
-  const int64_t pass = (int64_t)8 * cols;
-  const int nblocks = rows / 32;
+  float* const s_row = reinterpret_cast<float*>(smem);   // [row block parity][strip][row][sum of ghat, of ghat xhat]
+  int8_t* const own = smem + t.nstrips * kSumsRowBytes + t.wave * kSumsWaveBytes;   // with AHEAD
+  const int nblocks = rows / 32, lane = threadIdx.x & 63;
   const float inv_cols = 1.0f / (float)cols;
+  const uint32_t off = (uint32_t)(t.rsub * cols + t.col), off_scale = (uint32_t)(t.col / block) * 4;
+  auto request = [&](int g) __attribute__((always_inline)) {
+    const int8_t* const x = uniform_pointer(X + (int64_t)g * 32 * cols);
+    const int8_t* const gr = uniform_pointer(G + (int64_t)g * 32 * cols);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      load_lds_16(x + (int64_t)p * 8 * cols, off, own, 1024 * p);
+      load_lds_16(gr + (int64_t)p * 8 * cols, off, own, kSumsG + 1024 * p);
+    }
+    const int64_t grid_row = (int64_t)(g * 32 / block) * t.lc;
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(SX + grid_row)), off_scale, own, kSumsScaleX);
+    load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(SG + grid_row)), off_scale, own, kSumsScaleG);
+    if (lane < 32) {   // 32 floats each
+      load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(mean_in + g * 32)), (uint32_t)lane * 4, own, kSumsMean);
+      load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(rstd_in + g * 32)), (uint32_t)lane * 4, own, kSumsRstd);
+    }
+  };
+  if (AHEAD) request(blockIdx.x);
   float gm[16], cgs[16], cbs[16];
   load16f(gamma + t.col, gm);
 #pragma unroll
   for (int e = 0; e < 16; ++e) cgs[e] = cbs[e] = 0.0f;
+  if (AHEAD) wait_all_loads();
 
   int parity = 0;
   for (int bi = blockIdx.x; bi < nblocks; bi += gridDim.x, parity ^= 1) {
-    const int64_t base = t.base(bi, cols);
     uint4 px[4], pg[4];
-    float mu[4], rs[4];
+    float mu[4], rs[4], sx, sg;
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        px[p] = *reinterpret_cast<const uint4*>(own + 1024 * p + 16 * lane);
+        pg[p] = *reinterpret_cast<const uint4*>(own + kSumsG + 1024 * p + 16 * lane);
+        mu[p] = reinterpret_cast<const float*>(own + kSumsMean)[t.rsub + 8 * p];
+        rs[p] = reinterpret_cast<const float*>(own + kSumsRstd)[t.rsub + 8 * p];
+      }
+      sx = *reinterpret_cast<const float*>(own + kSumsScaleX + 4 * lane);
+      sg = *reinterpret_cast<const float*>(own + kSumsScaleG + 4 * lane);
+      wait_lds();                                        // the strips are in registers: their LDS may be filled again
+      if (bi + (int)gridDim.x < nblocks) request(bi + gridDim.x);
+    } else {
+      const int64_t base = t.base(bi, cols);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        px[p] = *reinterpret_cast<const uint4*>(X + base + (int64_t)p * 8 * cols);
+        pg[p] = *reinterpret_cast<const uint4*>(G + base + (int64_t)p * 8 * cols);
+        mu[p] = mean_in[bi * 32 + t.rsub + 8 * p];
+        rs[p] = rstd_in[bi * 32 + t.rsub + 8 * p];
+      }
+      sx = SX[t.block_index(bi)];
+      sg = SG[t.block_index(bi)];
+    }
+    sg = t.ok ? sg : 0.0f;                               // lanes outside the matrix add nothing to the sums
+    float kx[4], cx[4], m1[4], m2[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      px[p] = *reinterpret_cast<const uint4*>(X + base + p * pass);
-      pg[p] = *reinterpret_cast<const uint4*>(G + base + p * pass);
-      mu[p] = mean_in[bi * 32 + t.rsub + 8 * p];
-      rs[p] = rstd_in[bi * 32 + t.rsub + 8 * p];
+      kx[p] = sx * rs[p];
+      cx[p] = -mu[p] * rs[p];                          // xhat = code kx + cx
+      m1[p] = m2[p] = 0.0f;
     }
-    const float sx = SX[t.block_index(bi)];
-    const float sg = t.ok ? SG[t.block_index(bi)] : 0.0f;   // lanes outside the matrix add nothing to the sums
-    const float g128 = -128.0f * sg;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      float ux[16], ug[16];
-      unpack16_biased(px[p], ux);
-      unpack16_biased(pg[p], ug);
-      const float kx = sx * rs[p], cx0 = __builtin_fmaf(-128.0f, kx, -mu[p] * rs[p]);
-      float m1 = 0.0f, m2 = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float xh = __builtin_fmaf(ux[e], kx, cx0);
-        const float gv = __builtin_fmaf(ug[e], sg, g128);
-        const float gh = gv * gm[e];
-        m1 += gh;
-        m2 = __builtin_fmaf(gh, xh, m2);
-        // the column sums are updated in place, in program order (left to itself the compiler parks them in
-        // scratch memory and keeps the operands of sixteen deferred updates alive instead)
-        asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(cgs[e]) : "v"(gv), "v"(xh));
-        asm volatile("v_add_f32 %0, %0, %1" : "+v"(cbs[e]) : "v"(gv));
-      }
-      m1 = wave_group_sum<7>(m1);
-      m2 = wave_group_sum<7>(m2);
-      if (t.ch == 0) {
-        s_row[parity][t.wave][t.rsub + 8 * p][0] = m1;
-        s_row[parity][t.wave][t.rsub + 8 * p][1] = m2;
-      }
-      __builtin_amdgcn_sched_barrier(0);   // one pass at a time: interleaved passes keep their unpacked values live together
-    }
-    __syncthreads();
-    if (threadIdx.x < 32) {   // row threadIdx.x of the block: the strips in a fixed order
-      float q1 = 0.0f, q2 = 0.0f;
-      for (int w = 0; w < t.nstrips; ++w) {
-        q1 += s_row[parity][w][threadIdx.x][0];
-        q2 += s_row[parity][w][threadIdx.x][1];
-      }
-      // (the share of this workgroup's column range; the second kernel adds the ranges)
-      *reinterpret_cast<float2*>(row_means + 2 * ((int64_t)blockIdx.y * rows + bi * 32 + threadIdx.x)) =
-          make_float2(q1 * inv_cols, q2 * inv_cols);
-    }
-  }
-
-  // column sums over the 8 row lanes of the wave; the lanes of row 0 write the wave's 128 columns of the partial row
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    cgs[e] = wave_group_sum<56>(cgs[e]);
-    cbs[e] = wave_group_sum<56>(cbs[e]);
-  }
-  if (t.ok && t.rsub == 0) {
-    float* dst = partials + (int64_t)blockIdx.x * 2 * cols + t.col;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      *reinterpret_cast<float4*>(dst + 4 * d) = make_float4(cgs[4 * d], cgs[4 * d + 1], cgs[4 * d + 2], cgs[4 * d + 3]);
-      *reinterpret_cast<float4*>(dst + cols + 4 * d) = make_float4(cbs[4 * d], cbs[4 * d + 1], cbs[4 * d + 2], cbs[4 * d + 3]);
+      // g in units of its block scale, which goes onto the sums of the four rows instead of onto every element
+      float tg[4], tb[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        float x[4], gr[4];
+        unpack4(dword_of(px[p], d), x);
+        unpack4(dword_of(pg[p], d), gr);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float xh = __builtin_fmaf(x[e], kx[p], cx[p]), gh = gr[e] * gm[4 * d + e];
+          // the sums are updated in place, in program order (left to itself the compiler keeps the operands of many deferred
+          // updates alive instead)
+          asm volatile("v_add_f32 %0, %0, %1" : "+v"(m1[p]) : "v"(gh));
+          asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(m2[p]) : "v"(gh), "v"(xh));
+          tg[e] = p == 0 ? gr[e] * xh : __builtin_fmaf(gr[e], xh, tg[e]);
+          if (p == 0) tb[e] = gr[e];
+          else asm volatile("v_add_f32 %0, %0, %1" : "+v"(tb[e]) : "v"(gr[e]));
+        }
+        __builtin_amdgcn_sched_barrier(0);             // interleaved passes would keep their unpacked values live together
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(cgs[4 * d + e]) : "v"(sg), "v"(tg[e]));
+        asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(cbs[4 * d + e]) : "v"(sg), "v"(tb[e]));
+      }
     }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      m1[p] = wave_group_sum<7>(m1[p] * sg);
+      m2[p] = wave_group_sum<7>(m2[p] * sg);
+      if (t.ch == 0) *reinterpret_cast<float2*>(s_row + ((parity * t.nstrips + t.wave) * 32 + t.rsub + 8 * p) * 2) = make_float2(m1[p], m2[p]);
+    }
+    lds_barrier();
+    if (AHEAD) wait_all_loads();                         // before the store, see jf_layernorm_rows.hpp
+    // lanes 2 i and 2 i + 1: the two means of row i, the strips in a fixed order (the share of this workgroup's column range; the
+    // second kernel adds the ranges)
+    if (threadIdx.x < 64)
+      row_means[2 * ((int64_t)blockIdx.y * rows + bi * 32) + threadIdx.x] =
+          sum_over_strips(s_row + parity * t.nstrips * 64 + threadIdx.x, t.nstrips) * inv_cols;
+  }
+
+  float sums[8];
+  reduce_rows32(cgs, cbs, sums);
+  if (t.ok && (t.rsub & 1) == 0) {
+    float* dst = partials + (int64_t)blockIdx.x * 2 * cols + t.col - 16 * t.ch + reduced_column(threadIdx.x & 63);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) dst[(j / 4) * cols + 4 * (j % 4)] = sums[j];
   }
 }
 
@@ -321,23 +362,30 @@ __global__ void __launch_bounds__(1024) row_stats_from_partials_kernel(const flo
                                                                         const float* __restrict__ row_sumsq, float eps,
                                                                         int rows, int lc, int cols,
                                                                         float* __restrict__ mean_out, float* __restrict__ rstd_out) {
-  __shared__ double s_part[16][64][2];
+  __shared__ double s_part[2][16][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
   const int row = min((int)blockIdx.x * 64 + lane, rows - 1);   // lanes past the last row repeat it and write nothing
   double s = 0.0, q = 0.0;
-  for (int j = wave; j < lc; j += NW) {
-    s += (double)row_mean[(int64_t)j * rows + row];
-    q += (double)row_sumsq[(int64_t)j * rows + row];
+  for (int j0 = wave; j0 < lc; j0 += 4 * NW) {   // four block columns in flight at a time
+    float m[4], v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t at = (int64_t)min(j0 + k * NW, lc - 1) * rows + row;
+      m[k] = row_mean[at];
+      v[k] = row_sumsq[at];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      s += j0 + k * NW < lc ? (double)m[k] : 0.0;
+      q += j0 + k * NW < lc ? (double)v[k] : 0.0;
+    }
   }
-  s_part[wave][lane][0] = s;
-  s_part[wave][lane][1] = q;
+  s_part[0][wave][lane] = s;
+  s_part[1][wave][lane] = q;
   __syncthreads();
   if (wave != 0 || (int)blockIdx.x * 64 + lane >= rows) return;
-  s = q = 0.0;
-  for (int w = 0; w < NW; ++w) {
-    s += s_part[w][lane][0];
-    q += s_part[w][lane][1];
-  }
+  s = sum_over_strips(&s_part[0][0][lane], NW);
+  q = sum_over_strips(&s_part[1][0][lane], NW);
   const double mu = s / (double)lc;
   const float var = fmaxf((float)(q / (double)cols - mu * mu), 0.0f);
   const float ve = var + eps;
@@ -477,12 +525,22 @@ __global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __res
 // ------------------------------------------------------------------------------------------------ host
 }  // namespace jf
 
+// Strips are shared evenly by the column ranges.  The next row block is requested ahead (AHEAD) where a workgroup takes four or more:
+// 131072 x 1088 at block 64, whole backward pass, 175 -> 165 us, 262144 x 3072 850 -> 815; with one or two the way through LDS costs
+// more than it hides (4096 x 4096 22.0 and 23.1, 32768 x 2048 69.2 and 70.4).
 template <typename... Args>
-static void launch_ln_bwd_sums(int64_t C, dim3 grid, hipStream_t st, Args... args) {
-  const int ns = (int)std::min<int64_t>(16, (C + 127) / 128);   // waves; the last column range may use fewer of them
-  if (ns <= 4) hipLaunchKernelGGL((jf::layernorm_bwd_sums_kernel<4>), grid, dim3(64 * ns), 0, st, args...);
-  else if (ns <= 8) hipLaunchKernelGGL((jf::layernorm_bwd_sums_kernel<8>), grid, dim3(64 * ns), 0, st, args...);
-  else hipLaunchKernelGGL((jf::layernorm_bwd_sums_kernel<16>), grid, dim3(64 * ns), 0, st, args...);
+static void launch_ln_bwd_sums(int64_t N, int64_t C, dim3 grid, hipStream_t st, Args... args) {
+  using namespace jf;
+  const int ns = (int)(((C + 127) / 128 + grid.y - 1) / grid.y);   // waves
+  if (N / 32 < 4 * (int64_t)grid.x) {
+    hipLaunchKernelGGL(layernorm_bwd_sums_kernel<false>, grid, dim3(64 * ns), ns * kSumsRowBytes, st, args...);
+    return;
+  }
+  constexpr int BYTES = kSumsRowBytes + kSumsWaveBytes;
+  static_assert(16 * BYTES <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
+  // (see launch_rows)
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(layernorm_bwd_sums_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 16 * BYTES) != hipSuccess) return;
+  hipLaunchKernelGGL(layernorm_bwd_sums_kernel<true>, grid, dim3(64 * ns), ns * BYTES, st, args...);
 }
 
 // A statistics kernel (from the Add's partials, or from the codes), then the normalisation on tiles.
@@ -581,7 +639,7 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
   // the workspace holds the partial rows, then the two row means of every row (per range of 2048 columns)
   float* row_means = partials + (size_t)nparts * 2 * (size_t)C;
   const int ranges = (int)((C + 2047) / 2048);
-  launch_ln_bwd_sums(C, dim3((unsigned)nparts, (unsigned)ranges), st, dY, SdY, X, SX, gamma, mean, rstd, (int)N, (int)C, (int)block,
+  launch_ln_bwd_sums(N, C, dim3((unsigned)nparts, (unsigned)ranges), st, dY, SdY, X, SX, gamma, mean, rstd, (int)N, (int)C, (int)block,
                      row_means, partials);
   const int32_t rc1 = launch_status();
   if (rc1 != JF_OK) return rc1;

@@ -5,6 +5,28 @@
 
 namespace jf {
 
+// s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8
+__device__ __forceinline__ void wait_all_loads() {
+  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds() {
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
+  asm volatile("" ::: "memory");
+}
+// LDS writes of all waves before, LDS reads after; global loads stay in flight (unlike __syncthreads)
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
+  asm volatile("s_barrier" ::: "memory");
+}
+// a wave's own LDS writes before its own reads
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // exact sums of the 16 codes of a chunk and of their squares
 __device__ __forceinline__ void chunk_moments(const uint4& p, int& s1, int& s2) {
   s1 = __builtin_amdgcn_sdot4((int)p.x, 0x01010101, 0, false);
@@ -16,6 +38,49 @@ __device__ __forceinline__ void chunk_moments(const uint4& p, int& s1, int& s2) 
   s2 = __builtin_amdgcn_sdot4((int)p.z, (int)p.z, s2, false);
   s2 = __builtin_amdgcn_sdot4((int)p.w, (int)p.w, s2, false);
 }
+
+// Signed codes of one packed dword as floats (a byte-select conversion each).
+__device__ __forceinline__ void unpack4(uint32_t w, float (&c)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) c[k] = (float)(int)(int8_t)(w >> (8 * k));
+}
+__device__ __forceinline__ uint32_t dword_of(const uint4& v, int d) { return d == 0 ? v.x : (d == 1 ? v.y : (d == 2 ? v.z : v.w)); }
+
+// v[0] + v[64] + v[128] + ... of the `strips` waves of a team, in that order, four LDS reads in flight at a time (one after
+// the other they are one LDS latency per strip, beside which nothing runs where a workgroup has a single row group).
+template <class T>
+__device__ __forceinline__ T sum_over_strips(const T* v, int strips) {
+  T sum = 0;
+  for (int w = 0; w < strips; w += 4) {
+    T q[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = v[64 * min(w + j, strips - 1)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sum += w + j < strips ? q[j] : (T)0;
+  }
+  return sum;
+}
+
+// Sums over the 8 row lanes of a wave (lane bits 3, 4, 5, in that order) of 16 + 16 values.  The half-row swaps of two values
+// and one addition reduce both: 80 instructions where 32 butterflies take 320, at the end of a workgroup with nothing beside it
+// (with two rows of ghat kept: 8192 x 1280 17.2 -> 15.0 us, 4096 x 768 11.5 -> 10.1, 1056 x 800 7.1 -> 6.5).  Lane (bits 4, 5) ends with values 4 j + bit 4 + 2 (bit 5), j = 0 .. 7, of {a, b}.
+__device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float (&b)[16], float (&out)[8]) {
+  const auto half = [](float x, float y, auto swap) __attribute__((always_inline)) {
+    const auto p = swap(__builtin_bit_cast(int, x), __builtin_bit_cast(int, y));
+    return __builtin_bit_cast(float, (int)p[0]) + __builtin_bit_cast(float, (int)p[1]);
+  };
+  const auto swap16 = [](int x, int y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); };
+  const auto swap32 = [](int x, int y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); };
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = wave_group_sum<8>(j < 4 ? a[4 * j + k] : b[4 * (j - 4) + k]);
+    out[j] = half(half(v[0], v[1], swap16), half(v[2], v[3], swap16), swap32);
+  }
+}
+// Column of the strip whose sums a lane ends with: 4 (j % 4) behind this one, of a for j < 4, of b beyond.
+__device__ __forceinline__ int reduced_column(int lane) { return 16 * (lane & 7) + (((lane >> 4) & 1) | ((lane >> 5) << 1)); }
 
 struct LayerNormRows {
   const int8_t* X;
@@ -68,8 +133,9 @@ int launch_layernorm_bwd_rows_b128(const LayerNormBwdRows& a, bool in_place, hip
 // returns its number of partial rows (at most 256 and at most rows / 32).  Forward not from the row partials of an Add: those say what
 // the first of the two kernels reads the codes for.  A compute unit takes whole row groups: few of them, or a last round that is nearly
 // empty, leave too many idle.  Two kernels -> one in us:
-//   backward   4096 x 4096 (128 groups) 24.6 -> 29.5, 5120 x 2560 (160) 29.1 -> 22.2, 5120 x 4096 34.8 -> 30.6, 8192 x 4096 46.1 -> 35.3,
-//              8256 x 4096 (258) 53.5 -> 55.0, 10240 x 4096 (320) 58.6 -> 56.2, 18432 x 2560 (576) 70.1 -> 56.8, 8192 x 11008 148 -> 99;
+//   backward   4096 x 4096 (128 groups) 23.2 -> 29.5, 5120 x 2560 (160) 24.9 -> 22.2, 5120 x 4096 31.3 -> 31.1, 8192 x 4096 43.8 -> 34.6,
+//              8256 x 4096 (258) 50.3 -> 55.0, 10240 x 4096 (320) 55.4 -> 58.8, 11264 x 3072 (352) 44.0 -> 39.7, 18432 x 2560 (576) 59.3 -> 56.5,
+//              65536 x 3072 223 -> 151, 8192 x 11008 136 -> 98;
 //              beyond kLayerNormWideCols LDS has room for the column sums of few waves only
 //   forward    4096 x 4096 12.8 -> 13.4, 5120 x 2560 11.7 -> 9.9, 8192 x 3072 15.5 -> 12.3, 8256 x 4096 22.4 -> 25.8, 9600 x 4096 (300) 25.3 -> 26.8,
 //              18432 x 2560 27.5 -> 28.6, 20480 x 4096 (640) 43.7 -> 41.3, 22528 x 3072 (704) 36.1 -> 32.3, 25600 x 2560 (800) 36.6 -> 38.9,
@@ -78,7 +144,7 @@ constexpr int kLayerNormWideCols = 11264;
 inline bool layernorm_wide_fits(int64_t N, int64_t C, int32_t block, bool backward) {
   const int64_t groups = N / 32, room = (groups + 255) / 256 * 256;   // row groups of full rounds
   if (block != 32 || C > (backward ? kLayerNormWideCols : 7168) || groups < 160) return false;
-  return room == 256 || (backward ? 8 * groups >= 5 * room : 5 * groups >= 4 * room);
+  return room == 256 || (backward ? 3 * groups >= 2 * room : 5 * groups >= 4 * room);
 }
 void launch_layernorm_wide(LayerNormRows a, hipStream_t st);
 int launch_layernorm_bwd_wide(LayerNormBwdRows a, hipStream_t st);

@@ -24,28 +24,6 @@
 
 namespace jf {
 
-// s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8
-__device__ __forceinline__ void wait_all_loads() {
-  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
-  asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ void wait_lds() {
-  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
-  asm volatile("" ::: "memory");
-}
-// LDS writes of all waves before, LDS reads after; global loads stay in flight (unlike __syncthreads)
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
-  asm volatile("s_barrier" ::: "memory");
-}
-// a wave's own LDS writes before its own reads
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // 16 bytes per lane at a scalar base and a 32-bit lane offset (see store_out, store_as)
 template <StorePolicy SP>
 __device__ __forceinline__ void store_as_at(int8_t* uniform_base, uint32_t off, v4i v) {
@@ -56,28 +34,6 @@ __device__ __forceinline__ void store_as_at(int8_t* uniform_base, uint32_t off, 
   if constexpr (SP == kStoreThrough) __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) v4u*)p, __builtin_bit_cast(v4u, v), "agent");
   else if constexpr (SP == kStoreStream) __builtin_nontemporal_store(v, (gbl_v4i)p);
   else *(gbl_v4i)p = v;
-}
-
-// Signed codes of one packed dword as floats (a byte-select conversion each).
-__device__ __forceinline__ void unpack4(uint32_t w, float (&c)[4]) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) c[k] = (float)(int)(int8_t)(w >> (8 * k));
-}
-__device__ __forceinline__ uint32_t dword_of(const uint4& v, int d) { return d == 0 ? v.x : (d == 1 ? v.y : (d == 2 ? v.z : v.w)); }
-
-// v[0] + v[64] + v[128] + ... of the `strips` waves of a team, in that order, four LDS reads in flight at a time (one after
-// the other they are one LDS latency per strip, beside which nothing runs where a workgroup has a single row group).
-template <class T>
-__device__ __forceinline__ T sum_over_strips(const T* v, int strips) {
-  T sum = 0;
-  for (int w = 0; w < strips; w += 4) {
-    T q[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) q[j] = v[64 * min(w + j, strips - 1)];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) sum += w + j < strips ? q[j] : (T)0;
-  }
-  return sum;
 }
 
 // A wave's place: workgroups hold `teams` teams of `strips` waves; a team owns a group of 32 rows.
@@ -316,25 +272,6 @@ __device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, in
   }
 }
 
-// Sums over the 8 row lanes of a wave (lane bits 3, 4, 5, in that order) of 16 + 16 values.  The half-row swaps of two values
-// and one addition reduce both: 80 instructions where 32 butterflies take 320, at the end of a workgroup with nothing beside it
-// (with two rows of ghat kept: 8192 x 1280 17.2 -> 15.0 us, 4096 x 768 11.5 -> 10.1, 1056 x 800 7.1 -> 6.5).  Lane (bits 4, 5) ends with values 4 j + bit 4 + 2 (bit 5), j = 0 .. 7, of {a, b}.
-__device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float (&b)[16], float (&out)[8]) {
-  const auto half = [](float x, float y, auto swap) __attribute__((always_inline)) {
-    const auto p = swap(__builtin_bit_cast(int, x), __builtin_bit_cast(int, y));
-    return __builtin_bit_cast(float, (int)p[0]) + __builtin_bit_cast(float, (int)p[1]);
-  };
-  const auto swap16 = [](int x, int y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); };
-  const auto swap32 = [](int x, int y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); };
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    float v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = wave_group_sum<8>(j < 4 ? a[4 * j + k] : b[4 * (j - 4) + k]);
-    out[j] = half(half(v[0], v[1], swap16), half(v[2], v[3], swap16), swap32);
-  }
-}
-
 // dx = rstd (ghat - mean_C(ghat) - xhat mean_C(ghat xhat)) with ghat = g gamma, xhat = (x - mean) rstd; the column sums
 // of g xhat and g stay in registers over all row groups and end as one partial row of dgamma | dbeta per workgroup.
 // COLUMNS_APART: the column sums are left to workgroups of their own behind the row_wgs that own rows (column_sums_direct).
@@ -517,8 +454,7 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
   // column sums over the 8 row lanes of the wave, then over the teams through LDS, in a fixed order
   float sums[8];
   reduce_rows32(cgs, cbs, sums);
-  // lane: sum j of column 16 ch + 4 (j % 4) + its place among the four lanes 16 apart; dgamma for j < 4, dbeta beyond
-  const int place = 16 * t.ch + (((t.lane >> 4) & 1) | ((t.lane >> 5) << 1));
+  const int place = reduced_column(t.lane);            // dgamma for j < 4, dbeta beyond
   if (a.teams > 1) {
     float* const mine = reinterpret_cast<float*>(own);   // all requests have landed and nobody else uses this wave's part
 #pragma unroll

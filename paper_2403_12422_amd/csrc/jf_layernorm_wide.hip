@@ -8,7 +8,7 @@
 // below is requested into the same LDS with direct-to-LDS loads, across the passes and across row groups.  As in
 // jf_layernorm_rows.hpp a step waits for all its loads and only then stores, so that no wait includes the stores just made.
 // Two kernels over strips -> this, in us: forward 8192 x 4096 20.6 -> 16.9, 65536 x 3072 91 -> 77, 131072 x 4096 277 -> 225;
-// backward 8192 x 4096 46.1 -> 35.3, 65536 x 3072 240 -> 153, 131072 x 4096 573 -> 405.
+// backward 8192 x 4096 43.8 -> 34.6, 65536 x 3072 223 -> 151.
 #include "jf_layernorm_rows.hpp"
 
 namespace jf {
@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(768) layernorm_bwd_wide_kernel(const LayerNorm
   wait_all_loads();
   wave_lds_fence();
 
-  const int place = 16 * t.ch + (((t.lane >> 4) & 1) | ((t.lane >> 5) << 1));   // see reduce_rows32
+  const int place = reduced_column(t.lane);
   int copy = 0;
   for (int g = blockIdx.x; g < groups; g += gridDim.x, copy ^= 1) {
     uint4 px[4], pg[4];

@@ -11,7 +11,7 @@ from test_gpu_parity import say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,C", [(5120, 2080), (5088, 2080), (8192, 2176), (8224, 2080), (5152, 3104), (5120, 4128), (10240, 2080), (13120, 2112),
+@pytest.mark.parametrize("N,C", [(5120, 2080), (5088, 2080), (8192, 2176), (8224, 2080), (5152, 3104), (5120, 4128), (10240, 2080), (11264, 2080), (13120, 2112),
                                  (16672, 2080), (5120, 7168), (5120, 7200)])
 def test_layernorm_wide_rows(N, C):
     block_rows.test_layernorm_block_rows(32, N, C)
