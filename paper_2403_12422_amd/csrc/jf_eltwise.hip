@@ -5,8 +5,8 @@
 //   * GELU: within one quantization block the input takes at most 255 values (code * block scale), so GELU (or its
 //     derivative) is tabulated once per block in LDS and every element is a table lookup indexed by its code byte -- the
 //     dequantize step of Alg. 2 and the erf evaluation collapse into it;
-//   * one wave per strip of 32 x 128 (64 for small tensors), 64 (32) elements of one block per lane, see jf_rowops.hpp; at block
-//     size 32 no barrier.
+//   * one wave per strip of 32 x 128, 64 elements of one block per lane, see jf_rowops.hpp; at block size 32 no barrier.  A few
+//     million elements give a SIMD a wave or two, whose time is that serial chain: there waves of 16 rows halve it.
 #include "jf_rowops.hpp"
 
 namespace jf {
@@ -54,18 +54,19 @@ __device__ __forceinline__ void gelu_table_entries(float a, float& pos, float& n
 }
 
 template <bool BWD>
+__device__ __forceinline__ void gelu_build_half_table(float* tab, float sx, int i) {
+  float pos, neg;
+  gelu_table_entries<BWD>((float)i * sx, pos, neg);
+  // code 0: GELU(0) = 0 comes out exactly; GELU'(0) = 1/2 is set, because the fit is only good to 4e-7 there and a
+  // derivative of 0.49999997 would push every halved gradient code off its rounding tie.  Entry 128 (code -128,
+  // which no quantizer output holds) is 0.
+  tab[i] = (BWD && i == 0) ? 0.5f : pos;
+  tab[i == 0 ? 128 : 256 - i] = i == 0 ? 0.0f : neg;
+}
+template <bool BWD>
 __device__ __forceinline__ void gelu_build_table(float* tab, float sx, int lane) {
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int i = lane + 64 * h;
-    float pos, neg;
-    gelu_table_entries<BWD>((float)i * sx, pos, neg);
-    // code 0: GELU(0) = 0 comes out exactly; GELU'(0) = 1/2 is set, because the fit is only good to 4e-7 there and a
-    // derivative of 0.49999997 would push every halved gradient code off its rounding tie.  Entry 128 (code -128,
-    // which no quantizer output holds) is 0.
-    tab[i] = (BWD && i == 0) ? 0.5f : pos;
-    tab[i == 0 ? 128 : 256 - i] = i == 0 ? 0.0f : neg;
-  }
+  for (int h = 0; h < 2; ++h) gelu_build_half_table<BWD>(tab, sx, lane + 64 * h);
 }
 
 // Between LDS accesses of one wave, which LDS serves in program order: keeps the compiler from moving one past the other.
@@ -75,17 +76,19 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// GELU forward and backward (BWD: dx = g GELU'(x)) on strips: a table per block and wave.
-template <bool BWD, int B, int WAVES, int COLS, StorePolicy SP>
+// GELU forward and backward (BWD: dx = g GELU'(x)) on strips: a table per block and wave, or, with waves of 16 rows, per block of a
+// strip, built by the waves that share it.
+template <bool BWD, int B, int WAVES, int RW, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX, const int8_t* __restrict__ G,
                                                          const float* __restrict__ SG, int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
-  constexpr int NBC = COLS / B;   // blocks of a strip
-  __shared__ float s_tabs[WAVES][NBC][256];
-  __shared__ float s_amax[WAVES][2];
-  const Strip<B, WAVES, COLS> t(rows, cols);
-  constexpr int P = Strip<B, WAVES, COLS>::PASSES;
-  if (B == 32 && !t.inside) return;   // a whole wave; there is no workgroup barrier
-  const int64_t pass = (int64_t)t.ROWS * cols;
+  constexpr int NBC = 128 / B;   // blocks of a strip
+  constexpr int SHARED = RW < 32 ? Strip<B, WAVES, RW>::BT : 1;   // waves that share a strip's tables
+  __shared__ float s_tabs[WAVES / SHARED][NBC][256];
+  __shared__ float s_amax[WAVES][4];
+  const Strip<B, WAVES, RW> t(rows, cols);
+  constexpr int P = Strip<B, WAVES, RW>::PASSES;
+  if (t.BT == 1 && !t.inside) return;   // a whole wave; there is no workgroup barrier
+  const int64_t pass = (int64_t)8 * cols;
   uint4 px[P], pg[BWD ? P : 1];   // requested first: their latency runs beside the table build
 #pragma unroll
   for (int p = 0; p < P; ++p) {
@@ -97,11 +100,20 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
   typedef const __attribute__((address_space(4))) float* const_f32_ptr;
   const const_f32_ptr sx_row = (const_f32_ptr)SX + (int64_t)(t.bi / t.BT) * t.lc + t.c0 / B;
   const int nblk = min(NBC, t.lc - t.c0 / B);
+  if constexpr (SHARED == 1) {
 #pragma unroll
-  for (int k = 0; k < NBC; ++k)
-    if (k < nblk) gelu_build_table<BWD>(s_tabs[t.wave][k], sx_row[k], t.lane);
-  wave_lds_order();
-  const float* const tab = s_tabs[t.wave][t.ch / (B / 16)];   // lanes outside the matrix may read a table nobody built: see Strip::base
+    for (int k = 0; k < NBC; ++k)
+      if (k < nblk) gelu_build_table<BWD>(s_tabs[t.wave][k], sx_row[k], t.lane);
+    wave_lds_order();
+  } else {   // half a table at a time, in turn
+#pragma unroll
+    for (int u = 0; u < 2 * NBC; u += SHARED) {
+      const int h = u + t.wave % SHARED;
+      if (h < 2 * nblk) gelu_build_half_table<BWD>(s_tabs[t.wave / SHARED][h / 2], sx_row[h / 2], t.lane + 64 * (h & 1));
+    }
+    __syncthreads();
+  }
+  const float* const tab = s_tabs[t.wave / SHARED][t.ch / (B / 16)];   // lanes outside the matrix may read a table nobody built: see Strip::base
   float sg = 0.0f, sg128 = 0.0f;
   if (BWD) {
     sg = SG[t.block_index()];
@@ -136,79 +148,6 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
   for (int p = 0; p < P; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
-// The same for block size 64 and results that are written through but not small, with one quantization block per WAVE: no workgroup
-// barrier and no LDS exchange between waves, so the four waves of a workgroup (four neighbouring block columns)
-// run independently and one wave's table build overlaps its neighbours' loads and stores (8192 x 1280 backward 7.3 us, on
-// strips 7.9; 4096 x 3072 8.0 and 8.7; from HBM its 64-byte row pieces cost a third of the bandwidth).  Lane = (row l / CPR,
-// 16-byte chunk l % CPR) with CPR = B/16 chunks per block row, in B*CPR/64 passes; the four waves of a workgroup
-// read neighbouring 32- or 64-byte pieces of the same memory lines.
-template <bool BWD, StorePolicy SP>
-__global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
-                                                         const int8_t* __restrict__ G, const float* __restrict__ SG,
-                                                         int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
-  constexpr int B = 64, CPR = B / 16, RPP = 64 / CPR, P = B / RPP;  // chunks per block row, rows per pass, passes
-  __shared__ float s_tab[4][256];  // one table per wave, indexed by the code byte taken as unsigned
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lc = cols / B;
-  const TileIndex wg = tile_of_workgroup((lc + 3) / 4);
-  const int bi = wg.y, bj = wg.x * 4 + wave;
-  if (bj >= lc) return;  // wave-uniform; the kernel has no workgroup barrier
-  const int ch = lane % CPR, rsub = lane / CPR;
-  const int64_t base = (int64_t)(bi * B + rsub) * cols + bj * B + 16 * ch;
-
-  // codes first: their latency runs beside the table build
-  uint4 px[P], pg[BWD ? P : 1];
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    px[p] = *reinterpret_cast<const uint4*>(X + base + (int64_t)p * RPP * cols);
-    if (BWD) pg[p] = *reinterpret_cast<const uint4*>(G + base + (int64_t)p * RPP * cols);
-  }
-
-  // the block's scales through the scalar cache
-  typedef const __attribute__((address_space(4))) float* const_f32_ptr;
-  float* const tab = s_tab[wave];
-  gelu_build_table<BWD>(tab, ((const_f32_ptr)SX)[(int64_t)bi * lc + bj], lane);
-  wave_lds_order();
-
-  float sg = 0.0f, sg128 = 0.0f;
-  if (BWD) {
-    sg = ((const_f32_ptr)SG)[(int64_t)bi * lc + bj];
-    sg128 = -128.0f * sg;
-  }
-  float y[P][16];
-  float m = 0.0f;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const uint32_t w[4] = {px[p].x, px[p].y, px[p].z, px[p].w};
-    float f[16];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      f[4 * d + 0] = tab[w[d] & 0xffu];
-      f[4 * d + 1] = tab[(w[d] >> 8) & 0xffu];
-      f[4 * d + 2] = tab[(w[d] >> 16) & 0xffu];
-      f[4 * d + 3] = tab[w[d] >> 24];
-    }
-    if (BWD) {
-      float ug[16];
-      unpack16_biased(pg[p], ug);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) y[p][e] = __builtin_fmaf(ug[e], sg, sg128) * f[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) y[p][e] = f[e];
-    }
-    m = amax16(m, y[p]);
-  }
-  m = wave_group_max<63>(m);
-  float scale;
-  double inv;
-  block_scale(m, scale, inv);
-  if (lane == 0) store_scale<SP>(&SY[(int64_t)bi * lc + bj], scale);
-#pragma unroll
-  for (int p = 0; p < P; ++p) store_as<SP>(Y + base + (int64_t)p * RPP * cols, quantize16(y[p], inv));
-}
-
 // ------------------------------------------------------------------------------------------------
 // Add (App. A): y = x1 + x2 on the dequantized operands, re-quantized per block (Alg. 2), and optionally
 // the row partials that App. A's LayerNorm paragraph attaches to this operator: for every row and block
@@ -217,16 +156,16 @@ __global__ void __launch_bounds__(256) gelu_wave_kernel(const int8_t* __restrict
 // codes' policy, since a wave has whole lines of them at block sizes 64 and 128 only (streamed in pieces, 1048576 x 768 at
 // block 32 took 653 us, written through 543, back 472), and each lane stores those of another pass: two or four stores per
 // strip for eight of a few lanes each (8192 x 1280 7.6 -> 7.3 us, 1048576 x 768 469 -> 447; at block 128 7.5 -> 7.4, 468 -> 409).
-template <int B, int WAVES, int COLS, bool PARTIALS, StorePolicy SP>
+template <int B, int WAVES, int RW, bool PARTIALS, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) add_kernel(const int8_t* __restrict__ X1, const float* __restrict__ S1,
                                                               const int8_t* __restrict__ X2, const float* __restrict__ S2, int rows, int cols,
                                                               int8_t* __restrict__ Y, float* __restrict__ SY, float* __restrict__ row_mean,
                                                               float* __restrict__ row_sumsq) {
-  __shared__ float s_amax[WAVES][2];
-  const Strip<B, WAVES, COLS> t(rows, cols);
-  constexpr int P = Strip<B, WAVES, COLS>::PASSES;
-  if (B == 32 && !t.inside) return;   // a whole wave; there is no workgroup barrier
-  const int64_t pass = (int64_t)t.ROWS * cols;
+  __shared__ float s_amax[WAVES][4];
+  const Strip<B, WAVES, RW> t(rows, cols);
+  constexpr int P = Strip<B, WAVES, RW>::PASSES;
+  if (t.BT == 1 && !t.inside) return;   // a whole wave; there is no workgroup barrier
+  const int64_t pass = (int64_t)8 * cols;
   float y[P][16], ps[P], pq[P];
   float m = 0.0f;
   uint4 p1[P], p2[P];
@@ -252,33 +191,32 @@ __global__ void __launch_bounds__(64 * WAVES) add_kernel(const int8_t* __restric
         ps[p] += y[p][e];
         pq[p] = __builtin_fmaf(y[p][e], y[p][e], pq[p]);
       }
-      ps[p] = wave_group_sum<Strip<B, WAVES, COLS>::BLOCK_CHUNK_LANES>(ps[p]) * (1.0f / (float)B);
-      pq[p] = wave_group_sum<Strip<B, WAVES, COLS>::BLOCK_CHUNK_LANES>(pq[p]);
+      ps[p] = wave_group_sum<B / 16 - 1>(ps[p]) * (1.0f / (float)B);
+      pq[p] = wave_group_sum<B / 16 - 1>(pq[p]);
     }
   }
   if (PARTIALS && t.ok) {
     // Block-column-major: the 32 rows of the strip are one 128-byte line per block column.  All lanes of a block hold its sums
     // of the four passes; each stores those of another pass.
-    float* const mean = row_mean + (int64_t)(t.col / B) * rows + t.bi * 32 + t.rsub;
-    float* const sumsq = row_sumsq + (int64_t)(t.col / B) * rows + t.bi * 32 + t.rsub;
+    float* const mean = row_mean + (int64_t)(t.col / B) * rows + t.bi * RW + t.rsub;
+    float* const sumsq = row_sumsq + (int64_t)(t.col / B) * rows + t.bi * RW + t.rsub;
     const auto pick = [](bool second, float a, float b) { return second ? b : a; };   // (by value: of references it would be an address)
-    const int p = t.ch & (P - 1);
+    const int k = t.ch & (B / 16 - 1), p = k & (P - 1);
     const auto of_pass = [&](const float(&v)[P]) {
       if constexpr (P == 4) return pick(p & 2, pick(p & 1, v[0], v[1]), pick(p & 1, v[2], v[3]));
-      else return pick(p, v[0], v[P - 1]);
+      else return pick(p, v[0], v[1]);
     };
     if constexpr (B == 32) {
-      const int odd = t.ch & 1;
 #pragma unroll
       for (int i = 0; i < P; i += 2) {
-        store_part(&mean[t.ROWS * (i + odd)], pick(odd, ps[i], ps[i + 1]));
-        store_part(&sumsq[t.ROWS * (i + odd)], pick(odd, pq[i], pq[i + 1]));
+        store_part(&mean[8 * (i + k)], pick(k, ps[i], ps[i + 1]));
+        store_part(&sumsq[8 * (i + k)], pick(k, pq[i], pq[i + 1]));
       }
-    } else if constexpr (B == 64 && P == 4) {
+    } else if constexpr (B / 16 < 2 * P) {
       store_part(&mean[8 * p], of_pass(ps));
       store_part(&sumsq[8 * p], of_pass(pq));
-    } else {
-      store_part((t.ch < P ? mean : sumsq) + t.ROWS * p, pick(t.ch < P, of_pass(pq), of_pass(ps)));
+    } else if (k < 2 * P) {
+      store_part((k < P ? mean : sumsq) + 8 * p, pick(k < P, of_pass(pq), of_pass(ps)));
     }
   }
   float scale;
@@ -304,28 +242,29 @@ __device__ __forceinline__ uint32_t keep_bytes(uint32_t nibble) {
 // columns per byte (bit c % 8 of byte c / 8 of a row).  The backward pass is the same operator on the upstream gradient.
 // Dropped codes are cleared in the packed dwords (a code of 0 dequantizes to exactly 0), so the mask costs a few integer
 // instructions per four elements and none per element.
-template <int B, int WAVES, StorePolicy SP>
+template <int B, int WAVES, int RW, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                                   const uint8_t* __restrict__ mask, float keep_scale, int rows, int cols,
                                                                   int8_t* __restrict__ Y, float* __restrict__ SY) {
-  __shared__ float s_amax[WAVES][2];
-  const Strip<B, WAVES> t(rows, cols);
-  if (B == 32 && !t.inside) return;   // a whole wave; there is no workgroup barrier
+  __shared__ float s_amax[WAVES][4];
+  const Strip<B, WAVES, RW> t(rows, cols);
+  constexpr int P = Strip<B, WAVES, RW>::PASSES;
+  if (t.BT == 1 && !t.inside) return;   // a whole wave; there is no workgroup barrier
   const int64_t pass = (int64_t)8 * cols;
-  float y[4][16];
+  float y[P][16];
   float m = 0.0f;
-  uint4 px[4];
-  uint32_t bits[4];
+  uint4 px[P];
+  uint32_t bits[P];
   const int64_t mbase = t.base >> 3;   // row * (cols / 8) + column / 8: cols is a multiple of 32, the column of 16
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < P; ++p) {
     px[p] = *reinterpret_cast<const uint4*>(X + t.base + p * pass);
     bits[p] = *reinterpret_cast<const uint16_t*>(mask + mbase + (int64_t)p * cols);   // 8 rows further: 8 * cols / 8 bytes
   }
   const float k = SX[t.block_index()] * keep_scale;
   const float k128 = -128.0f * k;  // the unpacked codes carry +128
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < P; ++p) {
     uint4 c = px[p];
     c.x &= keep_bytes(bits[p] & 15u);
     c.y &= keep_bytes((bits[p] >> 4) & 15u);
@@ -343,33 +282,40 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
   if (!t.ok) return;
   if (t.owns_scale()) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < P; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
 }
 
 // ------------------------------------------------------------------------------------------------ host
-// Whether an operator at block size 32 or 64 takes strips of 64 columns: half the serial chain of a wave (two tables instead of
-// four) on twice the waves, against 64-byte row pieces.  Kernel times in us on operands that are not in L2, 128 -> 64 columns:
-//   GELU           256 x 256 4.0 -> 3.3, 1056 x 2080 4.8 -> 4.1, 8192 x 1280 7.2 -> 6.4, 4096 x 3072 7.4 -> 6.6, 8192 x 4096 13.8 -> 12.9,
-//                  16384 x 2880 20.4 -> 21.4; block 64 (wave kernel) 1024 x 768 4.0 -> 3.4, 8192 x 1280 6.9 -> 6.2, 8192 x 2048 7.8 -> 7.9
-//   GELU backward  1056 x 2080 5.1 -> 4.6, 8192 x 1280 8.7 -> 7.8, 8192 x 3072 14.2 -> 13.9, 8192 x 4096 16.9 -> 17.5; block 64 1024 x 768
-//                  4.5 -> 3.7, 8192 x 1280 8.0 -> 7.6, 4096 x 3072 8.7 -> 8.8
-//   Add            1056 x 800 4.0 -> 3.6, 8192 x 1280 7.1 -> 6.9, 8192 x 2048 8.9 -> 9.7; with partials 4.8 -> 4.3, 8.0 -> 7.6, 9.6 -> 11.0
-//   Dropout        has nothing but its loads and the rounding: 4096 x 768 3.5 -> 3.7, 16384 x 1280 8.4 -> 9.5; always 128.
-static bool narrow_gelu(bool backward, int block, int64_t rows, int64_t cols) {
-  return rows * cols <= (int64_t)(block == 64 ? (backward ? 10 : 12) : (backward ? 24 : 32)) << 20;
+// Whether an operator takes waves of 16 rows (for results that are written through).  Kernel times in us with 32 -> 16 rows, operands
+// and results in no cache; in the last-level cache:
+//   GELU           block 32   256 x 256 3.8 -> 3.4; 3.9 -> 3.4   1056 x 2080 4.8 -> 4.4; 4.6 -> 4.1   8192 x 1280 7.2 -> 6.2; 7.0 -> 6.2
+//                             4096 x 3072 7.4 -> 7.4; 7.2 -> 6.9   8192 x 2048 8.0 -> 9.7; 8.4 -> 8.2
+//                  block 128  1024 x 768 4.1 -> 4.2; 3.7 -> 3.8   16384 x 1280 10.5 -> 11.0; 8.8 -> 9.3: two tables' halves for eight waves
+//   GELU backward  block 32   1056 x 800 4.8 -> 4.0; 4.8 -> 3.8   4096 x 1280 6.8 -> 6.0; 6.5 -> 5.6   4096 x 3072 10.0 -> 9.8; 9.1 -> 8.7
+//                             8192 x 1280 9.2 -> 9.6; 8.7 -> 8.1   8192 x 4096 20.8 -> 21.5; 17.5 -> 18.0
+//                  block 128  2048 x 2048 5.2 -> 5.0; 5.0 -> 4.8   8192 x 2048 14.1 -> 13.1; 10.8 -> 9.7   16384 x 1280 14.5 -> 14.4; 12.0 -> 12.6
+//   at block 64 (from one block of 64 x 64 per wave) all sizes: 1024 x 768 4.3 -> 3.5; 4.2 -> 3.4, backward 4.6 -> 3.6; 4.3 -> 3.4
+//                             8192 x 1280 8.6 -> 6.3; 6.9 -> 6.1, 10.8 -> 9.4; 8.3 -> 7.6   8192 x 5120 23.3 -> 20.4; 15.0 -> 14.3, 32.2 -> 28.9; 23.6 -> 21.8
+//   Add            block 32   1056 x 800 4.5 -> 3.8; 3.8 -> 3.3   8192 x 1280 8.7 -> 8.1; 7.2 -> 6.8, with partials 9.7 -> 8.9; 8.1 -> 7.5
+//                             8192 x 2048 11.4 -> 11.6; 9.1 -> 9.4, 12.6 -> 12.7; 9.8 -> 10.3
+//                  block 64   1024 x 768 4.4 -> 3.6; 3.9 -> 3.2   4096 x 3072 10.2 -> 9.7; 7.9 -> 7.6   8192 x 4096 21.1 -> 22.1; 17.0 -> 16.8
+//                  block 128  1024 x 768 4.5 -> 4.0; 4.0 -> 3.6   8192 x 4096 22.7 -> 21.8; 16.9 -> 16.7, with partials 23.7 -> 22.7; 18.6 -> 17.6
+//   Dropout        block 32   2048 x 1024 3.8 -> 3.6; 3.4 -> 3.1   1056 x 2080 4.3 -> 4.2; 3.6 -> 3.7   16384 x 1280 10.2 -> 10.6; 8.0 -> 8.9
+//                  block 128  1024 x 768 3.8 -> 3.9; 3.6 -> 3.5
+static bool low_gelu(bool backward, int block, int64_t rows, int64_t cols) {
+  if (block == 128) return backward && rows * cols <= 16 << 20;
+  return block == 64 || rows * cols <= 12 << 20;
 }
-static bool narrow_add(int64_t rows, int64_t cols) { return rows * cols <= 10 << 20; }
+static bool low_add(int block, int64_t rows, int64_t cols) { return rows * cols <= (block == 128 ? 32 : 12) << 20; }
+static bool low_dropout(int block, int64_t rows, int64_t cols) { return block <= 64 && rows * cols <= 2 << 20; }
 
 template <bool BWD>
 static void launch_gelu(int block, const int8_t* X, const float* SX, const int8_t* G, const float* SG, int rows, int cols, int8_t* Y, float* SY,
                         hipStream_t st) {
-  with_instance(block, rows, cols, narrow_gelu(BWD, block, rows, cols), [&](auto b, auto w, auto c, auto sp) {
-    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, COLS = decltype(c)::value;
+  with_instance(block, rows, cols, low_gelu(BWD, block, rows, cols), [&](auto b, auto w, auto r, auto sp) {
+    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, RW = decltype(r)::value;
     constexpr StorePolicy SP = decltype(sp)::value;
-    if constexpr (B == 64 && SP == kStoreThrough && COLS == 128)
-      hipLaunchKernelGGL((gelu_wave_kernel<BWD, SP>), dim3(tile_grid((cols + 255) / 256, rows / 64)), dim3(256), 0, st, X, SX, G, SG, rows, cols, Y, SY);
-    else
-      hipLaunchKernelGGL((gelu_kernel<BWD, B, WAVES, COLS, SP>), (strip_grid<B, WAVES, COLS>(rows, cols)), dim3(64 * WAVES), 0, st, X, SX, G, SG, rows, cols, Y, SY);
+    hipLaunchKernelGGL((gelu_kernel<BWD, B, WAVES, RW, SP>), (strip_grid<B, WAVES, RW>(rows, cols)), dim3(64 * WAVES), 0, st, X, SX, G, SG, rows, cols, Y, SY);
   });
 }
 
@@ -405,9 +351,9 @@ extern "C" int32_t jf_dropout_q(const int8_t* X, const float* SX, const uint8_t*
   if (reinterpret_cast<uintptr_t>(mask_bits) & 1u) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const float keep_scale = (float)(1.0 / (1.0 - (double)p));
-  with_instance(block, N, C, [&](auto b, auto w, auto sp) {
-    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value;
-    hipLaunchKernelGGL((dropout_kernel<B, WAVES, decltype(sp)::value>), (strip_grid<B, WAVES>(N, C)), dim3(64 * WAVES), 0, st, X, SX, mask_bits,
+  with_instance(block, N, C, low_dropout(block, N, C), [&](auto b, auto w, auto r, auto sp) {
+    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, RW = decltype(r)::value;
+    hipLaunchKernelGGL((dropout_kernel<B, WAVES, RW, decltype(sp)::value>), (strip_grid<B, WAVES, RW>(N, C)), dim3(64 * WAVES), 0, st, X, SX, mask_bits,
                        keep_scale, (int)N, (int)C, Y, SY);
   });
   return launch_status();
@@ -422,14 +368,14 @@ extern "C" int32_t jf_add_q(const int8_t* X1, const float* S1, const int8_t* X2,
   if ((row_mean == nullptr) != (row_sumsq == nullptr)) return JF_ERR_NULL;
   if (!aligned16(X2) || !aligned4(S2) || (row_mean && (!aligned4(row_mean) || !aligned4(row_sumsq)))) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  with_instance(block, N, C, narrow_add(N, C), [&](auto b, auto w, auto c, auto sp) {
-    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, COLS = decltype(c)::value;
+  with_instance(block, N, C, low_add(block, N, C), [&](auto b, auto w, auto r, auto sp) {
+    constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, RW = decltype(r)::value;
     constexpr StorePolicy SP = decltype(sp)::value;
     const auto launch = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, (strip_grid<B, WAVES, COLS>(N, C)), dim3(64 * WAVES), 0, st, X1, S1, X2, S2, (int)N, (int)C, Y, SY, row_mean, row_sumsq);
+      hipLaunchKernelGGL(kernel, (strip_grid<B, WAVES, RW>(N, C)), dim3(64 * WAVES), 0, st, X1, S1, X2, S2, (int)N, (int)C, Y, SY, row_mean, row_sumsq);
     };
-    if (row_mean) launch(add_kernel<B, WAVES, COLS, true, SP>);
-    else launch(add_kernel<B, WAVES, COLS, false, SP>);
+    if (row_mean) launch(add_kernel<B, WAVES, RW, true, SP>);
+    else launch(add_kernel<B, WAVES, RW, false, SP>);
   });
   return launch_status();
 }

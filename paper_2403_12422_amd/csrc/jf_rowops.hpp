@@ -35,7 +35,9 @@ __device__ __forceinline__ void unpack16_biased(const uint4& p, float (&u)[16]) 
 // exchanged between waves, no barrier.  At block sizes 64 and 128 two or four waves of a workgroup stand one above the other
 // and exchange it through LDS.  Per element the kernels spend what Alg. 2 needs (unpack, the operator, max-abs, Eq. 1) and
 // little else; the per-lane overhead is paid once per 64 elements.
-// For small tensors a strip is 64 columns wide, in two passes of 16 rows (block sizes 32 and 64).
+// RW = 16: waves of 16 rows, twice as many one above the other (block size 32 exchanges its max-abs like the others then): half the
+// serial chain of a wave, and still whole lines.  (Strips of 64 columns and 32 rows do as well while everything is in a cache, but their
+// 64-byte pieces cost a third of the memory's bandwidth: GELU 8192 x 2048 8.0 -> 11.1 us from memory, 8.4 -> 7.7 from the cache.)
 // Waves per workgroup: at block size 32 four neighbouring strips of the same rows, so that 512 contiguous bytes of every row
 // are requested close together in time (on 0.8 GB tensors of 3072 columns 5.4-5.7 TB/s instead of 4.4-5.0 with one strip per
 // workgroup); two by two at 64 and one above the other at 128, and twice as wide for results that go to memory (262144 x
@@ -43,15 +45,12 @@ __device__ __forceinline__ void unpack16_biased(const uint4& p, float (&u)[16]) 
 // 6.7 and 7.2, GELU backward at 128 7.7 and 8.7).
 constexpr int kStripWaves = 4;
 constexpr int strip_waves(int block, StorePolicy sp) { return block == 32 || sp == kStoreThrough ? 4 : 8; }
-template <int B, int WAVES = kStripWaves, int COLS = 128>
+template <int B, int WAVES = kStripWaves, int RW = 32>
 struct Strip {
-  static constexpr int BT = B / 32;   // waves that share a block
-  static constexpr int LANES = COLS / 16, ROWS = 64 / LANES, PASSES = 32 / ROWS;   // lanes of a row, rows of a pass
-  // lane id bits: chunk column (of 64 columns: bits 0 and 3, so that the lanes of a block of 32 share bits 0 to 2)
-  static constexpr int CHUNK_LANES = LANES == 4 ? 9 : LANES - 1, BLOCK_CHUNK_LANES = LANES == 4 && B == 64 ? 9 : B / 16 - 1;
-  static constexpr int BLOCK_LANES = (63 & ~CHUNK_LANES) | BLOCK_CHUNK_LANES;      // bits in which the lanes of a block differ
+  static constexpr int BT = B / RW;        // waves that share a block
+  static constexpr int PASSES = RW / 8;    // passes of eight rows
   int ch, rsub;     // chunk column and row of the lane inside an 8-row pass
-  int bi, lc;       // 32-row group of the strip, block columns of the matrix
+  int bi, lc;       // RW-row group of the strip, block columns of the matrix
   int c0, col;      // first column of the strip, first column of the lane's chunks
   bool ok;          // the lane's chunks lie inside the matrix (cols % 32 == 0: a block is all in or all out)
   int64_t base;     // element offset of the lane's chunk in pass 0; pass p adds 8 p cols.  Lanes outside the matrix
@@ -62,23 +61,23 @@ struct Strip {
   __device__ __forceinline__ Strip(int rows, int cols, unsigned first = 0) {   // first: workgroups before the strips
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    ch = LANES == 4 ? (lane & 1) | ((lane >> 2) & 2) : lane & (LANES - 1);
-    rsub = LANES == 4 ? ((lane >> 1) & 3) | ((lane >> 2) & 12) : lane / LANES;
-    const unsigned groups = (unsigned)((cols + COLS - 1) / COLS), strips = groups * (unsigned)(rows / B);
+    ch = lane & 7;
+    rsub = lane >> 3;
+    const unsigned groups = (unsigned)((cols + 127) / 128), strips = groups * (unsigned)(rows / B);
     const unsigned id = (blockIdx.x - first) * (WAVES / BT) + wave / BT;   // numbered column group fastest
     inside = id < strips;
     const unsigned sid = inside ? id : strips - 1;
-    c0 = (int)(sid % groups) * COLS;
+    c0 = (int)(sid % groups) * 128;
     bi = (int)(sid / groups) * BT + wave % BT;
     lc = cols / B;
     col = c0 + 16 * ch;
     ok = col < cols;
-    base = (int64_t)(bi * 32 + rsub) * cols + (ok ? col : c0);
+    base = (int64_t)(bi * RW + rsub) * cols + (ok ? col : c0);
     ok = ok && inside;
   }
   // index of the lane's block in a scale grid (clamped like base), and whether the lane is the one to store its scale
   __device__ __forceinline__ int64_t block_index() const { return (int64_t)(bi / BT) * lc + (col < lc * B ? col : c0) / B; }
-  __device__ __forceinline__ bool owns_scale() const { return (lane & BLOCK_LANES) == 0 && (BT == 1 || wave % BT == 0); }
+  __device__ __forceinline__ bool owns_scale() const { return (lane & (56 | (B / 16 - 1))) == 0 && (BT == 1 || wave % BT == 0); }
 };
 
 typedef Strip<32> Strip32;
@@ -92,12 +91,12 @@ __device__ __forceinline__ float amax16(float m, const float (&y)[16]) {
 }
 
 // Block max-abs, over the lanes of a strip that share a block column and over the waves that share the block through `exchange`
-// (two values per wave), then Eq. 1's scale.  At block sizes 64 and 128 every wave of the workgroup has to get here.
-template <int B, int WAVES, int COLS>
-__device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES, COLS>& t, float (*exchange)[2], float& scale, double& inv) {
-  m = wave_group_max<Strip<B, WAVES, COLS>::BLOCK_LANES>(m);
-  if constexpr (B > 32) {
-    if ((t.lane & t.BLOCK_LANES) == 0) exchange[t.wave][t.ch / (B / 16)] = m;
+// (up to four values per wave), then Eq. 1's scale.  At block sizes 64 and 128 every wave of the workgroup has to get here.
+template <int B, int WAVES, int RW>
+__device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES, RW>& t, float (*exchange)[4], float& scale, double& inv) {
+  m = wave_group_max<56 | (B / 16 - 1)>(m);
+  if constexpr (B > RW) {
+    if ((t.lane & (56 | (B / 16 - 1))) == 0) exchange[t.wave][t.ch / (B / 16)] = m;
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < t.BT; ++k) m = fmaxf(m, exchange[t.wave / t.BT * t.BT + k][t.ch / (B / 16)]);
@@ -117,9 +116,9 @@ __device__ __forceinline__ void load16f(const float* p, float (&v)[16]) {
 
 // ------------------------------------------------------------------------------------------------ host
 // workgroups of the strip kernels: WAVES strips of 32 rows each
-template <int B = 32, int WAVES = kStripWaves, int COLS = 128>
+template <int B = 32, int WAVES = kStripWaves, int RW = 32>
 static inline dim3 strip_grid(int64_t rows, int64_t cols) {
-  const int64_t strips = ((cols + COLS - 1) / COLS) * (rows / B), per_wg = WAVES * 32 / B;
+  const int64_t strips = ((cols + 127) / 128) * (rows / B), per_wg = WAVES * RW / B;
   return dim3((unsigned)((strips + per_wg - 1) / per_wg));
 }
 // f(integral_constant<int, B>) for a block size
@@ -130,23 +129,18 @@ static inline void with_block(int block, F&& f) {
   else f(std::integral_constant<int, 128>());
 }
 
-// f(block size, waves per workgroup, store policy) as integral constants
+// f(block size, waves per workgroup, rows of a wave, store policy) as integral constants: 16 rows instead of 32 if `low`, for results
+// that are written through
 template <class F>
-static void with_instance(int block, int64_t rows, int64_t cols, F&& f) {
+static void with_instance(int block, int64_t rows, int64_t cols, bool low, F&& f) {
   with_block(block, [&](auto b) {
     with_store_policy(rows, cols, [&](auto sp) {
-      f(b, std::integral_constant<int, strip_waves(decltype(b)::value, decltype(sp)::value)>(), sp);
+      constexpr int B = decltype(b)::value;
+      constexpr StorePolicy SP = decltype(sp)::value;
+      if constexpr (SP == kStoreThrough)
+        if (low) return f(b, std::integral_constant<int, B == 128 ? 8 : 4>(), std::integral_constant<int, 16>(), sp);
+      f(b, std::integral_constant<int, strip_waves(B, SP)>(), std::integral_constant<int, 32>(), sp);
     });
-  });
-}
-// f(block size, waves per workgroup, columns of a strip, store policy): 64 columns instead of 128 if `narrow`, at block sizes 32
-// and 64 and for results that are written through
-template <class F>
-static void with_instance(int block, int64_t rows, int64_t cols, bool narrow, F&& f) {
-  with_instance(block, rows, cols, [&](auto b, auto w, auto sp) {
-    if constexpr (decltype(b)::value <= 64 && decltype(sp)::value == kStoreThrough)
-      if (narrow) return f(b, w, std::integral_constant<int, 64>(), sp);
-    f(b, w, std::integral_constant<int, 128>(), sp);
   });
 }
 
