@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
 //   at block 64 (from one block of 64 x 64 per wave) all sizes: 1024 x 768 4.3 -> 3.5; 4.2 -> 3.4, backward 4.6 -> 3.6; 4.3 -> 3.4
 //                             8192 x 1280 8.6 -> 6.3; 6.9 -> 6.1, 10.8 -> 9.4; 8.3 -> 7.6   8192 x 5120 23.3 -> 20.4; 15.0 -> 14.3, 32.2 -> 28.9; 23.6 -> 21.8
 //   Add            block 32   1056 x 800 4.5 -> 3.8; 3.8 -> 3.3   8192 x 1280 8.7 -> 8.1; 7.2 -> 6.8, with partials 9.7 -> 8.9; 8.1 -> 7.5
-//                             8192 x 2048 11.4 -> 11.6; 9.1 -> 9.4, 12.6 -> 12.7; 9.8 -> 10.3
+//                             4096 x 3072 9.4 -> 9.3; 7.7 -> 7.7 (from L2 5.6 -> 6.2), 8192 x 2048 11.4 -> 11.6; 9.1 -> 9.4
 //                  block 64   1024 x 768 4.4 -> 3.6; 3.9 -> 3.2   4096 x 3072 10.2 -> 9.7; 7.9 -> 7.6   8192 x 4096 21.1 -> 22.1; 17.0 -> 16.8
 //                  block 128  1024 x 768 4.5 -> 4.0; 4.0 -> 3.6   8192 x 4096 22.7 -> 21.8; 16.9 -> 16.7, with partials 23.7 -> 22.7; 18.6 -> 17.6
 //   Dropout        block 32   2048 x 1024 3.8 -> 3.6; 3.4 -> 3.1   1056 x 2080 4.3 -> 4.2; 3.6 -> 3.7   16384 x 1280 10.2 -> 10.6; 8.0 -> 8.9
@@ -306,7 +306,7 @@ static bool low_gelu(bool backward, int block, int64_t rows, int64_t cols) {
   if (block == 128) return backward && rows * cols <= 16 << 20;
   return block == 64 || rows * cols <= 12 << 20;
 }
-static bool low_add(int block, int64_t rows, int64_t cols) { return rows * cols <= (block == 128 ? 32 : 12) << 20; }
+static bool low_add(int block, int64_t rows, int64_t cols) { return rows * cols <= (block == 128 ? 32 : block == 64 ? 12 : 11) << 20; }
 static bool low_dropout(int block, int64_t rows, int64_t cols) { return block <= 64 && rows * cols <= 2 << 20; }
 
 template <bool BWD>
