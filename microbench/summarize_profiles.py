@@ -29,7 +29,7 @@ def short(name, n=120):
 
 def product(name):
     """fwd, dgrad, wgrad or pair of a GEMM kernel, from its operands' layouts (A K-major, B K-major)."""
-    if "gemm_pair_kernel" in name:
+    if "pair_kernel" in name:
         return "pair"
     flags = tuple(re.findall(r"true|false", name)[:2])
     return {("true", "true"): "fwd", ("true", "false"): "dgrad", ("false", "false"): "wgrad"}.get(flags, "other")
@@ -222,17 +222,19 @@ def gemm_pmc():
                     res[r["Kernel_Name"]][r["Counter_Name"]].append(float(r["Counter_Value"]))
         out += [title, hdr]
         for k, c in res.items():
-            m = re.search(r"(gemm_(?:pair_)?kernel)<(.*)>", k)
-            name = (("pair " if "pair" in m.group(1) else "") + m.group(2))[:64]
+            m = re.search(r"(gemm_(?:wide_)?(?:pair_)?kernel)<(.*)>", k)
+            name = (("wide " if "wide" in m.group(1) else "") + ("pair " if "pair" in m.group(1) else "") + m.group(2))[:64]
             a = lambda n: sum(c[n]) / len(c[n]) if c[n] else float("nan")
             busy = a("SQ_BUSY_CU_CYCLES") * 4
             out.append(f"{name:66s} {a('SQ_VALU_MFMA_BUSY_CYCLES') / busy:9.3f} {4 * a('SQ_ACTIVE_INST_VALU') / busy:9.3f} "
                        f"{(a('SQ_INSTS_VALU') - a('SQ_INSTS_MFMA')) / a('SQ_INSTS_MFMA'):9.1f} {a('SQ_LDS_IDX_ACTIVE') / a('SQ_BUSY_CU_CYCLES'):8.3f} "
                        f"{a('TCC_MISS_sum') / a('TCC_REQ_sum'):8.3f} {a('TCC_REQ_sum') / 1e6:9.2f} {a('SQ_WAIT_INST_ANY') / a('SQ_WAVE_CYCLES'):6.3f}")
         out.append("")
-    out += ["Template arguments: block, sub-blocks per wave (rows, columns), waves per workgroup (rows, columns), A K-major, B K-major, test hook.",
-            "Reading: at block 32 and 64 the vector ALU is the saturated pipe and the matrix cores are busy a fraction of the time that",
-            "follows from the fold's instruction count per MFMA (Sec. 5.3): the dequantize fold bounds the kernel, not the MFMA rate."]
+    out += ["Template arguments: block, sub-blocks per wave (rows, columns), waves per workgroup (rows, columns), A K-major, B K-major, test hook; of the",
+            "persistent 256 x 256 tiles (wide): block, A K-major, B K-major, or the block alone for the pair.",
+            "Reading: at block 32 the vector ALU is the saturated pipe and the matrix cores are busy a fraction of the time that follows from",
+            "the fold's instruction count per MFMA (Sec. 5.3): the dequantize fold bounds the kernel, not the MFMA rate.  At block 64 and 128",
+            "no pipe is: cycles are counted at the clock that the power limit leaves (1.6 to 1.95 GHz); what counts there is how few bytes move per MFMA."]
     write("gemm_pmc_mfma_valu_utilisation.txt", out)
 
 
