@@ -12,13 +12,12 @@
 //   8   128x64: four waves of 2x1 sub-blocks, four workgroups per compute unit (B = 32)
 //   10  32x32: four waves of 16x16 outputs, jf_gemm_fine.hpp (B = 32)
 //   11  256x256: eight waves of 2x4 sub-blocks in persistent workgroups, one per compute unit, jf_gemm_wide.hpp (B = 64, 128)
-// A model of the busiest SIMD predicts the time of each and the least is taken.  Its constants are least-squares fits to the
-// measured times of 276 products (92 layers drawn over the logarithm of their sizes, 128 .. 16384 tokens, 128 .. 8192
-// features; all three products) and 184 backward passes: rms error 4-9 % for one shape, and the shape taken is on
-// average within 0.8 % (B = 32) of the best one in each case; for the choice between one and two launches of the backward
-// products within 1.3 %.  With shape 11, whose constants and those of the pairs at B = 128 are fitted to 540 products and 180
-// backward passes per block size: 0.5 % (B = 64) and 0.2 % (128), pairs 0.2 % and 0.8 %.  Over the same layers shape 11 is taken
-// for 11 % (B = 64) and 44 % (128) of the products and gains 0.9 % and 7.0 % on the average of all.
+// A model of the busiest compute unit predicts the time of each and the least is taken.  Its constants are least-squares fits to the
+// measured times of all shapes and pairs on 400 (B = 32) and 280 (64, 128) layers, half of them drawn over the logarithm of their
+// sizes (128 .. 16384 tokens, 128 .. 11008 features), half from multiples of 256: rms error 3-8 % for one shape.  Fitted to every other
+// layer, the choice costs on the rest, against the best shape or pair of each, on average 0.35 % (B = 32; by its forerunner without
+// rounds, resident counts and distant operands 0.9 %), 0.3 % (64) and 0.0 % (128) for single products and 0.5 (2.1), 0.2 (0.7) and 0.5 %
+// (1.9) for backward passes; what is left are tensors of a few microseconds.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -27,57 +26,72 @@
 
 namespace jf {
 
-// A workgroup puts `sub` 32x32 sub-blocks on every SIMD of its compute unit; with T tiles the busiest unit holds
-// ceil(T / 256) workgroups while all are resident at once, T / 256 + tail beyond that.  A sub-block costs `ns` per 32 K on
-// a SIMD shared by several workgroups, `ns_alone` on one that holds a single one (which cannot overlap its own MFMA, fold
-// and waits) in the forward product, `dgrad` and `wgrad` times that in the others, whose operands are read transposed, and
+// A workgroup puts `sub` 32x32 sub-blocks on every SIMD of its compute unit.  A sub-block costs ns[n - 1] per 32 K with n workgroups
+// resident (one alone cannot overlap its own MFMA, fold and waits) in the forward product, `dgrad` and `wgrad` times that in the
+// others, whose operands are read transposed, up to 1 + `far` times that where the operands are too large for the caches, and
 // `epilogue_us` besides; fixed_us is the launch and the latency of the first stage.
 static constexpr int kPersistent = 1 << 24;   // as many as the largest output has
 enum Product { kForward, kDgrad, kWgrad };
 struct ShapeModel {
   int shape, tm, tn, resident;
-  double sub, fixed_us, ns, ns_alone, tail, epilogue_us, dgrad, wgrad;
+  double sub, fixed_us, tail, epilogue_us, dgrad, wgrad, far, fade, ns[4];
 
   double tiles(const GemmArgs& a) const { return (double)((a.M + tm - 1) / tm) * ((a.Nn + tn - 1) / tn); }
-  double tile_us(Product p, const GemmArgs& a, bool alone) const {
-    const double rate = (alone ? ns_alone : ns) * (p == kForward ? 1.0 : p == kDgrad ? dgrad : wgrad);
-    return sub * (a.K / 32 * rate * 1e-3 + epilogue_us);
+  // one tile's share of its unit with n workgroups resident
+  double tile_us(Product p, const GemmArgs& a, int n) const {
+    const double mb = ((double)a.M + a.Nn) * a.K * 1e-6, rate = ns[std::min(n, 4) - 1] * (1.0 + far * mb / (mb + 20.0));
+    return sub * (a.K / 32 * rate * (p == kForward ? 1.0 : p == kDgrad ? dgrad : wgrad) * 1e-3 + epilogue_us);
   }
-  double product_us(Product p, const GemmArgs& a) const {
-    // (a persistent workgroup takes whole tiles by turns, however many there are: `resident` is kPersistent there)
-    const double t = tiles(a), busiest = t <= 256.0 * resident ? std::ceil(t / 256.0) : t / 256.0 + tail;
-    return fixed_us + busiest * tile_us(p, a, busiest <= 1.0);
-  }
+  double product_us(Product p, const GemmArgs& a) const;
 };
+
+// Time of `per` workgroups a compute unit, u(n) each with n resident: whole rounds of `resident`, then the rest by itself, fewer
+// workgroups to a unit.  The more rounds have gone before, the less do workgroups end together (`fade` a round): then the rest runs
+// beside the others, and `tail` is what the last ones add.
+// (A persistent workgroup takes whole tiles by turns, however many there are: `resident` is kPersistent there.)
+template <class U>
+static double rounds_us(double per, int resident, const U& u, double fade, double tail) {
+  if (per <= resident) {
+    const int n = (int)std::ceil(per);
+    return n * u(n);
+  }
+  const double k = std::floor(per / resident), rest = per - k * resident, together = std::pow(fade, k);
+  const int n = (int)std::ceil(rest);
+  return k * resident * u(resident) + (n ? together * n * u(n) : 0.0) + (1.0 - together) * (rest + tail) * u(resident);
+}
+inline double ShapeModel::product_us(Product p, const GemmArgs& a) const {
+  return fixed_us + rounds_us(tiles(a) / 256.0, resident, [&](int n) { return tile_us(p, a, n); }, fade, tail);
+}
 
 static constexpr ShapeModel kShapes32[] = {
-    {6, 256, 128, 2, 8, 2.25, 51.8, 60.0, 0.78, 0.524, 1.028, 1.039},
-    {1, 128, 128, 3, 4, 3.11, 58.8, 87.2, 0.68, 0.480, 1.021, 0.995},
-    {8, 128, 64, 4, 2, 2.98, 66.8, 103.3, 0.65, 0.501, 1.026, 1.020},
-    {4, 64, 64, 4, 1, 2.95, 68.5, 109.1, 1.03, 0.703, 1.074, 1.206},
-    {10, 32, 32, 4, 0.25, 3.26, 110.0, 125.5, 0.72, 1.798, 1.511, 2.205}};
+    {6, 256, 128, 2, 8, 2.788, 2.368, 0.4550, 1.021, 1.031, 0.0952, 0.923, {56.07, 45.61, 45.61, 45.61}},
+    {1, 128, 128, 3, 4, 3.457, 1.268, 0.3633, 1.020, 0.994, 0.0545, 0.837, {82.35, 53.42, 51.33, 51.33}},
+    {8, 128, 64, 4, 2, 2.956, 1.145, 0.4533, 1.016, 0.999, 0.1229, 0.788, {96.07, 60.13, 55.10, 56.05}},
+    {4, 64, 64, 4, 1, 2.801, 2.493, 0.7624, 1.061, 1.182, 0.3667, 0.990, {97.87, 56.00, 50.30, 50.06}},
+    {10, 32, 32, 4, 0.25, 3.209, 1.020, 2.0237, 1.654, 2.570, 0.5469, 1.000, {105.91, 80.90, 81.07, 70.29}}};
 static constexpr ShapeModel kShapes64[] = {
-    {1, 128, 128, 3, 4, 2.82, 42.2, 58.5, 0.51, 0.464, 0.967, 1.001},
-    {4, 64, 64, 3, 1, 2.71, 58.3, 66.0, 0.59, 0.827, 1.055, 1.237},
-    {11, 256, 256, kPersistent, 16, 0.0, 41.3, 38.4, 0.0, 0.490, 0.995, 0.990}};
+    {1, 128, 128, 3, 4, 3.314, 3.011, 0.3236, 1.005, 1.015, 0.0838, 0.905, {53.31, 36.74, 36.44, 36.44}},
+    {4, 64, 64, 3, 1, 2.834, 4.580, 0.8016, 1.177, 1.387, 0.2486, 0.948, {54.10, 41.61, 40.66, 40.66}},
+    {11, 256, 256, kPersistent, 16, 2.233, 0.0, 0.3669, 1.018, 1.041, 0.1604, 0.0, {31.38, 34.68, 34.68, 34.68}}};
 static constexpr ShapeModel kShapes128[] = {
-    {6, 256, 128, 1, 8, -1.22, 29.8, 25.3, 0.38, 0.945, 1.014, 1.070},
-    {1, 128, 128, 1, 4, 1.44, 34.2, 30.7, 0.79, 0.890, 1.001, 1.046},
-    {11, 256, 256, kPersistent, 16, 0.0, 25.1, 21.8, 0.0, 0.474, 0.993, 1.015}};
+    {6, 256, 128, 1, 8, 1.976, 4.369, 0.5626, 0.997, 1.017, 0.1561, 0.933, {23.17, 23.17, 23.17, 23.17}},
+    {1, 128, 128, 1, 4, 1.701, 13.765, 0.7992, 1.011, 1.080, 0.1634, 0.986, {27.13, 27.13, 27.13, 27.13}},
+    {11, 256, 256, kPersistent, 16, 2.794, 0.0, 0.3786, 1.030, 1.002, 0.2910, 0.0, {18.88, 21.92, 21.92, 21.92}}};
 
-// Both backward products in one launch: input gradient on shape `dgrad`, weight gradient on shape `wgrad`.  The compute
-// units share the work of both, W = their average (more by 0.6 of what the rounding to whole workgroups adds while all are
-// resident), so that the time is fixed_us + work * W + longest * (the longer tile's own time), at least that tile's time
-// alone; with at most one tile per compute unit it is that.
+// Both backward products in one launch: input gradient on shape `dgrad`, weight gradient on shape `wgrad`, the longer tiles dealt
+// first.  While all are resident the busiest unit counts for `dealt` and the average for the rest; beyond that whole rounds and a rest
+// as above, of tiles of the mean time.  `work` is what running side by side saves or costs; never less than one tile alone.
 struct PairModel {
   int pair, dgrad, wgrad;   // `pair` as in jf_debug_set_gemm_shape
-  double fixed_us, work, longest;
+  double fixed_us, work, dealt, fade;
 };
-static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.14, 0.922, 0.243}, {22, 8, 8, 3.15, 0.986, 0.148}, {23, 4, 4, 2.69, 0.998, 0.310},
-                                         {24, 10, 4, 2.91, 0.974, 0.378}, {25, 4, 10, 2.64, 1.032, 0.217}};
-// Pair 26 is one list of tiles dealt to persistent workgroups: time = work * (the longest workgroup's tiles).
-static constexpr PairModel kPairs64[] = {{21, 1, 1, 2.71, 0.983, 0.204}, {22, 4, 4, 2.93, 0.945, 0.385}, {26, 11, 11, 0.0, 0.973, 0.0}};
-static constexpr PairModel kPairs128[] = {{21, 6, 6, -1.50, 0.910, 0.310}, {22, 1, 1, 1.46, 1.090, 0.118}, {26, 11, 11, 0.0, 1.011, 0.0}};
+static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.749, 1.062, 0.671, 0.556}, {22, 8, 8, 3.269, 1.040, 0.795, 0.653},
+                                         {23, 4, 4, 3.093, 1.017, 0.974, 1.0},   {24, 10, 4, 3.230, 1.004, 1.153, 1.0},
+                                         {25, 4, 10, 3.314, 1.013, 0.808, 1.0}};
+static constexpr PairModel kPairs64[] = {{21, 1, 1, 3.762, 1.062, 0.708, 0.665}, {22, 4, 4, 3.225, 1.088, 0.669, 0.747},
+                                         {26, 11, 11, 2.822, 1.037, 0.825, 0.0}};
+static constexpr PairModel kPairs128[] = {{21, 6, 6, 2.371, 1.284, 0.800, 0.416}, {22, 1, 1, 2.089, 1.212, 0.800, 0.596},
+                                          {26, 11, 11, 4.458, 1.089, 0.737, 0.0}};
 
 struct ShapeTable {
   const ShapeModel* shapes;
@@ -102,25 +116,29 @@ struct ShapeTable {
   }
   double pair_us(const PairModel& p, const GemmArgs& d, const GemmArgs& w) const {
     const ShapeModel &sd = *find(p.dgrad), &sw = *find(p.wgrad);
-    if (sd.resident == kPersistent) {
-      // as gemm_wide_pair_kernel deals them; the workgroup with most tiles is the first of either product
-      const bool second_first = w.K > d.K;
-      const int64_t td = (int64_t)sd.tiles(d), tw = (int64_t)sw.tiles(w), t1 = second_first ? tw : td, t2 = second_first ? td : tw;
-      const double us_d = sd.tile_us(kDgrad, d, false), us_w = sw.tile_us(kWgrad, w, false);
-      const int64_t split = (t1 + 7) & ~int64_t(7), n = std::min<int64_t>(256, split + t2);
-      double busiest = 0.0;
-      for (const int64_t i : {int64_t(0), split % n}) {
-        const int64_t n1 = i < t1 ? (t1 - i + n - 1) / n : 0, j = (n - split % n + i) % n, n2 = j < t2 ? (t2 - j + n - 1) / n : 0;
-        busiest = std::max(busiest, n1 * (second_first ? us_w : us_d) + n2 * (second_first ? us_d : us_w));
-      }
-      return p.fixed_us + p.work * busiest;
+    const auto ud = [&](int n) { return sd.tile_us(kDgrad, d, n); };
+    const auto uw = [&](int n) { return sw.tile_us(kWgrad, w, n); };
+    const double td = sd.tiles(d), tw = sw.tiles(w), per = (td + tw) / 256.0, alone = std::max(ud(1), uw(1));
+    const int resident = std::min(sd.resident, sw.resident);
+    if (per <= 1.0) return p.fixed_us + alone;
+    if (per > resident) {
+      const auto mean = [&](int n) { return (td * ud(n) + tw * uw(n)) / (td + tw); };
+      return p.fixed_us + std::max(alone, p.work * rounds_us(per, resident, mean, p.fade, 0.0));
     }
-    const double td = sd.tiles(d), tw = sw.tiles(w), per_cu = (td + tw) / 256.0;
-    const double alone = std::max(sd.tile_us(kDgrad, d, true), sw.tile_us(kWgrad, w, true));
-    if (per_cu <= 1.0) return p.fixed_us + alone;
-    double work = (td * sd.tile_us(kDgrad, d, false) + tw * sw.tile_us(kWgrad, w, false)) / 256.0;
-    if (per_cu <= std::min(sd.resident, sw.resident)) work *= 1.0 + 0.6 * (std::ceil(per_cu) / per_cu - 1.0);
-    return p.fixed_us + std::max(alone, p.work * work + p.longest * alone);
+    // dealt to the units in turn, as gemm_pair_kernel and gemm_wide_pair_kernel number them: the unit with most is the first or the
+    // last of the first product's last round, or the first of the second's
+    const int n = (int)std::ceil(per);
+    const bool second_first = (int64_t)w.K * sw.tm * sw.tn > (int64_t)d.K * sd.tm * sd.tn;
+    const int64_t t1 = (int64_t)(second_first ? tw : td), t2 = (int64_t)(second_first ? td : tw), split = (t1 + 7) & ~int64_t(7);
+    const double u1 = second_first ? uw(n) : ud(n), u2 = second_first ? ud(n) : uw(n);
+    double busiest = 0.0;
+    for (const int64_t i : {int64_t(0), split % 256, (t1 - 1) % 256}) {
+      const int64_t j = (i - split % 256 + 256) % 256;
+      const int64_t n1 = i < t1 ? (t1 - i + 255) / 256 : 0, n2 = j < t2 ? (t2 - j + 255) / 256 : 0;
+      busiest = std::max(busiest, n1 * u1 + n2 * u2);
+    }
+    const double average = (t1 * u1 + t2 * u2) / 256.0;
+    return p.fixed_us + std::max(alone, p.work * (p.dealt * busiest + (1.0 - p.dealt) * average));
   }
 };
 template <int NS, int NP>
