@@ -267,9 +267,9 @@ int32_t jf_debug_linear_partials(int32_t which, const int8_t* A, const int8_t* B
  * Test hook: force the tile shape of the GEMM entry points.  This is the one piece of state the library keeps
  * besides the last-error slot: a process-wide atomic integer, 0 (automatic) unless a test sets it, read once per
  * launch.  Production callers never call this.
- *   0 automatic (cost model), 1 128x128, 4 64x64 (blocks 32, 64), 6 256x128 (blocks 32, 128), 8 128x64, 10 32x32 (block
- *   32), 11 256x256 (blocks 64, 128); 21 .. 26 the pairs of shapes that jf_linear_bwd knows for its two products in one launch
- *   (21 .. 25 for block 32; 21, 22, 26 for blocks 64 and 128); 7, a former shape: automatic; other values: JF_ERR_SHAPE.
+ *   0 automatic (cost model), 1 128x128, 4 64x64 (blocks 32, 64), 6 256x128 (blocks 32, 128), 7 and 8 128x64, 10
+ *   32x32 (block 32), 11 256x256 (blocks 64, 128); 21 .. 26 the pairs of shapes that jf_linear_bwd knows for its two products in
+ *   one launch (21, 22, 26 for blocks 64 and 128); other values: JF_ERR_SHAPE.
  * A shape that the block size does not have leaves the choice automatic.
  */
 int32_t jf_debug_set_gemm_shape(int32_t shape);

@@ -605,9 +605,9 @@ template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DUMP =
 struct GemmInstance {
   typedef GemmShape<B, WM, WN, WGM, WGN, AK, BK> Shape;
   // Resident waves per SIMD the register allocation has to allow.  Four waves: 3 for the 128x128 tile and for the 64x64
-  // tile at B = 64 (three workgroups share the LDS of a compute unit), else 4.  Eight waves: 4 for the 256x128 tile at
-  // B = 32 (two workgroups per compute unit), else 2 (one).
-  static constexpr int WMIN = Shape::NW == 8 ? (B == 32 ? 4 : 2) : (WM * WN == 4 || B == 64) ? 3 : 4;
+  // tile at B = 64 (three workgroups share the LDS of a compute unit), else 4.  Eight waves: 4 for the 256x128 tile and 6 for
+  // the 128x64 tile at B = 32 (two and three workgroups per compute unit), else 2 (one).
+  static constexpr int WMIN = Shape::NW == 8 ? (B == 32 ? (WM * WN == 1 ? 6 : 4) : 2) : (WM * WN == 4 || B == 64) ? 3 : 4;
   static __device__ __forceinline__ void run(const GemmArgs& g, int tile_index, int ntiles, int8_t* s_ring, float (*s_amax)[8]) {
     gemm_tile<B, WM, WN, WGM, WGN, AK, BK, DUMP>(g, tile_index, ntiles, s_ring, s_amax);
   }
@@ -682,6 +682,7 @@ static void launch_shape(int shape, const GemmArgs& a, hipStream_t st) {
     else if constexpr (B == 32) {
       if (shape == 6) launch_one<GemmInstance<B, 2, 2, 4, 2, AK, BK, DUMP>>(a, st);
       else if (shape == 8) launch_one<GemmInstance<B, 2, 1, 2, 2, AK, BK, DUMP>>(a, st);
+      else if (shape == 7) launch_one<GemmInstance<B, 1, 1, 4, 2, AK, BK, DUMP>>(a, st);
       else if (DUMP || shape == 4) launch_one<GemmInstance<B, 1, 1, 2, 2, AK, BK, DUMP>>(a, st);
       else launch_one<FineInstance<AK, BK>>(a, st);
     } else {

@@ -9,15 +9,20 @@
 //   6   256x128: eight waves of 2x2 sub-blocks; two workgroups per compute unit at B = 32, one at B = 128 (not at B = 64).
 //       A quarter less operand traffic per MFMA than 128x128, and at B = 32 four waves per SIMD instead of three:
 //       8192^3 alone, forward / dgrad / wgrad: 990 / 965 / 951 us on 128x128, 943 / 940 / 933 us on 256x128
+//   7   128x64: eight waves of one sub-block, three workgroups per compute unit (B = 32).  More fragment reads per MFMA than 8, but
+//       twice the waves: up to six on a SIMD, where one or two tiles a unit leave 8 a wave or two.  2048^3 alone, forward / dgrad /
+//       wgrad, on 4, 8 and 7: 20.2 / 20.8 / 23.0, 21.7 / 21.7 / 21.5 and 20.1 / 20.0 / 20.0 us; both backward products of
+//       4096 x 768 -> 3072 48.0 -> 45.9 us; 8 keeps outputs of little K in three to four tiles a unit (4704 x 992 x 320 8.6 and 10.2)
 //   8   128x64: four waves of 2x1 sub-blocks, four workgroups per compute unit (B = 32)
 //   10  32x32: four waves of 16x16 outputs, jf_gemm_fine.hpp (B = 32)
 //   11  256x256: eight waves of 2x4 sub-blocks in persistent workgroups, one per compute unit, jf_gemm_wide.hpp (B = 64, 128)
 // A model of the busiest compute unit predicts the time of each and the least is taken.  Its constants are least-squares fits to the
 // measured times of all shapes and pairs on 400 (B = 32) and 280 (64, 128) layers, half of them drawn over the logarithm of their
 // sizes (128 .. 16384 tokens, 128 .. 11008 features), half from multiples of 256: rms error 3-8 % for one shape.  Fitted to every other
-// layer, the choice costs on the rest, against the best shape or pair of each, on average 0.35 % (B = 32; by its forerunner without
-// rounds, resident counts and distant operands 0.9 %), 0.3 % (64) and 0.0 % (128) for single products and 0.5 (2.1), 0.2 (0.7) and 0.5 %
-// (1.9) for backward passes; what is left are tensors of a few microseconds.
+// layer, the choice costs on the rest, against the best shape or pair of each, on average 0.3 % (B = 64) and 0.0 % (128) for single
+// products and 0.2 and 0.5 % for backward passes (their forerunner, without rounds, resident counts and distant operands, 0.7 and 1.9).
+// At B = 32 shape 7 and pair 26 were fitted with the rest held, every layer scaled by the shapes that both fits know; on 120 further
+// layers the choice costs 0.6 % (without shape 7 1.2) and 1.1 %.  What is left are tensors of a few microseconds.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -66,6 +71,7 @@ inline double ShapeModel::product_us(Product p, const GemmArgs& a) const {
 static constexpr ShapeModel kShapes32[] = {
     {6, 256, 128, 2, 8, 2.788, 2.368, 0.4550, 1.021, 1.031, 0.0952, 0.923, {56.07, 45.61, 45.61, 45.61}},
     {1, 128, 128, 3, 4, 3.457, 1.268, 0.3633, 1.020, 0.994, 0.0545, 0.837, {82.35, 53.42, 51.33, 51.33}},
+    {7, 128, 64, 3, 2, 2.653, 1.035, 0.6787, 1.019, 1.025, 0.2504, 0.904, {67.30, 48.65, 47.49, 47.49}},
     {8, 128, 64, 4, 2, 2.956, 1.145, 0.4533, 1.016, 0.999, 0.1229, 0.788, {96.07, 60.13, 55.10, 56.05}},
     {4, 64, 64, 4, 1, 2.801, 2.493, 0.7624, 1.061, 1.182, 0.3667, 0.990, {97.87, 56.00, 50.30, 50.06}},
     {10, 32, 32, 4, 0.25, 3.209, 1.020, 2.0237, 1.654, 2.570, 0.5469, 1.000, {105.91, 80.90, 81.07, 70.29}}};
@@ -87,7 +93,7 @@ struct PairModel {
 };
 static constexpr PairModel kPairs32[] = {{21, 1, 1, 3.749, 1.062, 0.671, 0.556}, {22, 8, 8, 3.269, 1.040, 0.795, 0.653},
                                          {23, 4, 4, 3.093, 1.017, 0.974, 1.0},   {24, 10, 4, 3.230, 1.004, 1.153, 1.0},
-                                         {25, 4, 10, 3.314, 1.013, 0.808, 1.0}};
+                                         {25, 4, 10, 3.314, 1.013, 0.808, 1.0},   {26, 7, 7, 3.041, 1.050, 0.844, 0.801}};
 static constexpr PairModel kPairs64[] = {{21, 1, 1, 3.762, 1.062, 0.708, 0.665}, {22, 4, 4, 3.225, 1.088, 0.669, 0.747},
                                          {26, 11, 11, 2.822, 1.037, 0.825, 0.0}};
 static constexpr PairModel kPairs128[] = {{21, 6, 6, 2.371, 1.284, 0.800, 0.416}, {22, 1, 1, 2.089, 1.212, 0.800, 0.596},
