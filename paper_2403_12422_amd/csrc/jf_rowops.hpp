@@ -73,7 +73,7 @@ struct Strip {
     col = c0 + 16 * ch;
     ok = col < cols;
     base = (int64_t)(bi * RW + rsub) * cols + (ok ? col : c0);
-    ok = ok && inside;
+    if (BT > 1) ok = ok && inside;   // with BT == 1 a wave that is not inside ends at once
   }
   // index of the lane's block in a scale grid (clamped like base), and whether the lane is the one to store its scale
   __device__ __forceinline__ int64_t block_index() const { return (int64_t)(bi / BT) * lc + (col < lc * B ? col : c0) / B; }
