@@ -286,25 +286,19 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
 }
 
 // ------------------------------------------------------------------------------------------------ host
-// Whether an operator takes waves of 16 rows (for results that are written through).  Kernel times in us with 32 -> 16 rows, operands
-// and results in no cache; in the last-level cache:
-//   GELU           block 32   256 x 256 3.8 -> 3.4; 3.9 -> 3.4   1056 x 2080 4.8 -> 4.4; 4.6 -> 4.1   8192 x 1280 7.2 -> 6.2; 7.0 -> 6.2
-//                             4096 x 3072 7.4 -> 7.4; 7.2 -> 6.9   8192 x 2048 8.0 -> 9.7; 8.4 -> 8.2
-//                  block 128  1024 x 768 4.1 -> 4.2; 3.7 -> 3.8   16384 x 1280 10.5 -> 11.0; 8.8 -> 9.3: two tables' halves for eight waves
-//   GELU backward  block 32   1056 x 800 4.8 -> 4.0; 4.8 -> 3.8   4096 x 1280 6.8 -> 6.0; 6.5 -> 5.6   4096 x 3072 10.0 -> 9.8; 9.1 -> 8.7
-//                             8192 x 1280 9.2 -> 9.6; 8.7 -> 8.1   8192 x 4096 20.8 -> 21.5; 17.5 -> 18.0
-//                  block 128  2048 x 2048 5.2 -> 5.0; 5.0 -> 4.8   8192 x 2048 14.1 -> 13.1; 10.8 -> 9.7   16384 x 1280 14.5 -> 14.4; 12.0 -> 12.6
-//   at block 64 (from one block of 64 x 64 per wave) all sizes: 1024 x 768 4.3 -> 3.5; 4.2 -> 3.4, backward 4.6 -> 3.6; 4.3 -> 3.4
-//                             8192 x 1280 8.6 -> 6.3; 6.9 -> 6.1, 10.8 -> 9.4; 8.3 -> 7.6   8192 x 5120 23.3 -> 20.4; 15.0 -> 14.3, 32.2 -> 28.9; 23.6 -> 21.8
-//   Add            block 32   1056 x 800 4.5 -> 3.8; 3.8 -> 3.3   8192 x 1280 8.7 -> 8.1; 7.2 -> 6.8, with partials 9.7 -> 8.9; 8.1 -> 7.5
-//                             4096 x 3072 9.4 -> 9.3; 7.7 -> 7.7 (from L2 5.6 -> 6.2), 8192 x 2048 11.4 -> 11.6; 9.1 -> 9.4
-//                  block 64   1024 x 768 4.4 -> 3.6; 3.9 -> 3.2   4096 x 3072 10.2 -> 9.7; 7.9 -> 7.6   8192 x 4096 21.1 -> 22.1; 17.0 -> 16.8
-//                  block 128  1024 x 768 4.5 -> 4.0; 4.0 -> 3.6   8192 x 4096 22.7 -> 21.8; 16.9 -> 16.7, with partials 23.7 -> 22.7; 18.6 -> 17.6
-//   Dropout        block 32   2048 x 1024 3.8 -> 3.6; 3.4 -> 3.1   1056 x 2080 4.3 -> 4.2; 3.6 -> 3.7   16384 x 1280 10.2 -> 10.6; 8.0 -> 8.9
-//                  block 128  1024 x 768 3.8 -> 3.9; 3.6 -> 3.5
+// Whether an operator takes waves of 16 rows (for results that are written through).  Small tensors give a SIMD a wave or two, and a wave of
+// 16 rows has half the serial chain.  From a few million elements on it matters how the waves come out on 1024 SIMDs: 32-row waves fill
+// rounds of 4 M elements, half waves round a rest less up, and cost twice the scales, reductions and exchanges.  The lines lie where the
+// gain over sizes and widths ends, alone and in the paths of a training step (profiles/strip_heights.txt).  32 -> 16 rows in us:
+//   GELU, forward and backward one after the other: block 32 4 M elements 10.8 -> 9.5, 13 M 16.3 -> 14.8, 17 M 19.1 -> 18.2, 20 M 21.5 -> 22.0
+//     (beyond 21 M up to 5 % faster again, 40 M 40.8 -> 40.3); block 64 10 M 13.1 -> 12.0, 17 M 18.4 -> 17.0, 20 M 21.0 -> 21.6, 36 M 35.8 -> 34.7;
+//     block 128 only backward, alone 1 M 4.8 -> 4.2, 12 M 10.5 -> 10.1 (forward 12 M 7.7 -> 7.6, from the cache 28 M 10.1 -> 11.2: eight waves to a table)
+//   Add, alone 1 M 3.8 -> 3.3, block 64 and 128 3.9 -> 3.2 and 4.1 -> 3.6; in the residual path at block 32 10 M 53.7 -> 53.8, 12 M 63.8 -> 63.4, 16 M
+//     76.5 -> 75.7, 20 M 86.7 -> 86.0, by up to 2 % the one or the other way from width to width; block 128 16 M 83.8 -> 82.7
+//   Dropout, alone 1 M 3.5 -> 3.1, 4 M 4.1 -> 4.4; in the residual path 8 M 48.4 -> 49.0, 12 M 63.4 -> 63.4, 20 M 86.0 -> 86.5
 static bool low_gelu(bool backward, int block, int64_t rows, int64_t cols) {
   if (block == 128) return backward && rows * cols <= 16 << 20;
-  return block == 64 || rows * cols <= 12 << 20;
+  return block == 64 || rows * cols <= 18 << 20;
 }
 static bool low_add(int block, int64_t rows, int64_t cols) { return rows * cols <= (block == 128 ? 32 : block == 64 ? 12 : 11) << 20; }
 static bool low_dropout(int block, int64_t rows, int64_t cols) { return block <= 64 && rows * cols <= 2 << 20; }

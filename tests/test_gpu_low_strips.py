@@ -1,5 +1,5 @@
 """GELU, Add and Dropout of small tensors in waves of 16 rows: a last strip with one block, a last workgroup with strips that do not exist
-(against the oracle), and sizes behind the lines to waves of 32 rows (against their small calls, bit for bit)."""
+(against the oracle), and sizes up to and behind the lines to waves of 32 rows (against their small calls, bit for bit)."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,8 @@ from test_gpu_parity import _check_eltwise, dev, host, say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("block,N,C", [(32, 2176, 992), (32, 9856, 1280), (64, 2176, 1024), (64, 9856, 1280), (128, 13184, 1280), (128, 26368, 1280)])
+@pytest.mark.parametrize("block,N,C", [(32, 2176, 992), (32, 9856, 1280), (64, 2176, 1024), (64, 9856, 1280), (128, 13184, 1280), (128, 26368, 1280),
+                                       (32, 14720, 1280), (32, 14752, 1280), (64, 40256, 832)])
 def test_behind_the_lines(block, N, C):
     policies.test_large_results_equal_those_of_small_calls(block, N, C)
 
