@@ -399,7 +399,8 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
       asm volatile("" : "+v"(px[p].x), "+v"(px[p].y), "+v"(px[p].z), "+v"(px[p].w));
       asm volatile("" : "+v"(pg[p].x), "+v"(pg[p].y), "+v"(pg[p].z), "+v"(pg[p].w));
     }
-    // dx = (g_code gamma) (rstd sg) + x_code kxm + krow
+    // dx = (g_code gamma) (rstd sg) + x_code kxm + krow.  The order is part of the result: another one, as accurate, moves one code in a
+    // million over a rounding tie, and with it now and then the scale of a block in the operators that take dx.
     float kxm[4], krow[4], rsg[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
