@@ -41,9 +41,8 @@ struct GemmArgs {
 };
 
 // ---------------------------------------------------------------------------------------------
-// LDS staging.  A stage holds KC bytes of K for both operand tiles: KC = 64 (two MFMA K steps), or
-// 128 for B = 128 so that a stage always holds whole quantization blocks and block boundaries are
-// known at compile time.  Tiles go global -> LDS with global_load_lds_dwordx4: no VGPR staging, no
+// LDS staging.  A stage holds KC bytes of K for both operand tiles, 64 (two MFMA K steps) or 128 (see
+// GemmShape), so that it always holds whole quantization blocks and block boundaries are known at compile time.  Tiles go global -> LDS with global_load_lds_dwordx4: no VGPR staging, no
 // ds_write; the 64 lanes of one such instruction fill 64 consecutive 16-byte LDS slots, so the
 // layout cannot be padded.  Bank conflicts are avoided by an XOR swizzle instead: the tile is a
 // matrix of 16-byte chunks with CPR chunks per row, and chunk c of row r lives in slot
@@ -214,7 +213,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Renumber them so that every XCD
   // works on one contiguous run of tiles, and order the tiles in groups of GROUP_M tile rows, column by column
   // inside a group: the workgroups that are resident on an XCD at the same time then form a compact patch
-  // (8 tile rows x a few tile columns) that re-reads few distinct operand tiles from that XCD's L2.
+  // (GROUP_M tile rows x a few tile columns) that re-reads few distinct operand tiles from that XCD's L2.
   constexpr int GROUP_M = TM >= 256 ? 4 : 8;
   const int tiles_n = (g.Nn + TN - 1) / TN, tiles_m = (g.M + TM - 1) / TM;
   const int xcd = tile_index & 7, idx = tile_index >> 3;

@@ -1,8 +1,8 @@
 // INT8-in / INT8-out LayerNorm, forward and backward (App. A).
 //
 // Rows of at most 2048 / 1024 / 512 columns at block size 32 / 64 / 128 go through jf_layernorm_rows.hpp where there are enough
-// of them (layernorm_rows_fits).  Otherwise each pass is a small kernel
-// that only leaves sums (row statistics forward; row means and dgamma | dbeta partial rows backward) followed by an
+// of them (layernorm_rows_fits), wider ones at block size 32 through jf_layernorm_wide.hip (layernorm_wide_fits).  Otherwise each
+// pass is a small kernel that only leaves sums (row statistics forward; row means and dgamma | dbeta partial rows backward) followed by an
 // element-wise operator on tiles: the 32 x 128 strips of jf_rowops.hpp at block size 32, workgroups of B rows x 128
 // columns at block sizes 64 and 128.  No workgroup holds a row in registers, so rows may be of any width.
 // Row sums of the forward pass come from exact integer dot products of the codes (v_dot4), scaled per block -- the
@@ -15,13 +15,11 @@
 namespace jf {
 
 // ------------------------------------------------------------------------------------------------
-// Where whole rows are needed a workgroup owns 32 of them (at every block size: a block row is one, two or four such
+// The backward sums kernel: a workgroup owns 32 whole rows at a time (at every block size: a block row is one, two or four such
 // groups) and is made of strip waves: wave w holds the 32 x 128 strip w of those rows with the lane mapping of Strip32
-// (C / 128 waves, at most 16).  What
-// needs a whole row (the row sums) is reduced over the 8 chunk lanes of a row inside each wave (three DPP steps)
-// and over the strips through a few hundred bytes of LDS, in a fixed order; what belongs to a block (max-abs,
-// scale) or to a column (gamma, beta, the column sums of the backward pass) never leaves its wave.
-// WMAX = most waves the instance is compiled for (the register budget follows from it).
+// (C / 128 waves, at most 16).  What needs a whole row (the row sums) is reduced over the 8 chunk lanes of a row inside each wave (three DPP steps)
+// and over the strips through a few hundred bytes of LDS, in a fixed order; what belongs to a column (gamma, the column sums)
+// never leaves its wave.
 struct RowStrips {
   int ch, rsub, wave, nstrips;
   int lc, col, block;
@@ -50,10 +48,10 @@ struct RowStrips {
 // Per 16-code chunk the sum and the sum of squares of the codes are exact integers (v_dot4); times the block scale,
 // in double, they are the chunk's share of the row's sum and sum of squares.  The shares are added over a lane's
 // strips, over the 8 chunk lanes of a row (three DPP steps) and over the waves through LDS, in a fixed order.  The
-// normalisation itself is layernorm_apply_strip32_kernel, an element-wise operator on strips.
+// normalisation itself is an element-wise operator on strips or tiles.
 __global__ void __launch_bounds__(1024) layernorm_row_stats_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
                                                                   float eps, int rows, int cols, int block,
-                                                                           float* __restrict__ mean_out, float* __restrict__ rstd_out) {
+                                                                  float* __restrict__ mean_out, float* __restrict__ rstd_out) {
   __shared__ double s_row[16][32][2];
   const int lane = threadIdx.x & 63, ch = lane & 7, rsub = lane >> 3;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
@@ -113,7 +111,8 @@ __global__ void __launch_bounds__(1024) layernorm_row_stats_kernel(const int8_t*
 // First kernel: the workgroup of strip waves described above walks over the row blocks blockIdx.x, blockIdx.x +
 // gridDim.x, ..., one 32 x 128 strip of each in a wave.  Ten instructions per element (the block scale of g goes onto sums, not
 // onto elements; in place of fifteen, with the column reduction of jf_layernorm.hpp and even column ranges: 4096 x 2560 at block 32,
-// whole pass, 19.5 -> 16.6 us, 4096 x 4096 at 64 22.6 -> 21.3, 2048 x 1024 at 128 11.1 -> 10.2).  The row sums go over the chunk lanes, then over the strips through LDS (two copies used by alternate row blocks: one barrier per block); the running column sums of
+// whole pass, 19.5 -> 16.6 us, 4096 x 4096 at 64 22.6 -> 21.3, 2048 x 1024 at 128 11.1 -> 10.2).  The row sums go over the chunk
+// lanes, then over the strips through LDS (two copies used by alternate row blocks: one barrier per block); the running column sums of
 // g xhat and g stay in registers over all row blocks -- a lane always holds the same 16 columns -- and are added
 // over the 8 row lanes of the wave at the end (every wave owns its own 128 columns of the partial row).  All orders
 // are fixed: results are bit-stable from run to run.

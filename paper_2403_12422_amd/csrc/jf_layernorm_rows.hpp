@@ -342,7 +342,7 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
     if (first + stride < groups) request(min(g + stride, groups - 1));
     sg = t.ok && g < groups ? sg : 0.0f;               // what lies outside adds nothing to the sums
     float kx[4], cx[4], m1[4], m2[4];
-    float y[4][16];                                    // dx; with KEEP ghat in units of g's block scale before
+    float y[4][16];                                    // dx; ghat in units of g's block scale before, of KEPT rows
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       kx[p] = sx * rs[p];

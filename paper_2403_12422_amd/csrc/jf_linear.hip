@@ -1,6 +1,6 @@
 // Per-block INT8 linear layer (Sec. 5, Alg. 1): C entry points of forward, dgrad, wgrad and the INT32-partial
-// test hook.  The kernels live in jf_gemm_kernel.hpp and jf_gemm_fine.hpp and are instantiated per product and block size
-// in jf_gemm_<product>_b<block>.hip; jf_gemm_shapes.hpp picks among them.
+// test hook.  The kernels live in jf_gemm_kernel.hpp, jf_gemm_fine.hpp and jf_gemm_wide.hpp and are instantiated per product and
+// block size in jf_gemm_<product>_b<block>.hip and jf_gemm_bwd_pair_b<block>.hip; jf_gemm_shapes.hpp picks among them.
 #include <atomic>
 
 #include "jf_gemm_shapes.hpp"
@@ -171,7 +171,7 @@ extern "C" int32_t jf_debug_linear_partials(int32_t which, const int8_t* A, cons
   return launch_status();
 }
 
-// (7 was a 64x64 tile with longer stages, which shape 4 has now; it is still accepted and leaves the choice automatic)
+// A shape or pair that the block size does not have (jf_gemm_shapes.hpp) leaves the choice automatic.
 extern "C" int32_t jf_debug_set_gemm_shape(int32_t shape) {
   if (shape != 0 && shape != 1 && shape != 4 && shape != 6 && shape != 7 && shape != 8 && shape != 10 && shape != 11 && (shape < 21 || shape > 26)) return JF_ERR_SHAPE;
   jf::g_forced_shape.store(shape, std::memory_order_relaxed);

@@ -319,8 +319,7 @@ def _check_eltwise(name, q, s, oq, os_, of64, block):
     say(f"  {name}: {nbad} / {oq.size} codes differ by one")
 
 
-# Block 64 takes one block per wave up to 64 M elements; the last case is past that and runs the 256-column workgroups,
-# with a ragged last column group
+# The last two cases are large enough to be written back, in waves of 32 rows, with a ragged last column group
 @pytest.mark.parametrize("block,N,C", [(32, 96, 352), (64, 128, 192), (128, 256, 384), (32, 4096, 3072),
                                        (32, 32768, 1120), (64, 65536, 1088)])
 def test_gelu_fwd_bwd(block, N, C):
