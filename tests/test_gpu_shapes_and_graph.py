@@ -107,11 +107,13 @@ def test_more_row_groups_than_a_grid_dimension_holds(block):
         np.testing.assert_allclose(host(ln[3][r0:r1]), orstd, rtol=1e-5)
 
 
-def test_hot_path_replayed_from_a_hip_graph():
+# small tiles and rows; rows beyond 2048 columns; whole block rows and persistent tiles at block sizes 64 and 128; the two-kernel LayerNorm
+@pytest.mark.parametrize("block,N,C,D", [(32, 512, 256, 384), (32, 5120, 2304, 256), (64, 10240, 320, 4096), (128, 20480, 384, 2048), (64, 4096, 1088, 4096)])
+def test_hot_path_replayed_from_a_hip_graph(block, N, C, D):
     """The whole step (quantize, LayerNorm, the three products, GELU forward / backward, LayerNorm backward) captured
     once and replayed: every replay must reproduce the eager results bit for bit, with eager work and
     synchronisations between the replays (the library records no memset nodes and allocates nothing)."""
-    block, N, C, D = 32, 512, 256, 384
+    say(f"graph block={block} {N} x {C} -> {D}")
     Xh, Wh, dHh = workloads.linear_layer(77, N, C, D)
     g = workloads.rng(78)
     gamma = dev((1.0 + 0.1 * g.standard_normal(C, dtype=np.float32)).astype(np.float32))

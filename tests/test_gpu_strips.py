@@ -1,5 +1,5 @@
-"""Element-wise operators at block sizes 64 and 128 on strips: a last workgroup with strips that do not exist, in workgroups of four
-waves (against the oracle) and of eight (against small calls, bit for bit)."""
+"""Element-wise operators at block sizes 64 and 128 on strips: a last workgroup of eight waves with strips that do not exist (against
+small calls, bit for bit), and the smallest and ragged tensors in workgroups of one block row (against the oracle)."""
 import pytest
 
 import oracle
