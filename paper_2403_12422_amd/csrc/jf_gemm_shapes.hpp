@@ -7,15 +7,14 @@
 //   1   128x128: four waves of 2x2 sub-blocks (B = 128: eight of 2x1), three workgroups per compute unit (B = 128: one)
 //   4   64x64: four waves of one sub-block (not at B = 128)
 //   6   256x128: eight waves of 2x2 sub-blocks; two workgroups per compute unit at B = 32, one at B = 128 (not at B = 64).
-//       A quarter less operand traffic per MFMA than 128x128, and at B = 32 four waves per SIMD instead of three:
-//       8192^3 alone, forward / dgrad / wgrad: 990 / 965 / 951 us on 128x128, 943 / 940 / 933 us on 256x128
+//       A quarter less operand traffic per MFMA than 128x128, and at B = 32 four waves per SIMD instead of three (8192^3 969 -> 939 us)
 //   7   128x64: eight waves of one sub-block, three workgroups per compute unit (B = 32).  More fragment reads per MFMA than 8, but
-//       twice the waves: up to six on a SIMD, where one or two tiles a unit leave 8 a wave or two.  2048^3 alone, forward / dgrad /
-//       wgrad, on 4, 8 and 7: 20.2 / 20.8 / 23.0, 21.7 / 21.7 / 21.5 and 20.1 / 20.0 / 20.0 us; both backward products of
-//       4096 x 768 -> 3072 48.0 -> 45.9 us; 8 keeps outputs of little K in three to four tiles a unit (4704 x 992 x 320 8.6 and 10.2)
+//       twice the waves: up to six on a SIMD, where one or two tiles a unit leave 8 a wave or two (2048^3 alone 21.6 -> 20.0 us); 8 keeps
+//       outputs of little K in three to four tiles a unit (4704 x 992 x 320 8.6 and 10.2)
 //   8   128x64: four waves of 2x1 sub-blocks, four workgroups per compute unit (B = 32)
 //   10  32x32: four waves of 16x16 outputs, jf_gemm_fine.hpp (B = 32)
 //   11  256x256: eight waves of 2x4 sub-blocks in persistent workgroups, one per compute unit, jf_gemm_wide.hpp (B = 64, 128)
+// (More in profiles/kernel_choice.txt.)
 // A model of the busiest compute unit predicts the time of each and the least is taken.  Its constants are least-squares fits to the
 // measured times of all shapes and pairs on 400 (B = 32) and 280 (64, 128) layers, half of them drawn over the logarithm of their
 // sizes (128 .. 16384 tokens, 128 .. 11008 features), half from multiples of 256: rms error 3-8 % for one shape.  Fitted to every other

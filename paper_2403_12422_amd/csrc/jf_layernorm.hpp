@@ -63,7 +63,8 @@ __device__ __forceinline__ T sum_over_strips(const T* v, int strips) {
 
 // Sums over the 8 row lanes of a wave (lane bits 3, 4, 5, in that order) of 16 + 16 values.  The half-row swaps of two values
 // and one addition reduce both: 80 instructions where 32 butterflies take 320, at the end of a workgroup with nothing beside it
-// (with two rows of ghat kept: 8192 x 1280 17.2 -> 15.0 us, 4096 x 768 11.5 -> 10.1, 1056 x 800 7.1 -> 6.5).  Lane (bits 4, 5) ends with values 4 j + bit 4 + 2 (bit 5), j = 0 .. 7, of {a, b}.
+// (with two rows of ghat kept: 8192 x 1280 17.2 -> 15.0 us, 4096 x 768 11.5 -> 10.1, 1056 x 800 7.1 -> 6.5).  Lane (bits 4, 5) ends with
+// values 4 j + bit 4 + 2 (bit 5), j = 0 .. 7, of {a, b}.
 __device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float (&b)[16], float (&out)[8]) {
   const auto half = [](float x, float y, auto swap) __attribute__((always_inline)) {
     const auto p = swap(__builtin_bit_cast(int, x), __builtin_bit_cast(int, y));
@@ -107,14 +108,10 @@ struct LayerNormBwdRows {
 // Whether the one-pass kernels take a pass, and their launches.  The backward one returns the number of partial rows of
 // dgamma | dbeta that it leaves in `partials` (at most 256 and at most rows / 32), or 0 if it has written dgamma and dbeta
 // themselves, which it does not do where an output shares memory with an input (in_place).
-// A block row has to fit sixteen waves.  At block sizes 64 and 128 its workgroup is long, and few of them leave compute units
-// idle that the two-kernel scheme fills with tiles.  Forward, two kernels -> one pass in us:
-//   sixteen waves   8192 x 512 at block 128 (64 block rows) 7.1 -> 7.7, 8192 x 1024 at 64 (128) 8.6 -> 8.0, 24576 x 1024 17.2 -> 14.8
-//   fewer           1024 x 768 at 64 8.7 -> 6.5, 4096 x 256 at 128 8.6 -> 5.4, 262144 x 768 at 64 102 -> 79, 262144 x 384 at 128 51 -> 40
-// Backward, where more than 2048 rows need the launch that adds the partial rows:
-//   more than 2048 rows   8192 x 384 at 128 (64) 10.3 -> 13.1, 8192 x 896 at 64 (128) 14.4 -> 16.0, 10240 x 768 (160) 16.5 -> 14.1,
-//                         12288 x 1024 (192) 20.5 -> 19.3, 262144 x 768 200 -> 142, 262144 x 512 at 128 132 -> 97
-//   up to 2048            1024 x 768 at 64 (twelve waves) 9.9 -> 8.2, 2048 x 256 at 128 8.9 -> 7.0; sixteen: 1024 x 512 at 128 9.3 -> 10.6
+// A block row has to fit sixteen waves.  At block sizes 64 and 128 its workgroup is long, and few of them leave compute units idle that
+// the two-kernel scheme fills with tiles; backward, more than 2048 rows need another launch for the partial rows.  Two kernels -> one pass in
+// us (profiles/kernel_choice.txt): forward on sixteen waves 64 block rows 7.1 -> 7.7, 128 8.6 -> 8.0, on fewer 1024 x 768 8.7 -> 6.5;
+// backward 128 block rows 14.4 -> 16.0, 160 16.5 -> 14.1, up to 2048 rows twelve waves 9.9 -> 8.2, sixteen 9.3 -> 10.6.
 inline bool layernorm_rows_fits(int64_t N, int64_t C, int32_t block, bool backward) {
   const int64_t waves = (C + 127) / 128 * (block / 32), block_rows = N / block;
   if (waves > 16 || block == 32) return waves <= 16;
@@ -128,18 +125,12 @@ int launch_layernorm_bwd_rows_b32(const LayerNormBwdRows& a, bool in_place, hipS
 int launch_layernorm_bwd_rows_b64(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
 int launch_layernorm_bwd_rows_b128(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
 
-
 // Whether the kernels for wider rows (jf_layernorm_wide.hip) take a pass at block size 32, and their launches; the backward one
 // returns its number of partial rows (at most 256 and at most rows / 32).  Forward not from the row partials of an Add: those say what
 // the first of the two kernels reads the codes for.  A compute unit takes whole row groups: few of them, or a last round that is nearly
-// empty, leave too many idle.  Two kernels -> one in us:
-//   backward   4096 x 4096 (128 groups) 23.2 -> 29.5, 5120 x 2560 (160) 24.9 -> 22.2, 5120 x 4096 31.3 -> 31.1, 8192 x 4096 43.8 -> 34.6,
-//              8256 x 4096 (258) 50.3 -> 55.0, 10240 x 4096 (320) 55.4 -> 58.8, 11264 x 3072 (352) 44.0 -> 39.7, 18432 x 2560 (576) 59.3 -> 56.5,
-//              65536 x 3072 223 -> 151, 8192 x 11008 136 -> 98;
-//              beyond kLayerNormWideCols LDS has room for the column sums of few waves only
-//   forward    4096 x 4096 12.8 -> 13.4, 5120 x 2560 11.7 -> 9.9, 8192 x 3072 15.5 -> 12.3, 8256 x 4096 22.4 -> 25.8, 9600 x 4096 (300) 25.3 -> 26.8,
-//              18432 x 2560 27.5 -> 28.6, 20480 x 4096 (640) 43.7 -> 41.3, 22528 x 3072 (704) 36.1 -> 32.3, 25600 x 2560 (800) 36.6 -> 38.9,
-//              8192 x 7168 31.6 -> 27.7, 8192 x 8192 40.1 -> 42.0
+// empty, leave too many idle.  Two kernels -> one in us (profiles/kernel_choice.txt): backward 128 groups 23.2 -> 29.5, 160 24.9 -> 22.2, 256
+// 43.8 -> 34.6, 320 55.4 -> 58.8, 352 44.0 -> 39.7; forward 300 groups 25.3 -> 26.8, 640 43.7 -> 41.3, 8192 x 7168 31.6 -> 27.7, x 8192 40.1 -> 42.0.
+// Beyond kLayerNormWideCols LDS has room for the column sums of few waves only.
 constexpr int kLayerNormWideCols = 11264;
 inline bool layernorm_wide_fits(int64_t N, int64_t C, int32_t block, bool backward) {
   const int64_t groups = N / 32, room = (groups + 255) / 256 * 256;   // row groups of full rounds

@@ -118,14 +118,11 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
   }
 }
 
-// Narrow strips, in workgroups of one block row and, at block size 128, one block: 64 columns a wave up to 256 tiles of 128 x 128
-// (one for each compute unit; FP16, half the bytes in flight a lane, up to 768), 32 columns for the smallest tensors and, in
-// FP16 at block sizes 64 and 128, up to 256 tiles.  Kernel times in us with 128, 64 and 32 columns, operands not in L2:
-//   FP32  block 32   256 x 256 3.4, 3.0, 2.8; 1056 x 800 (63 tiles) 4.1, 3.4, 3.2; 2048 x 1024 (128) 5.0, 4.0, 4.3; 4096 x 768 (192)
-//                    5.6, 5.0, 5.8; 4096 x 1536 (384) 6.3, 6.8, 7.7
-//         block 64   1024 x 768 4.2, 3.3, 3.3; 2048 x 2048 (256) 5.6, 5.4, 6.0; 4096 x 1536 8.1, 8.4, 9.0     128: 4.3, 4.0, 4.2; 5.6, 5.4, 5.9
-//   FP16  block 32   1024 x 768 5.6, 3.8, 3.3; 2048 x 2048 8.4, 6.5, 6.8; 4096 x 3072 (768) 10.7, 10.1, 15.0; 8192 x 2048 (1024) 13.3, 14.0
-//         block 64   1024 x 768 5.7, 4.0, 3.5; 2048 x 2048 7.8, 6.8, 6.3; 8192 x 1280 (640) 10.4, 10.0, 11.4     128: 5.7, 4.5, 4.3; 8.1, 6.5, 6.0
+// Narrow strips, in workgroups of one block row and, at block size 128, one block: 64 columns a wave up to 256 tiles of 128 x 128, one
+// for each compute unit (FP16, half the bytes in flight a lane, up to 768); 32 columns for the smallest tensors and, in FP16 at block
+// sizes 64 and 128, up to 256 tiles.  Beyond, the waves fill the chip as they are and narrower ones only take more instructions.  With 128,
+// 64 and 32 columns in us: FP32 at block 32 63 tiles 4.1, 3.4, 3.2, 192 tiles 5.6, 5.0, 5.8, 384 tiles 6.3, 6.8, 7.7; FP16 768 tiles 10.7, 10.1,
+// 15.0, 1024 tiles 13.3, 14.0 (profiles/kernel_choice.txt).
 template <typename T, int B>
 static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t* q, int64_t ldq, float* s, int8_t* qT,
                             int64_t ldqT, float* sT, hipStream_t st) {
