@@ -139,6 +139,56 @@ __device__ __forceinline__ double wave_group_sum_f64(double v) {
                                  [](double x, auto bit) { return lane_xor_f64<decltype(bit)::value>(x); });
 }
 
+// Max-abs of 16 values folded into m: eight v_max3_f32 with absolute-value modifiers (the compiler's fmaxf
+// quiets each operand with an extra instruction first).
+__device__ __forceinline__ float amax16(float m, const float (&y)[16]) {
+#pragma unroll
+  for (int e = 0; e < 16; e += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(y[e]), "v"(y[e + 1]));
+  return m;
+}
+
+// The maxima over all lanes of N = 1, 2 or 4 values (none negative) at once: lane l ends with that of value lane_value<N>(l),
+// lane value_lane<N>(k) with that of value k.  A swap of half waves or rows between two values and one maximum do a step for
+// both, so that four values take 17 instructions where a butterfly each takes 80, and what follows from a maximum (Eq. 1's
+// scale, about 30 instructions) is computed once for all of them, each row of lanes for its own.
+template <int N>
+__device__ __forceinline__ float wave_max_of(const float (&m)[N]) {
+  static_assert(N == 1 || N == 2 || N == 4, "halves and rows of a wave");
+  // (the swaps read what inline assembly may just have written, which they have to keep two wait states away from)
+  const auto larger = [](auto p) __attribute__((always_inline)) {
+    float r;
+    asm("v_max_f32 %0, %1, %2\n\ts_nop 1" : "=v"(r) : "v"((int)p[0]), "v"((int)p[1]));
+    return r;
+  };
+  const auto bits = [](float v) __attribute__((always_inline)) { return __builtin_bit_cast(int, v); };
+  float v[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    v[k] = m[k];
+    asm("s_nop 1" : "+v"(v[k]));
+  }
+  const float a = larger(__builtin_amdgcn_permlane32_swap(bits(v[0]), bits(v[N > 1 ? 1 : 0]), false, false));
+  const float b = N == 4 ? larger(__builtin_amdgcn_permlane32_swap(bits(v[N - 2]), bits(v[N - 1]), false, false)) : a;
+  float r = larger(__builtin_amdgcn_permlane16_swap(bits(a), bits(b), false, false));
+#define JF_ROW_STEP(CTRL) r = __builtin_fmaxf(r, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(bits(r), CTRL, 0xf, 0xf, false)))
+  JF_ROW_STEP(0xB1);    // as lane_xor_i32
+  JF_ROW_STEP(0x4E);
+  JF_ROW_STEP(0x141);
+  JF_ROW_STEP(0x128);
+#undef JF_ROW_STEP
+  return r;
+}
+template <int N>
+__device__ __forceinline__ int lane_value(int lane) { return N == 1 ? 0 : N == 2 ? lane >> 5 : (lane >> 5) | ((lane >> 3) & 2); }
+template <int N>
+constexpr int value_lane(int k) { return N == 1 ? 0 : 32 * (k & 1) + 16 * (k >> 1); }
+// a double from a lane that is the same for all
+__device__ __forceinline__ double read_lane_f64(double v, int lane) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane), hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
 typedef __attribute__((address_space(3))) void* lds_ptr;
 // One direct-to-LDS load of 16 bytes per lane: lane l's bytes from ubase + voff go to LDS address lds + 16*l.
 // Written out because the compiler only selects the 64-bit per-lane address form for the builtin; the form with

@@ -57,19 +57,15 @@ __device__ __forceinline__ void gemm_fine_tile(const GemmArgs& g, const int tile
   constexpr int SEG = 64 / SPS;   // stages per segment of 64 scales
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const unsigned wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;   // this wave's quarter
 
   // tiles to XCDs as in gemm_tile: a contiguous run per XCD, in groups of 8 tile rows
   constexpr int GROUP_M = 8;
-  const int tiles_n = g.Nn / TN, tiles_m = g.M / TM;
-  const int xcd = tile_index & 7, idx = tile_index >> 3;
-  const int tile = xcd * (ntiles >> 3) + min(xcd, ntiles & 7) + idx;
-  const int group = tile / (GROUP_M * tiles_n), first_m = group * GROUP_M;
-  const int in_group = tile - group * GROUP_M * tiles_n, group_rows = min(GROUP_M, tiles_m - first_m);
-  const int m0 = (first_m + in_group % group_rows) * TM, n0 = (in_group / group_rows) * TN;
+  int m0, n0;
+  tile_origin<TM, TN, GROUP_M>(tile_index, ntiles, g.M, g.Nn, m0, n0);
 
-  const int nstages = (g.K + KC - 1) / KC, nkb = g.K / B;
+  const int nstages = (unsigned)(g.K + KC - 1) / KC, nkb = (unsigned)g.K / B;
   const int last_first = (nstages - 1) * SPS, overlap = nstages > 1 ? nstages * SPS - nkb : 0;   // see gemm_tile
   uint32_t offA = chunk_offset<TM, AK, KC>(wave * 64 + lane, TM, g.K, (uint32_t)g.lda);
   uint32_t offB = chunk_offset<TN, BK, KC>(wave * 64 + lane, TN, g.K, (uint32_t)g.ldb);
@@ -175,8 +171,8 @@ __device__ __forceinline__ void gemm_fine_tile(const GemmArgs& g, const int tile
   const int row = 16 * wm + (lane & 15), col = 16 * wn + 4 * (lane >> 4);
   if (g.Of) store_part(g.Of + (int64_t)(m0 + row) * g.Nn + n0 + col, make_float4(acc[0], acc[1], acc[2], acc[3]));
   if (!g.Oq) return;
-  float amax = fmaxf(fmaxf(fabsf(acc[0]), fabsf(acc[1])), fmaxf(fabsf(acc[2]), fabsf(acc[3])));
-  amax = wave_group_max<63>(amax);
+  const float quarter[1] = {fmaxf(fmaxf(fabsf(acc[0]), fabsf(acc[1])), fmaxf(fabsf(acc[2]), fabsf(acc[3])))};
+  float amax = wave_max_of<1>(quarter);
   if (lane == 0) s_amax[wave] = amax;
   __syncthreads();
   amax = fmaxf(fmaxf(s_amax[0], s_amax[1]), fmaxf(s_amax[2], s_amax[3]));

@@ -60,7 +60,7 @@ struct TileLayout {
   // (64) bytes starts at bank group 8*(r%2) (4*(r%4)), so the XOR term has to run through its 8 (4) values
   // over the rows that share that start.  M-major tiles are read with 8-byte transposing reads, 8 rows per
   // 16 lanes: 8 consecutive rows at a fixed chunk cover 8 bank groups.
-  static __device__ __forceinline__ int swz(int r) {
+  static __device__ __forceinline__ int swz(unsigned r) {
     if (KMAJOR) return (r / (16 / kCPR)) % kCPR;
     if (kCPR == 2) return (r / 8) % 2;   // 8 rows cover the banks once, half of them; the next 8 take the other half
     return (r / (kCPR == 4 ? 2 : 1)) % (kCPR == 16 ? 8 : kCPR);
@@ -114,12 +114,11 @@ struct FragAddr {
 // columns outside the matrix (outer_left: from the origin to its edge) and K beyond klim are clamped to valid addresses:
 // what they deliver only reaches outputs that are never stored, or K blocks of scale 0, so no zero fill is needed.
 template <int TILE, bool KMAJOR, int KC>
-__device__ __forceinline__ uint32_t chunk_offset(int slot_idx, int outer_left, int klim, uint32_t ld) {
+__device__ __forceinline__ uint32_t chunk_offset(unsigned slot_idx, unsigned outer_left, unsigned klim, uint32_t ld) {
   typedef TileLayout<TILE, KMAJOR, KC> L;
-  const int r = min(slot_idx / L::kCPR, L::kRows - 1);  // slots past the tile are padding: any valid source will do
-  const int c = (slot_idx % L::kCPR) ^ L::swz(r);
-  return KMAJOR ? (uint32_t)min(r, outer_left - 1) * ld + (uint32_t)min(16 * c, klim - 16)
-                : (uint32_t)min(r, klim - 1) * ld + (uint32_t)min(16 * c, outer_left - 16);
+  const unsigned r = min(slot_idx / L::kCPR, L::kRows - 1u);  // slots past the tile are padding: any valid source will do
+  const unsigned c = (slot_idx % L::kCPR) ^ L::swz(r);
+  return KMAJOR ? min(r, outer_left - 1) * ld + min(16 * c, klim - 16) : min(r, klim - 1) * ld + min(16 * c, outer_left - 16);
 }
 
 // f(integral_constant<int, I>) for I = BEGIN .. END-1, unrolled at compile time
@@ -141,6 +140,25 @@ __device__ __forceinline__ void fold(float (&acc)[N], const V& v, float t) {
     const float c = (float)v[r];
     asm("v_fmac_f32 %0, %1, %2" : "+v"(acc[r]) : "s"(t), "v"(c));
   }
+}
+
+// First row and column of the tile that a workgroup takes.  Workgroups are dealt round-robin to the 8 XCDs (each with its own
+// L2).  Renumber them so that every XCD works on one contiguous run of tiles, and order the tiles in groups of GROUP_M tile rows,
+// column by column inside a group: the workgroups that are resident on an XCD at the same time then form a compact patch
+// (GROUP_M tile rows x a few tile columns) that re-reads few distinct operand tiles from that XCD's L2.
+// All of it stands in front of a tile's first load, one instruction after the other: unsigned, and one division in all groups but
+// the last (with the lane offsets of the loads unsigned too, 50 of the 310 instructions in front of the first stage: 1024^3
+// 6.8 -> 6.65 us, 1056 x 800 -> 2080 8.7 -> 8.5).
+template <int TM, int TN, int GROUP_M>
+__device__ __forceinline__ void tile_origin(unsigned index, unsigned ntiles, int M, int Nn, int& m0, int& n0) {
+  const unsigned tiles_n = (unsigned)(Nn + TN - 1) / TN, tiles_m = (unsigned)(M + TM - 1) / TM;
+  const unsigned xcd = index & 7, tile = xcd * (ntiles >> 3) + min(xcd, ntiles & 7) + (index >> 3);
+  const unsigned group = tile / (GROUP_M * tiles_n), in_group = tile - group * GROUP_M * tiles_n;
+  const unsigned first_m = group * GROUP_M, group_rows = tiles_m - first_m;
+  unsigned row = in_group % GROUP_M, col = in_group / GROUP_M;
+  if (group_rows < GROUP_M) row = in_group % group_rows, col = in_group / group_rows;   // the last group
+  m0 = (int)((first_m + row) * TM);
+  n0 = (int)(col * TN);
 }
 
 // Compile-time shape of one kernel instance: tile, stage and LDS ring.
@@ -207,22 +225,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   };
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const unsigned wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;  // first 32-granule of this wave inside the tile
 
-  // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Renumber them so that every XCD
-  // works on one contiguous run of tiles, and order the tiles in groups of GROUP_M tile rows, column by column
-  // inside a group: the workgroups that are resident on an XCD at the same time then form a compact patch
-  // (GROUP_M tile rows x a few tile columns) that re-reads few distinct operand tiles from that XCD's L2.
   constexpr int GROUP_M = TM >= 256 ? 4 : 8;
-  const int tiles_n = (g.Nn + TN - 1) / TN, tiles_m = (g.M + TM - 1) / TM;
-  const int xcd = tile_index & 7, idx = tile_index >> 3;
-  const int tile = xcd * (ntiles >> 3) + min(xcd, ntiles & 7) + idx;
-  const int group = tile / (GROUP_M * tiles_n), first_m = group * GROUP_M;
-  const int in_group = tile - group * GROUP_M * tiles_n, group_rows = min(GROUP_M, tiles_m - first_m);
-  const int m0 = (first_m + in_group % group_rows) * TM, n0 = (in_group / group_rows) * TN;
+  int m0, n0;
+  tile_origin<TM, TN, GROUP_M>(tile_index, ntiles, g.M, g.Nn, m0, n0);
 
-  const int nstages = (g.K + KC - 1) / KC, nkb = g.K / B;
+  const int nstages = (unsigned)(g.K + KC - 1) / KC, nkb = (unsigned)g.K / B;
   constexpr int NKB = SPS / KPB;  // quantization blocks along K per stage
   // Stages are whole: when K is not a multiple of KC the last one starts earlier, `overlap` blocks back, at K - KC, and
   // the blocks it shares with the one before it carry scale 0.  (A K shorter than one stage is clamped in the lane
@@ -332,11 +342,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
     const int kb = min(scale_block(seg * SEG + lane), nkb - 1);
 #pragma unroll
     for (int r0 = 0; r0 < Shape::SCALE_ROWS; r0 += NW) {
-      const int r = r0 + wave;
+      const int r = r0 + (int)wave;
       if (r < Shape::SCALE_ROWS) {
         const int rb = r - Shape::SCALE_ROWS_A;
-        const float* p = rb < 0 ? g.SA + (int64_t)(min(m0 + B * r, g.M - B) / B) * g.sa_p + (int64_t)kb * g.sa_k
-                                : g.SB + (int64_t)(min(n0 + B * rb, g.Nn - B) / B) * g.sb_p + (int64_t)kb * g.sb_k;
+        const float* p = rb < 0 ? g.SA + (int64_t)((unsigned)min(m0 + B * r, g.M - B) / B) * g.sa_p + (int64_t)kb * g.sa_k
+                                : g.SB + (int64_t)((unsigned)min(n0 + B * rb, g.Nn - B) / B) * g.sb_p + (int64_t)kb * g.sb_k;
         load_lds_4_vaddr(p, s_scale, ((seg & 1) * Shape::SCALE_ROWS + r) * 256);
       }
     }
@@ -509,43 +519,45 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   __builtin_amdgcn_s_waitcnt(7 << 4 | 15 << 8);   // vmcnt 0: nothing may land in the ring any more
   if (DUMP) return;
 
-  // ---- epilogue: optional FP32 store, per-block max-abs, Eq. 1, packed INT8 store
-  float amax[WM][WN];
+  // ---- epilogue: optional FP32 store, per-block max-abs, Eq. 1, packed INT8 store.  Vector-ALU work like the loop, and the last
+  // workgroup's has nothing beside it: the maxima of the wave's blocks are reduced together and Eq. 1's scale is computed once for all
+  // of them (four blocks: 600 -> 470 instructions, 4096 x 768 -> 3072 23.85 -> 23.2 us, 8192 x 1280 -> 5120 112 -> 110).
+  // Pieces of quantization blocks that this wave holds: at B = 32 its sub-blocks, else one, whole or shared with other waves.
+  constexpr int PM = WM * 32 < B ? WM : B / 32, PN = WN * 32 < B ? WN : B / 32, PIECES_N = WN / PN, PIECES = WM / PM * PIECES_N;
+  float piece[PIECES];
 #pragma unroll
-  for (int a = 0; a < WM; ++a)
+  for (int k = 0; k < PIECES; ++k) {
+    piece[k] = 0.0f;
 #pragma unroll
-    for (int b = 0; b < WN; ++b) {
-      float m = 0.0f;
+    for (int a = 0; a < PM; ++a)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) m = fmaxf(m, fabsf(acc[a][b][r]));
-      amax[a][b] = wave_group_max<63>(m);
-    }
-  if (B > 32) {
-    if (lane == 0) {
-#pragma unroll
-      for (int a = 0; a < WM; ++a)
-#pragma unroll
-        for (int b = 0; b < WN; ++b) s_amax[wm0 + a][wn0 + b] = amax[a][b];
-    }
+      for (int b = 0; b < PN; ++b) piece[k] = amax16(piece[k], acc[k / PIECES_N * PM + a][k % PIECES_N * PN + b]);
+  }
+  float amax = wave_max_of<PIECES>(piece);   // of the lane's piece
+  if constexpr (PM * 32 < B || PN * 32 < B) {
+    static_assert(PIECES == 1, "the waves of a block exchange one value each");
+    if (lane == 0) s_amax[wm0][wn0] = amax;
     __syncthreads();
     constexpr int G = B / 32;
+    const int ga = wm0 / G * G, gb = wn0 / G * G;
 #pragma unroll
-    for (int a = 0; a < WM; ++a)
+    for (int x = 0; x < G; x += WM)
 #pragma unroll
-      for (int b = 0; b < WN; ++b) {
-        const int ga = ((wm0 + a) / G) * G, gb = ((wn0 + b) / G) * G;
-        float m = 0.0f;
-        for (int x = 0; x < G; ++x)
-          for (int y = 0; y < G; ++y) m = fmaxf(m, s_amax[ga + x][gb + y]);
-        amax[a][b] = m;
-      }
+      for (int y = 0; y < G; y += WN) amax = fmaxf(amax, s_amax[ga + x][gb + y]);
   }
-  const int ln = g.Nn / B;
+  float scale_out = 0.0f;
+  double inv_out = 0.0;
+  if (g.Oq) {
+    block_scale(amax, scale_out, inv_out);
+    const int k = lane_value<PIECES>(lane), row = m0 + 32 * (wm0 + k / PIECES_N * PM), col = n0 + 32 * (wn0 + k % PIECES_N * PN);
+    if (lane == value_lane<PIECES>(k) && row < g.M && col < g.Nn && row % B == 0 && col % B == 0)
+      store_out(&g.Os[(int64_t)(row / B) * (g.Nn / B) + col / B], scale_out);
+  }
   // The code tile is staged in the operand ring: in one slot, or split by rows over two slots when a slot is
   // smaller than the tile.  The last stage of the K loop ends without a barrier, so a wave may still be reading its
   // fragments of that stage out of the ring while a faster one is already here: meet once before the ring is
-  // overwritten (for B > 32 the barrier of the max-abs exchange above has done that).
-  if (B == 32 && g.Oq != nullptr) __syncthreads();
+  // overwritten (where waves share a block, the barrier of the max-abs exchange above has done that).
+  if (PM * 32 >= B && PN * 32 >= B && g.Oq != nullptr) __syncthreads();
   constexpr int CODE_ROWS_PER_SLOT = TM * TN <= STAGE_BYTES ? TM : TM / 2;
   static_assert(CODE_ROWS_PER_SLOT * TN <= STAGE_BYTES, "half the code tile fits a ring slot");
   auto code_row = [&](int row) __attribute__((always_inline)) -> int8_t* {
@@ -566,10 +578,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
                     make_float4(acc[a][b][4 * q4], acc[a][b][4 * q4 + 1], acc[a][b][4 * q4 + 2], acc[a][b][4 * q4 + 3]));
       }
       if (g.Oq) {
-        float scale;
-        double inv;
-        block_scale(amax[a][b], scale, inv);
-        if (lane == 0 && (mrow0 % B) == 0 && (ncol0 % B) == 0) store_out(&g.Os[(int64_t)(mrow0 / B) * ln + ncol0 / B], scale);
+        const double inv = PIECES == 1 ? inv_out : read_lane_f64(inv_out, value_lane<PIECES>(a / PM * PIECES_N + b / PN));
         // Codes go to LDS first, laid out as the TM x TN byte tile with its 16-byte chunks XOR-swizzled by the
         // row, so that the tile can be written to memory as whole rows.
         const int row = 32 * (wm0 + a) + (lane & 31);

@@ -82,14 +82,6 @@ struct Strip {
 
 typedef Strip<32> Strip32;
 
-// max-abs of 16 values folded into m: eight v_max3_f32 with absolute-value modifiers (the compiler's fmaxf
-// quiets each operand with an extra instruction first)
-__device__ __forceinline__ float amax16(float m, const float (&y)[16]) {
-#pragma unroll
-  for (int e = 0; e < 16; e += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(y[e]), "v"(y[e + 1]));
-  return m;
-}
-
 // Block max-abs, over the lanes of a strip that share a block column and over the waves that share the block through `exchange`
 // (up to four values per wave), then Eq. 1's scale.  At block sizes 64 and 128 every wave of the workgroup has to get here.
 template <int B, int WAVES, int RW>
