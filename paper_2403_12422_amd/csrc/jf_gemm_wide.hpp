@@ -12,6 +12,7 @@
 //   block 128  8192^3           593 / 594 / 598 -> 528 / 533 / 531      16384 x 4096 -> 11008  876 / 787 / 840 -> 734 / 712 / 731
 //   block 128  4096^3           79.5 / 80.2 / 80.7 -> 72.0 / 72.8 / 72.6
 //   block 64   8192^3           764 / 738 / 722 -> 708 / 687 / 725      4096^3  102.5 / 100.0 / 98.3 -> 92.6 / 91.4 / 90.5
+// and less since, by the priorities in run_stage and the instruction that WideMfma chooses (8192^3 at block 128 forward 541 -> 514).
 // (At block 64 the vector ALU bounds the loop, for which two waves per SIMD do a little worse than three: what is gained is the
 // start and end of the tiles, and it is lost again where 256x256 tiles fill the compute units unevenly.)
 #pragma once
@@ -31,23 +32,42 @@ struct WideShape {
   static_assert(RING_A <= 65536 && LDS_BYTES - RING_A <= 65536, "16-bit offsets");
 };
 
+// A wave's MFMA on the sub-blocks of a 256x256 tile: v_mfma_i32_32x32x32_i8, or v_mfma_i32_16x16x64_i8 on their quarters.  Both take
+// 16 bytes of K per lane and the same matrix cycles per multiply-add.  The latter writes its INT32 tile, and reads it in a chain, half
+// as often, which is power, what bounds large products at B = 128, at the price of twice the instructions to issue: bare chains of
+// random codes with their folds 24.9 -> 23.7 ns per 32x32x32, of zeros, at full clock, 18.5 -> 20.9.  8192^3 at B = 128 forward 536 -> 513
+// us, 16384 x 4096 -> 11008 forward 741 -> 720, input gradient 714 -> 694; where both operands are read transposed, by twice the LDS
+// instructions, it loses (weight gradient 734 -> 742), and at B = 64 the bare chains do (33.4 -> 34.9).
+template <int B, bool AK>
+struct WideMfma {
+  static constexpr bool QUARTERS = B == 128 && AK;
+  static constexpr int ROWS = QUARTERS ? 16 : 32;   // rows of a fragment; its 64 lanes hold 1 KB either way
+};
+
 // LDS addresses of an operand's fragments: as FragAddr, of whose offsets every one is the first with bits of the chunk number
-// toggled, so that a lane keeps one address per operand.
-template <int TILE, bool KMAJOR, int KC>
+// toggled, so that a lane keeps one address per operand.  Fragment j of a sub-tile: K step j of 32 bytes, or, of 16 rows, the half
+// j % 2 of the rows and 64 bytes of K from 64 (j / 2) on.
+template <int TILE, bool KMAJOR, int KC, int ROWS>
 struct WideFrag {
   typedef TileLayout<TILE, KMAJOR, KC> L;
   uint32_t at;
   __device__ __forceinline__ void init(const int8_t* ring, int region, int sub0, int lane) {
-    FragAddr<TILE, KMAJOR, KC, 1> first;
-    first.init(sub0, lane);
-    at = (uint32_t)(uintptr_t)(lds_ptr)(ring) + (uint32_t)(region + first.off[0]);
-  }
-  // fragment of sub-tile u (relative to the wave's first), K step j, of the stage `stage` bytes into the region
-  __device__ __forceinline__ v4i read(int stage, int u, int j) const {
+    int first;
     if (KMAJOR) {
-      return *(lds_v4i)(uintptr_t)((at ^ (32 * j)) + stage + u * (32 * L::kCPR * 16));
+      first = 16 * L::slot(sub0 * 32 + lane % ROWS, lane / ROWS);
+    } else {   // transposing reads, see FragAddr
+      const int i = lane & 15, g = lane >> 4;
+      first = 16 * L::slot(16 * (ROWS == 32 ? g >> 1 : g) + (i >> 1), sub0 * 2 + (ROWS == 32 ? g & 1 : 0)) + 8 * (i & 1);
+    }
+    at = (uint32_t)(uintptr_t)(lds_ptr)(ring) + (uint32_t)(region + first);
+  }
+  // fragment j of sub-tile u (relative to the wave's first), of the stage `stage` bytes into the region
+  __device__ __forceinline__ v4i read(int stage, int u, int j) const {
+    const int k = ROWS == 32 ? 32 * j : 64 * (j >> 1), half = ROWS == 32 ? 0 : j & 1;   // first byte of K, rows 16 half on
+    if (KMAJOR) {
+      return *(lds_v4i)(uintptr_t)((at ^ k) + stage + (u * 32 + half * 16) * (L::kCPR * 16));
     } else {
-      const uint32_t p = (at ^ (32 * u)) + stage + j * (32 * L::kCPR * 16);
+      const uint32_t p = (at ^ (32 * u + 16 * half)) + stage + k * (L::kCPR * 16);
       const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(uintptr_t)(p));
       const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(uintptr_t)(p + 8 * L::kCPR * 16));
       return v4i{lo[0], lo[1], hi[0], hi[1]};
@@ -95,6 +115,14 @@ __device__ __forceinline__ KernelArgs read_again(KernelArgs a) {
   return a;
 }
 
+// The lane's number, computed where it is needed, so that neither it nor what follows from it takes a register through the K loop (where
+// one too many goes to scratch memory, whose loads wait for the stages in flight: weight gradient 735 -> 796 us).
+__device__ __forceinline__ int lane_again() {
+  int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
 // Tiles tile_index, tile_index + stride, ... of `ntiles`, on a workgroup of eight waves; tile_index < ntiles.
 template <int B, bool AK, bool BK>
 __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index, const int stride, const int ntiles,
@@ -136,6 +164,7 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
     const KernelArgs g = read_again(args);
     int m, n;
     origin_of(load_index, m, n);
+    const int lane = lane_again();
     loadA.set_tile(g->A + (AK ? (int64_t)m * g->lda : (int64_t)m), g->M - m, (uint32_t)g->lda, wave, lane);
     loadB.set_tile(g->Bm + (BK ? (int64_t)n * g->ldb : (int64_t)n), g->Nn - n, (uint32_t)g->ldb, wave, lane);
     load_left = nstages;
@@ -191,8 +220,9 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
   // i + 1 is issued beside the fold of unit i.  A fragment is read into the registers that have just come out of use: those of
   // the second sub-block row beside unit WN - 2, behind the last chain of the first; those of the next stage beside the
   // units from SYNC on, which the barrier stands before.
-  WideFrag<TM, AK, KC> fragA;
-  WideFrag<TN, BK, KC> fragB;
+  constexpr bool QUARTERS = WideMfma<B, AK>::QUARTERS;
+  WideFrag<TM, AK, KC, WideMfma<B, AK>::ROWS> fragA;
+  WideFrag<TN, BK, KC, WideMfma<B, AK>::ROWS> fragB;
   fragA.init(s_ring, 0, wm0, lane);
   fragB.init(s_ring, S::RING_A, wn0, lane);
   v4i fa[KPB], fb[WN][KPB];
@@ -201,9 +231,19 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
   const v16i zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   auto read_a = [&](int slot, int a, int j) __attribute__((always_inline)) { fa[j] = fragA.read(slot * S::A_BYTES, a, j); };
   auto read_b = [&](int slot, int b, int j) __attribute__((always_inline)) { fb[b][j] = fragB.read(slot * S::B_BYTES, b, j); };
-  auto chain_step = [&](int i, int js, v16i& dst) __attribute__((always_inline)) {
-    dst = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[i % WN][js], fa[js], js == 0 ? zero16 : dst, 0, 0, 0);
+  // step js of the chain of unit i: an MFMA, or two, of the quarters (js % 2, 0) and (js % 2, 1) over half of K (part 0 and 1)
+  auto chain_step = [&](int i, int js, int part, v16i& dst) __attribute__((always_inline)) {
+    if constexpr (QUARTERS) {
+      const int q = 2 * (js & 1) + part;
+      const v4i c = js < 2 ? v4i{0, 0, 0, 0} : v4i{dst[4 * q], dst[4 * q + 1], dst[4 * q + 2], dst[4 * q + 3]};
+      const v4i d = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[i % WN][(js & 2) + part], fa[js], c, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) dst[4 * q + r] = d[r];
+    } else {
+      dst = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[i % WN][js], fa[js], js == 0 ? zero16 : dst, 0, 0, 0);
+    }
   };
+  constexpr int PARTS = QUARTERS ? 2 : 1;   // MFMAs of a step; each has its share of the fold behind it
   auto zero_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int a = 0; a < WM; ++a)
@@ -225,6 +265,10 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
     static_for<0, NT>([&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value, a = i / WN, b = i % WN;
       v16i &cur = vi[i & 1], &nxt = vi[(i & 1) ^ 1];
+      // The arbiter favours the older of a SIMD's two waves, which then waits at the barrier while the other, alone, leaves the pipes
+      // idle.  Between two barriers the wave that is behind goes first (16384 x 4096 -> 11008 at B = 128 759 / 732 / 749 -> 741 / 715 /
+      // 734 us forward / dgrad / wgrad, both gradients 1488 -> 1450; 4096^3 at B = 64 93.2 / 92.5 / 91.9 -> 92.8 / 91.4 / 89.7).
+      if constexpr (i % 2 == 0) __builtin_amdgcn_s_setprio(3 - ((i - SYNC + NT) % NT) / 2);
       if constexpr (i == SYNC) {
         if (NBUF > 2 && !after_store) wait_loads(std::integral_constant<int, LOADS * (NBUF - 2)>());
         else wait_loads(std::integral_constant<int, 0>());
@@ -234,10 +278,10 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
       }
       static_for<0, KPB>([&](auto js_tag) __attribute__((always_inline)) {
         constexpr int js = decltype(js_tag)::value;
-        chain_step((i + 1) % NT, js, nxt);
+        chain_step((i + 1) % NT, js, 0, nxt);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (i == WN - 2) read_a(slot, 1, js);
-        if constexpr (i == 2 * WN - 2) read_a(nslot, 0, js);
+        if constexpr (PARTS == 1 && i == WN - 2) read_a(slot, 1, js);
+        if constexpr (PARTS == 1 && i == 2 * WN - 2) read_a(nslot, 0, js);
         if constexpr (i >= SYNC) {
           read_b(nslot, i - SYNC, js);
           // the loads of the stage NBUF ahead, into the slot of which every wave has read the last fragment
@@ -246,8 +290,17 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
             if constexpr (decltype(n)::value * P / LOADS == at) issue_load(u_tag, n);
           });
         }
-        fold<16 * js / KPB, 16 * (js + 1) / KPB>(acc[a][b], cur, scale[b * NSB / WN]);
+        constexpr int R0 = 16 * js / KPB, R1 = 16 * (js + 1) / KPB, RM = QUARTERS ? (R0 + R1) / 2 : R1;
+        fold<R0, RM>(acc[a][b], cur, scale[b * NSB / WN]);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PARTS == 2) {
+          chain_step((i + 1) % NT, js, 1, nxt);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (i == WN - 2) read_a(slot, 1, js);
+          if constexpr (i == 2 * WN - 2) read_a(nslot, 0, js);
+          fold<RM, R1>(acc[a][b], cur, scale[b * NSB / WN]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       });
     });
 #pragma unroll
@@ -260,6 +313,7 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
   // together (written through, 8192^3 at block 128 takes 560 instead of 549 us, 16384 x 4096 -> 11008 802 instead of 766).
   auto store_tile = [&](int m0, int n0) __attribute__((always_inline)) {
     const KernelArgs g = read_again(args);
+    const int lane = lane_again();
     float amax[NSB];
 #pragma unroll
     for (int k = 0; k < NSB; ++k) {
@@ -278,7 +332,8 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
       meet();
       amax[0] = fmaxf(amax[0], s_amax[wave ^ 2]);
     }
-    const int mrow0 = m0 + 32 * wm0, m = mrow0 + (lane & 31), h = lane >> 5;
+    const int mrow0 = m0 + 32 * wm0, h = lane >> 5, g4 = lane >> 4;
+    const int first_row = QUARTERS ? lane & 15 : lane & 31;
     if (mrow0 >= g->M) return;   // wave-uniform, as the skipped columns below
 #pragma unroll
     for (int k = 0; k < NSB; ++k) {
@@ -293,11 +348,13 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
 #pragma unroll
         for (int b = 0; b < WN / NSB; ++b) {
           const float(&v)[16] = acc[a][k * (WN / NSB) + b];
-          const int64_t at = (int64_t)(m + 32 * a) * g->Nn + ncol0 + 32 * b;
+          // Quad q holds columns 8 q + 4 h on of row lane % 32, or 16 (q % 2) + 4 g4 on of row 16 (q / 2) + lane % 16.
+          const int64_t at = (int64_t)(mrow0 + 32 * a + first_row) * g->Nn + ncol0 + 32 * b;
           if (g->Of) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-              store_part(g->Of + at + 8 * q + 4 * h, make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]));
+              store_part(g->Of + at + (QUARTERS ? (int64_t)16 * (q >> 1) * g->Nn + 16 * (q & 1) + 4 * g4 : 8 * q + 4 * h),
+                         make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]));
           }
           if (g->Oq) {
             uint32_t c[4];
@@ -305,7 +362,13 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
             for (int q = 0; q < 4; ++q) c[q] = quantize4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3], inv);
             const auto even = __builtin_amdgcn_permlane32_swap(c[0], c[2], false, false);
             const auto odd = __builtin_amdgcn_permlane32_swap(c[1], c[3], false, false);
-            store_part(g->Oq + at + 16 * h, v4i{(int)even[0], (int)even[1], (int)odd[0], (int)odd[1]});
+            if constexpr (QUARTERS) {   // rows of lanes too: a lane ends with the 16 bytes of quarter g4
+              const auto lo = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
+              const auto hi = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
+              store_part(g->Oq + at + (int64_t)16 * (g4 >> 1) * g->Nn + 16 * (g4 & 1), v4i{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]});
+            } else {
+              store_part(g->Oq + at + 16 * h, v4i{(int)even[0], (int)even[1], (int)odd[0], (int)odd[1]});
+            }
           }
         }
     }
@@ -326,7 +389,9 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
     read_a(0, 0, decltype(j)::value);
     static_for<0, WN>([&](auto b) __attribute__((always_inline)) { read_b(0, decltype(b)::value, decltype(j)::value); });
   });
-  static_for<0, KPB>([&](auto js) __attribute__((always_inline)) { chain_step(0, decltype(js)::value, vi[0]); });
+  static_for<0, KPB * PARTS>([&](auto n) __attribute__((always_inline)) {
+    chain_step(0, decltype(n)::value / PARTS, decltype(n)::value % PARTS, vi[0]);
+  });
 
   // passes over the ring; a tile begins at the slot behind the last stage of the tile before it
   bool stored = false;
