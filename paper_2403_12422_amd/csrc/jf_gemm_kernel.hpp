@@ -384,6 +384,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   constexpr bool STEPWISE = GemmPipeline<B, WM, WN>::STEPWISE, ONE_SET = GemmPipeline<B, WM, WN>::ONE_SET;
   static_assert(!STEPWISE || (KPB == 1 && SPS % 2 == 0), "the register sets alternate");
   static_assert(!ONE_SET || (WM == 2 && WN == 2 && NT == 4), "the order in which fragments come out of use");
+  // Two waves of a workgroup on every SIMD: priorities fall from one meeting of the waves to the next instead of over the whole loop,
+  // so that the two arrive together (256x128 tiles: 8192^3 at B = 32 990 / 986 / 959 -> 982 / 975 / 947 us, 4096 x 4096 -> 2048 at B = 128
+  // forward 41.6 -> 40.1; eight waves of one sub-block, six to a SIMD, gain 1 % alone and lose 1.4 as a pair).
+  constexpr bool BY_STAGE = NW == 8 && NTILE > 1;
   constexpr int SETS = STEPWISE || !ONE_SET ? 2 : 1, STEPS = STEPWISE ? 1 : SPS;   // register sets, K steps in each
   constexpr int AHEAD = NTILE == 1 ? 2 : 1;   // STEPWISE: K steps between a read and the step beside which it stands
   v16i vi[2];
@@ -429,6 +433,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
     static_for<0, NT>([&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value, kb = i / NTILE, q = i % NTILE;
       v16i &cur = vi[i & 1], &nxt = vi[(i & 1) ^ 1];
+      if constexpr (BY_STAGE) {
+        constexpr int done = (i - SYNC + NT) % NT;   // units since the last meeting
+        if constexpr (done == 0 || 4 * done / NT != 4 * (done - 1) / NT) __builtin_amdgcn_s_setprio(3 - 4 * done / NT);
+      }
       if constexpr (i == SYNC) wait_stage(std::integral_constant<int, NBUF - 2>());
       // The loads of the stage NBUF ahead, into the slot that this one has left: all at once, or, from the eight waves of
       // a compute unit's only workgroup, one after another over the units -- requested together they wait for each other
@@ -498,7 +506,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
     // The instruction arbiter favours the oldest wave of a SIMD, so co-resident waves would finish one after
     // the other and leave the SIMD to a single wave at the end.  Each wave therefore lowers its own priority
     // as it advances: whoever is ahead yields, and the waves of a SIMD reach the end together.
-    if (4 * t < nstages) __builtin_amdgcn_s_setprio(3);
+    if (BY_STAGE) {
+    } else if (4 * t < nstages) __builtin_amdgcn_s_setprio(3);
     else if (2 * t < nstages) __builtin_amdgcn_s_setprio(2);
     else if (4 * t < 3 * nstages) __builtin_amdgcn_s_setprio(1);
     else __builtin_amdgcn_s_setprio(0);
