@@ -557,7 +557,11 @@ static int32_t layernorm_fwd(const int8_t* X, const float* SX, const float* row_
     LayerNormRows a{};
     a.X = X; a.SX = SX; a.row_mean = row_mean; a.row_sumsq = row_sumsq; a.gamma = gamma; a.beta = beta; a.eps = eps;
     a.rows = (int)N; a.cols = (int)C; a.Y = Y; a.SY = SY; a.mean = mean; a.rstd = rstd;
+    const int64_t grid_bytes = N / block * (C / block) * 4, part_bytes = N * (C / block) * 4;
+    const MemRange in[] = {{X, N * C}, {SX, grid_bytes}, {row_mean, part_bytes}, {row_sumsq, part_bytes}, {gamma, 4 * C}, {beta, 4 * C}};
+    const MemRange out[] = {{Y, N * C}, {SY, grid_bytes}, {mean, 4 * N}, {rstd, 4 * N}};
     if (!whole_rows) launch_layernorm_wide(a, st);
+    else if (block == 32 && layernorm_split_parts(N, C, false) > 1 && !any_overlap(out, in)) launch_layernorm_split(a, st);
     else (block == 32 ? launch_layernorm_rows_b32 : block == 64 ? launch_layernorm_rows_b64 : launch_layernorm_rows_b128)(a, st);
     return launch_status();
   }
@@ -629,7 +633,10 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
     a.dX = dX; a.SdX = SdX; a.partials = partials;
     a.dgamma = dgamma; a.dbeta = dbeta;
     if (!whole_rows) nparts = launch_layernorm_bwd_wide(a, st);
-    else
+    else if (block == 32 && layernorm_split_parts(N, C, true) > 1 && !sums_in_place && !any_overlap(out, in)) {
+      launch_layernorm_bwd_split(a, st);
+      return launch_status();
+    } else
       nparts = (block == 32 ? launch_layernorm_bwd_rows_b32 : block == 64 ? launch_layernorm_bwd_rows_b64 : launch_layernorm_bwd_rows_b128)(
           a, sums_in_place || any_overlap(out, in), st);
     const int32_t rc = launch_status();

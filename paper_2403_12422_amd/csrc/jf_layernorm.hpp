@@ -83,6 +83,36 @@ __device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float 
 // Column of the strip whose sums a lane ends with: 4 (j % 4) behind this one, of a for j < 4, of b beyond.
 __device__ __forceinline__ int reduced_column(int lane) { return 16 * (lane & 7) + (((lane >> 4) & 1) | ((lane >> 5) << 1)); }
 
+// Sums over the 32 lanes of each half wave of 32 values, by halves: a step adds two values at once, lanes with the bit clear for one,
+// with it set for the other (rows of lanes, then halves of a row and of those, by masked moves; then whole quads): 110 instructions, a
+// butterfly for each value takes 480.  Every lane ends with one of the 32 sums in v[0]; returned is which.
+__device__ __forceinline__ int reduce_rows_of_32(float (&v)[32], int lane) {
+  const auto bits = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(int, x); };
+  const auto real = [](int x) __attribute__((always_inline)) { return __builtin_bit_cast(float, x); };
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const auto p = __builtin_amdgcn_permlane16_swap(bits(v[2 * j]), bits(v[2 * j + 1]), false, false);
+    v[j] = real((int)p[0]) + real((int)p[1]);
+  }
+  // of a and b, lanes in BANKS take b, each plus its partner's across STEP
+#define JF_MERGE(A, B, BANKS, STEP)                                                                        \
+  (real(__builtin_amdgcn_update_dpp(bits(A), bits(B), 0xE4, 0xf, BANKS, false)) +                          \
+   real(__builtin_amdgcn_mov_dpp(__builtin_amdgcn_update_dpp(bits(B), bits(A), 0xE4, 0xf, BANKS, false), STEP, 0xf, 0xf, false)))
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = JF_MERGE(v[2 * j], v[2 * j + 1], 0xC, 0x128);    // across 8 lanes
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = JF_MERGE(v[2 * j], v[2 * j + 1], 0xA, 0x141);    // lane i and 7 - i
+#undef JF_MERGE
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    v[j] += lane_xor_f32<0>(v[j]);
+    v[j] += lane_xor_f32<1>(v[j]);
+  }
+  const int j = lane & 3;
+  v[0] = j == 0 ? v[0] : j == 1 ? v[1] : j == 2 ? v[2] : v[3];
+  return 8 * j + (lane & 4) + ((lane >> 2) & 2) + ((lane >> 4) & 1);
+}
+
 struct LayerNormRows {
   const int8_t* X;
   const float *SX, *row_mean, *row_sumsq, *gamma, *beta;   // row partials nullable: statistics of the codes themselves
@@ -124,6 +154,20 @@ void launch_layernorm_rows_b128(const LayerNormRows& a, hipStream_t st);
 int launch_layernorm_bwd_rows_b32(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
 int launch_layernorm_bwd_rows_b64(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
 int launch_layernorm_bwd_rows_b128(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
+
+// How many workgroups share a row group at block size 32 (jf_layernorm_split.hip), 1: the one-pass kernels.  Not where an output shares
+// memory with an input, which the other workgroups of a group still read.  Every workgroup needs a compute unit to itself, backward with
+// those that own columns (32 each, behind the rows' workgroups, which come in eights); forward four parts pay for half the chip
+// only.  One workgroup, two, four in us: forward 1024 x 1280 6.65, 5.68, 5.36; 1536 x 768 5.42, 4.72, 4.83; 4096 x 768 5.58, 4.94, 6.5;
+// 6144 x 768 5.71, 6.69, 7.6; backward 1056 x 800 6.6, 6.1, 5.9; 1536 x 1536 8.6, 8.25, 8.05; 2048 x 2048 12.1, 10.05, 15; 3072 x 1536 14.1,
+// 9.65, 14.3; 4096 x 768 10.3, 13.9, 16.9.
+inline int layernorm_split_parts(int64_t N, int64_t C, bool backward) {
+  const int64_t groups = backward ? (N / 32 + 7) / 8 * 8 : N / 32, units = 256 - (backward ? C / 32 : 0);
+  if (C > 2048) return 1;
+  return 4 * groups <= (backward ? units : 128) ? 4 : 2 * groups <= units ? 2 : 1;
+}
+void launch_layernorm_split(LayerNormRows a, hipStream_t st);
+void launch_layernorm_bwd_split(LayerNormBwdRows a, hipStream_t st);
 
 // Whether the kernels for wider rows (jf_layernorm_wide.hip) take a pass at block size 32, and their launches; the backward one
 // returns its number of partial rows (at most 256 and at most rows / 32).  Forward not from the row partials of an Add: those say what

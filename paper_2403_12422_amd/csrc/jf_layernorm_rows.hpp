@@ -223,47 +223,60 @@ constexpr int kBwdG = 4096, kBwdScaleX = 8192, kBwdScaleG = kBwdScaleX + 256, kB
               kBwdGamma = kBwdRstd + 128, kBwdMeans = kBwdGamma + 512, kBwdWaveBytes = kBwdMeans + 256;
 constexpr int kBwdRowBytes = 2 * 32 * 8;
 
-// dgamma and dbeta of one block column straight from g and x: a lane owns 16 columns of row l % 32 of its wave's row groups.
-// The column sums need nothing of the row pass, only its operands a second time, which for a short tensor come out of L2:
-// up to 2048 rows this saves the launch that adds the partial rows (512 x 544: 16.2 -> 13.3 us forward and backward), and
-// the row pass 8 of its 20 instructions per element.  Beyond that, or with few waves in a workgroup (2048 x 160: two), the
-// workgroups of the few block columns take longer than the row pass.
+// dgamma and dbeta of 32 columns straight from g and x: a lane owns 16 columns of row l % 32 of its wave's row groups.
+// The column sums need nothing of the row pass, only its operands a second time, which for a short tensor come out of L2: this saves the
+// launch that adds the partial rows, and the row pass 8 of its 20 instructions per element.  Bound by the lines that a compute unit
+// pulls in for a quarter of each: with many rows the workgroups of the few block columns take longer than the row pass (4096 x 768 10.3
+// -> 13.9 us; with 16 columns to a workgroup 16.5).
 template <int B>
-__device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, int group, float* s_sum) {
+__device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, int index, float* s_sum) {
   const int lane = threadIdx.x & 63, row = lane & 31, waves = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // A line of 128 columns belongs to four of these workgroups: they are on one XCD (to which workgroups come in turns), so that its L2
+  // fetches the line once.
+  const int columns = a.cols / 32, xcd = index & 7, group = xcd * (columns >> 3) + min(xcd, columns & 7) + (index >> 3);
   const int col = group * 32 + 16 * (lane >> 5), lc = a.cols / B;
-  float sgx[16], sgb[16];
+  float sums[32];   // of g xhat, then of g
 #pragma unroll
-  for (int e = 0; e < 16; ++e) sgx[e] = sgb[e] = 0.0f;
-  for (int g = wave; g < a.rows / 32; g += waves) {
-    const int64_t at = (int64_t)(g * 32 + row) * a.cols + col;
-    const uint4 px = *reinterpret_cast<const uint4*>(a.X + at), pg = *reinterpret_cast<const uint4*>(a.G + at);
-    const int64_t block = (int64_t)(g / (B / 32)) * lc + group / (B / 32);
-    const float rs = a.rstd[g * 32 + row], sg = a.SG[block];
-    const float kx = a.SX[block] * rs, cx = -a.mean[g * 32 + row] * rs;
+  for (int e = 0; e < 32; ++e) sums[e] = 0.0f;
+  // four row groups requested together: one after the other each waits for memory by itself (2048 x 768 7.9 -> 7.65 us, and with the
+  // sums over the lanes by halves 7.0)
+  constexpr int AHEAD = 4;
+  const int groups = a.rows / 32;
+  for (int first = wave; first < groups; first += AHEAD * waves) {
+    uint4 px[AHEAD], pg[AHEAD];
+    float rs[AHEAD], mu[AHEAD], sx[AHEAD], sg[AHEAD];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      float x[4], gr[4];
-      unpack4(dword_of(px, d), x);
-      unpack4(dword_of(pg, d), gr);
+    for (int i = 0; i < AHEAD; ++i) {
+      const int g = min(first + i * waves, groups - 1);
+      const int64_t at = (int64_t)(g * 32 + row) * a.cols + col, block = (int64_t)(g / (B / 32)) * lc + group / (B / 32);
+      px[i] = *reinterpret_cast<const uint4*>(a.X + at);
+      pg[i] = *reinterpret_cast<const uint4*>(a.G + at);
+      rs[i] = a.rstd[g * 32 + row];
+      mu[i] = a.mean[g * 32 + row];
+      sx[i] = a.SX[block];
+      sg[i] = a.SG[block];
+    }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float gv = gr[e] * sg;
-        sgx[4 * d + e] = __builtin_fmaf(gv, __builtin_fmaf(x[e], kx, cx), sgx[4 * d + e]);
-        sgb[4 * d + e] += gv;
+    for (int i = 0; i < AHEAD; ++i) {
+      if (first + i * waves >= groups) break;   // the same for the whole wave
+      const float kx = sx[i] * rs[i], cx = -mu[i] * rs[i];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        float x[4], gr[4];
+        unpack4(dword_of(px[i], d), x);
+        unpack4(dword_of(pg[i], d), gr);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float gv = gr[e] * sg[i];
+          sums[4 * d + e] = __builtin_fmaf(gv, __builtin_fmaf(x[e], kx, cx), sums[4 * d + e]);
+          sums[16 + 4 * d + e] += gv;
+        }
       }
     }
   }
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    sgx[e] = wave_group_sum<31>(sgx[e]);
-    sgb[e] = wave_group_sum<31>(sgb[e]);
-    if (row == 0) {
-      s_sum[64 * wave + 16 * (lane >> 5) + e] = sgx[e];
-      s_sum[64 * wave + 32 + 16 * (lane >> 5) + e] = sgb[e];
-    }
-  }
+  const int value = reduce_rows_of_32(sums, lane);
+  s_sum[64 * wave + 32 * (value >> 4) + 16 * (lane >> 5) + (value & 15)] = sums[0];
   __syncthreads();
   if (threadIdx.x < 64) {   // the waves in order
     float v = 0.0f;
@@ -520,11 +533,11 @@ static int launch_layernorm_bwd_rows_b(LayerNormBwdRows a, bool in_place, hipStr
   const int waves = a.strips * a.teams;
   a.row_wgs = std::min((groups + a.teams - 1) / a.teams, 256);
   static_assert(16 * (kBwdRowBytes + kBwdWaveBytes) <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
-  const bool apart = !in_place && a.rows <= 2048 && groups <= 12 * waves;   // at most 12 row groups for a wave of the column workgroups
+  const bool apart = B > 32 && !in_place && a.rows <= 2048 && groups <= 12 * waves;   // at most 12 row groups for a wave of the column workgroups
   constexpr size_t BYTES = kBwdRowBytes + kBwdWaveBytes;
   with_store_policy(a.rows, a.cols, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
-    if constexpr (SP == kStoreThrough) {   // (2048 rows are always stored through)
+    if constexpr (SP == kStoreThrough && B > 32) {   // (2048 rows are always stored through; block size 32: jf_layernorm_split.hip)
       if (apart) {
         const int grid = a.row_wgs + a.cols / 32;
         if (waves <= 12) launch_rows<layernorm_bwd_rows_kernel<B, SP, true, 4>>(BYTES, grid, waves, a, st);
