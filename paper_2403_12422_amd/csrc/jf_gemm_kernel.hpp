@@ -18,6 +18,7 @@
 // "A" port) so that a lane ends up with 4 consecutive output columns of one
 // output row per register quad: codes pack into dwords without shuffles.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "jf_common.hpp"
@@ -638,21 +639,61 @@ __global__ void __launch_bounds__(64 * P::Shape::NW, P::WMIN) gemm_kernel(const 
   P::run(g, blockIdx.x, gridDim.x, s_ring, s_amax);
 }
 
+// How the tiles of two products are dealt to the workgroups of one launch.  Numbers below `split` are tiles of the product whose tiles
+// take longer, the rest the other's; both counts are rounded up to multiples of 8, so that tile i is on XCD i % 8 (what exceeds a
+// product's tiles is idle).  few == 0: in that order.  A launch of which all workgroups are resident at once puts workgroups b, b + 256, ...
+// on one compute unit (measured: of 672 and 768 workgroups all), some units with one more than the `few` others.  Dealt in order,
+// units come to have one more tile and more of the long ones as well; instead the `few` get `few_long` of those, by turns, and
+// the units with one more the rest.
+struct PairDeal {
+  int split, few, few_long, few_slots;   // few_slots: workgroups on the units that have one less
+  // the tile of workgroup `index`: of the product that goes first?
+  __host__ __device__ bool place(int index, int& tile) const {
+    if (few == 0) {
+      tile = index < split ? index : index - split;
+      return index < split;
+    }
+    const int unit = index % 256, turn = index / 256, many = 256 - few;
+    const int slot = unit >= many ? turn * few + unit - many : turn * many + unit, longs = unit >= many ? few_long : split - few_long;
+    if (slot < longs) tile = unit >= many ? slot : few_long + slot;
+    else tile = unit >= many ? slot - longs : few_slots - few_long + slot - longs;
+    return slot < longs;
+  }
+};
+// `first`, `second`: tiles of the products, that with the longer ones first; work: what a tile of each takes; resident: workgroups of a
+// unit.  (672 tiles of 4096 x 768 -> 3072, of work 4 and 3: at most 10 on a unit instead of 11, 47.5 -> 45.3 us.)  *most: the work of the
+// busiest unit, where few > 0.
+inline PairDeal deal_pair(int first, int second, double first_work, double second_work, int resident, double* most = nullptr) {
+  PairDeal d = {(first + 7) & ~7, 0, 0, 0};
+  const int all = d.split + ((second + 7) & ~7), turns = all / 256, many = all % 256, few = 256 - many;
+  if (all <= 256 || all > 256 * resident || many == 0) return d;
+  double least = 1e300;
+  for (int n = 0; n <= turns; ++n) {   // long tiles on the units with fewer
+    const int there = d.split < n * few ? d.split : n * few, rest = d.split - there;
+    const int most_few = (there + few - 1) / few, most_many = (rest + many - 1) / many;
+    if (most_many > turns + 1) continue;
+    const double a = most_few * first_work + (turns - most_few) * second_work, b = most_many * first_work + (turns + 1 - most_many) * second_work;
+    const double busiest = a > b ? a : b;
+    if (busiest < least) least = busiest, d.few = few, d.few_long = there, d.few_slots = turns * few;
+  }
+  if (most) *most = least;
+  return d;
+}
+
 // Two independent products in one launch -- the input gradient and the weight gradient of a layer (Sec. 4), which
 // need the same dY and nothing of each other.  Each product alone leaves compute units idle in its last round of tiles
 // and pays its own ramp-up, first-stage latency and epilogue; in one launch the scheduler starts tiles of the second as
-// those of the first finish, so that those phases of some workgroups run beside the K loops of others.  Workgroups
-// 0 .. split - 1 take the product whose tiles take longer (`second_first`: the second), the rest the other; split is a
-// multiple of 8, so that both see the same numbering of the XCDs, and what it exceeds the product's tiles by is idle.
+// those of the first finish, so that those phases of some workgroups run beside the K loops of others.
+// (second_first: the second product's tiles are the longer ones.)
 template <class P1, class P2>
 __global__ void __launch_bounds__(64 * P1::Shape::NW, (P1::WMIN < P2::WMIN ? P1::WMIN : P2::WMIN))
-gemm_pair_kernel(const GemmArgs g1, const GemmArgs g2, const int tiles1, const int tiles2, const int split, const int second_first) {
+gemm_pair_kernel(const GemmArgs g1, const GemmArgs g2, const int tiles1, const int tiles2, const PairDeal deal, const int second_first) {
   static_assert(P1::Shape::NW == P2::Shape::NW, "one workgroup size");
   constexpr int LDS = P1::Shape::LDS_BYTES > P2::Shape::LDS_BYTES ? P1::Shape::LDS_BYTES : P2::Shape::LDS_BYTES;
   __shared__ __align__(1024) int8_t s_ring[LDS];
   __shared__ float s_amax[8][8];
-  const bool early = (int)blockIdx.x < split;
-  const int i = early ? blockIdx.x : blockIdx.x - split;
+  int i;
+  const bool early = deal.place(blockIdx.x, i);
   if (early != (second_first != 0)) {
     if (i < tiles1) P1::run(g1, i, tiles1, s_ring, s_amax);
   } else {
@@ -673,10 +714,13 @@ static void launch_one(const GemmArgs& a, hipStream_t st) {
 template <class P1, class P2>
 static void launch_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t st) {
   const int t1 = tiles_of<P1>(a1), t2 = tiles_of<P2>(a2);
-  const bool second_first = (int64_t)a2.K * P2::Shape::TM * P2::Shape::TN > (int64_t)a1.K * P1::Shape::TM * P1::Shape::TN;
-  const int split = ((second_first ? t2 : t1) + 7) & ~7;
-  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(split + (second_first ? t1 : t2)), dim3(64 * P1::Shape::NW), 0, st, a1, a2, t1, t2,
-                     split, (int)second_first);
+  const double w1 = (double)a1.K * P1::Shape::TM * P1::Shape::TN, w2 = (double)a2.K * P2::Shape::TM * P2::Shape::TN;
+  const bool second_first = w2 > w1;
+  constexpr int LDS = P1::Shape::LDS_BYTES > P2::Shape::LDS_BYTES ? P1::Shape::LDS_BYTES : P2::Shape::LDS_BYTES;
+  constexpr int BY_WAVES = 4 * (P1::WMIN < P2::WMIN ? P1::WMIN : P2::WMIN) / P1::Shape::NW, BY_LDS = 160 * 1024 / (LDS + 256);
+  const PairDeal deal = second_first ? deal_pair(t2, t1, w2, w1, std::min(BY_WAVES, BY_LDS)) : deal_pair(t1, t2, w1, w2, std::min(BY_WAVES, BY_LDS));
+  const int all = deal.split + (((second_first ? t1 : t2) + 7) & ~7);
+  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(all), dim3(64 * P1::Shape::NW), 0, st, a1, a2, t1, t2, deal, (int)second_first);
 }
 
 template <bool AK, bool BK>

@@ -131,14 +131,15 @@ struct ShapeTable {
       const auto mean = [&](int n) { return (td * ud(n) + tw * uw(n)) / (td + tw); };
       return p.fixed_us + std::max(alone, p.work * rounds_us(per, resident, mean, p.fade, 0.0));
     }
-    // dealt to the units in turn, as gemm_pair_kernel and gemm_wide_pair_kernel number them: the unit with most is the first or the
-    // last of the first product's last round, or the first of the second's
+    // dealt as deal_pair says, or to the units in turn: the unit with most is then the first or the last of the first product's last round,
+    // or the first of the second's
     const int n = (int)std::ceil(per);
     const bool second_first = (int64_t)w.K * sw.tm * sw.tn > (int64_t)d.K * sd.tm * sd.tn;
     const int64_t t1 = (int64_t)(second_first ? tw : td), t2 = (int64_t)(second_first ? td : tw), split = (t1 + 7) & ~int64_t(7);
     const double u1 = second_first ? uw(n) : ud(n), u2 = second_first ? ud(n) : uw(n);
     double busiest = 0.0;
-    for (const int64_t i : {int64_t(0), split % 256, (t1 - 1) % 256}) {
+    const bool dealt_evenly = sd.resident != kPersistent && deal_pair((int)t1, (int)t2, u1, u2, resident, &busiest).few > 0;
+    if (!dealt_evenly) for (const int64_t i : {int64_t(0), split % 256, (t1 - 1) % 256}) {
       const int64_t j = (i - split % 256 + 256) % 256;
       const int64_t n1 = i < t1 ? (t1 - i + 255) / 256 : 0, n2 = j < t2 ? (t2 - j + 255) / 256 : 0;
       busiest = std::max(busiest, n1 * u1 + n2 * u2);
