@@ -48,9 +48,9 @@ struct FineFrag {
   }
 };
 
-template <bool AK, bool BK>
-__device__ __forceinline__ void gemm_fine_tile(const GemmArgs& g, const int tile_index, const int ntiles, int8_t* const s_ring,
-                                               float* const s_amax) {
+template <bool AK, bool BK, class LATE>
+__device__ __forceinline__ void gemm_fine_tile(GemmArgs g, const int tile_index, const int ntiles, int8_t* const s_ring,
+                                               float* const s_amax, LATE&& late) {
   typedef FineShape<AK, BK> S;
   constexpr int B = 32, TM = S::TM, TN = S::TN, KC = S::KC, NBUF = S::NBUF;
   constexpr int SPS = KC / 32;    // K steps (= quantization blocks) per stage
@@ -137,9 +137,11 @@ __device__ __forceinline__ void gemm_fine_tile(const GemmArgs& g, const int tile
     asm volatile("s_barrier" ::: "memory");
   };
 
-  issue_scales(0);
+  issue(0);
+  late(g);
+  issue_scales(0);   // as in gemm_tile
 #pragma unroll 1
-  for (int t = 0; t < NBUF; ++t) issue(t);
+  for (int t = 1; t < NBUF; ++t) issue(t);
   wait_stage(std::integral_constant<int, NBUF - 1>());
   scales = read_scales(0);
   read_frags(0, 0);
@@ -192,9 +194,12 @@ __device__ __forceinline__ void gemm_fine_tile(const GemmArgs& g, const int tile
 template <bool AK, bool BK>
 struct FineInstance {
   typedef FineShape<AK, BK> Shape;
+  static constexpr int BLOCK = 32;
+  static constexpr bool A_KMAJOR = AK, B_KMAJOR = BK;
   static constexpr int WMIN = 4;   // four workgroups per compute unit fit the LDS
-  static __device__ __forceinline__ void run(const GemmArgs& g, int tile_index, int ntiles, int8_t* s_ring, float (*s_amax)[8]) {
-    gemm_fine_tile<AK, BK>(g, tile_index, ntiles, s_ring, s_amax[0]);
+  template <class LATE>
+  static __device__ __forceinline__ void run(const GemmArgs& g, int tile_index, int ntiles, int8_t* s_ring, float (*s_amax)[8], LATE&& late) {
+    gemm_fine_tile<AK, BK>(g, tile_index, ntiles, s_ring, s_amax[0], late);
   }
 };
 

@@ -39,6 +39,16 @@ struct GemmArgs {
   float* Of;           // M x Nn FP32 accumulator (nullable)
   int32_t* dump;       // test hook: INT32 partials of K block dump_kb
   int dump_kb;
+
+  // leading dimensions and scale strides: operands and grids are dense
+  __host__ __device__ __forceinline__ void set_strides(int block, bool a_kmajor, bool b_kmajor) {
+    lda = a_kmajor ? K : M;
+    ldb = b_kmajor ? K : Nn;
+    sa_p = a_kmajor ? (unsigned)K / block : 1;
+    sa_k = a_kmajor ? 1 : (unsigned)M / block;
+    sb_p = b_kmajor ? (unsigned)K / block : 1;
+    sb_k = b_kmajor ? 1 : (unsigned)Nn / block;
+  }
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -198,10 +208,11 @@ struct GemmPipeline {
 
 // One output tile: K loop and epilogue.  `tile_index` of `ntiles` is this workgroup's position in the launch (or in
 // its part of a launch that holds two products); s_ring is the workgroup's LDS ring of NBUF stages with the scales behind
-// it, s_amax its max-abs exchange area, both owned by the calling kernel.
-template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DUMP>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_index, const int ntiles, int8_t* const s_ring,
-                                          float (*const s_amax)[8]) {
+// it, s_amax its max-abs exchange area, both owned by the calling kernel.  late(g) completes the arguments by those that are not
+// needed for the first stage's loads, behind which it is called.
+template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DUMP, class LATE>
+__device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, const int ntiles, int8_t* const s_ring,
+                                          float (*const s_amax)[8], LATE&& late) {
   typedef GemmShape<B, WM, WN, WGM, WGN, AK, BK> Shape;
   constexpr int NW = Shape::NW;
   constexpr int TM = Shape::TM, TN = Shape::TN;
@@ -490,9 +501,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
   };
 
   static_assert(NBUF >= 2, "a stage in flight beside the one in use");
-  issue_scales(0);
+  const auto issue_stage = [&](int t) __attribute__((always_inline)) {
+    static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { issue_load(t, decltype(n)::value); });
+  };
+  issue_stage(0);
+  late(g);
+  issue_scales(0);   // the wait for the first stage takes them in
 #pragma unroll 1
-  for (int t = 0; t < NBUF; ++t) static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { issue_load(t, decltype(n)::value); });
+  for (int t = 1; t < NBUF; ++t) issue_stage(t);
   wait_stage(std::integral_constant<int, NBUF - 1>());
   read_scales(0);
   if (nkb > SEG) issue_scales(1);
@@ -622,21 +638,68 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int tile_inde
 template <int B, int WM, int WN, int WGM, int WGN, bool AK, bool BK, bool DUMP = false>
 struct GemmInstance {
   typedef GemmShape<B, WM, WN, WGM, WGN, AK, BK> Shape;
+  static constexpr int BLOCK = B;
+  static constexpr bool A_KMAJOR = AK, B_KMAJOR = BK;
   // Resident waves per SIMD the register allocation has to allow.  Four waves: 3 for the 128x128 tile and for the 64x64
   // tile at B = 64 (three workgroups share the LDS of a compute unit), else 4.  Eight waves: 4 for the 256x128 tile and 6 for
   // the 128x64 tile at B = 32 (two and three workgroups per compute unit), else 2 (one).
   static constexpr int WMIN = Shape::NW == 8 ? (B == 32 ? (WM * WN == 1 ? 6 : 4) : 2) : (WM * WN == 4 || B == 64) ? 3 : 4;
-  static __device__ __forceinline__ void run(const GemmArgs& g, int tile_index, int ntiles, int8_t* s_ring, float (*s_amax)[8]) {
-    gemm_tile<B, WM, WN, WGM, WGN, AK, BK, DUMP>(g, tile_index, ntiles, s_ring, s_amax);
+  template <class LATE>
+  static __device__ __forceinline__ void run(const GemmArgs& g, int tile_index, int ntiles, int8_t* s_ring, float (*s_amax)[8], LATE&& late) {
+    gemm_tile<B, WM, WN, WGM, WGN, AK, BK, DUMP>(g, tile_index, ntiles, s_ring, s_amax, late);
   }
 };
 
+// ---- Kernel arguments.  The first 14 dwords are in registers when the waves start (the build's argument preload): operands and sizes, all
+// that the first stage's loads need; strides are computed, since reading them would hold the first load up by a trip to memory (0.3 us
+// of a launch).  The compiler would read the rest at the kernel's beginning and wait for it there, so it is read from the argument
+// segment behind those loads; the structures below are what the segment holds, the kernels' parameters in order.
+struct GemmResults {   // as in GemmArgs
+  int8_t* Oq;
+  float *Os, *Of;
+  int32_t* dump;
+  int dump_kb;
+};
+struct GemmKernelArgs {
+  const int8_t *A, *Bm;
+  const float *SA, *SB;
+  int M, Nn, K, ntiles;
+  GemmResults results;
+};
+struct GemmPairKernelArgs {
+  const int8_t *dY, *W, *X;
+  int N, C, D, split, few, few_long, few_slots, second_first;
+  const float *SdY, *SW, *SX;
+  GemmResults dgrad, wgrad;
+};
+template <class ARGS>
+__device__ __forceinline__ const __attribute__((address_space(4))) ARGS* kernel_arguments_from_here() {
+  auto p = (const __attribute__((address_space(4))) ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+__device__ __forceinline__ void set_results(GemmArgs& g, const __attribute__((address_space(4))) GemmResults& r) {
+  g.Oq = r.Oq, g.Os = r.Os, g.Of = r.Of, g.dump = r.dump, g.dump_kb = r.dump_kb;
+}
+template <class P>
+__device__ __forceinline__ GemmArgs operands(const int8_t* A, const int8_t* Bm, const float* SA, const float* SB, int M, int Nn, int K) {
+  GemmArgs g{A, Bm, SA, SB, M, Nn, K, 0, 0, 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+  g.set_strides(P::BLOCK, P::A_KMAJOR, P::B_KMAJOR);
+  return g;
+}
+template <class P>
+__host__ __device__ __forceinline__ int tiles_of(int M, int Nn) {
+  return (int)((unsigned)(M + P::Shape::TM - 1) / P::Shape::TM * ((unsigned)(Nn + P::Shape::TN - 1) / P::Shape::TN));
+}
+
 // One product per launch.
 template <class P>
-__global__ void __launch_bounds__(64 * P::Shape::NW, P::WMIN) gemm_kernel(const GemmArgs g) {
+__global__ void __launch_bounds__(64 * P::Shape::NW, P::WMIN) gemm_kernel(const int8_t* A, const int8_t* Bm, const float* SA, const float* SB, int M, int Nn,
+                                                                          int K, int ntiles, const GemmResults) {
   __shared__ __align__(1024) int8_t s_ring[P::Shape::LDS_BYTES];
   __shared__ float s_amax[8][8];
-  P::run(g, blockIdx.x, gridDim.x, s_ring, s_amax);
+  P::run(operands<P>(A, Bm, SA, SB, M, Nn, K), blockIdx.x, ntiles, s_ring, s_amax,
+         [](GemmArgs& g) __attribute__((always_inline)) { set_results(g, kernel_arguments_from_here<GemmKernelArgs>()->results); });
 }
 
 // How the tiles of two products are dealt to the workgroups of one launch.  Numbers below `split` are tiles of the product whose tiles
@@ -687,40 +750,52 @@ inline PairDeal deal_pair(int first, int second, double first_work, double secon
 // (second_first: the second product's tiles are the longer ones.)
 template <class P1, class P2>
 __global__ void __launch_bounds__(64 * P1::Shape::NW, (P1::WMIN < P2::WMIN ? P1::WMIN : P2::WMIN))
-gemm_pair_kernel(const GemmArgs g1, const GemmArgs g2, const int tiles1, const int tiles2, const PairDeal deal, const int second_first) {
+gemm_pair_kernel(const int8_t* dY, const int8_t* W, const int8_t* X, int N, int C, int D, int split, int few, int few_long, int few_slots, int second_first,
+                 const float*, const float*, const float*, const GemmResults, const GemmResults) {
   static_assert(P1::Shape::NW == P2::Shape::NW, "one workgroup size");
   constexpr int LDS = P1::Shape::LDS_BYTES > P2::Shape::LDS_BYTES ? P1::Shape::LDS_BYTES : P2::Shape::LDS_BYTES;
   __shared__ __align__(1024) int8_t s_ring[LDS];
   __shared__ float s_amax[8][8];
   int i;
-  const bool early = deal.place(blockIdx.x, i);
+  const bool early = PairDeal{split, few, few_long, few_slots}.place(blockIdx.x, i);
   if (early != (second_first != 0)) {
-    if (i < tiles1) P1::run(g1, i, tiles1, s_ring, s_amax);
+    const int tiles = tiles_of<P1>(N, C);
+    if (i < tiles)
+      P1::run(operands<P1>(dY, W, nullptr, nullptr, N, C, D), i, tiles, s_ring, s_amax, [](GemmArgs& g) __attribute__((always_inline)) {
+        const auto a = kernel_arguments_from_here<GemmPairKernelArgs>();
+        g.SA = a->SdY, g.SB = a->SW;
+        set_results(g, a->dgrad);
+      });
   } else {
-    if (i < tiles2) P2::run(g2, i, tiles2, s_ring, s_amax);
+    const int tiles = tiles_of<P2>(D, C);
+    if (i < tiles)
+      P2::run(operands<P2>(dY, X, nullptr, nullptr, D, C, N), i, tiles, s_ring, s_amax, [](GemmArgs& g) __attribute__((always_inline)) {
+        const auto a = kernel_arguments_from_here<GemmPairKernelArgs>();
+        g.SA = a->SdY, g.SB = a->SX;
+        set_results(g, a->wgrad);
+      });
   }
 }
 
 // --------------------------------------------------------------------- host
-template <class P>
-static int tiles_of(const GemmArgs& a) {
-  return ((a.M + P::Shape::TM - 1) / P::Shape::TM) * ((a.Nn + P::Shape::TN - 1) / P::Shape::TN);
-}
+inline GemmResults results_of(const GemmArgs& a) { return {a.Oq, a.Os, a.Of, a.dump, a.dump_kb}; }
 template <class P>
 static void launch_one(const GemmArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((gemm_kernel<P>), dim3(tiles_of<P>(a)), dim3(64 * P::Shape::NW), 0, st, a);
+  const int tiles = tiles_of<P>(a.M, a.Nn);
+  hipLaunchKernelGGL((gemm_kernel<P>), dim3(tiles), dim3(64 * P::Shape::NW), 0, st, a.A, a.Bm, a.SA, a.SB, a.M, a.Nn, a.K, tiles, results_of(a));
 }
-// the product with the longer tiles goes first
+// input gradient (first) and weight gradient; the product with the longer tiles goes first
 template <class P1, class P2>
 static void launch_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t st) {
-  const int t1 = tiles_of<P1>(a1), t2 = tiles_of<P2>(a2);
+  const int t1 = tiles_of<P1>(a1.M, a1.Nn), t2 = tiles_of<P2>(a2.M, a2.Nn);
   const double w1 = (double)a1.K * P1::Shape::TM * P1::Shape::TN, w2 = (double)a2.K * P2::Shape::TM * P2::Shape::TN;
   const bool second_first = w2 > w1;
   constexpr int LDS = P1::Shape::LDS_BYTES > P2::Shape::LDS_BYTES ? P1::Shape::LDS_BYTES : P2::Shape::LDS_BYTES;
   constexpr int BY_WAVES = 4 * (P1::WMIN < P2::WMIN ? P1::WMIN : P2::WMIN) / P1::Shape::NW, BY_LDS = 160 * 1024 / (LDS + 256);
   const PairDeal deal = second_first ? deal_pair(t2, t1, w2, w1, std::min(BY_WAVES, BY_LDS)) : deal_pair(t1, t2, w1, w2, std::min(BY_WAVES, BY_LDS));
   const int all = deal.split + (((second_first ? t1 : t2) + 7) & ~7);
-  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(all), dim3(64 * P1::Shape::NW), 0, st, a1, a2, t1, t2, deal, (int)second_first);
+  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(all), dim3(64 * P1::Shape::NW), 0, st, a1.A, a1.Bm, a2.Bm, a1.M, a1.Nn, a1.K, deal.split, deal.few,
+                     deal.few_long, deal.few_slots, (int)second_first, a1.SA, a1.SB, a2.SB, results_of(a1), results_of(a2));
 }
 
 template <bool AK, bool BK>

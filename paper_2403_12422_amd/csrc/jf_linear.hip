@@ -67,17 +67,10 @@ static GemmArgs make_args(int which, const int8_t* a, const float* sa, const int
                           int64_t C, int64_t D, int32_t block) {
   GemmArgs g{};
   g.A = a; g.SA = sa; g.Bm = b; g.SB = sb;
-  const int LC = (int)(C / block), LD = (int)(D / block);
-  if (which == 0) {         // Y = X W^T : A = X (N x C) K-major, Bm = W (D x C) K-major
-    g.M = (int)N; g.Nn = (int)D; g.K = (int)C; g.lda = C; g.ldb = C;
-    g.sa_p = LC; g.sa_k = 1; g.sb_p = LC; g.sb_k = 1;
-  } else if (which == 1) {  // dX = dY W : A = dY (N x D) K-major, Bm = W^T stored as W (D x C) = K rows x Nn
-    g.M = (int)N; g.Nn = (int)C; g.K = (int)D; g.lda = D; g.ldb = C;
-    g.sa_p = LD; g.sa_k = 1; g.sb_p = 1; g.sb_k = LC;
-  } else {                  // dW = dY^T X : A = dY^T stored as dY (N x D), Bm = X^T stored as X (N x C)
-    g.M = (int)D; g.Nn = (int)C; g.K = (int)N; g.lda = D; g.ldb = C;
-    g.sa_p = 1; g.sa_k = LD; g.sb_p = 1; g.sb_k = LC;
-  }
+  if (which == 0) g.M = (int)N, g.Nn = (int)D, g.K = (int)C;        // Y = X W^T: A = X (N x C), Bm = W (D x C), both K-major
+  else if (which == 1) g.M = (int)N, g.Nn = (int)C, g.K = (int)D;   // dX = dY W: A = dY (N x D) K-major, Bm = W^T stored as W (D x C)
+  else g.M = (int)D, g.Nn = (int)C, g.K = (int)N;                   // dW = dY^T X: A = dY^T stored as dY (N x D), Bm = X^T stored as X (N x C)
+  g.set_strides(block, which != 2, which == 0);
   return g;
 }
 
