@@ -219,6 +219,16 @@ __device__ __forceinline__ void load_lds_4_vaddr(const void* vaddr, const int8_t
                : "v"(vaddr), "s"(lds_address(lds_tile, lds_byte))
                : "memory", "m0");
 }
+// Kernel arguments.  The first 14 dwords are in registers when the waves start (the build's argument preload); what stands behind them costs
+// a trip to memory, 0.3 us in front of a workgroup's first request if the kernel simply has it as a parameter, because the compiler
+// reads and awaits parameters at the beginning.  So kernels of a few microseconds have first what their first loads need, and
+// read the others where this is called, behind those loads.  ARGS: the argument segment, that is the kernel's parameters in order.
+template <class ARGS>
+__device__ __forceinline__ const __attribute__((address_space(4))) ARGS* kernel_arguments_from_here() {
+  auto p = (const __attribute__((address_space(4))) ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
 // A pointer that is the same for all lanes, moved to scalar registers for good.
 template <class T>
 __device__ __forceinline__ T* uniform_pointer(T* p) {

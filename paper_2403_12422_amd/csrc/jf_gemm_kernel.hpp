@@ -650,10 +650,8 @@ struct GemmInstance {
   }
 };
 
-// ---- Kernel arguments.  The first 14 dwords are in registers when the waves start (the build's argument preload): operands and sizes, all
-// that the first stage's loads need; strides are computed, since reading them would hold the first load up by a trip to memory (0.3 us
-// of a launch).  The compiler would read the rest at the kernel's beginning and wait for it there, so it is read from the argument
-// segment behind those loads; the structures below are what the segment holds, the kernels' parameters in order.
+// ---- Kernel arguments: operands and sizes first, all that the first stage's loads need (strides are computed), the rest read behind
+// those loads (see kernel_arguments_from_here); the structures below are what the argument segment holds, the kernels' parameters in order.
 struct GemmResults {   // as in GemmArgs
   int8_t* Oq;
   float *Os, *Of;
@@ -672,12 +670,6 @@ struct GemmPairKernelArgs {
   const float *SdY, *SW, *SX;
   GemmResults dgrad, wgrad;
 };
-template <class ARGS>
-__device__ __forceinline__ const __attribute__((address_space(4))) ARGS* kernel_arguments_from_here() {
-  auto p = (const __attribute__((address_space(4))) ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return p;
-}
 __device__ __forceinline__ void set_results(GemmArgs& g, const __attribute__((address_space(4))) GemmResults& r) {
   g.Oq = r.Oq, g.Os = r.Os, g.Of = r.Of, g.dump = r.dump, g.dump_kb = r.dump_kb;
 }

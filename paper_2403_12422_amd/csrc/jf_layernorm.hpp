@@ -46,17 +46,18 @@ __device__ __forceinline__ void unpack4(uint32_t w, float (&c)[4]) {
 }
 __device__ __forceinline__ uint32_t dword_of(const uint4& v, int d) { return d == 0 ? v.x : (d == 1 ? v.y : (d == 2 ? v.z : v.w)); }
 
-// v[0] + v[64] + v[128] + ... of the `strips` waves of a team, in that order, four LDS reads in flight at a time (one after
+// v[0] + v[64] + v[128] + ... of the `strips` waves of a team, in that order, eight LDS reads in flight at a time (one after
 // the other they are one LDS latency per strip, beside which nothing runs where a workgroup has a single row group).
 template <class T>
 __device__ __forceinline__ T sum_over_strips(const T* v, int strips) {
   T sum = 0;
-  for (int w = 0; w < strips; w += 4) {
-    T q[4];
+#pragma unroll 1
+  for (int w = 0; w < strips; w += 8) {
+    T q[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) q[j] = v[64 * min(w + j, strips - 1)];
+    for (int j = 0; j < 8; ++j) q[j] = v[64 * min(w + j, strips - 1)];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) sum += w + j < strips ? q[j] : (T)0;
+    for (int j = 0; j < 8; ++j) sum += w + j < strips ? q[j] : (T)0;
   }
   return sum;
 }
@@ -134,6 +135,48 @@ struct LayerNormBwdRows {
   int strips, teams, row_wgs;     // row_wgs: workgroups that own rows; those behind them own columns
   float inv_cols;
 };
+
+// Arguments of the kernels whose workgroups own whole rows: what their first loads need in the dwords that are preloaded, the rest read
+// behind those.  layout: strips, teams and waves of a workgroup, 8 bits each; wgs: workgroups that own rows.
+struct LayerNormRowsArgs {
+  const int8_t* X;
+  const float *SX, *first, *second;   // row partials if there are any, else gamma and beta
+  int rows, cols, layout, wgs;
+  LayerNormRows all;
+};
+struct LayerNormBwdRowsArgs {
+  const int8_t* G;
+  const float* SG;
+  const int8_t* X;
+  const float* SX;
+  int rows, cols, layout, wgs;
+  const float* gamma;
+  LayerNormBwdRows all;
+};
+template <bool PARTIALS>
+__device__ __forceinline__ LayerNormRows first_arguments(const int8_t* X, const float* SX, const float* first, const float* second, int rows, int cols, int layout) {
+  LayerNormRows a{};
+  a.X = X, a.SX = SX, a.rows = rows, a.cols = cols, a.strips = layout & 255, a.teams = layout >> 8 & 255;
+  if (PARTIALS) a.row_mean = first, a.row_sumsq = second;
+  else a.gamma = first, a.beta = second;
+  return a;
+}
+template <bool PARTIALS>
+__device__ __forceinline__ void other_arguments(LayerNormRows& a) {
+  const auto& k = kernel_arguments_from_here<LayerNormRowsArgs>()->all;
+  if (PARTIALS) a.gamma = k.gamma, a.beta = k.beta;
+  a.eps = k.eps, a.Y = k.Y, a.SY = k.SY, a.mean = k.mean, a.rstd = k.rstd, a.inv_cols = k.inv_cols, a.inv_blocks = k.inv_blocks;
+}
+__device__ __forceinline__ LayerNormBwdRows first_arguments(const int8_t* G, const float* SG, const int8_t* X, const float* SX, int rows, int cols, int layout,
+                                                            int wgs, const float* gamma) {
+  LayerNormBwdRows a{};
+  a.G = G, a.SG = SG, a.X = X, a.SX = SX, a.rows = rows, a.cols = cols, a.strips = layout & 255, a.teams = layout >> 8 & 255, a.row_wgs = wgs, a.gamma = gamma;
+  return a;
+}
+__device__ __forceinline__ void other_arguments(LayerNormBwdRows& a) {
+  const auto& k = kernel_arguments_from_here<LayerNormBwdRowsArgs>()->all;
+  a.mean = k.mean, a.rstd = k.rstd, a.dX = k.dX, a.SdX = k.SdX, a.partials = k.partials, a.dgamma = k.dgamma, a.dbeta = k.dbeta, a.inv_cols = k.inv_cols;
+}
 
 // Whether the one-pass kernels take a pass, and their launches.  The backward one returns the number of partial rows of
 // dgamma | dbeta that it leaves in `partials` (at most 256 and at most rows / 32), or 0 if it has written dgamma and dbeta

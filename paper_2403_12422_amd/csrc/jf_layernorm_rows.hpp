@@ -41,12 +41,13 @@ struct RowWave {
   int lane, ch, rsub, wave, waves, team, strip;
   int c0, col;   // first column of the strip, of the lane's chunks (lanes outside the matrix: the strip's first chunk)
   bool ok;       // the lane's chunks lie inside the matrix
-  __device__ __forceinline__ RowWave(int cols, int strips) {
+  __device__ __forceinline__ RowWave(int cols, int layout) {
+    const int strips = layout & 255;
     lane = threadIdx.x & 63;
     ch = lane & 7;
     rsub = lane >> 3;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    waves = blockDim.x >> 6;
+    waves = layout >> 16;
     team = wave / strips;
     strip = wave - team * strips;
     c0 = strip * 128;
@@ -82,9 +83,11 @@ constexpr int kFwdScale = 4096, kFwdPart = kFwdScale + 256, kFwdGamma = kFwdPart
 constexpr int kFwdRowBytes = 2 * 32 * 16;   // per wave: two copies (alternate row groups) of a sum pair for each of 32 rows
 
 template <int B, bool PARTIALS, StorePolicy SP>
-__global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRows a) {
+__global__ void __launch_bounds__(1024) layernorm_rows_kernel(const int8_t* X, const float* SX, const float* first_in, const float* second_in, int rows, int cols,
+                                                              int layout, int wgs, const LayerNormRows) {
   extern __shared__ __align__(16) int8_t smem[];
-  const RowWave t(a.cols, a.strips);
+  LayerNormRows a = first_arguments<PARTIALS>(X, SX, first_in, second_in, rows, cols, layout);
+  const RowWave t(a.cols, layout);
   double* const s_row = reinterpret_cast<double*>(smem);                       // [copy][wave][row][sum]
   int8_t* const own = smem + t.waves * kFwdRowBytes + t.wave * kFwdWaveBytes;
   constexpr int BT = B / 32, NBC = 128 / B;            // teams of a block row, block columns of a strip
@@ -107,8 +110,9 @@ __global__ void __launch_bounds__(1024) layernorm_rows_kernel(const LayerNormRow
   };
 
   int first = blockIdx.x * a.teams;                    // first row group of the workgroup's teams
-  const int stride = gridDim.x * a.teams;
+  const int stride = wgs * a.teams;
   request(min(first + t.team, groups - 1));
+  other_arguments<PARTIALS>(a);
   float* const s_gamma = reinterpret_cast<float*>(own + kFwdGamma);
   float* const s_beta = reinterpret_cast<float*>(own + kFwdBeta);
 #pragma unroll
@@ -229,8 +233,8 @@ constexpr int kBwdRowBytes = 2 * 32 * 8;
 // pulls in for a quarter of each: with many rows the workgroups of the few block columns take longer than the row pass (4096 x 768 10.3
 // -> 13.9 us; with 16 columns to a workgroup 16.5).
 template <int B>
-__device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, int index, float* s_sum) {
-  const int lane = threadIdx.x & 63, row = lane & 31, waves = blockDim.x >> 6;
+__device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, int index, int waves, float* s_sum) {
+  const int lane = threadIdx.x & 63, row = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // A line of 128 columns belongs to four of these workgroups: they are on one XCD (to which workgroups come in turns), so that its L2
   // fetches the line once.
@@ -293,20 +297,23 @@ __device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, in
 // for two rows beside the column sums, for all four without them; 16 waves have none.  More than fits goes to scratch
 // memory, whose loads also wait for the strips in flight (1 M x 768 with three rows 513 us, two 484, one 515, none 535).
 template <int B, StorePolicy SP, bool COLUMNS_APART, int KEPT>
-__global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(const LayerNormBwdRows a) {
+__global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(
+    const int8_t* G, const float* SG, const int8_t* X, const float* SX, int rows, int cols, int layout, int wgs, const float* gamma, const LayerNormBwdRows) {
   extern __shared__ __align__(16) int8_t smem[];
+  LayerNormBwdRows a = first_arguments(G, SG, X, SX, rows, cols, layout, wgs, gamma);
   if (COLUMNS_APART && (int)blockIdx.x >= a.row_wgs) {
-    column_sums_direct<B>(a, blockIdx.x - a.row_wgs, reinterpret_cast<float*>(smem));
+    other_arguments(a);
+    column_sums_direct<B>(a, blockIdx.x - a.row_wgs, layout >> 16, reinterpret_cast<float*>(smem));
     return;
   }
-  const RowWave t(a.cols, a.strips);
+  const RowWave t(a.cols, layout);
   float* const s_row = reinterpret_cast<float*>(smem);                         // [copy][wave][row][sum]
   int8_t* const own = smem + t.waves * kBwdRowBytes + t.wave * kBwdWaveBytes;
   constexpr int BT = B / 32, NBC = 128 / B;            // teams of a block row, block columns of a strip
   const int groups = a.rows / 32, lc = a.cols / B;
   const uint32_t off = (uint32_t)(t.rsub * a.cols + t.col), off_scale = (uint32_t)(t.col / B) * 4;
 
-  auto request = [&](int g) __attribute__((always_inline)) {
+  auto request_codes = [&](int g) __attribute__((always_inline)) {
     const int8_t* const x = uniform_pointer(a.X + (int64_t)g * 32 * a.cols);
     const int8_t* const gr = uniform_pointer(a.G + (int64_t)g * 32 * a.cols);
 #pragma unroll
@@ -316,6 +323,8 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
     }
     load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)(g / BT) * lc)), off_scale, own, kBwdScaleX);
     load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SG + (int64_t)(g / BT) * lc)), off_scale, own, kBwdScaleG);
+  };
+  auto request_stats = [&](int g) __attribute__((always_inline)) {
     if (t.lane < 32) {   // 32 floats each
       load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.mean + g * 32)), (uint32_t)t.lane * 4, own, kBwdMean);
       load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.rstd + g * 32)), (uint32_t)t.lane * 4, own, kBwdRstd);
@@ -323,8 +332,10 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
   };
 
   int first = blockIdx.x * a.teams;
-  const int stride = (COLUMNS_APART ? a.row_wgs : (int)gridDim.x) * a.teams;
-  request(min(first + t.team, groups - 1));
+  const int stride = a.row_wgs * a.teams;
+  request_codes(min(first + t.team, groups - 1));
+  other_arguments(a);
+  request_stats(min(first + t.team, groups - 1));
   float* const s_gamma = reinterpret_cast<float*>(own + kBwdGamma);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -352,7 +363,7 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
     const float sx = *reinterpret_cast<const float*>(own + kBwdScaleX + 4 * t.lane);
     float sg = *reinterpret_cast<const float*>(own + kBwdScaleG + 4 * t.lane);
     wait_lds();                                        // the strips are in registers: their LDS may be filled again
-    if (first + stride < groups) request(min(g + stride, groups - 1));
+    if (first + stride < groups) request_codes(min(g + stride, groups - 1)), request_stats(min(g + stride, groups - 1));
     sg = t.ok && g < groups ? sg : 0.0f;               // what lies outside adds nothing to the sums
     float kx[4], cx[4], m1[4], m2[4];
     float y[4][16];                                    // dx; ghat in units of g's block scale before, of KEPT rows
@@ -493,10 +504,22 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(c
 // A launch needs more LDS than a kernel gets by default.  The limit belongs to the kernel on the current device, so it is
 // raised in front of every launch (0.07 us) instead of once; where it cannot be, nothing is launched and launch_status()
 // reports the error.
-template <auto KERNEL, class Args>
-static void launch_rows(size_t wave_bytes, int grid, int waves, const Args& a, hipStream_t st) {
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(16 * wave_bytes)) != hipSuccess) return;
-  hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(64 * waves), waves * wave_bytes, st, a);
+template <auto KERNEL>
+static bool raise_lds(size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+}
+inline int rows_layout(int strips, int teams, int waves) { return strips | teams << 8 | waves << 16; }
+template <auto KERNEL>
+static void launch_rows(size_t wave_bytes, int grid, int waves, const LayerNormRows& a, hipStream_t st) {
+  if (!raise_lds<KERNEL>(16 * wave_bytes)) return;
+  hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(64 * waves), waves * wave_bytes, st, a.X, a.SX, a.row_mean ? a.row_mean : a.gamma,
+                     a.row_mean ? a.row_sumsq : a.beta, a.rows, a.cols, rows_layout(a.strips, a.teams, waves), grid, a);
+}
+template <auto KERNEL>
+static void launch_rows(size_t wave_bytes, int grid, int waves, const LayerNormBwdRows& a, hipStream_t st) {
+  if (!raise_lds<KERNEL>(16 * wave_bytes)) return;
+  hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(64 * waves), waves * wave_bytes, st, a.G, a.SG, a.X, a.SX, a.rows, a.cols,
+                     rows_layout(a.strips, a.teams, waves), a.row_wgs, a.gamma, a);
 }
 
 // Teams per workgroup, one workgroup per compute unit.  The waves of a workgroup are dealt to the four SIMDs in turn, so

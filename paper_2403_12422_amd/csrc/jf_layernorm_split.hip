@@ -58,12 +58,14 @@ __device__ __forceinline__ void store_part_of_strip(const float (&y)[SplitLane<P
 }
 
 template <bool PARTIALS, int PARTS>
-__global__ void __launch_bounds__(1024) layernorm_split_kernel(const LayerNormRows a) {
+__global__ void __launch_bounds__(1024) layernorm_split_kernel(const int8_t* X, const float* SX, const float* first_in, const float* second_in, int rows,
+                                                               int cols, int layout, int, const LayerNormRows) {
   extern __shared__ __align__(16) int8_t smem[];
+  LayerNormRows a = first_arguments<PARTIALS>(X, SX, first_in, second_in, rows, cols, layout);
   const SplitPlace place = SplitPlace::of<PARTS>(blockIdx.x);
   const int g = place.group, lc = a.cols / 32;
   if (g >= a.rows / 32) return;
-  const RowWave t(a.cols, a.strips);
+  const RowWave t(a.cols, layout);
   double* const s_row = reinterpret_cast<double*>(smem);
   int8_t* const own = smem + t.waves * kFwdRowBytes + t.wave * kFwdWaveBytes;
   const int8_t* const x = uniform_pointer(a.X + (int64_t)g * 32 * a.cols);
@@ -79,6 +81,7 @@ __global__ void __launch_bounds__(1024) layernorm_split_kernel(const LayerNormRo
       load_lds_4_vaddr(a.row_sumsq + o, own, kFwdPart + 512 + 256 * i);
     }
   }
+  other_arguments<PARTIALS>(a);
   const SplitLane<PARTS> s(place.part, t.lane);
   const bool ok = t.c0 + 16 * s.chunk < a.cols;
   const int col = ok ? t.c0 + 16 * s.chunk : t.c0;
@@ -145,15 +148,18 @@ __global__ void __launch_bounds__(1024) layernorm_split_kernel(const LayerNormRo
 // Backward, the column sums in workgroups of their own behind row_wgs that have rows (column_sums_direct); waves past the strips
 // are for those only.
 template <int PARTS>
-__global__ void __launch_bounds__(1024) layernorm_bwd_split_kernel(const LayerNormBwdRows a) {
+__global__ void __launch_bounds__(1024) layernorm_bwd_split_kernel(const int8_t* G, const float* SG, const int8_t* X, const float* SX, int rows, int cols,
+                                                                   int layout, int wgs, const float* gamma, const LayerNormBwdRows) {
   extern __shared__ __align__(16) int8_t smem[];
+  LayerNormBwdRows a = first_arguments(G, SG, X, SX, rows, cols, layout, wgs, gamma);
   if ((int)blockIdx.x >= a.row_wgs) {
-    column_sums_direct<32>(a, blockIdx.x - a.row_wgs, reinterpret_cast<float*>(smem));
+    other_arguments(a);
+    column_sums_direct<32>(a, blockIdx.x - a.row_wgs, layout >> 16, reinterpret_cast<float*>(smem));
     return;
   }
   const SplitPlace place = SplitPlace::of<PARTS>(blockIdx.x);
   const int g = place.group, lc = a.cols / 32;
-  const RowWave t(a.cols, a.strips);
+  const RowWave t(a.cols, layout);
   if (g >= a.rows / 32 || t.team > 0) return;
   float* const s_row = reinterpret_cast<float*>(smem);
   int8_t* const own = smem + a.strips * kBwdRowBytes + t.wave * kBwdWaveBytes;
@@ -167,6 +173,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_split_kernel(const LayerNo
   }
   load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SX + (int64_t)g * lc)), off_scale, own, kBwdScaleX);
   load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.SG + (int64_t)g * lc)), off_scale, own, kBwdScaleG);
+  other_arguments(a);
   if (t.lane < 32) {
     load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.mean + g * 32)), (uint32_t)t.lane * 4, own, kBwdMean);
     load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(a.rstd + g * 32)), (uint32_t)t.lane * 4, own, kBwdRstd);
@@ -263,6 +270,7 @@ static void launch_split(const LayerNormRows& a, hipStream_t st) {
 
 void launch_layernorm_split(LayerNormRows a, hipStream_t st) {
   a.strips = (a.cols + 127) / 128;
+  a.teams = 1;
   a.inv_cols = 1.0 / (double)a.cols;
   a.inv_blocks = 1.0 / (double)(a.cols / 32);
   const bool four = layernorm_split_parts(a.rows, a.cols, false) == 4;
@@ -274,6 +282,7 @@ void launch_layernorm_split(LayerNormRows a, hipStream_t st) {
 // 4.55, sixteen 4.75).
 void launch_layernorm_bwd_split(LayerNormBwdRows a, hipStream_t st) {
   a.strips = (a.cols + 127) / 128;
+  a.teams = 1;
   a.inv_cols = 1.0f / (float)a.cols;
   const bool four = layernorm_split_parts(a.rows, a.cols, true) == 4;
   a.row_wgs = four ? split_grid<4>(a.rows / 32) : split_grid<2>(a.rows / 32);
