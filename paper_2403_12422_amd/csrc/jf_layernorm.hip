@@ -235,11 +235,8 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_sums_kernel(
 
   float sums[8];
   reduce_rows32(cgs, cbs, sums);
-  if (t.ok && (t.rsub & 1) == 0) {
-    float* dst = partials + (int64_t)blockIdx.x * 2 * cols + t.col - 16 * t.ch + reduced_column(threadIdx.x & 63);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) dst[(j / 4) * cols + 4 * (j % 4)] = sums[j];
-  }
+  if (t.ok && (t.rsub & 1) == 0)
+    store_partials(partials + (int64_t)blockIdx.x * 2 * cols + t.col - 16 * t.ch + reduced_column(threadIdx.x & 63), cols, sums);
 }
 
 // Column sums: the partial rows of dgamma | dbeta (2 cols wide) of one group of 64 columns, added in a fixed order by a
@@ -255,6 +252,14 @@ __device__ __forceinline__ void colsum_group(int group, const float* __restrict_
   float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   if (c < cols2) {
     int p = wave;
+    // sixteen rows requested together, all that a wave has of 256 partial rows
+    for (; p + 15 * NW < nparts; p += 16 * NW) {
+      float v[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) v[j] = partials[(int64_t)(p + NW * j) * cols2 + c];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[j & 7] += v[j];
+    }
     for (; p + 7 * NW < nparts; p += 8 * NW) {
       float v[8];
 #pragma unroll

@@ -65,7 +65,7 @@ __device__ __forceinline__ T sum_over_strips(const T* v, int strips) {
 // Sums over the 8 row lanes of a wave (lane bits 3, 4, 5, in that order) of 16 + 16 values.  The half-row swaps of two values
 // and one addition reduce both: 80 instructions where 32 butterflies take 320, at the end of a workgroup with nothing beside it
 // (with two rows of ghat kept: 8192 x 1280 17.2 -> 15.0 us, 4096 x 768 11.5 -> 10.1, 1056 x 800 7.1 -> 6.5).  Lane (bits 4, 5) ends with
-// values 4 j + bit 4 + 2 (bit 5), j = 0 .. 7, of {a, b}.
+// values 4 (bit 4 + 2 (bit 5)) + j of a (out[j]) and of b (out[4 + j]), j = 0 .. 3, which lie beside each other in memory.
 __device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float (&b)[16], float (&out)[8]) {
   const auto half = [](float x, float y, auto swap) __attribute__((always_inline)) {
     const auto p = swap(__builtin_bit_cast(int, x), __builtin_bit_cast(int, y));
@@ -77,12 +77,18 @@ __device__ __forceinline__ void reduce_rows32(const float (&a)[16], const float 
   for (int j = 0; j < 8; ++j) {
     float v[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = wave_group_sum<8>(j < 4 ? a[4 * j + k] : b[4 * (j - 4) + k]);
+    for (int k = 0; k < 4; ++k) v[k] = wave_group_sum<8>(j < 4 ? a[4 * k + j] : b[4 * k + j - 4]);
     out[j] = half(half(v[0], v[1], swap16), half(v[2], v[3], swap16), swap32);
   }
 }
-// Column of the strip whose sums a lane ends with: 4 (j % 4) behind this one, of a for j < 4, of b beyond.
-__device__ __forceinline__ int reduced_column(int lane) { return 16 * (lane & 7) + (((lane >> 4) & 1) | ((lane >> 5) << 1)); }
+// First of the four columns of the strip whose sums a lane ends with.
+__device__ __forceinline__ int reduced_column(int lane) { return 16 * (lane & 7) + 4 * (((lane >> 4) & 1) | ((lane >> 5) << 1)); }
+// A strip's part of a partial row of dgamma | dbeta: 512 bytes of each in two instructions, whole lines, so they can be written through like
+// other results (in pieces of a float, left for the end of the kernel to write back, 8192 x 1280 14.5 us).
+__device__ __forceinline__ void store_partials(float* dgamma, int cols, const float (&sums)[8]) {
+  store_out(dgamma, v4f{sums[0], sums[1], sums[2], sums[3]});
+  store_out(dgamma + cols, v4f{sums[4], sums[5], sums[6], sums[7]});
+}
 
 // Sums over the 32 lanes of each half wave of 32 values, by halves: a step adds two values at once, lanes with the bit clear for one,
 // with it set for the other (rows of lanes, then halves of a row and of those, by masked moves; then whole quads): 110 instructions, a

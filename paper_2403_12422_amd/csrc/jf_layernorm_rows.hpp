@@ -479,25 +479,21 @@ __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(
   // column sums over the 8 row lanes of the wave, then over the teams through LDS, in a fixed order
   float sums[8];
   reduce_rows32(cgs, cbs, sums);
-  const int place = reduced_column(t.lane);            // dgamma for j < 4, dbeta beyond
+  const int place = reduced_column(t.lane);            // + j % 4: dgamma for j < 4, dbeta beyond
   if (a.teams > 1) {
     float* const mine = reinterpret_cast<float*>(own);   // all requests have landed and nobody else uses this wave's part
 #pragma unroll
-    for (int j = 0; j < 8; ++j) mine[128 * (j / 4) + 4 * (j % 4) + place] = sums[j];   // (twice, by lanes 8 apart)
+    for (int j = 0; j < 8; ++j) mine[128 * (j / 4) + j % 4 + place] = sums[j];   // (twice, by lanes 8 apart)
     lds_barrier();
     if (t.team == 0) {
       for (int k = 1; k < a.teams; ++k) {
         const float* other = reinterpret_cast<const float*>(own + k * a.strips * kBwdWaveBytes);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sums[j] += other[128 * (j / 4) + 4 * (j % 4) + place];
+        for (int j = 0; j < 8; ++j) sums[j] += other[128 * (j / 4) + j % 4 + place];
       }
     }
   }
-  if (t.team == 0 && t.ok && (t.lane & 8) == 0) {
-    float* dst = a.partials + (int64_t)blockIdx.x * 2 * a.cols + t.c0 + place;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) dst[(j / 4) * a.cols + 4 * (j % 4)] = sums[j];
-  }
+  if (t.team == 0 && t.ok && (t.lane & 8) == 0) store_partials(a.partials + (int64_t)blockIdx.x * 2 * a.cols + t.c0 + place, a.cols, sums);
 }
 
 // ------------------------------------------------------------------------------------------------ host

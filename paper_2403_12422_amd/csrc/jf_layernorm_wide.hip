@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(768) layernorm_bwd_wide_kernel(const LayerNorm
       reduce_rows32(cgs, cbs, part);
       if ((t.lane & 8) == 0) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sums[256 * s + 128 * (j / 4) + 4 * (j % 4) + place] += part[j];
+        for (int j = 0; j < 8; ++j) sums[256 * s + 128 * (j / 4) + j % 4 + place] += part[j];
       }
       wait_all_loads();
     }
