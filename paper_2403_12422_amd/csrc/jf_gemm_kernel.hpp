@@ -132,6 +132,15 @@ __device__ __forceinline__ uint32_t chunk_offset(unsigned slot_idx, unsigned out
   return KMAJOR ? min(r, outer_left - 1) * ld + min(16 * c, klim - 16) : min(r, klim - 1) * ld + min(16 * c, outer_left - 16);
 }
 
+// The lane's number, computed where it is needed, so that neither it nor what follows from it takes a register through the K loop (where
+// one too many goes to scratch memory, whose loads wait for the stages in flight: weight gradient 735 -> 796 us).
+__device__ __forceinline__ int lane_again() {
+  int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(lane));
+  __builtin_assume(lane >= 0 && lane < 64);
+  return lane;
+}
+
 // f(integral_constant<int, I>) for I = BEGIN .. END-1, unrolled at compile time
 template <int BEGIN, int END, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -240,6 +249,8 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   const unsigned wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;  // first 32-granule of this wave inside the tile
 
+  // 256x128 at B = 32, 128 registers for 64 accumulators and two INT32 tiles: five others went to scratch memory, the lane's number among them
+  constexpr bool LANE_AGAIN = B == 32 && NW == 8 && NTILE == 4;
   constexpr int GROUP_M = TM >= 256 ? 4 : 8;
   int m0, n0;
   tile_origin<TM, TN, GROUP_M>(tile_index, ntiles, g.M, g.Nn, m0, n0);
@@ -300,12 +311,6 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   addrB.init(wn0, lane);
 
   float acc[WM][WN][16];
-#pragma unroll
-  for (int a = 0; a < WM; ++a)
-#pragma unroll
-    for (int b = 0; b < WN; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
   const v16i zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 
   auto dump_tile = [&](const v16i& v, int a, int b) __attribute__((always_inline)) {
@@ -351,7 +356,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   };
   auto issue_scales = [&](int seg) __attribute__((always_inline)) {
     if (DUMP) return;
-    const int kb = min(scale_block(seg * SEG + lane), nkb - 1);
+    const int lane = LANE_AGAIN ? lane_again() : tid & 63, kb = min(scale_block(seg * SEG + lane), nkb - 1);
 #pragma unroll
     for (int r0 = 0; r0 < Shape::SCALE_ROWS; r0 += NW) {
       const int r = r0 + (int)wave;
@@ -367,6 +372,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   auto read_scales = [&](int seg) __attribute__((always_inline)) {
     if (DUMP) return;
     typedef __attribute__((address_space(3))) float* lds_f32;
+    const int lane = LANE_AGAIN ? lane_again() : tid & 63;
     const int8_t* p = s_scale + (seg & 1) * Shape::SCALE_ROWS * 256 + 4 * lane;
     const int slot = seg * SEG + lane, kb = scale_block(slot);
     const bool counts = slot < last_first || (kb >= last_first && kb < nkb);
@@ -509,13 +515,20 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   issue_scales(0);   // the wait for the first stage takes them in
 #pragma unroll 1
   for (int t = 1; t < NBUF; ++t) issue_stage(t);
+  // while the first stage is on its way (the compiler would do it behind the wait, 64 instructions of every wave of a SIMD)
+#pragma unroll
+  for (int a = 0; a < WM; ++a)
+#pragma unroll
+    for (int b = 0; b < WN; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) asm volatile("v_mov_b32 %0, 0" : "=v"(acc[a][b][r]));
   wait_stage(std::integral_constant<int, NBUF - 1>());
-  read_scales(0);
-  if (nkb > SEG) issue_scales(1);
   static_for<0, (STEPWISE ? AHEAD : STEPS) * READS>([&](auto n) __attribute__((always_inline)) {
     constexpr int j = decltype(n)::value / READS;
     read_frag(0, STEPWISE ? j : 0, j, decltype(n)::value % READS);
   });
+  read_scales(0);
+  if (nkb > SEG) issue_scales(1);
   static_for<0, KPB>([&](auto js) __attribute__((always_inline)) { chain_step(0, 0, decltype(js)::value, vi[0]); });
   scale = scale_of(0, 0);
 #pragma unroll 1
@@ -548,6 +561,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   // ---- epilogue: optional FP32 store, per-block max-abs, Eq. 1, packed INT8 store.  Vector-ALU work like the loop, and the last
   // workgroup's has nothing beside it: the maxima of the wave's blocks are reduced together and Eq. 1's scale is computed once for all
   // of them (four blocks: 600 -> 470 instructions, 4096 x 768 -> 3072 23.85 -> 23.2 us, 8192 x 1280 -> 5120 112 -> 110).
+  const int lane_out = LANE_AGAIN ? lane_again() : lane, tid_out = LANE_AGAIN ? (int)(64 * wave) + lane_out : tid;
   // Pieces of quantization blocks that this wave holds: at B = 32 its sub-blocks, else one, whole or shared with other waves.
   constexpr int PM = WM * 32 < B ? WM : B / 32, PN = WN * 32 < B ? WN : B / 32, PIECES_N = WN / PN, PIECES = WM / PM * PIECES_N;
   float piece[PIECES];
@@ -562,7 +576,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   float amax = wave_max_of<PIECES>(piece);   // of the lane's piece
   if constexpr (PM * 32 < B || PN * 32 < B) {
     static_assert(PIECES == 1, "the waves of a block exchange one value each");
-    if (lane == 0) s_amax[wm0][wn0] = amax;
+    if (lane_out == 0) s_amax[wm0][wn0] = amax;
     __syncthreads();
     constexpr int G = B / 32;
     const int ga = wm0 / G * G, gb = wn0 / G * G;
@@ -575,8 +589,8 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
   double inv_out = 0.0;
   if (g.Oq) {
     block_scale(amax, scale_out, inv_out);
-    const int k = lane_value<PIECES>(lane), row = m0 + 32 * (wm0 + k / PIECES_N * PM), col = n0 + 32 * (wn0 + k % PIECES_N * PN);
-    if (lane == value_lane<PIECES>(k) && row < g.M && col < g.Nn && row % B == 0 && col % B == 0)
+    const int k = lane_value<PIECES>(lane_out), row = m0 + 32 * (wm0 + k / PIECES_N * PM), col = n0 + 32 * (wn0 + k % PIECES_N * PN);
+    if (lane_out == value_lane<PIECES>(k) && row < g.M && col < g.Nn && row % B == 0 && col % B == 0)
       store_out(&g.Os[(int64_t)(row / B) * (g.Nn / B) + col / B], scale_out);
   }
   // The code tile is staged in the operand ring: in one slot, or split by rows over two slots when a slot is
@@ -595,8 +609,8 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
     for (int b = 0; b < WN; ++b) {
       const int mrow0 = m0 + 32 * (wm0 + a), ncol0 = n0 + 32 * (wn0 + b);
       if (mrow0 >= g.M || ncol0 >= g.Nn) continue;  // wave-uniform: the whole sub-block is outside
-      const int m = mrow0 + (lane & 31);
-      const int nb = ncol0 + 4 * (lane >> 5);
+      const int m = mrow0 + (lane_out & 31);
+      const int nb = ncol0 + 4 * (lane_out >> 5);
       if (g.Of) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
@@ -607,10 +621,10 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
         const double inv = PIECES == 1 ? inv_out : read_lane_f64(inv_out, value_lane<PIECES>(a / PM * PIECES_N + b / PN));
         // Codes go to LDS first, laid out as the TM x TN byte tile with its 16-byte chunks XOR-swizzled by the
         // row, so that the tile can be written to memory as whole rows.
-        const int row = 32 * (wm0 + a) + (lane & 31);
+        const int row = 32 * (wm0 + a) + (lane_out & 31);
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const int col = 32 * (wn0 + b) + 8 * q4 + 4 * (lane >> 5);
+          const int col = 32 * (wn0 + b) + 8 * q4 + 4 * (lane_out >> 5);
           const int chunk = (col >> 4) ^ (row & (TN / 16 - 1));
           *reinterpret_cast<uint32_t*>(code_row(row) + 16 * chunk + (col & 15)) =
               quantize4(acc[a][b][4 * q4], acc[a][b][4 * q4 + 1], acc[a][b][4 * q4 + 2], acc[a][b][4 * q4 + 3], inv);
@@ -624,7 +638,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, const int tile_index, cons
     static_assert((TM * CPRO) % (64 * NW) == 0, "whole passes over the code tile");
 #pragma unroll
     for (int i = 0; i < (TM * CPRO) / (64 * NW); ++i) {
-      const int id = i * 64 * NW + tid;
+      const int id = i * 64 * NW + tid_out;
       const int row = id / CPRO, c = id % CPRO;
       if (m0 + row < g.M && n0 + 16 * c < g.Nn) {
         const uint4 v = *reinterpret_cast<const uint4*>(code_row(row) + 16 * (c ^ (row & (CPRO - 1))));

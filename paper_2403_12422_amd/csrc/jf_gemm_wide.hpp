@@ -115,14 +115,6 @@ __device__ __forceinline__ KernelArgs read_again(KernelArgs a) {
   return a;
 }
 
-// The lane's number, computed where it is needed, so that neither it nor what follows from it takes a register through the K loop (where
-// one too many goes to scratch memory, whose loads wait for the stages in flight: weight gradient 735 -> 796 us).
-__device__ __forceinline__ int lane_again() {
-  int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  asm volatile("" : "+v"(lane));
-  return lane;
-}
-
 // Tiles tile_index, tile_index + stride, ... of `ntiles`, on a workgroup of eight waves; tile_index < ntiles.
 template <int B, bool AK, bool BK>
 __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index, const int stride, const int ntiles,
