@@ -30,6 +30,7 @@ inline int32_t launch_status() {
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline bool aligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
 inline bool valid_block(int32_t b) { return b == 32 || b == 64 || b == 128; }
+inline int block_log2(int32_t b) { return b == 32 ? 5 : b == 64 ? 6 : 7; }
 // Dimensions are kept below 2^24 so that every index fits an int32 after
 // division by the block size and element offsets fit 48 bits.
 // Rows of dgamma | dbeta partial sums that the first kernel of LayerNorm backward leaves in the workspace: one per

@@ -22,16 +22,16 @@ namespace jf {
 // never leaves its wave.
 struct RowStrips {
   int ch, rsub, wave, nstrips;
-  int lc, col, block;
+  int lc, col, log2b;
   bool ok;
-  __device__ __forceinline__ RowStrips(int cols, int block_size) {
+  __device__ __forceinline__ RowStrips(int cols, int block_log2, int strips) {
     const int lane = threadIdx.x & 63;
     ch = lane & 7;
     rsub = lane >> 3;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    nstrips = blockDim.x >> 6;
-    block = block_size;
-    lc = cols / block;
+    nstrips = strips;
+    log2b = block_log2;
+    lc = cols >> log2b;
     // rows wider than 16 strips (2048 columns) are shared evenly by the workgroups blockIdx.y = 0, 1, ...
     const int c0 = (blockIdx.y * nstrips + wave) * 128, c = c0 + 16 * ch;
     ok = c < cols;
@@ -40,7 +40,7 @@ struct RowStrips {
   // element offset of the lane's chunk of row rsub of the 32-row group g; pass p adds 8 p cols
   __device__ __forceinline__ int64_t base(int g, int cols) const { return (int64_t)(g * 32 + rsub) * cols + col; }
   // index of the lane's quantization block in a scale grid
-  __device__ __forceinline__ int64_t block_index(int g) const { return (int64_t)(g * 32 / block) * lc + col / block; }
+  __device__ __forceinline__ int64_t block_index(int g) const { return (int64_t)(g * 32 >> log2b) * lc + (col >> log2b); }
 };
 
 // Row statistics of LayerNorm from the codes (the per-row mean and sum of squares of App. A, here taken of the INT8 input
@@ -50,12 +50,12 @@ struct RowStrips {
 // strips, over the 8 chunk lanes of a row (three DPP steps) and over the waves through LDS, in a fixed order.  The
 // normalisation itself is an element-wise operator on strips or tiles.
 __global__ void __launch_bounds__(1024) layernorm_row_stats_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX,
-                                                                  float eps, int rows, int cols, int block,
+                                                                  float eps, int rows, int cols, int block_log2, int nwaves,
                                                                   float* __restrict__ mean_out, float* __restrict__ rstd_out) {
   __shared__ double s_row[16][32][2];
   const int lane = threadIdx.x & 63, ch = lane & 7, rsub = lane >> 3;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
-  const int bi = blockIdx.x, lc = cols / block;   // bi: group of 32 rows
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bi = blockIdx.x, lc = cols >> block_log2;   // bi: group of 32 rows
   const int64_t pass = (int64_t)8 * cols;
   double cs[4] = {0.0, 0.0, 0.0, 0.0}, cq[4] = {0.0, 0.0, 0.0, 0.0};
   for (int c0 = wave * 128; c0 < cols; c0 += nwaves * 128) {
@@ -65,7 +65,7 @@ __global__ void __launch_bounds__(1024) layernorm_row_stats_kernel(const int8_t*
     uint4 px[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) px[p] = *reinterpret_cast<const uint4*>(X + base + p * pass);
-    const double sd = ok ? (double)SX[(int64_t)(bi * 32 / block) * lc + col / block] : 0.0;
+    const double sd = ok ? (double)SX[(int64_t)(bi * 32 >> block_log2) * lc + (col >> block_log2)] : 0.0;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       int s1, s2;
@@ -121,16 +121,16 @@ constexpr int kSumsG = 4096, kSumsScaleX = 8192, kSumsScaleG = kSumsScaleX + 256
               kSumsWaveBytes = kSumsRstd + 128, kSumsRowBytes = 2 * 32 * 8;
 template <bool AHEAD>
 __global__ void __launch_bounds__(1024) layernorm_bwd_sums_kernel(
-    const int8_t* __restrict__ G, const float* __restrict__ SG, const int8_t* __restrict__ X, const float* __restrict__ SX,
-    const float* __restrict__ gamma, const float* __restrict__ mean_in, const float* __restrict__ rstd_in, int rows,
-    int cols, int block, float* __restrict__ row_means, float* __restrict__ partials) {
+    const int8_t* __restrict__ G, const int8_t* __restrict__ X, const float* __restrict__ SG, const float* __restrict__ SX, int rows, int cols, int block_log2,
+    int strips, const float* __restrict__ gamma, const float* __restrict__ mean_in, const float* __restrict__ rstd_in, float* __restrict__ row_means,
+    float* __restrict__ partials) {
   extern __shared__ __align__(16) int8_t smem[];
-  const RowStrips t(cols, block);
+  const RowStrips t(cols, block_log2, strips);
   float* const s_row = reinterpret_cast<float*>(smem);   // [row block parity][strip][row][sum of ghat, of ghat xhat]
   int8_t* const own = smem + t.nstrips * kSumsRowBytes + t.wave * kSumsWaveBytes;   // with AHEAD
   const int nblocks = rows / 32, lane = threadIdx.x & 63;
   const float inv_cols = 1.0f / (float)cols;
-  const uint32_t off = (uint32_t)(t.rsub * cols + t.col), off_scale = (uint32_t)(t.col / block) * 4;
+  const uint32_t off = (uint32_t)(t.rsub * cols + t.col), off_scale = (uint32_t)(t.col >> block_log2) * 4;
   auto request = [&](int g) __attribute__((always_inline)) {
     const int8_t* const x = uniform_pointer(X + (int64_t)g * 32 * cols);
     const int8_t* const gr = uniform_pointer(G + (int64_t)g * 32 * cols);
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_sums_kernel(
       load_lds_16(x + (int64_t)p * 8 * cols, off, own, 1024 * p);
       load_lds_16(gr + (int64_t)p * 8 * cols, off, own, kSumsG + 1024 * p);
     }
-    const int64_t grid_row = (int64_t)(g * 32 / block) * t.lc;
+    const int64_t grid_row = (int64_t)(g * 32 >> block_log2) * t.lc;
     load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(SX + grid_row)), off_scale, own, kSumsScaleX);
     load_lds_4(uniform_pointer(reinterpret_cast<const int8_t*>(SG + grid_row)), off_scale, own, kSumsScaleG);
     if (lane < 32) {   // 32 floats each
@@ -298,15 +298,14 @@ struct ColumnSums {
 // width.
 template <StorePolicy SP>
 __global__ void __launch_bounds__(64 * kStripWaves) layernorm_bwd_apply_strip32_kernel(
-    const int8_t* __restrict__ G, const float* __restrict__ SG, const int8_t* __restrict__ X, const float* __restrict__ SX,
-    const float* __restrict__ gamma, const float* __restrict__ mean_in, const float* __restrict__ rstd_in,
-    const float* __restrict__ row_means, int ranges, int rows, int cols, int8_t* __restrict__ dX, float* __restrict__ SdX,
-    const ColumnSums cs) {
-  if ((int)blockIdx.x < cs.groups) {
+    const int8_t* __restrict__ G, const int8_t* __restrict__ X, const float* __restrict__ SG, const float* __restrict__ SX, int rows, int cols, int groups,
+    int ranges, const float* __restrict__ gamma, const float* __restrict__ mean_in, const float* __restrict__ rstd_in, const float* __restrict__ row_means,
+    int8_t* __restrict__ dX, float* __restrict__ SdX, const ColumnSums cs) {
+  if ((int)blockIdx.x < groups) {
     colsum_group<kStripWaves>(blockIdx.x, cs.partials, cs.nparts, 2 * cols, cs.dgamma, cs.dbeta);
     return;
   }
-  const Strip32 t(rows, cols, cs.groups);
+  const Strip32 t(rows, cols, groups);
   if (!t.inside) return;   // a whole wave; the strip kernels have no workgroup barrier
   const int64_t pass = (int64_t)8 * cols;
   uint4 px[4], pg[4];
@@ -364,10 +363,10 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_bwd_apply_strip32_
 // ... and their shares are added through LDS in wave order.
 __global__ void __launch_bounds__(1024) row_stats_from_partials_kernel(const float* __restrict__ row_mean,
                                                                         const float* __restrict__ row_sumsq, float eps,
-                                                                        int rows, int lc, int cols,
+                                                                        int rows, int lc, int cols, int NW,
                                                                         float* __restrict__ mean_out, float* __restrict__ rstd_out) {
   __shared__ double s_part[2][16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = min((int)blockIdx.x * 64 + lane, rows - 1);   // lanes past the last row repeat it and write nothing
   double s = 0.0, q = 0.0;
   for (int j0 = wave; j0 < lc; j0 += 4 * NW) {   // four block columns in flight at a time
@@ -449,23 +448,23 @@ __global__ void __launch_bounds__(64 * kStripWaves) layernorm_apply_strip32_kern
 // block column inside a wave and over the four waves through LDS.  MODE 0: y = (x - mean) rstd gamma + beta (forward),
 // MODE 1: dx from the row means of the sums kernel (backward).
 template <int B, int MODE, StorePolicy SP>
-__global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __restrict__ G, const float* __restrict__ SG,
-                                                              const int8_t* __restrict__ X, const float* __restrict__ SX,
+__global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __restrict__ G, const int8_t* __restrict__ X, const float* __restrict__ SG,
+                                                              const float* __restrict__ SX, int rows, int cols, int groups, int ranges,
                                                               const float* __restrict__ gamma, const float* __restrict__ beta,
                                                               const float* __restrict__ mean_in, const float* __restrict__ rstd_in,
-                                                              const float* __restrict__ row_means, int ranges, int rows, int cols,
-                                                              int8_t* __restrict__ Y, float* __restrict__ SY, const ColumnSums cs) {
+                                                              const float* __restrict__ row_means, int8_t* __restrict__ Y,
+                                                              float* __restrict__ SY, const ColumnSums cs) {
   constexpr int P = B / 32;
   __shared__ float s_amax[4][4];
   if constexpr (MODE == 1) {
-    if ((int)blockIdx.x < cs.groups) {
+    if ((int)blockIdx.x < groups) {
       colsum_group<4>(blockIdx.x, cs.partials, cs.nparts, 2 * cols, cs.dgamma, cs.dbeta);
       return;
     }
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int ch = lane & 7, rsub = lane >> 3;
-  const TileIndex wg = tile_of_workgroup((cols + 127) / 128, MODE == 1 ? cs.groups : 0);
+  const TileIndex wg = tile_of_workgroup((cols + 127) / 128, MODE == 1 ? groups : 0);
   const int col = wg.x * 128 + 16 * ch;
   const int r0 = wg.y * B + wave * (B / 4);
   const bool col_ok = col < cols;
@@ -532,19 +531,20 @@ __global__ void __launch_bounds__(256) layernorm_tile_kernel(const int8_t* __res
 // Strips are shared evenly by the column ranges.  The next row block is requested ahead (AHEAD) where a workgroup takes four or more:
 // 131072 x 1088 at block 64, whole backward pass, 175 -> 165 us, 262144 x 3072 850 -> 815; with one or two the way through LDS costs
 // more than it hides (4096 x 4096 22.0 and 23.1, 32768 x 2048 69.2 and 70.4).
-template <typename... Args>
-static void launch_ln_bwd_sums(int64_t N, int64_t C, dim3 grid, hipStream_t st, Args... args) {
+static void launch_ln_bwd_sums(const int8_t* dY, const float* SdY, const int8_t* X, const float* SX, const float* gamma, const float* mean, const float* rstd,
+                               int64_t N, int64_t C, int32_t block, float* row_means, float* partials, dim3 grid, hipStream_t st) {
   using namespace jf;
   const int ns = (int)(((C + 127) / 128 + grid.y - 1) / grid.y);   // waves
-  if (N / 32 < 4 * (int64_t)grid.x) {
-    hipLaunchKernelGGL(layernorm_bwd_sums_kernel<false>, grid, dim3(64 * ns), ns * kSumsRowBytes, st, args...);
-    return;
-  }
+  const auto launch = [&](auto kernel, int wave_bytes) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * ns), ns * wave_bytes, st, dY, X, SdY, SX, (int)N, (int)C, block_log2(block), ns, gamma, mean, rstd,
+                       row_means, partials);
+  };
+  if (N / 32 < 4 * (int64_t)grid.x) return launch(layernorm_bwd_sums_kernel<false>, kSumsRowBytes);
   constexpr int BYTES = kSumsRowBytes + kSumsWaveBytes;
   static_assert(16 * BYTES <= 160 * 1024, "sixteen waves share the LDS of a compute unit");
   // (see launch_rows)
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(layernorm_bwd_sums_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 16 * BYTES) != hipSuccess) return;
-  hipLaunchKernelGGL(layernorm_bwd_sums_kernel<true>, grid, dim3(64 * ns), ns * BYTES, st, args...);
+  launch(layernorm_bwd_sums_kernel<true>, BYTES);
 }
 
 // A statistics kernel (from the Add's partials, or from the codes), then the normalisation on tiles.
@@ -573,11 +573,11 @@ static int32_t layernorm_fwd(const int8_t* X, const float* SX, const float* row_
   if (row_mean != nullptr) {
     const int waves = (int)std::min<int64_t>(16, std::max<int64_t>(4, C / block / 4));
     hipLaunchKernelGGL(row_stats_from_partials_kernel, dim3((unsigned)((N + 63) / 64)), dim3(64 * waves), 0, st, row_mean, row_sumsq,
-                       eps, (int)N, (int)(C / block), (int)C, mean, rstd);
+                       eps, (int)N, (int)(C / block), (int)C, waves, mean, rstd);
   } else {
     const int waves = (int)std::min<int64_t>(16, (C + 127) / 128);
     hipLaunchKernelGGL(layernorm_row_stats_kernel, dim3((unsigned)(N / 32)), dim3(64 * waves), 0, st, X, SX, eps, (int)N, (int)C,
-                       (int)block, mean, rstd);
+                       block_log2(block), waves, mean, rstd);
   }
   rc = launch_status();
   if (rc != JF_OK) return rc;
@@ -589,11 +589,11 @@ static int32_t layernorm_fwd(const int8_t* X, const float* SX, const float* row_
       hipLaunchKernelGGL((layernorm_apply_strip32_kernel<SP>), strip_grid(N, C), dim3(64 * kStripWaves), 0, st, X, SX, gamma, beta, mean,
                          rstd, (int)N, (int)C, Y, SY);
     else if (block == 64)
-      hipLaunchKernelGGL((layernorm_tile_kernel<64, 0, SP>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, none, X, SX, gamma, beta,
-                         (const float*)mean, (const float*)rstd, none, 1, (int)N, (int)C, Y, SY, ColumnSums{});
+      hipLaunchKernelGGL((layernorm_tile_kernel<64, 0, SP>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, X, none, SX, (int)N, (int)C, 0, 1, gamma,
+                         beta, (const float*)mean, (const float*)rstd, none, Y, SY, ColumnSums{});
     else
-      hipLaunchKernelGGL((layernorm_tile_kernel<128, 0, SP>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, none, X, SX, gamma, beta,
-                         (const float*)mean, (const float*)rstd, none, 1, (int)N, (int)C, Y, SY, ColumnSums{});
+      hipLaunchKernelGGL((layernorm_tile_kernel<128, 0, SP>), tiles, dim3(256), 0, st, (const int8_t*)nullptr, X, none, SX, (int)N, (int)C, 0, 1, gamma,
+                         beta, (const float*)mean, (const float*)rstd, none, Y, SY, ColumnSums{});
   });
   return launch_status();
 }
@@ -650,8 +650,7 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
   // the workspace holds the partial rows, then the two row means of every row (per range of 2048 columns)
   float* row_means = partials + (size_t)nparts * 2 * (size_t)C;
   const int ranges = (int)((C + 2047) / 2048);
-  launch_ln_bwd_sums(N, C, dim3((unsigned)nparts, (unsigned)ranges), st, dY, SdY, X, SX, gamma, mean, rstd, (int)N, (int)C, (int)block,
-                     row_means, partials);
+  launch_ln_bwd_sums(dY, SdY, X, SX, gamma, mean, rstd, N, C, block, row_means, partials, dim3((unsigned)nparts, (unsigned)ranges), st);
   const int32_t rc1 = launch_status();
   if (rc1 != JF_OK) return rc1;
   const ColumnSums cs = {partials, dgamma, dbeta, nparts, sums_in_place ? 0 : (int)((2 * C + 63) / 64)};
@@ -660,14 +659,14 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
   with_store_policy(N, C, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
     if (block == 32)
-      hipLaunchKernelGGL((layernorm_bwd_apply_strip32_kernel<SP>), strips, dim3(64 * kStripWaves), 0, st, dY, SdY, X, SX, gamma,
-                         mean, rstd, row_means, ranges, (int)N, (int)C, dX, SdX, cs);
+      hipLaunchKernelGGL((layernorm_bwd_apply_strip32_kernel<SP>), strips, dim3(64 * kStripWaves), 0, st, dY, X, SdY, SX, (int)N, (int)C, cs.groups,
+                         ranges, gamma, mean, rstd, row_means, dX, SdX, cs);
     else if (block == 64)
-      hipLaunchKernelGGL((layernorm_tile_kernel<64, 1, SP>), tiles, dim3(256), 0, st, dY, SdY, X, SX, gamma, none, mean, rstd,
-                         (const float*)row_means, ranges, (int)N, (int)C, dX, SdX, cs);
+      hipLaunchKernelGGL((layernorm_tile_kernel<64, 1, SP>), tiles, dim3(256), 0, st, dY, X, SdY, SX, (int)N, (int)C, cs.groups, ranges, gamma, none,
+                         mean, rstd, (const float*)row_means, dX, SdX, cs);
     else
-      hipLaunchKernelGGL((layernorm_tile_kernel<128, 1, SP>), tiles, dim3(256), 0, st, dY, SdY, X, SX, gamma, none, mean, rstd,
-                         (const float*)row_means, ranges, (int)N, (int)C, dX, SdX, cs);
+      hipLaunchKernelGGL((layernorm_tile_kernel<128, 1, SP>), tiles, dim3(256), 0, st, dY, X, SdY, SX, (int)N, (int)C, cs.groups, ranges, gamma, none,
+                         mean, rstd, (const float*)row_means, dX, SdX, cs);
   });
   const int32_t rc2 = launch_status();
   return rc2 != JF_OK || !sums_in_place ? rc2 : launch_colsum();

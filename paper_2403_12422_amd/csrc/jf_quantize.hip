@@ -210,16 +210,15 @@ extern "C" int32_t jf_dequantize_block(const int8_t* q, const float* s, int64_t 
   if (!valid_dim(rows, block) || !valid_dim(cols, block) || !valid_size(rows, cols) || ldo < cols) return JF_ERR_SHAPE;
   if (!aligned16(q) || !aligned4(s) || !aligned16(out) || (ldo % 8)) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const int log2b = block == 32 ? 5 : (block == 64 ? 6 : 7);
   const int64_t per_wg = 256 * DQ_CHUNKS * (out_dtype == 0 ? 4 : 8);
   const unsigned grid = (unsigned)((rows * cols + per_wg - 1) / per_wg);
   with_store_policy(rows, ldo * (out_dtype == 0 ? 4 : 2), [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
     if (out_dtype == 0)
-      hipLaunchKernelGGL((dequantize_kernel<float, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
+      hipLaunchKernelGGL((dequantize_kernel<float, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, block_log2(block),
                          static_cast<float*>(out), ldo);
     else
-      hipLaunchKernelGGL((dequantize_kernel<_Float16, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, log2b,
+      hipLaunchKernelGGL((dequantize_kernel<_Float16, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, block_log2(block),
                          static_cast<_Float16*>(out), ldo);
   });
   return launch_status();
