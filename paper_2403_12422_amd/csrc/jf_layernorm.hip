@@ -638,10 +638,8 @@ static int32_t layernorm_bwd_launch(const int8_t* dY, const float* SdY, const in
     a.dX = dX; a.SdX = SdX; a.partials = partials;
     a.dgamma = dgamma; a.dbeta = dbeta;
     if (!whole_rows) nparts = launch_layernorm_bwd_wide(a, st);
-    else if (block == 32 && layernorm_split_parts(N, C, true) > 1 && !sums_in_place && !any_overlap(out, in)) {
-      launch_layernorm_bwd_split(a, st);
-      return launch_status();
-    } else
+    else if (block == 32 && layernorm_split_parts(N, C, true) > 1 && !sums_in_place && !any_overlap(out, in)) nparts = launch_layernorm_bwd_split(a, st);
+    else
       nparts = (block == 32 ? launch_layernorm_bwd_rows_b32 : block == 64 ? launch_layernorm_bwd_rows_b64 : launch_layernorm_bwd_rows_b128)(
           a, sums_in_place || any_overlap(out, in), st);
     const int32_t rc = launch_status();

@@ -205,18 +205,26 @@ int launch_layernorm_bwd_rows_b64(const LayerNormBwdRows& a, bool in_place, hipS
 int launch_layernorm_bwd_rows_b128(const LayerNormBwdRows& a, bool in_place, hipStream_t st);
 
 // How many workgroups share a row group at block size 32 (jf_layernorm_split.hip), 1: the one-pass kernels.  Not where an output shares
-// memory with an input, which the other workgroups of a group still read.  Every workgroup needs a compute unit to itself, backward with
-// those that own columns (32 each, behind the rows' workgroups, which come in eights); forward four parts pay for half the chip
-// only.  One workgroup, two, four in us: forward 1024 x 1280 6.65, 5.68, 5.36; 1536 x 768 5.42, 4.72, 4.83; 4096 x 768 5.58, 4.94, 6.5;
-// 6144 x 768 5.71, 6.69, 7.6; backward 1056 x 800 6.6, 6.1, 5.9; 1536 x 1536 8.6, 8.25, 8.05; 2048 x 2048 12.1, 10.05, 15; 3072 x 1536 14.1,
-// 9.65, 14.3; 4096 x 768 10.3, 13.9, 16.9.
+// memory with an input, which the other workgroups of a group still read.  Every workgroup needs a compute unit to itself, backward four
+// of them with those that own columns (32 each, behind the rows' workgroups, which come in eights); forward four parts pay for half the
+// chip only.  One workgroup, two, four in us: forward 1024 x 1280 6.65, 5.68, 5.36; 1536 x 768 5.42, 4.72, 4.83; 4096 x 768 5.58, 4.94, 6.5;
+// 6144 x 768 5.71, 6.69, 7.6; backward 1056 x 800 6.6, 6.1, 5.9; 1536 x 1536 8.6, 8.25, 8.05; 2048 x 2048 12.1, 10.05, 15; 4096 x 768 9.4, 8.4;
+// 4096 x 2048 15.8, 13.75.
 inline int layernorm_split_parts(int64_t N, int64_t C, bool backward) {
   const int64_t groups = backward ? (N / 32 + 7) / 8 * 8 : N / 32, units = 256 - (backward ? C / 32 : 0);
   if (C > 2048) return 1;
-  return 4 * groups <= (backward ? units : 128) ? 4 : 2 * groups <= units ? 2 : 1;
+  return 4 * groups <= (backward ? units : 128) ? 4 : 2 * groups <= (backward ? 256 : units) ? 2 : 1;
+}
+// Backward: whether the two workgroups of a group leave the sums of their columns as partial rows, for another launch, instead of to workgroups
+// that own columns: where there is no room for those, and where they take longer than the rows, which is by the row groups that
+// each of their waves has (as many waves as strips, at least eight).  Columns apart -> partial rows in us: 2048 x 768 8.55 -> 8.95, x 1280 9.3 ->
+// 11.05; 2560 x 768 10.1 -> 9.25, x 1024 8.6 -> 9.5; 2688 x 768 10.55 -> 9.45, x 1536 12.1 -> 12.15, x 2048 12.5 -> 14.0; 3072 x 768 11.9 -> 9.6, x 1536 13.6 ->
+// 12.3, x 2048 13.9 -> 14.2; 3840 x 512 13.7 -> 8.45.
+inline bool layernorm_split_columns(int64_t N, int64_t C) {
+  return 2 * ((N / 32 + 7) / 8 * 8) > 256 - C / 32 || (N / 32 > 80 && C <= 1536);
 }
 void launch_layernorm_split(LayerNormRows a, hipStream_t st);
-void launch_layernorm_bwd_split(LayerNormBwdRows a, hipStream_t st);
+int launch_layernorm_bwd_split(LayerNormBwdRows a, hipStream_t st);   // returns as those above
 
 // Whether the kernels for wider rows (jf_layernorm_wide.hip) take a pass at block size 32, and their launches; the backward one
 // returns its number of partial rows (at most 256 and at most rows / 32).  Forward not from the row partials of an Add: those say what

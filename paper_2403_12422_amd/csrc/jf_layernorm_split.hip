@@ -6,7 +6,7 @@
 // each goes on with its part of every strip: one block of the four, or two.  The sums are those of the one-pass kernels, in the
 // same order, and so are the results.
 // Forward / backward in us: 128 x 128 4.1 -> 3.55 / 4.45 -> 4.2, 1056 x 800 5.4 -> 4.75 / 6.6 -> 5.9, 1024 x 2048 7.9 -> 6.65 / 11.0 -> 9.05,
-// 2048 x 768 5.4 -> 4.75 / 7.9 -> 6.85, 4096 x 768 forward 5.6 -> 4.95.  What is left is mostly the launch, the way to memory and back
+// 2048 x 768 5.4 -> 4.75 / 7.9 -> 6.85, 4096 x 768 5.6 -> 4.95 / 9.4 -> 8.4.  What is left is mostly the launch, the way to memory and back
 // (an empty kernel 1.6, 1 MB copied 1.7), and the rows themselves, of which a compute unit gets 26 bytes a nanosecond.
 #include "jf_layernorm_rows.hpp"
 
@@ -145,14 +145,44 @@ __global__ void __launch_bounds__(1024) layernorm_split_kernel(const int8_t* X, 
   store_part_of_strip<PARTS>(y, s, t.lane, ok, col, (int64_t)g * 32, a.cols, a.Y, a.SY);
 }
 
-// Backward, the column sums in workgroups of their own behind row_wgs that have rows (column_sums_direct); waves past the strips
-// are for those only.
-template <int PARTS>
+// Sums over the sixteen lanes that differ in bits 1 to 4 of 16 values, by halves as in reduce_rows_of_32 (lanes with the bit clear go on
+// with one value of a pair, with it set with the other): 50 instructions.  A lane ends with value (lane / 2) % 16.
+__device__ __forceinline__ float reduce_sixteen_rows(const float (&a)[16], int lane) {
+  const auto bits = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(int, x); };
+  const auto real = [](int x) __attribute__((always_inline)) { return __builtin_bit_cast(float, x); };
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const auto p = __builtin_amdgcn_permlane16_swap(bits(a[j]), bits(a[j + 8]), false, false);
+    v[j] = real((int)p[0]) + real((int)p[1]);
+  }
+  constexpr int SAME = 0xE4;   // quad_perm [0,1,2,3]
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {   // across 8 lanes
+    const int mine = __builtin_amdgcn_update_dpp(bits(v[j]), bits(v[j + 4]), SAME, 0xf, 0xC, false);
+    const int other = __builtin_amdgcn_update_dpp(bits(v[j + 4]), bits(v[j]), SAME, 0xf, 0xC, false);
+    v[j] = real(mine) + real(__builtin_amdgcn_mov_dpp(other, 0x128, 0xf, 0xf, false));
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {   // across 4 lanes: row_shl and row_shr, each for the lanes that it is right for
+    const int mine = __builtin_amdgcn_update_dpp(bits(v[j]), bits(v[j + 2]), SAME, 0xf, 0xA, false);
+    const int other = __builtin_amdgcn_update_dpp(bits(v[j + 2]), bits(v[j]), SAME, 0xf, 0xA, false);
+    const int low = __builtin_amdgcn_update_dpp(other, other, 0x104, 0xf, 0x5, false);
+    v[j] = real(mine) + real(__builtin_amdgcn_update_dpp(low, other, 0x114, 0xf, 0xA, false));
+  }
+  const bool second = (lane & 2) != 0;   // across 2 lanes
+  return (second ? v[1] : v[0]) + lane_xor_f32<1>(second ? v[0] : v[1]);
+}
+
+// Backward.  Column sums: in workgroups of their own behind row_wgs that have rows (column_sums_direct; waves past the strips are for
+// those only), or, COLUMNS, each workgroup's of its part, as one partial row for a row group, which another launch adds: where the rows
+// of many groups take a chip by themselves.
+template <int PARTS, bool COLUMNS>
 __global__ void __launch_bounds__(1024) layernorm_bwd_split_kernel(const int8_t* G, const float* SG, const int8_t* X, const float* SX, int rows, int cols,
                                                                    int layout, int wgs, const float* gamma, const LayerNormBwdRows) {
   extern __shared__ __align__(16) int8_t smem[];
   LayerNormBwdRows a = first_arguments(G, SG, X, SX, rows, cols, layout, wgs, gamma);
-  if ((int)blockIdx.x >= a.row_wgs) {
+  if (!COLUMNS && (int)blockIdx.x >= a.row_wgs) {
     other_arguments(a);
     column_sums_direct<32>(a, blockIdx.x - a.row_wgs, layout >> 16, reinterpret_cast<float*>(smem));
     return;
@@ -242,7 +272,7 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_split_kernel(const int8_t*
     const float4 v = *reinterpret_cast<const float4*>(s_gamma + 16 * s.chunk + 4 * d);
     gm[4 * d] = v.x, gm[4 * d + 1] = v.y, gm[4 * d + 2] = v.z, gm[4 * d + 3] = v.w;
   }
-  float y[s.PASSES][16];
+  float y[s.PASSES][16], cg[16], cb[16];   // cg, cb: sums of g xhat and g, in units of g's block scale
 #pragma unroll
   for (int p = 0; p < s.PASSES; ++p) {
     const int r = s.row0 + s.PASS_ROWS * p;
@@ -256,10 +286,25 @@ __global__ void __launch_bounds__(1024) layernorm_bwd_split_kernel(const int8_t*
       unpack4(dword_of(px, d), xc);
       unpack4(dword_of(pg, d), gc);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) y[p][4 * d + e] = __builtin_fmaf(xc[e], kxm, __builtin_fmaf(gc[e] * gm[4 * d + e], rsg, krow));
+      for (int e = 0; e < 4; ++e) {
+        y[p][4 * d + e] = __builtin_fmaf(xc[e], kxm, __builtin_fmaf(gc[e] * gm[4 * d + e], rsg, krow));
+        if (!COLUMNS) continue;
+        const float xh = __builtin_fmaf(xc[e], kx, cx);
+        cg[4 * d + e] = p == 0 ? gc[e] * xh : __builtin_fmaf(gc[e], xh, cg[4 * d + e]);
+        cb[4 * d + e] = p == 0 ? gc[e] : cb[4 * d + e] + gc[e];
+      }
     }
   }
   store_part_of_strip<PARTS>(y, s, t.lane, ok, col, (int64_t)g * 32, a.cols, a.dX, a.SdX);
+  if constexpr (COLUMNS) {
+    static_assert(PARTS == 2, "a chunk belongs to the lanes that differ in bits 1 to 4");
+    const float sum_g = reduce_sixteen_rows(cg, t.lane) * sg, sum_b = reduce_sixteen_rows(cb, t.lane) * sg;
+    if (ok) {
+      float* const dst = a.partials + (int64_t)g * 2 * a.cols + col + ((t.lane >> 1) & 15);
+      store_out(dst, sum_g);
+      store_out(dst + a.cols, sum_b);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------------ host
@@ -279,17 +324,23 @@ void launch_layernorm_split(LayerNormRows a, hipStream_t st) {
 }
 
 // Workgroups of at least eight waves for the sake of those that own columns (1056 x 160, whose rows need two: with four waves 5.8 us, eight
-// 4.55, sixteen 4.75).
-void launch_layernorm_bwd_split(LayerNormBwdRows a, hipStream_t st) {
+// 4.55, sixteen 4.75).  Returns the number of partial rows of dgamma | dbeta left in `partials`, 0 if it has written dgamma and dbeta.
+int launch_layernorm_bwd_split(LayerNormBwdRows a, hipStream_t st) {
   a.strips = (a.cols + 127) / 128;
   a.teams = 1;
   a.inv_cols = 1.0f / (float)a.cols;
+  constexpr size_t BYTES = kBwdRowBytes + kBwdWaveBytes;
+  static_assert(BYTES >= 64 * sizeof(float), "the column workgroups' sums, 64 a wave");
+  if (layernorm_split_columns(a.rows, a.cols)) {
+    a.row_wgs = split_grid<2>(a.rows / 32);
+    launch_rows<layernorm_bwd_split_kernel<2, true>>(BYTES, a.row_wgs, a.strips, a, st);
+    return a.rows / 32;
+  }
   const bool four = layernorm_split_parts(a.rows, a.cols, true) == 4;
   a.row_wgs = four ? split_grid<4>(a.rows / 32) : split_grid<2>(a.rows / 32);
   const int waves = std::max(a.strips, 8), grid = a.row_wgs + a.cols / 32;
-  constexpr size_t BYTES = kBwdRowBytes + kBwdWaveBytes;
-  static_assert(BYTES >= 64 * sizeof(float), "the column workgroups' sums, 64 a wave");
-  four ? launch_rows<layernorm_bwd_split_kernel<4>>(BYTES, grid, waves, a, st) : launch_rows<layernorm_bwd_split_kernel<2>>(BYTES, grid, waves, a, st);
+  four ? launch_rows<layernorm_bwd_split_kernel<4, false>>(BYTES, grid, waves, a, st) : launch_rows<layernorm_bwd_split_kernel<2, false>>(BYTES, grid, waves, a, st);
+  return 0;
 }
 
 }  // namespace jf

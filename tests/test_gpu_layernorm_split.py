@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 EPS, BLOCK = 1e-5, 32
 
 
-# one block, one group; a ragged last strip; groups that are no multiple of eight; four parts, two, and where they end, forward (1024
-# and 4096 rows) and backward (by the columns: 2048 x 768 and 1792 x 512, 3072 x 2048, 3840 x 512)
-@pytest.mark.parametrize("N,C", [(32, 32), (32, 2048), (96, 160), (1024, 800), (1056, 800), (1056, 160), (1792, 512), (1824, 96), (2048, 768), (3072, 2048),
-                                 (3840, 512), (3872, 512), (4096, 352), (4128, 352)])
+# one block, one group; a ragged last strip; groups that are no multiple of eight; four parts, two, and where they end, forward (1024 and 4096
+# rows) and backward (by the columns: 2048 x 768 and 1792 x 512); column sums as partial rows from 2592 x 1536 and behind 3072 x 2048 on
+@pytest.mark.parametrize("N,C", [(32, 32), (32, 2048), (96, 160), (1024, 800), (1056, 800), (1056, 160), (1792, 512), (1824, 96), (2048, 768), (2560, 1536),
+                                 (2592, 1536), (3072, 2048), (3104, 1952), (3840, 512), (3872, 512), (4064, 2048), (4096, 352), (4128, 352)])
 def test_parts_of_a_row_group(N, C):
     say(f"layernorm split {N} x {C}")
     g = workloads.rng(9300 + N + C)
