@@ -283,9 +283,9 @@ __device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, in
   s_sum[64 * wave + 32 * (value >> 4) + 16 * (lane >> 5) + (value & 15)] = sums[0];
   __syncthreads();
   if (threadIdx.x < 64) {   // the waves in order
-    float v = 0.0f;
-    for (int w = 0; w < waves; ++w) v += s_sum[64 * w + lane];
-    (lane < 32 ? a.dgamma : a.dbeta)[group * 32 + row] = v;
+    double v = 0.0;
+    for (int w = 0; w < waves; ++w) v += (double)s_sum[64 * w + lane];
+    (lane < 32 ? a.dgamma : a.dbeta)[group * 32 + row] = (float)v;
   }
 }
 
