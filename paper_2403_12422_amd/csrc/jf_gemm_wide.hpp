@@ -117,7 +117,7 @@ __device__ __forceinline__ KernelArgs read_again(KernelArgs a) {
 
 // Tiles tile_index, tile_index + stride, ... of `ntiles`, on a workgroup of eight waves; tile_index < ntiles.
 template <int B, bool AK, bool BK>
-__device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index, const int stride, const int ntiles,
+__device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave, int tile_index, const int stride, const int ntiles,
                                           int8_t* const s_ring, float* const s_amax) {
   typedef WideShape<B, AK, BK> S;
   constexpr int KC = S::KC, NBUF = S::NBUF, NW = S::NW, TM = S::TM, TN = S::TN, WM = S::WM, WN = S::WN;
@@ -125,8 +125,6 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
   constexpr int NSB = WN * 32 / B;            // block columns of a wave
   static_assert(WM * 32 <= B && NSB >= 1, "a wave has one block row and whole block columns");
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;   // first sub-block of this wave inside the tile
   const int nstages = args->K / KC;
 
@@ -215,6 +213,7 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
   constexpr bool QUARTERS = WideMfma<B, AK>::QUARTERS;
   WideFrag<TM, AK, KC, WideMfma<B, AK>::ROWS> fragA;
   WideFrag<TN, BK, KC, WideMfma<B, AK>::ROWS> fragB;
+  const int lane = lane_again();
   fragA.init(s_ring, 0, wm0, lane);
   fragB.init(s_ring, S::RING_A, wn0, lane);
   v4i fa[KPB], fb[WN][KPB];
@@ -254,6 +253,9 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, int tile_index,
   // stage in ring slot u; after_store: the stores of an epilogue may be outstanding, which are not counted in order with loads
   auto run_stage = [&](auto u_tag, bool after_store) __attribute__((always_inline)) {
     constexpr int slot = decltype(u_tag)::value, nslot = (slot + 1) % NBUF, SYNC = WN;
+    // The toggled addresses are formed again in each stage: kept over the loop they go to scratch memory, for whose loads the stages in
+    // flight are waited for.
+    if constexpr (B == 128 && AK && !BK) asm volatile("" : "+v"(fragB.at));
     static_for<0, NT>([&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value, a = i / WN, b = i % WN;
       v16i &cur = vi[i & 1], &nxt = vi[(i & 1) ^ 1];
@@ -420,7 +422,7 @@ template <int B, bool AK, bool BK>
 __global__ void __launch_bounds__(512, 2) gemm_wide_kernel(const GemmArgs, const int ntiles) {
   __shared__ __align__(1024) int8_t s_ring[WideShape<B, AK, BK>::LDS_BYTES];
   __shared__ float s_amax[8];
-  gemm_wide<B, AK, BK>((KernelArgs)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x, gridDim.x, ntiles, s_ring, s_amax);
+  gemm_wide<B, AK, BK>((KernelArgs)__builtin_amdgcn_kernarg_segment_ptr(), __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), blockIdx.x, gridDim.x, ntiles, s_ring, s_amax);
 }
 
 // Both backward products of a layer in one launch, the one with the longer tiles first (`second_first`: the weight gradient).
@@ -433,15 +435,15 @@ __global__ void __launch_bounds__(512, 2) gemm_wide_pair_kernel(const GemmArgs, 
   __shared__ float s_amax[8];
   static_assert(sizeof(GemmArgs) % 8 == 0, "the second product's arguments follow the first's");
   const KernelArgs args = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
-  const int n = gridDim.x, i = blockIdx.x;
+  const int n = gridDim.x, i = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int behind = (n - split % n + i) % n;   // this workgroup's first tile of the product that comes second
 #pragma unroll 1
   for (int turn = 0; turn < 2; ++turn) {
     const int first = turn == 0 ? i : behind;
     if ((turn == 0) != (second_first != 0)) {
-      if (first < tiles1) gemm_wide<B, true, false>(args, first, n, tiles1, s_ring, s_amax);
+      if (first < tiles1) gemm_wide<B, true, false>(args, wave, first, n, tiles1, s_ring, s_amax);
     } else {
-      if (first < tiles2) gemm_wide<B, false, false>(args + 1, first, n, tiles2, s_ring, s_amax);
+      if (first < tiles2) gemm_wide<B, false, false>(args + 1, wave, first, n, tiles2, s_ring, s_amax);
     }
     __syncthreads();   // the next product's loads may not land before every wave is through with this one's
   }
