@@ -162,12 +162,7 @@ static int choose_shape(int block, Product p, const GemmArgs& a, int forced) {
 // Pair of the backward products, 0 for two launches.
 static int choose_pair(int block, const GemmArgs& dgrad, const GemmArgs& wgrad, int forced) {
   const ShapeTable t = shape_table(block);
-  const ShapeTable::Choice d = t.best(kDgrad, dgrad), w = t.best(kWgrad, wgrad);
-  double least = d.us + w.us;
-  // Both on persistent tiles at B = 128, under the power limit, two launches in turn take 1.25 to 1.5 times the sum of the model's times, a pair
-  // 1.1 times its own (4096^3 163 us and 107, 151 and 131; 16384 x 4096 -> 11008 1655 and 1317, 1550 and 1412).  On two times 40 and 70
-  // layers timed by turns the choice then costs 1.1 and 1.2 % against the best instead of 1.75 and 1.7; at B = 64 it would gain nothing.
-  if (block == 128 && t.find(d.shape)->resident == kPersistent && t.find(w.shape)->resident == kPersistent) least *= 1.25;
+  double least = t.best(kDgrad, dgrad).us + t.best(kWgrad, wgrad).us;
   int pair = 0;
   for (int i = 0; i < t.npairs; ++i) {
     if (t.pairs[i].pair == forced) return forced;
