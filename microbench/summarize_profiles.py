@@ -231,7 +231,8 @@ def gemm_pmc():
                        f"{a('TCC_MISS_sum') / a('TCC_REQ_sum'):8.3f} {a('TCC_REQ_sum') / 1e6:9.2f} {a('SQ_WAIT_INST_ANY') / a('SQ_WAVE_CYCLES'):6.3f}")
         out.append("")
     out += ["Template arguments: block, sub-blocks per wave (rows, columns), waves per workgroup (rows, columns), A K-major, B K-major, test hook; of the",
-            "persistent 256 x 256 tiles (wide): block, A K-major, B K-major, or the block alone for the pair.",
+            "persistent 256 x 256 tiles (wide): block, A K-major, B K-major, or the block alone for the pair.  Those with a K-major A at block 128",
+            "issue 16x16x64 MFMAs, two for each 32x32x32 of the others: half the cycles and 4 vector instructions each.",
             "Reading: at block 32 the vector ALU is the saturated pipe and the matrix cores are busy a fraction of the time that follows from",
             "the fold's instruction count per MFMA (Sec. 5.3): the dequantize fold bounds the kernel, not the MFMA rate.  At block 64 and 128",
             "no pipe is: cycles are counted at the clock that the power limit leaves (1.6 to 1.95 GHz); what counts there is how few bytes move per MFMA."]
