@@ -708,16 +708,18 @@ struct GemmResults {   // as in GemmArgs
   int32_t* dump;
   int dump_kb;
 };
-struct GemmKernelArgs {
-  const int8_t *A, *Bm;
-  const float *SA, *SB;
-  int M, Nn, K, ntiles;
+typedef unsigned long long v2u64 __attribute__((ext_vector_type(2)));
+struct GemmKernelArgs {   // few and wide, each costs the host 0.01 us of a launch (256^3 back to back 4.05 us; as nine 4.14)
+  v2u64 operands, scales;
+  v4i sizes;
   GemmResults results;
 };
 struct GemmPairKernelArgs {
-  const int8_t *dY, *W, *X;
-  int N, C, D, split, few, few_long, few_slots, second_first;
-  const float *SdY, *SW, *SX;
+  v2u64 dY_W;
+  v4i sizes, deal;
+  const int8_t* X;
+  v2u64 SdY_SW;
+  const float* SX;
   GemmResults dgrad, wgrad;
 };
 __device__ __forceinline__ void set_results(GemmArgs& g, const __attribute__((address_space(4))) GemmResults& r) {
@@ -736,11 +738,11 @@ __host__ __device__ __forceinline__ int tiles_of(int M, int Nn) {
 
 // One product per launch.
 template <class P>
-__global__ void __launch_bounds__(64 * P::Shape::NW, P::WMIN) gemm_kernel(const int8_t* A, const int8_t* Bm, const float* SA, const float* SB, int M, int Nn,
-                                                                          int K, int ntiles, const GemmResults) {
+__global__ void __launch_bounds__(64 * P::Shape::NW, P::WMIN) gemm_kernel(const v2u64 pointers, const v2u64 scales, const v4i sizes, const GemmResults) {
   __shared__ __align__(1024) int8_t s_ring[P::Shape::LDS_BYTES];
   __shared__ float s_amax[8][8];
-  P::run(operands<P>(A, Bm, SA, SB, M, Nn, K), blockIdx.x, ntiles, s_ring, s_amax,
+  P::run(operands<P>((const int8_t*)pointers[0], (const int8_t*)pointers[1], (const float*)scales[0], (const float*)scales[1], sizes[0], sizes[1], sizes[2]),
+         blockIdx.x, sizes[3], s_ring, s_amax,
          [](GemmArgs& g) __attribute__((always_inline)) { set_results(g, kernel_arguments_from_here<GemmKernelArgs>()->results); });
 }
 
@@ -792,20 +794,21 @@ inline PairDeal deal_pair(int first, int second, double first_work, double secon
 // (second_first: the second product's tiles are the longer ones.)
 template <class P1, class P2>
 __global__ void __launch_bounds__(64 * P1::Shape::NW, (P1::WMIN < P2::WMIN ? P1::WMIN : P2::WMIN))
-gemm_pair_kernel(const int8_t* dY, const int8_t* W, const int8_t* X, int N, int C, int D, int split, int few, int few_long, int few_slots, int second_first,
-                 const float*, const float*, const float*, const GemmResults, const GemmResults) {
+gemm_pair_kernel(const v2u64 dY_W, const v4i sizes, const v4i deal, const int8_t* X, const v2u64, const float*, const GemmResults, const GemmResults) {
   static_assert(P1::Shape::NW == P2::Shape::NW, "one workgroup size");
   constexpr int LDS = P1::Shape::LDS_BYTES > P2::Shape::LDS_BYTES ? P1::Shape::LDS_BYTES : P2::Shape::LDS_BYTES;
   __shared__ __align__(1024) int8_t s_ring[LDS];
   __shared__ float s_amax[8][8];
+  const int8_t *const dY = (const int8_t*)dY_W[0], *const W = (const int8_t*)dY_W[1];
+  const int N = sizes[0], C = sizes[1], D = sizes[2], second_first = sizes[3];
   int i;
-  const bool early = PairDeal{split, few, few_long, few_slots}.place(blockIdx.x, i);
+  const bool early = PairDeal{deal[0], deal[1], deal[2], deal[3]}.place(blockIdx.x, i);
   if (early != (second_first != 0)) {
     const int tiles = tiles_of<P1>(N, C);
     if (i < tiles)
       P1::run(operands<P1>(dY, W, nullptr, nullptr, N, C, D), i, tiles, s_ring, s_amax, [](GemmArgs& g) __attribute__((always_inline)) {
         const auto a = kernel_arguments_from_here<GemmPairKernelArgs>();
-        g.SA = a->SdY, g.SB = a->SW;
+        g.SA = (const float*)a->SdY_SW[0], g.SB = (const float*)a->SdY_SW[1];
         set_results(g, a->dgrad);
       });
   } else {
@@ -813,7 +816,7 @@ gemm_pair_kernel(const int8_t* dY, const int8_t* W, const int8_t* X, int N, int 
     if (i < tiles)
       P2::run(operands<P2>(dY, X, nullptr, nullptr, D, C, N), i, tiles, s_ring, s_amax, [](GemmArgs& g) __attribute__((always_inline)) {
         const auto a = kernel_arguments_from_here<GemmPairKernelArgs>();
-        g.SA = a->SdY, g.SB = a->SX;
+        g.SA = (const float*)a->SdY_SW[0], g.SB = a->SX;
         set_results(g, a->wgrad);
       });
   }
@@ -824,7 +827,8 @@ inline GemmResults results_of(const GemmArgs& a) { return {a.Oq, a.Os, a.Of, a.d
 template <class P>
 static void launch_one(const GemmArgs& a, hipStream_t st) {
   const int tiles = tiles_of<P>(a.M, a.Nn);
-  hipLaunchKernelGGL((gemm_kernel<P>), dim3(tiles), dim3(64 * P::Shape::NW), 0, st, a.A, a.Bm, a.SA, a.SB, a.M, a.Nn, a.K, tiles, results_of(a));
+  const v2u64 pointers = {(unsigned long long)a.A, (unsigned long long)a.Bm}, scales = {(unsigned long long)a.SA, (unsigned long long)a.SB};
+  hipLaunchKernelGGL((gemm_kernel<P>), dim3(tiles), dim3(64 * P::Shape::NW), 0, st, pointers, scales, v4i{a.M, a.Nn, a.K, tiles}, results_of(a));
 }
 // input gradient (first) and weight gradient; the product with the longer tiles goes first
 template <class P1, class P2>
@@ -836,8 +840,9 @@ static void launch_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t st) 
   constexpr int BY_WAVES = 4 * (P1::WMIN < P2::WMIN ? P1::WMIN : P2::WMIN) / P1::Shape::NW, BY_LDS = 160 * 1024 / (LDS + 256);
   const PairDeal deal = second_first ? deal_pair(t2, t1, w2, w1, std::min(BY_WAVES, BY_LDS)) : deal_pair(t1, t2, w1, w2, std::min(BY_WAVES, BY_LDS));
   const int all = deal.split + (((second_first ? t1 : t2) + 7) & ~7);
-  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(all), dim3(64 * P1::Shape::NW), 0, st, a1.A, a1.Bm, a2.Bm, a1.M, a1.Nn, a1.K, deal.split, deal.few,
-                     deal.few_long, deal.few_slots, (int)second_first, a1.SA, a1.SB, a2.SB, results_of(a1), results_of(a2));
+  const v2u64 dY_W = {(unsigned long long)a1.A, (unsigned long long)a1.Bm}, SdY_SW = {(unsigned long long)a1.SA, (unsigned long long)a1.SB};
+  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(all), dim3(64 * P1::Shape::NW), 0, st, dY_W, v4i{a1.M, a1.Nn, a1.K, (int)second_first},
+                     v4i{deal.split, deal.few, deal.few_long, deal.few_slots}, a2.Bm, SdY_SW, a2.SB, results_of(a1), results_of(a2));
 }
 
 template <bool AK, bool BK>
