@@ -3,9 +3,10 @@
 #include "jf_gemm_wide.hpp"
 
 namespace jf {
-void launch_gemm_bwd_pair_b128(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st) {
-  if (pair == 21) launch_pair<GemmInstance<128, 2, 2, 4, 2, true, false>, GemmInstance<128, 2, 2, 4, 2, false, false>>(dgrad, wgrad, st);
+void launch_gemm_bwd_pair_b128(const PairChoice& choice, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st) {
+  const int pair = choice.pair;
+  if (pair == 21) launch_pair<GemmInstance<128, 2, 2, 4, 2, true, false>, GemmInstance<128, 2, 2, 4, 2, false, false>>(dgrad, wgrad, choice, st);
   else if (pair == 26) launch_wide_pair<128>(dgrad, wgrad, st);
-  else launch_pair<GemmInstance<128, 2, 1, 2, 4, true, false>, GemmInstance<128, 2, 1, 2, 4, false, false>>(dgrad, wgrad, st);
+  else launch_pair<GemmInstance<128, 2, 1, 2, 4, true, false>, GemmInstance<128, 2, 1, 2, 4, false, false>>(dgrad, wgrad, choice, st);
 }
 }  // namespace jf

@@ -9,13 +9,14 @@ using Dgrad = GemmInstance<32, WM, WN, 2, 2, true, false>;
 template <int WM, int WN>
 using Wgrad = GemmInstance<32, WM, WN, 2, 2, false, false>;
 
-void launch_gemm_bwd_pair_b32(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st) {
-  if (pair == 21) launch_pair<Dgrad<2, 2>, Wgrad<2, 2>>(dgrad, wgrad, st);
-  else if (pair == 22) launch_pair<Dgrad<2, 1>, Wgrad<2, 1>>(dgrad, wgrad, st);
-  else if (pair == 26) launch_pair<GemmInstance<32, 1, 1, 4, 2, true, false>, GemmInstance<32, 1, 1, 4, 2, false, false>>(dgrad, wgrad, st);
-  else if (pair == 23) launch_pair<Dgrad<1, 1>, Wgrad<1, 1>>(dgrad, wgrad, st);
-  else if (pair == 24) launch_pair<FineInstance<true, false>, Wgrad<1, 1>>(dgrad, wgrad, st);
-  else launch_pair<Dgrad<1, 1>, FineInstance<false, false>>(dgrad, wgrad, st);
+void launch_gemm_bwd_pair_b32(const PairChoice& choice, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st) {
+  const int pair = choice.pair;
+  if (pair == 21) launch_pair<Dgrad<2, 2>, Wgrad<2, 2>>(dgrad, wgrad, choice, st);
+  else if (pair == 22) launch_pair<Dgrad<2, 1>, Wgrad<2, 1>>(dgrad, wgrad, choice, st);
+  else if (pair == 26) launch_pair<GemmInstance<32, 1, 1, 4, 2, true, false>, GemmInstance<32, 1, 1, 4, 2, false, false>>(dgrad, wgrad, choice, st);
+  else if (pair == 23) launch_pair<Dgrad<1, 1>, Wgrad<1, 1>>(dgrad, wgrad, choice, st);
+  else if (pair == 24) launch_pair<FineInstance<true, false>, Wgrad<1, 1>>(dgrad, wgrad, choice, st);
+  else launch_pair<Dgrad<1, 1>, FineInstance<false, false>>(dgrad, wgrad, choice, st);
 }
 
 }  // namespace jf

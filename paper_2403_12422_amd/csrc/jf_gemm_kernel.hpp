@@ -746,11 +746,11 @@ __global__ void __launch_bounds__(64 * P::Shape::NW, P::WMIN) gemm_kernel(const 
          [](GemmArgs& g) __attribute__((always_inline)) { set_results(g, kernel_arguments_from_here<GemmKernelArgs>()->results); });
 }
 
-// How the tiles of two products are dealt to the workgroups of one launch.  Numbers below `split` are tiles of the product whose tiles
-// take longer, the rest the other's; both counts are rounded up to multiples of 8, so that tile i is on XCD i % 8 (what exceeds a
+// How the tiles of two products are dealt to the workgroups of one launch.  Numbers below `split` are tiles of the product that goes first,
+// the one with the larger K times tile, the rest the other's; both counts are rounded up to multiples of 8, so that tile i is on XCD i % 8 (what exceeds a
 // product's tiles is idle).  few == 0: in that order.  A launch of which all workgroups are resident at once puts workgroups b, b + 256, ...
 // on one compute unit (measured: of 672 and 768 workgroups all), some units with one more than the `few` others.  Dealt in order,
-// units come to have one more tile and more of the long ones as well; instead the `few` get `few_long` of those, by turns, and
+// units come to have one more tile and more of the long ones as well; instead the `few` get `few_long` of the first product's, by turns, and
 // the units with one more the rest.
 struct PairDeal {
   int split, few, few_long, few_slots;   // few_slots: workgroups on the units that have one less
@@ -767,23 +767,42 @@ struct PairDeal {
     return slot < longs;
   }
 };
-// `first`, `second`: tiles of the products, that with the longer ones first; work: what a tile of each takes; resident: workgroups of a
-// unit.  (672 tiles of 4096 x 768 -> 3072, of work 4 and 3: at most 10 on a unit instead of 11, 47.5 -> 45.3 us.)  *most: the work of the
-// busiest unit, where few > 0.
-inline PairDeal deal_pair(int first, int second, double first_work, double second_work, int resident, double* most = nullptr) {
+// Both products of a layer in one launch: on which tiles (numbered as in jf_gemm_shapes.hpp; 0: in two launches), whether the second, the
+// weight gradient, goes first, and how they are dealt.
+struct PairChoice {
+  int pair;
+  bool second_first;
+  PairDeal deal;
+};
+// `first`, `second`: tiles of the products in the order of the launch; work: what a tile of each takes, by the estimate that the choice
+// among the pairs goes by, so that the launch is dealt as the choice counts on; resident: workgroups of a unit.  *most: the work of the busiest unit.
+// (672 tiles of 4096 x 768 -> 3072, of work 4 and 3: at most 10 on a unit instead of 11, 47.5 -> 45.3 us.)  Dealt where that unit has
+// less to do than in order: by K times the tile's size instead, which for 32x32 beside 64x64 tiles is far from their times,
+// 6016 x 160 -> 1536 took 36.5 us, in order 21.4.
+inline PairDeal deal_pair(int first, int second, double first_work, double second_work, int resident, double* most) {
   PairDeal d = {(first + 7) & ~7, 0, 0, 0};
   const int all = d.split + ((second + 7) & ~7), turns = all / 256, many = all % 256, few = 256 - many;
-  if (all <= 256 || all > 256 * resident || many == 0) return d;
-  double least = 1e300;
-  for (int n = 0; n <= turns; ++n) {   // long tiles on the units with fewer
-    const int there = d.split < n * few ? d.split : n * few, rest = d.split - there;
-    const int most_few = (there + few - 1) / few, most_many = (rest + many - 1) / many;
-    if (most_many > turns + 1) continue;
-    const double a = most_few * first_work + (turns - most_few) * second_work, b = most_many * first_work + (turns + 1 - most_many) * second_work;
-    const double busiest = a > b ? a : b;
-    if (busiest < least) least = busiest, d.few = few, d.few_long = there, d.few_slots = turns * few;
+  // in order the unit with most is the first or the last of the first product's last round, or the first of the second's
+  double least = 0.0;
+  for (const int i : {0, d.split % 256, (first - 1) % 256}) {
+    const int j = (i - d.split % 256 + 256) % 256;
+    const int n1 = i < first ? (first - i + 255) / 256 : 0, n2 = j < second ? (second - j + 255) / 256 : 0;
+    least = std::max(least, n1 * first_work + n2 * second_work);
   }
-  if (most) *most = least;
+  if (all > 256 && all <= 256 * (int64_t)resident && many > 0) {
+    // `units` with `slots` workgroups each and `there` of the first product's among them by turns: the most that one has (its tiles may be the shorter ones)
+    const auto most_of = [&](int units, int slots, int there) {
+      const auto work = [&](int n) { return n * first_work + (slots - n) * second_work; };
+      return std::max(work(there / units), work((there + units - 1) / units));
+    };
+    for (int n = 0; n <= turns; ++n) {   // tiles of the first product on the units with fewer
+      const int there = std::min(d.split, n * few), rest = d.split - there;
+      if (rest > many * (turns + 1)) continue;
+      const double busiest = std::max(most_of(few, turns, there), most_of(many, turns + 1, rest));
+      if (busiest < least) least = busiest, d.few = few, d.few_long = there, d.few_slots = turns * few;
+    }
+  }
+  *most = least;
   return d;
 }
 
@@ -830,18 +849,13 @@ static void launch_one(const GemmArgs& a, hipStream_t st) {
   const v2u64 pointers = {(unsigned long long)a.A, (unsigned long long)a.Bm}, scales = {(unsigned long long)a.SA, (unsigned long long)a.SB};
   hipLaunchKernelGGL((gemm_kernel<P>), dim3(tiles), dim3(64 * P::Shape::NW), 0, st, pointers, scales, v4i{a.M, a.Nn, a.K, tiles}, results_of(a));
 }
-// input gradient (first) and weight gradient; the product with the longer tiles goes first
+// input gradient (first) and weight gradient
 template <class P1, class P2>
-static void launch_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t st) {
-  const int t1 = tiles_of<P1>(a1.M, a1.Nn), t2 = tiles_of<P2>(a2.M, a2.Nn);
-  const double w1 = (double)a1.K * P1::Shape::TM * P1::Shape::TN, w2 = (double)a2.K * P2::Shape::TM * P2::Shape::TN;
-  const bool second_first = w2 > w1;
-  constexpr int LDS = P1::Shape::LDS_BYTES > P2::Shape::LDS_BYTES ? P1::Shape::LDS_BYTES : P2::Shape::LDS_BYTES;
-  constexpr int BY_WAVES = 4 * (P1::WMIN < P2::WMIN ? P1::WMIN : P2::WMIN) / P1::Shape::NW, BY_LDS = 160 * 1024 / (LDS + 256);
-  const PairDeal deal = second_first ? deal_pair(t2, t1, w2, w1, std::min(BY_WAVES, BY_LDS)) : deal_pair(t1, t2, w1, w2, std::min(BY_WAVES, BY_LDS));
-  const int all = deal.split + (((second_first ? t1 : t2) + 7) & ~7);
+static void launch_pair(const GemmArgs& a1, const GemmArgs& a2, const PairChoice& choice, hipStream_t st) {
+  const PairDeal& deal = choice.deal;
+  const int all = deal.split + (((choice.second_first ? tiles_of<P1>(a1.M, a1.Nn) : tiles_of<P2>(a2.M, a2.Nn)) + 7) & ~7);
   const v2u64 dY_W = {(unsigned long long)a1.A, (unsigned long long)a1.Bm}, SdY_SW = {(unsigned long long)a1.SA, (unsigned long long)a1.SB};
-  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(all), dim3(64 * P1::Shape::NW), 0, st, dY_W, v4i{a1.M, a1.Nn, a1.K, (int)second_first},
+  hipLaunchKernelGGL((gemm_pair_kernel<P1, P2>), dim3(all), dim3(64 * P1::Shape::NW), 0, st, dY_W, v4i{a1.M, a1.Nn, a1.K, (int)choice.second_first},
                      v4i{deal.split, deal.few, deal.few_long, deal.few_slots}, a2.Bm, SdY_SW, a2.SB, results_of(a1), results_of(a2));
 }
 

@@ -120,30 +120,28 @@ struct ShapeTable {
     }
     return c;
   }
-  double pair_us(const PairModel& p, const GemmArgs& d, const GemmArgs& w) const {
+  // Time of a pair and, in *order, how its tiles are dealt: the product with the larger K times tile first, by turns or as deal_pair
+  // says.
+  double pair_us(const PairModel& p, const GemmArgs& d, const GemmArgs& w, PairChoice* order = nullptr) const {
     const ShapeModel &sd = *find(p.dgrad), &sw = *find(p.wgrad);
     const auto ud = [&](int n) { return sd.tile_us(kDgrad, d, n); };
     const auto uw = [&](int n) { return sw.tile_us(kWgrad, w, n); };
     const double td = sd.tiles(d), tw = sw.tiles(w), per = (td + tw) / 256.0, alone = std::max(ud(1), uw(1));
     const int resident = std::min(sd.resident, sw.resident);
+    const bool second_first = (int64_t)w.K * sw.tm * sw.tn > (int64_t)d.K * sd.tm * sd.tn;
+    const int t1 = (int)(second_first ? tw : td), t2 = (int)(second_first ? td : tw);
+    PairChoice in_order = {p.pair, second_first, {(t1 + 7) & ~7, 0, 0, 0}};
+    PairChoice& o = order ? *order : in_order;
+    o = in_order;
     if (per <= 1.0) return p.fixed_us + alone;
     if (per > resident) {
       const auto mean = [&](int n) { return (td * ud(n) + tw * uw(n)) / (td + tw); };
       return p.fixed_us + std::max(alone, p.work * rounds_us(per, resident, mean, p.fade, 0.0));
     }
-    // dealt as deal_pair says, or to the units in turn: the unit with most is then the first or the last of the first product's last round,
-    // or the first of the second's
     const int n = (int)std::ceil(per);
-    const bool second_first = (int64_t)w.K * sw.tm * sw.tn > (int64_t)d.K * sd.tm * sd.tn;
-    const int64_t t1 = (int64_t)(second_first ? tw : td), t2 = (int64_t)(second_first ? td : tw), split = (t1 + 7) & ~int64_t(7);
     const double u1 = second_first ? uw(n) : ud(n), u2 = second_first ? ud(n) : uw(n);
     double busiest = 0.0;
-    const bool dealt_evenly = sd.resident != kPersistent && deal_pair((int)t1, (int)t2, u1, u2, resident, &busiest).few > 0;
-    if (!dealt_evenly) for (const int64_t i : {int64_t(0), split % 256, (t1 - 1) % 256}) {
-      const int64_t j = (i - split % 256 + 256) % 256;
-      const int64_t n1 = i < t1 ? (t1 - i + 255) / 256 : 0, n2 = j < t2 ? (t2 - j + 255) / 256 : 0;
-      busiest = std::max(busiest, n1 * u1 + n2 * u2);
-    }
+    o.deal = deal_pair(t1, t2, u1, u2, sd.resident == kPersistent ? 0 : resident, &busiest);   // (persistent workgroups: in order)
     const double average = (t1 * u1 + t2 * u2) / 256.0;
     return p.fixed_us + std::max(alone, p.work * (p.dealt * busiest + (1.0 - p.dealt) * average));
   }
@@ -159,17 +157,18 @@ static int choose_shape(int block, Product p, const GemmArgs& a, int forced) {
   const ShapeTable t = shape_table(block);
   return t.find(forced) ? forced : t.best(p, a).shape;
 }
-// Pair of the backward products, 0 for two launches.
-static int choose_pair(int block, const GemmArgs& dgrad, const GemmArgs& wgrad, int forced) {
+// Pair of the backward products and the order of its tiles.
+static PairChoice choose_pair(int block, const GemmArgs& dgrad, const GemmArgs& wgrad, int forced) {
   const ShapeTable t = shape_table(block);
   double least = t.best(kDgrad, dgrad).us + t.best(kWgrad, wgrad).us;
-  int pair = 0;
+  PairChoice c = {};
   for (int i = 0; i < t.npairs; ++i) {
-    if (t.pairs[i].pair == forced) return forced;
-    const double us = t.pair_us(t.pairs[i], dgrad, wgrad);
-    if (us < least) least = us, pair = t.pairs[i].pair;
+    PairChoice order;
+    const double us = t.pair_us(t.pairs[i], dgrad, wgrad, &order);
+    if (t.pairs[i].pair == forced) return order;
+    if (us < least) least = us, c = order;
   }
-  return forced ? 0 : pair;   // a forced shape means the single-product kernels
+  return forced ? PairChoice{} : c;   // a forced shape means the single-product kernels
 }
 
 }  // namespace jf

@@ -18,17 +18,17 @@ void launch_gemm_dgrad_b128(int shape, const GemmArgs& a, bool dump, hipStream_t
 void launch_gemm_wgrad_b32(int shape, const GemmArgs& a, bool dump, hipStream_t st);
 void launch_gemm_wgrad_b64(int shape, const GemmArgs& a, bool dump, hipStream_t st);
 void launch_gemm_wgrad_b128(int shape, const GemmArgs& a, bool dump, hipStream_t st);
-void launch_gemm_bwd_pair_b32(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
-void launch_gemm_bwd_pair_b64(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
-void launch_gemm_bwd_pair_b128(int pair, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
+void launch_gemm_bwd_pair_b32(const PairChoice& choice, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
+void launch_gemm_bwd_pair_b64(const PairChoice& choice, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
+void launch_gemm_bwd_pair_b128(const PairChoice& choice, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st);
 
 // Input and weight gradient in one launch, if that is the faster way; false: nothing launched.
 static bool launch_bwd_pair(int block, const GemmArgs& dgrad, const GemmArgs& wgrad, hipStream_t st) {
-  const int pair = choose_pair(block, dgrad, wgrad, g_forced_shape.load(std::memory_order_relaxed));
-  if (pair == 0) return false;
-  if (block == 32) launch_gemm_bwd_pair_b32(pair, dgrad, wgrad, st);
-  else if (block == 64) launch_gemm_bwd_pair_b64(pair, dgrad, wgrad, st);
-  else launch_gemm_bwd_pair_b128(pair, dgrad, wgrad, st);
+  const PairChoice choice = choose_pair(block, dgrad, wgrad, g_forced_shape.load(std::memory_order_relaxed));
+  if (choice.pair == 0) return false;
+  if (block == 32) launch_gemm_bwd_pair_b32(choice, dgrad, wgrad, st);
+  else if (block == 64) launch_gemm_bwd_pair_b64(choice, dgrad, wgrad, st);
+  else launch_gemm_bwd_pair_b128(choice, dgrad, wgrad, st);
   return true;
 }
 

@@ -45,14 +45,102 @@ int main() {
 """
 
 
-def test_every_tile_once(tmp_path):
+# jf_linear_bwd itself, with the launches recorded instead of made: the deal that is launched against the one that the choice counts on
+LAUNCHED = r"""
+#include "jf_common.hpp"
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(KERNEL, GRID, BLOCK, LDS, STREAM, ...) record(GRID, __VA_ARGS__)
+struct { int pairs = 0, grid = 0, second_first = 0, deal[4] = {}; } seen;
+template <class... REST> void record(dim3, REST...) {}   // other kernels
+template <class A, class... REST> void record(dim3 grid, A, jf::v4i sizes, jf::v4i deal, REST...) {
+  seen.pairs += 1, seen.grid = (int)grid.x, seen.second_first = sizes[3];
+  for (int i = 0; i < 4; ++i) seen.deal[i] = deal[i];
+}
+#include "jf_gemm_fine.hpp"
+#include "jf_gemm_wide.hpp"
+#include "jf_gemm_bwd_pair_b32.hip"
+#include "jf_gemm_bwd_pair_b64.hip"
+#include "jf_gemm_bwd_pair_b128.hip"
+#include "jf_linear.hip"
+#include <cstdio>
+#include <random>
+#include <vector>
+namespace jf {
+thread_local int32_t g_last_hip_error = 0;
+#define ONE_PRODUCT(B) void launch_gemm_fwd_b##B(int, const GemmArgs&, bool, hipStream_t) {} \
+  void launch_gemm_dgrad_b##B(int, const GemmArgs&, bool, hipStream_t) {} void launch_gemm_wgrad_b##B(int, const GemmArgs&, bool, hipStream_t) {}
+ONE_PRODUCT(32) ONE_PRODUCT(64) ONE_PRODUCT(128)
+}
+using namespace jf;
+int main() {
+  std::mt19937 rng(5);
+  const auto size = [&](int b, double lo, double hi) {
+    return (int64_t)b * std::max(1, (int)std::lround(std::exp(std::uniform_real_distribution<double>(std::log(lo), std::log(hi))(rng)) / b));
+  };
+  long worse = 0, unforeseen = 0, launched = 0, dealt = 0;
+  for (int layer = 0; layer < 6000; ++layer) {
+    const int b = layer % 4 < 2 ? 32 : layer % 4 == 2 ? 64 : 128;
+    const int64_t N = size(b, 128, 16384), C = size(b, 128, 6144), D = size(b, 128, 6144);
+    const ShapeTable t = shape_table(b);
+    GemmArgs d{}, w{};
+    d.M = (int)N, d.Nn = (int)C, d.K = (int)D, w.M = (int)D, w.Nn = (int)C, w.K = (int)N;
+    const int chosen = choose_pair(b, d, w, 0).pair;
+    for (int i = -1; i < t.npairs; ++i) {   // the pair that is chosen, then each of them
+      const int pair = i < 0 ? chosen : t.pairs[i].pair;
+      if (pair == 0) continue;
+      const PairModel& p = *std::find_if(t.pairs, t.pairs + t.npairs, [&](const PairModel& m) { return m.pair == pair; });
+      const ShapeModel &sd = *t.find(p.dgrad), &sw = *t.find(p.wgrad);
+      if (sd.resident == kPersistent) continue;
+      int8_t* const q = (int8_t*)((size_t)1 << 40);   // never read
+      float* const s = (float*)((size_t)1 << 41);
+      const size_t far = (size_t)1 << 34;
+      seen.pairs = 0;
+      jf_debug_set_gemm_shape(i < 0 ? 0 : pair);
+      jf_linear_bwd(q, s, q + far, s + far, q + 2 * far, s + 2 * far, N, C, D, b, q + 3 * far, s + 3 * far, nullptr, q + 4 * far, s + 4 * far, nullptr, nullptr, 0, nullptr);
+      if (seen.pairs != 1) { ++unforeseen; continue; }
+      ++launched;
+      const int td = (int)sd.tiles(d), tw = (int)sw.tiles(w), per = (td + tw + 255) / 256, resident = std::min(sd.resident, sw.resident);
+      const double ud = sd.tile_us(kDgrad, d, per), uw = sw.tile_us(kWgrad, w, per);
+      const int first = seen.second_first ? tw : td, second = seen.second_first ? td : tw;
+      const PairDeal deal = {seen.deal[0], seen.deal[1], seen.deal[2], seen.deal[3]}, plain = {(first + 7) & ~7, 0, 0, 0};
+      std::vector<double> load(256), in_order(256);
+      for (int k = 0; k < seen.grid; ++k) {
+        int tile = 0;
+        bool early = deal.place(k, tile);
+        if (tile < (early ? first : second)) load[k % 256] += early != (seen.second_first != 0) ? ud : uw;
+        early = plain.place(k, tile);
+        if (tile < (early ? first : second)) in_order[k % 256] += early != (seen.second_first != 0) ? ud : uw;
+      }
+      const double busiest = *std::max_element(load.begin(), load.end()), before = *std::max_element(in_order.begin(), in_order.end());
+      worse += busiest > before + 1e-9;
+      dealt += deal.few > 0;
+      if (per > 1 && td + tw <= 256 * resident)
+        unforeseen += p.fixed_us + p.work * (p.dealt * busiest + (1.0 - p.dealt) * (td * ud + tw * uw) / 256.0) > t.pair_us(p, d, w) + 1e-9;
+    }
+  }
+  std::printf("launched %ld dealt %ld worse %ld unforeseen %ld\n", launched, dealt, worse, unforeseen);
+  return worse || unforeseen || dealt < 500;
+}
+"""
+
+
+def _run(tmp_path, source):
     src, exe = tmp_path / "deal.hip", tmp_path / "deal"
-    src.write_text(DEAL)
+    src.write_text(source)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     subprocess.run([hipcc, "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-O1", "-w", "-I", CSRC, "-I", INCLUDE, str(src),
-                    "-o", str(exe)], check=True, timeout=120)
-    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+                    "-o", str(exe)], check=True, timeout=240)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
     assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_every_tile_once(tmp_path):
+    _run(tmp_path, DEAL)
+
+
+def test_the_deal_that_is_launched(tmp_path):
+    """No compute unit has more to do than in order, by the times that the choice goes by, nor more than the choice counts on."""
+    _run(tmp_path, LAUNCHED)
 
 
 # tiles by turns of 256 with a rest: two and three on a unit, the longer ones in either product
