@@ -37,8 +37,8 @@ def sources():
 
 
 def source_digest() -> str:
-    """Digest of the device sources without their comments: tells whether a recorded profile is of the present kernels."""
-    h = hashlib.sha256()
+    """Digest of the device sources without their comments and of the compiler's flags: tells whether a recorded profile is of the present kernels."""
+    h = hashlib.sha256("\n".join(HIPCC_FLAGS).encode())
     for path in sorted(glob.glob(os.path.join(CSRC, "*.h*"))):      # .hip and .hpp
         with open(path) as f:
             code = [re.sub(r"\s+", " ", line.split("//")[0]).strip() for line in f]

@@ -44,3 +44,12 @@ def test_missing_extension_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "_EXT_PATH", str(tmp_path / "_native.so"))
     with pytest.raises(binding.JetfireError, match="load_library"):
         binding.jf_gelu_q(None, None)
+
+
+def test_digest_is_of_the_flags_too(monkeypatch):
+    """A recorded profile counts as one of the present kernels by this digest, and the flags make other kernels of the same sources."""
+    before = build.source_digest()
+    assert build.source_digest() == before
+    assert any("preload-count" in flag for flag in build.HIPCC_FLAGS)
+    monkeypatch.setattr(build, "HIPCC_FLAGS", [flag.replace("preload-count=14", "preload-count=13") for flag in build.HIPCC_FLAGS])
+    assert build.source_digest() != before
