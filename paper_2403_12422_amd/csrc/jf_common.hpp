@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstddef>
+#include <tuple>
 #include <type_traits>
 
 #include "jetfire.h"
@@ -231,6 +233,33 @@ __device__ __forceinline__ const __attribute__((address_space(4))) ARGS* kernel_
   asm volatile("" : "+s"(p));
   return p;
 }
+// What such a structure says of its kernel, checked where the kernel is launched: that parameter I is a T that stands `at` bytes into the segment,
+// and that the parameters up to I are among those that are preloaded.
+constexpr size_t kPreloadedBytes = 14 * 4;
+template <class KERNEL>
+struct KernelParameters;
+template <class... T>
+struct KernelParameters<void (*)(T...)> {
+  static constexpr size_t end(size_t index, size_t* begin = nullptr) {
+    constexpr size_t size[] = {sizeof(T)...}, align[] = {alignof(T)...};
+    size_t at = 0;
+    for (size_t i = 0; i <= index; ++i) {
+      at = (at + align[i] - 1) / align[i] * align[i];
+      if (begin) *begin = at;
+      at += size[i];
+    }
+    return at;
+  }
+  static constexpr size_t begin(size_t index) {
+    size_t at = 0;
+    end(index, &at);
+    return at;
+  }
+  template <size_t I, class U>
+  static constexpr bool stands_at(size_t at) { return std::is_same_v<std::tuple_element_t<I, std::tuple<T...>>, U> && begin(I) == at; }
+  template <size_t I>
+  static constexpr bool preloaded() { return end(I) <= kPreloadedBytes; }
+};
 // A pointer that is the same for all lanes, moved to scalar registers for good.
 template <class T>
 __device__ __forceinline__ T* uniform_pointer(T* p) {

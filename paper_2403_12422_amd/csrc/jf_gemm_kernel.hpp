@@ -845,6 +845,8 @@ gemm_pair_kernel(const v2u64 dY_W, const v4i sizes, const v4i deal, const int8_t
 inline GemmResults results_of(const GemmArgs& a) { return {a.Oq, a.Os, a.Of, a.dump, a.dump_kb}; }
 template <class P>
 static void launch_one(const GemmArgs& a, hipStream_t st) {
+  typedef KernelParameters<decltype(&gemm_kernel<P>)> Parameters;
+  static_assert(Parameters::template preloaded<2>() && Parameters::template stands_at<3, GemmResults>(offsetof(GemmKernelArgs, results)), "GemmKernelArgs");
   const int tiles = tiles_of<P>(a.M, a.Nn);
   const v2u64 pointers = {(unsigned long long)a.A, (unsigned long long)a.Bm}, scales = {(unsigned long long)a.SA, (unsigned long long)a.SB};
   hipLaunchKernelGGL((gemm_kernel<P>), dim3(tiles), dim3(64 * P::Shape::NW), 0, st, pointers, scales, v4i{a.M, a.Nn, a.K, tiles}, results_of(a));
@@ -852,6 +854,11 @@ static void launch_one(const GemmArgs& a, hipStream_t st) {
 // input gradient (first) and weight gradient
 template <class P1, class P2>
 static void launch_pair(const GemmArgs& a1, const GemmArgs& a2, const PairChoice& choice, hipStream_t st) {
+  typedef GemmPairKernelArgs Args;
+  typedef KernelParameters<decltype(&gemm_pair_kernel<P1, P2>)> Parameters;
+  static_assert(Parameters::template preloaded<3>() && Parameters::template stands_at<4, v2u64>(offsetof(Args, SdY_SW)) &&
+                    Parameters::template stands_at<5, const float*>(offsetof(Args, SX)) && Parameters::template stands_at<6, GemmResults>(offsetof(Args, dgrad)) &&
+                    Parameters::template stands_at<7, GemmResults>(offsetof(Args, wgrad)), "GemmPairKernelArgs");
   const PairDeal& deal = choice.deal;
   const int all = deal.split + (((choice.second_first ? tiles_of<P1>(a1.M, a1.Nn) : tiles_of<P2>(a2.M, a2.Nn)) + 7) & ~7);
   const v2u64 dY_W = {(unsigned long long)a1.A, (unsigned long long)a1.Bm}, SdY_SW = {(unsigned long long)a1.SA, (unsigned long long)a1.SB};

@@ -433,7 +433,6 @@ __global__ void __launch_bounds__(512, 2) gemm_wide_pair_kernel(const GemmArgs, 
                                                                 const int second_first) {
   __shared__ __align__(1024) int8_t s_ring[WideShape<B, true, false>::LDS_BYTES];
   __shared__ float s_amax[8];
-  static_assert(sizeof(GemmArgs) % 8 == 0, "the second product's arguments follow the first's");
   const KernelArgs args = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
   const int n = gridDim.x, i = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int behind = (n - split % n + i) % n;   // this workgroup's first tile of the product that comes second
@@ -452,12 +451,15 @@ __global__ void __launch_bounds__(512, 2) gemm_wide_pair_kernel(const GemmArgs, 
 template <int B, bool AK, bool BK>
 static void launch_wide(const GemmArgs& a, hipStream_t st) {
   const int tiles = ((a.M + 255) / 256) * ((a.Nn + 255) / 256);
+  static_assert(KernelParameters<decltype(&gemm_wide_kernel<B, AK, BK>)>::template stands_at<0, GemmArgs>(0), "read as KernelArgs");
   hipLaunchKernelGGL((gemm_wide_kernel<B, AK, BK>), dim3(tiles < kWideWorkgroups ? tiles : kWideWorkgroups), dim3(512), 0, st, a, tiles);
 }
 template <int B>
 static void launch_wide_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t st) {
   const int t1 = ((a1.M + 255) / 256) * ((a1.Nn + 255) / 256), t2 = ((a2.M + 255) / 256) * ((a2.Nn + 255) / 256);
   const bool second_first = a2.K > a1.K;
+  typedef KernelParameters<decltype(&gemm_wide_pair_kernel<B>)> Parameters;
+  static_assert(Parameters::template stands_at<0, GemmArgs>(0) && Parameters::template stands_at<1, GemmArgs>(sizeof(GemmArgs)), "read as KernelArgs and the next");
   const int split = ((second_first ? t2 : t1) + 7) & ~7, all = split + (second_first ? t1 : t2);
   hipLaunchKernelGGL((gemm_wide_pair_kernel<B>), dim3(all < kWideWorkgroups ? all : kWideWorkgroups), dim3(512), 0, st, a1, a2, t1, t2, split,
                      (int)second_first);

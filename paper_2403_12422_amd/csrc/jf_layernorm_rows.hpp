@@ -510,12 +510,16 @@ static bool raise_lds(size_t bytes) {
 inline int rows_layout(int strips, int teams, int waves) { return strips | teams << 8 | waves << 16; }
 template <auto KERNEL>
 static void launch_rows(size_t wave_bytes, int grid, int waves, const LayerNormRows& a, hipStream_t st) {
+  typedef KernelParameters<decltype(KERNEL)> Parameters;
+  static_assert(Parameters::template preloaded<7>() && Parameters::template stands_at<8, LayerNormRows>(offsetof(LayerNormRowsArgs, all)), "LayerNormRowsArgs");
   if (!raise_lds<KERNEL>(16 * wave_bytes)) return;
   hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(64 * waves), waves * wave_bytes, st, a.X, a.SX, a.row_mean ? a.row_mean : a.gamma,
                      a.row_mean ? a.row_sumsq : a.beta, a.rows, a.cols, rows_layout(a.strips, a.teams, waves), grid, a);
 }
 template <auto KERNEL>
 static void launch_rows(size_t wave_bytes, int grid, int waves, const LayerNormBwdRows& a, hipStream_t st) {
+  typedef KernelParameters<decltype(KERNEL)> Parameters;
+  static_assert(Parameters::template preloaded<8>() && Parameters::template stands_at<9, LayerNormBwdRows>(offsetof(LayerNormBwdRowsArgs, all)), "LayerNormBwdRowsArgs");
   if (!raise_lds<KERNEL>(16 * wave_bytes)) return;
   hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(64 * waves), waves * wave_bytes, st, a.G, a.SG, a.X, a.SX, a.rows, a.cols,
                      rows_layout(a.strips, a.teams, waves), a.row_wgs, a.gamma, a);
