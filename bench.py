@@ -604,6 +604,7 @@ def main():
         ceiling = {"bare_TOPS": fold["bare_fold_TOPS"][str(B)],
                    "measured": "by micro-benchmarks on another occasion",
                    "frac_of_bare": round(achieved / fold["bare_fold_TOPS"][str(B)], 4),
+                   "random_codes_TOPS": fold.get("random_codes_fold_TOPS", {}).get(str(B)),
                    "source": fold.get("source")}
 
     extra = {}
@@ -655,7 +656,8 @@ def main():
                                  "launches_timed": len(in_step),
                                  "note": "events around the launches inside the timed region; they add about 2.5 us per launch"},
             # second ceiling of this method on this chip: the per-K-block dequantize fold issues 32 / 16 / 8 vector
-            # instructions per MFMA at block 32 / 64 / 128 (micro-benchmarks, see the profile named in `source`)
+            # instructions per MFMA at block 32 / 64 / 128 (micro-benchmarks, see the profile named in `source`), on operands of a few
+            # small numbers and on random codes, for which the power limit lowers the clock of launches that last
             "valu_fold_ceiling": ceiling,
             "linear_only_TOPS": round(achieved, 2),
         },
