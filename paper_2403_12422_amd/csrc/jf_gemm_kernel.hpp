@@ -709,7 +709,7 @@ struct GemmResults {   // as in GemmArgs
   int dump_kb;
 };
 typedef unsigned long long v2u64 __attribute__((ext_vector_type(2)));
-struct GemmKernelArgs {   // few and wide, each costs the host 0.01 us of a launch (256^3 back to back 4.05 us; as nine 4.14)
+struct GemmKernelArgs {   // few and wide, each costs the host 0.01 us of a launch (256^3 back to back 4.00 us; as nine up to 4.14)
   v2u64 operands, scales;
   v4i sizes;
   GemmResults results;

@@ -218,7 +218,8 @@ inline int layernorm_split_parts(int64_t N, int64_t C, bool backward) {
 // that own columns: where there is no room for those, and where they take longer than the rows, which is by the row groups that
 // each of their waves has (as many waves as strips, at least eight).  Columns apart -> partial rows in us: 2048 x 768 8.55 -> 8.95, x 1280 9.3 ->
 // 11.05; 2560 x 768 10.1 -> 9.25, x 1024 8.6 -> 9.5; 2688 x 768 10.55 -> 9.45, x 1536 12.1 -> 12.15, x 2048 12.5 -> 14.0; 3072 x 768 11.9 -> 9.6, x 1536 13.6 ->
-// 12.3, x 2048 13.9 -> 14.2; 3840 x 512 13.7 -> 8.45.
+// 12.3, x 2048 13.9 -> 14.2; 3840 x 512 13.7 -> 8.45.  (One line for all widths: at 2560 rows 768 columns would gain 0.85 on its other side,
+// 1024 lose 0.85.  One workgroup to a group, before: 2560 x 768 10.7, x 1024 11.1.)
 inline bool layernorm_split_columns(int64_t N, int64_t C) {
   return 2 * ((N / 32 + 7) / 8 * 8) > 256 - C / 32 || (N / 32 > 80 && C <= 1536);
 }

@@ -14,8 +14,8 @@
 // includes the stores just made (loads and stores count in one counter and may finish out of order), only those of the
 // previous group, which are long done.
 //
-// 1 M x 768: forward 446 -> 313 us (5.2 TB/s), backward 784 -> 484 us (5.0 TB/s; vector ALU and memory both near their
-// limits: 19 instructions per element) against the two-kernel scheme of jf_layernorm.hip, which stays for rows of which a
+// 1 M x 768, back to back: forward 446 -> 315 us (5.1 TB/s), backward with its column sums 784 -> 502 us (4.8 TB/s; vector ALU and memory
+// both near their limits: 19 instructions per element) against the two-kernel scheme of jf_layernorm.hip, which stays for rows of which a
 // compute unit's registers (128 per lane: 16 waves) do not hold a block row.
 #pragma once
 #include <algorithm>
@@ -295,7 +295,8 @@ __device__ __forceinline__ void column_sums_direct(const LayerNormBwdRows& a, in
 // KEPT: of how many of a lane's four rows ghat stays in registers between the two passes over the strip, 16 each, instead of
 // being formed again (two instructions per element).  Workgroups of at most 12 waves, three on a SIMD, have 168 registers: room
 // for two rows beside the column sums, for all four without them; 16 waves have none.  More than fits goes to scratch
-// memory, whose loads also wait for the strips in flight (1 M x 768 with three rows 513 us, two 484, one 515, none 535).
+// memory, whose loads also wait for the strips in flight (1 M x 768 on the day of the choice, kernel alone, three rows 513 us, two 484, one 515,
+// none 535; two now 486 to 514 in a trace).
 template <int B, StorePolicy SP, bool COLUMNS_APART, int KEPT>
 __global__ void __launch_bounds__(KEPT ? 768 : 1024) layernorm_bwd_rows_kernel(
     const int8_t* G, const float* SG, const int8_t* X, const float* SX, int rows, int cols, int layout, int wgs, const float* gamma, const LayerNormBwdRows) {
