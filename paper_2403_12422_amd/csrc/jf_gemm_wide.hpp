@@ -12,7 +12,7 @@
 //   block 128  8192^3           593 / 594 / 598 -> 528 / 533 / 531      16384 x 4096 -> 11008  876 / 787 / 840 -> 734 / 712 / 731
 //   block 128  4096^3           79.5 / 80.2 / 80.7 -> 72.0 / 72.8 / 72.6
 //   block 64   8192^3           764 / 738 / 722 -> 708 / 687 / 725      4096^3  102.5 / 100.0 / 98.3 -> 92.6 / 91.4 / 90.5
-// and less since, by the priorities in run_stage and the instruction that WideMfma chooses (8192^3 at block 128 forward 541 -> 514).
+// and less since, by the priorities in run_stage and the instruction that wide_quarters chooses (8192^3 at block 128 forward 541 -> 514).
 // (At block 64 the vector ALU bounds the loop, for which two waves per SIMD do a little worse than three: what is gained is the
 // start and end of the tiles, and it is lost again where 256x256 tiles fill the compute units unevenly.)
 #pragma once
@@ -32,17 +32,18 @@ struct WideShape {
   static_assert(RING_A <= 65536 && LDS_BYTES - RING_A <= 65536, "16-bit offsets");
 };
 
-// A wave's MFMA on the sub-blocks of a 256x256 tile: v_mfma_i32_32x32x32_i8, or v_mfma_i32_16x16x64_i8 on their quarters.  Both take
-// 16 bytes of K per lane and the same matrix cycles per multiply-add.  The latter writes its INT32 tile, and reads it in a chain, half
+// A wave's MFMA on the sub-blocks of a 256x256 tile: v_mfma_i32_32x32x32_i8, or, QUARTERS, v_mfma_i32_16x16x64_i8 on their quarters.  Both
+// take 16 bytes of K per lane and the same matrix cycles per multiply-add.  The latter writes its INT32 tile, and reads it in a chain, half
 // as often, which is power, what bounds large products at B = 128, at the price of twice the instructions to issue: bare chains of
 // random codes with their folds 24.9 -> 23.7 ns per 32x32x32, of zeros, at full clock, 18.5 -> 20.9.  8192^3 at B = 128 forward 536 -> 513
 // us, 16384 x 4096 -> 11008 forward 741 -> 720, input gradient 714 -> 694; where both operands are read transposed, by twice the LDS
 // instructions, it loses (weight gradient 734 -> 742), and at B = 64 the bare chains do (33.4 -> 34.9).
-template <int B, bool AK>
-struct WideMfma {
-  static constexpr bool QUARTERS = B == 128 && AK;
-  static constexpr int ROWS = QUARTERS ? 16 : 32;   // rows of a fragment; its 64 lanes hold 1 KB either way
-};
+// Where units are left idle the others run at a higher clock, and what counts is the instructions.  Quarters and whole sub-blocks by tiles,
+// 256 at a time on the units, K = 4096, in us: forward 64 tiles 56.3 and 49.3, 128 56.9 and 49.9, 160 57.5 and 53.2, 176 57.9 and 56.1, 192 59.1 and 58.3, 208 61.7
+// and 62.2, 224 63.8 and 65.3, 256 68.5 and 70.0, 320 116.0 and 112.3, 384 116.8 and 115.8; input gradient, K = 2048, 160 34.1 and 31.2, 256 39.5
+// and 40.4, 272 64.7 and 62.3, 400 45.9 and 45.5, 448 equal, 480 71.4 and 73.4.  The line: four fifths of the rounds' places taken.
+inline bool wide_quarters(int64_t tiles) { return 5 * tiles >= 4 * 256 * ((tiles + 255) / 256); }
+constexpr int wide_fragment_rows(bool quarters) { return quarters ? 16 : 32; }   // its 64 lanes hold 1 KB either way
 
 // LDS addresses of an operand's fragments: as FragAddr, of whose offsets every one is the first with bits of the chunk number
 // toggled, so that a lane keeps one address per operand.  Fragment j of a sub-tile: K step j of 32 bytes, or, of 16 rows, the half
@@ -116,7 +117,7 @@ __device__ __forceinline__ KernelArgs read_again(KernelArgs a) {
 }
 
 // Tiles tile_index, tile_index + stride, ... of `ntiles`, on a workgroup of eight waves; tile_index < ntiles.
-template <int B, bool AK, bool BK>
+template <int B, bool AK, bool BK, bool QUARTERS>
 __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave, int tile_index, const int stride, const int ntiles,
                                           int8_t* const s_ring, float* const s_amax) {
   typedef WideShape<B, AK, BK> S;
@@ -210,9 +211,8 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
   // i + 1 is issued beside the fold of unit i.  A fragment is read into the registers that have just come out of use: those of
   // the second sub-block row beside unit WN - 2, behind the last chain of the first; those of the next stage beside the
   // units from SYNC on, which the barrier stands before.
-  constexpr bool QUARTERS = WideMfma<B, AK>::QUARTERS;
-  WideFrag<TM, AK, KC, WideMfma<B, AK>::ROWS> fragA;
-  WideFrag<TN, BK, KC, WideMfma<B, AK>::ROWS> fragB;
+  WideFrag<TM, AK, KC, wide_fragment_rows(QUARTERS)> fragA;
+  WideFrag<TN, BK, KC, wide_fragment_rows(QUARTERS)> fragB;
   const int lane = lane_again();
   fragA.init(s_ring, 0, wm0, lane);
   fragB.init(s_ring, S::RING_A, wn0, lane);
@@ -255,7 +255,7 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
     constexpr int slot = decltype(u_tag)::value, nslot = (slot + 1) % NBUF, SYNC = WN;
     // The toggled addresses are formed again in each stage: kept over the loop they go to scratch memory, for whose loads the stages in
     // flight are waited for.
-    if constexpr (B == 128 && AK && !BK) asm volatile("" : "+v"(fragB.at));
+    if constexpr (B == 128 && AK && !(BK && QUARTERS)) asm volatile("" : "+v"(fragB.at));
     static_for<0, NT>([&](auto i_tag) __attribute__((always_inline)) {
       constexpr int i = decltype(i_tag)::value, a = i / WN, b = i % WN;
       v16i &cur = vi[i & 1], &nxt = vi[(i & 1) ^ 1];
@@ -418,11 +418,11 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
 static constexpr int kWideWorkgroups = 256;   // one per compute unit: the ring takes 128 of its 160 KB of LDS
 
 // One product per launch.  The arguments are read through the kernel's argument segment (see KernelArgs).
-template <int B, bool AK, bool BK>
+template <int B, bool AK, bool BK, bool QUARTERS>
 __global__ void __launch_bounds__(512, 2) gemm_wide_kernel(const GemmArgs, const int ntiles) {
   __shared__ __align__(1024) int8_t s_ring[WideShape<B, AK, BK>::LDS_BYTES];
   __shared__ float s_amax[8];
-  gemm_wide<B, AK, BK>((KernelArgs)__builtin_amdgcn_kernarg_segment_ptr(), __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), blockIdx.x, gridDim.x, ntiles, s_ring, s_amax);
+  gemm_wide<B, AK, BK, QUARTERS>((KernelArgs)__builtin_amdgcn_kernarg_segment_ptr(), __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), blockIdx.x, gridDim.x, ntiles, s_ring, s_amax);
 }
 
 // Both backward products of a layer in one launch, the one with the longer tiles first (`second_first`: the weight gradient).
@@ -440,19 +440,26 @@ __global__ void __launch_bounds__(512, 2) gemm_wide_pair_kernel(const GemmArgs, 
   for (int turn = 0; turn < 2; ++turn) {
     const int first = turn == 0 ? i : behind;
     if ((turn == 0) != (second_first != 0)) {
-      if (first < tiles1) gemm_wide<B, true, false>(args, wave, first, n, tiles1, s_ring, s_amax);
+      if (first < tiles1) gemm_wide<B, true, false, B == 128>(args, wave, first, n, tiles1, s_ring, s_amax);
     } else {
-      if (first < tiles2) gemm_wide<B, false, false>(args + 1, wave, first, n, tiles2, s_ring, s_amax);
+      if (first < tiles2) gemm_wide<B, false, false, false>(args + 1, wave, first, n, tiles2, s_ring, s_amax);
     }
     __syncthreads();   // the next product's loads may not land before every wave is through with this one's
   }
 }
 
+template <int B, bool AK, bool BK, bool QUARTERS>
+static void launch_wide_as(const GemmArgs& a, int tiles, hipStream_t st) {
+  static_assert(KernelParameters<decltype(&gemm_wide_kernel<B, AK, BK, QUARTERS>)>::template stands_at<0, GemmArgs>(0), "read as KernelArgs");
+  hipLaunchKernelGGL((gemm_wide_kernel<B, AK, BK, QUARTERS>), dim3(tiles < kWideWorkgroups ? tiles : kWideWorkgroups), dim3(512), 0, st, a, tiles);
+}
 template <int B, bool AK, bool BK>
 static void launch_wide(const GemmArgs& a, hipStream_t st) {
   const int tiles = ((a.M + 255) / 256) * ((a.Nn + 255) / 256);
-  static_assert(KernelParameters<decltype(&gemm_wide_kernel<B, AK, BK>)>::template stands_at<0, GemmArgs>(0), "read as KernelArgs");
-  hipLaunchKernelGGL((gemm_wide_kernel<B, AK, BK>), dim3(tiles < kWideWorkgroups ? tiles : kWideWorkgroups), dim3(512), 0, st, a, tiles);
+  if constexpr (B == 128 && AK) {
+    if (wide_quarters(tiles)) return launch_wide_as<B, AK, BK, true>(a, tiles, st);
+  }
+  launch_wide_as<B, AK, BK, false>(a, tiles, st);
 }
 template <int B>
 static void launch_wide_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t st) {

@@ -63,6 +63,25 @@ def test_from_tile_to_tile(block, kblocks, forced):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("tiles", [(12, 17), (41, 5), (14, 15), (25, 20)])
+@pytest.mark.parametrize("kblocks", [1, 2, 3, 4, 5, 9])
+def test_quarters_and_whole_sub_blocks(tiles, kblocks, forced):
+    """Either side of the number of tiles from which on sub-blocks are multiplied in quarters (204 and 205), and two tiles to a workgroup so, the
+    last ones of a row and a column ragged."""
+    block, m, n, k = 128, tiles[0] * 256 - 128, tiles[1] * 256 - 128, kblocks * 128
+    g = torch.Generator(device="cuda").manual_seed(7400 + tiles[0] + kblocks)
+    draw = lambda r, c: jf.jf_quantize_block(torch.randn((r, c), generator=g, device="cuda"), block)
+    say(f"256x256 tiles {tiles} {kblocks} K blocks")
+    (a, sa), fwd_w, dgrad_w = draw(m, k), draw(n, k), draw(k, n)
+    both = lambda: (jf.jf_linear_fwd(a, sa, *fwd_w, block, want_f32=True), jf.jf_linear_dgrad(a, sa, *dgrad_w, block, want_f32=True))
+    forced(1)
+    want = both()
+    forced(WIDE)
+    for got, ref in zip(both(), want):
+        for x, y in zip(got, ref):
+            assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("block", [64, 128])
 @pytest.mark.parametrize("sizes", [(2816, 4352, 1408), (1408, 4352, 2816), (5120, 4096, 4352)])
 def test_both_backward_products_as_one_list(block, sizes, forced):
