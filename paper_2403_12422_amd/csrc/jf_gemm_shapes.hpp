@@ -21,9 +21,9 @@
 // layer, the choice costs on the rest, against the best shape or pair of each, on average 0.3 % (B = 64) and 0.0 % (128) for single
 // products and 0.2 and 0.5 % for backward passes (their forerunner, without rounds, resident counts and distant operands, 0.7 and 1.9).
 // At B = 32 shape 7 and pair 26 were fitted with the rest held, every layer scaled by the shapes that both fits know; on 120 further
-// layers the choice costs 0.6 % for single products (without shape 7 1.2).  Backward passes on the kernels and deals as they are now, 260 other
-// random layers at B = 32 and 100 each at 64 and 128, by replays of graphs: 1.1, 0.5 and 0.7 %, of which the measurement's own noise
-// is up to 0.5.  At B = 32 one layer in nine loses more than 3 %, nearly half of them beyond one residency, where a pair counts with the mean time of its
+// layers the choice costs 0.6 % for single products (without shape 7 1.2).  Backward passes on the kernels and deals as they are now, 820 other
+// layers at B = 32 and 100 each at 64 and 128, by replays of graphs: 1.0, 0.5 and 0.7 %, of which the measurement's own noise
+// is up to 0.5 (the pairs' constants fitted anew to half of 560 of these layers: 1.2 to 1.4 % on the other half, so they stay).  At B = 32 one layer in nine loses more than 3 %, nearly half of them beyond one residency, where a pair counts with the mean time of its
 // tiles though the last long ones end it alone: 2048 x 768 -> 7168 61 us on pair 23, 48 on 26; 9216 x 2560 -> 1024 114 and 105.
 // At B = 128 with both products on shape 11 one launch and two are within 2 % of each other: 4096^3 138.8 and 141.4 us, 8192 x 4096 -> 4096 265.7
 // and 268.0, 16384 x 4096 -> 11008 1428 and 1412.
