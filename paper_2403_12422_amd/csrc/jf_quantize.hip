@@ -1,7 +1,7 @@
 // jf_quantize_block: per-block quantizer Q of Sec. 4, Eq. 1 (FP32/FP16 -> INT8 + FP32 scale grid).
 //
-// HBM-bound: 4 (or 2) bytes in, 1 byte out per element.  A workgroup of four waves owns a 128 x 128 tile; wave w owns the
-// 32-row strip w of it.  Inside a strip a lane holds 16 bytes (4 FP32 or 8 FP16 columns) of 16 or 8 rows, so each row
+// HBM-bound: 4 (or 2) bytes in, 1 byte out per element.  A wave owns a strip of 32 rows x 128 columns, a workgroup the one, two or four strips
+// of a block row one above the other.  Inside a strip a lane holds 16 bytes (4 FP32 or 8 FP16 columns) of 16 or 8 rows, so each row
 // of the strip is read as one run of 512 or 256 bytes and written as one 128-byte line of codes.  A small tensor gives a
 // compute unit a wave or two of that kind, whose 64 elements a lane are a serial chain of loads and roundings with nothing beside
 // it; there the strips are narrower (launch_quantize).
@@ -9,16 +9,98 @@
 
 namespace jf {
 
-__device__ __forceinline__ void load_vec(const float* p, float (&v)[4]) {
-  float4 t = *reinterpret_cast<const float4*>(p);
-  v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-}
-__device__ __forceinline__ void load_vec(const _Float16* p, float (&v)[8]) {
-  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-  h8 t = *reinterpret_cast<const h8*>(p);
+// A lane's 16 bytes of a row, what the block's max-abs takes from the lane, and Eq. 1 for them (packed: one dword for four codes).
+template <typename T>
+struct Row16;
+
+template <>
+struct Row16<float> {
+  static constexpr int VEC = 4;
+  float4 t;
+  template <int NI>
+  static __device__ __forceinline__ float amax(const Row16 (&v)[NI]) {
+    float m = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = (float)t[i];
-}
+    for (int i = 0; i < NI; ++i) {   // (the compiler's fmaxf quiets operands with an instruction each)
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v[i].t.x), "v"(v[i].t.y));
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v[i].t.z), "v"(v[i].t.w));
+    }
+    return m;
+  }
+  struct Scale {
+    float scale;
+    double inv;
+    explicit __device__ __forceinline__ Scale(float amax) { block_scale(amax, scale, inv); }
+  };
+  __device__ __forceinline__ void codes(const Scale& s, uint32_t (&packed)[1]) const { packed[0] = quantize4(t.x, t.y, t.z, t.w, s.inv); }
+};
+
+// FP16: one FP32 FMA per element rounds the exact quotient x / s, which takes the three instructions of code_bits() for any FP32 number.
+// x has 11 bits, and s is within 2^-24 of amax / 127, where amax is one of the x.  So
+//   * 127 x / amax is a tie k + 1/2 or at least 1 / (254 * 2047) > 2^-19 of itself away from one (254 X and (2 k + 1) A 2^j are integers, X
+//     and A the 11-bit significands), and a reciprocal that is off by 2^-22 does not take x / s past a tie that 127 x / amax is not on;
+//   * where it is a tie, x / s lies beyond it if s < amax / 127 and short of it if s > amax / 127.  One ulp added to fl32(1 / s) or taken off it
+//     brings the reciprocal to the side of 127 / amax that 1 / s is on, whatever its own rounding did, and with it the product;
+//   * where s = amax / 127 exactly, a tie of x / s is one, and the FMA sends it to even if fl32(1 / s) = 1 / s, a power of two.  The other
+//     scales (amax a multiple of 127 other than by a power of two, 7 of 1024 significands) take code_bits().
+// (5.25 -> 2.75 vector instructions an element.  8192 x 1280 from memory 9.4 -> 8.2 us, 8192 x 3840 22.4 -> 18.9 = 5.0 TB/s, 32768 x 4096
+// 77.1 -> 73.8 = 5.5 TB/s: the waves of a tensor this size start together, and their arithmetic follows their loads.  Hand-over of 8192 x 1280 to
+// attention and back, four launches, 58.5 -> 53.6.)
+template <>
+struct Row16<_Float16> {
+  static constexpr int VEC = 8;
+  uint4 t;
+  template <int NI>
+  static __device__ __forceinline__ float amax(const Row16 (&v)[NI]) {
+    uint32_t m = 0;
+    const auto larger = [](uint32_t a, uint32_t b) __attribute__((always_inline)) {   // of two pairs (the compiler's fmax quiets its operands first)
+      uint32_t r;
+      asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+      return r;
+    };
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t w[4] = {v[i].t.x, v[i].t.y, v[i].t.z, v[i].t.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) m = larger(m, w[k] & 0x7fff7fffu);
+    }
+    m = larger(m, m >> 16);
+    return (float)__builtin_bit_cast(_Float16, (uint16_t)m);
+  }
+  struct Scale {
+    float scale, inv32;
+    double inv;
+    bool one_fma;   // for all blocks of the wave
+    explicit __device__ __forceinline__ Scale(float amax) {
+      block_scale(amax, scale, inv);
+      const float over = __builtin_fmaf(scale, 127.0f, -amax);   // exact in sign: of scale - amax / 127
+      const uint32_t near = __builtin_bit_cast(uint32_t, (float)inv);
+      inv32 = __builtin_bit_cast(float, over > 0.0f ? near - 1 : over < 0.0f ? near + 1 : near);
+      one_fma = !__any(over == 0.0f && (__builtin_bit_cast(uint32_t, scale) & 0x7fffffu));
+    }
+  };
+  // element H of the pair in w, as code_bits() leaves it: 1.5 * 2^23 added by the FMA rounds to an integer, to even, in the low mantissa bits
+  template <int H>
+  static __device__ __forceinline__ uint32_t element(uint32_t w, float inv32) {
+    uint32_t r;
+    if constexpr (H == 0) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(inv32), "v"(12582912.0f));
+    else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(inv32), "v"(12582912.0f));
+    return r;
+  }
+  __device__ __forceinline__ void codes(const Scale& s, uint32_t (&packed)[2]) const {
+    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const uint32_t a = w[2 * k], b = w[2 * k + 1];
+      if (__builtin_expect(s.one_fma, 1)) {
+        packed[k] = pack_codes(element<0>(a, s.inv32), element<1>(a, s.inv32), element<0>(b, s.inv32), element<1>(b, s.inv32));
+      } else {
+        const auto h = [](uint32_t pair, int i) __attribute__((always_inline)) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(pair >> (16 * i))); };
+        packed[k] = quantize4(h(a, 0), h(a, 1), h(b, 0), h(b, 1), s.inv);
+      }
+    }
+  }
+};
 
 // B = quantization block; a workgroup's tile is WR x WC waves of 32 rows and COLS columns each.
 template <typename T, int B, bool TRANSPOSED_COPY, int WR, int WC, int COLS, StorePolicy SP>
@@ -32,29 +114,21 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
   __shared__ __align__(16) uint8_t s_codes[TRANSPOSED_COPY ? 128 * 132 : 16];
   const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % WR, across = WC == 1 ? 0 : (threadIdx.x >> 6) / WR;
   const TileIndex wg = tile_of_workgroup((cols + TC - 1) / TC);
-  const int r0 = (wg.y * WR + wave) * 32;              // first row of this wave's strip
+  const int r0 = __builtin_amdgcn_readfirstlane((wg.y * WR + wave) * 32);   // first row of this wave's strip
   const int c0 = wg.x * TC;
-  constexpr int VEC = 16 / sizeof(T), LPR = COLS / VEC, RPI = 64 / LPR, NI = 32 / RPI;   // columns per lane, lanes per row, rows at once
+  constexpr int VEC = Row16<T>::VEC, LPR = COLS / VEC, RPI = 64 / LPR, NI = 32 / RPI;   // columns per lane, lanes per row, rows at once
   const int cl = lane % LPR + LPR * across, rh = lane / LPR;
   const int col = c0 + VEC * cl, cg = cl / (32 / VEC); // first column; 32-column group of the tile
-  const bool col_ok = col < cols;                      // cols % 32 == 0: the lanes of a group are in or out together
+  // rows and cols are multiples of 32: a strip and the lanes of a group are in or out together.  What is outside loads like the rest, from the
+  // last strip and the tile's first columns, without a branch, and stores nothing.  (With a branch and the address of its own around each
+  // load the kernel had 212 instructions for 145 at 32 columns of FP32, most of them before the loads: 0.1-0.2 us a launch.)
+  const bool inside = col < cols && (WR * 32 == B || r0 < rows);
 
-  float v[NI][VEC];
-  float amax = 0.0f;
+  Row16<T> v[NI];
+  const T* from = x + (int64_t)(WR * 32 == B ? r0 : min(r0, rows - 32)) * ldx + ((uint32_t)rh * (uint64_t)ldx + (col < cols ? col : c0));
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int row = r0 + RPI * i + rh;
-    if (col_ok && row < rows) {
-      load_vec(x + (int64_t)row * ldx + col, v[i]);
-    } else {
-#pragma unroll
-      for (int k = 0; k < VEC; ++k) v[i][k] = 0.0f;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) amax = fmaxf(amax, fabsf(v[i][k]));
+  for (int i = 0; i < NI; ++i, from += RPI * ldx) v[i] = *reinterpret_cast<const Row16<T>*>(from);
+  float amax = Row16<T>::amax(v);
   // lanes sharing a 32-column group: the lanes of the group in a row, and those of the rows read at once
   constexpr int GROUP_MASK = (32 / VEC - 1) | (63 & ~(LPR - 1));
   const bool group_first = (lane & GROUP_MASK) == 0;
@@ -70,27 +144,23 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
 #pragma unroll
       for (int b = 0; b < G; ++b) amax = fmaxf(amax, s_amax[w0 + a][g0 + b]);
   }
-  float scale;
-  double inv;
-  block_scale(amax, scale, inv);
+  const typename Row16<T>::Scale scale(amax);
 
   const int lr = rows / B, lc = cols / B;
   // one lane per block writes the scale: the top-left 32-granule of the block
-  if (group_first && col_ok && r0 < rows && (r0 % B) == 0 && ((c0 + 32 * cg) % B) == 0) {
+  if (group_first && inside && (r0 % B) == 0 && ((c0 + 32 * cg) % B) == 0) {
     const int bi = r0 / B, bj = (c0 + 32 * cg) / B;
-    store_scale<SP>(&s[(int64_t)bi * lc + bj], scale);
-    if (TRANSPOSED_COPY) store_scale<SP>(&sT[(int64_t)bj * lr + bi], scale);
+    store_scale<SP>(&s[(int64_t)bi * lc + bj], scale.scale);
+    if (TRANSPOSED_COPY) store_scale<SP>(&sT[(int64_t)bj * lr + bi], scale.scale);
   }
+  int8_t* to = q + (int64_t)r0 * ldq + ((uint32_t)rh * (uint64_t)ldq + col);
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int row = r0 + RPI * i + rh;
+  for (int i = 0; i < NI; ++i, to += RPI * ldq) {
     uint32_t packed[VEC / 4];
-#pragma unroll
-    for (int k = 0; k < VEC / 4; ++k)
-      packed[k] = quantize4(v[i][4 * k], v[i][4 * k + 1], v[i][4 * k + 2], v[i][4 * k + 3], inv);
-    if (col_ok && row < rows) {
-      if constexpr (VEC == 4) store_as<SP>(q + (int64_t)row * ldq + col, packed[0]);
-      else store_as<SP>(q + (int64_t)row * ldq + col, v2i{(int)packed[0], (int)packed[1]});
+    v[i].codes(scale, packed);
+    if (inside) {
+      if constexpr (VEC == 4) store_as<SP>(to, packed[0]);
+      else store_as<SP>(to, v2i{(int)packed[0], (int)packed[1]});
     }
     if (TRANSPOSED_COPY) {
 #pragma unroll
@@ -118,11 +188,13 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
   }
 }
 
-// Narrow strips, in workgroups of one block row and, at block size 128, one block: 64 columns a wave up to 256 tiles of 128 x 128, one
-// for each compute unit (FP16, half the bytes in flight a lane, up to 768); 32 columns for the smallest tensors and, in FP16 at block
-// sizes 64 and 128, up to 256 tiles.  Beyond, the waves fill the chip as they are and narrower ones only take more instructions.  With 128,
-// 64 and 32 columns in us: FP32 at block 32 63 tiles 4.1, 3.4, 3.2, 192 tiles 5.6, 5.0, 5.8, 384 tiles 6.3, 6.8, 7.7; FP16 768 tiles 10.7, 10.1,
-// 15.0, 1024 tiles 13.3, 14.0 (profiles/kernel_choice.txt).
+// Workgroups of one block row: of one strip of 128 columns, and up to 256 tiles of 128 x 128, one for each compute unit, of strips of 64 columns
+// (at block size 128 two, one block): half the serial chain of a wave, and more waves than the chip has SIMDs from 64 tiles on.  Beyond, the waves
+// fill it as they are, and half lines of codes cost more.  With 128 and 64 columns from memory, us: FP16 at block 32 48 tiles 3.5, 3.0, 128 tiles
+// 4.0, 3.3, 256 tiles 4.7, 4.7, 384 tiles 6.0, 6.2, 1920 tiles 19.7, 21.0; FP32 48 tiles 3.7, 2.9, 256 tiles 6.2, 6.1, 768 tiles 13.9, 14.0; block
+// 64 and 128 alike.  Strips of 32 columns gain in FP32 from the cache only (block 32, 64 and 32 columns: 48 tiles 3.1, 2.9, from memory 2.9, 3.2; the MLP
+// step 1056 x 800 -> 2080, 63 tiles for the activation, 51.5, 51.1), and in FP16 nowhere.  (Four block rows to a workgroup: FP16 8192 x 3840 20.4 for
+// 19.7, FP32 4096 x 3072 14.1 for 13.9.)
 template <typename T, int B>
 static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t* q, int64_t ldq, float* s, int8_t* qT,
                             int64_t ldqT, float* sT, hipStream_t st) {
@@ -131,18 +203,17 @@ static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t*
     const dim3 grid(tile_grid((cols + COLS * WC - 1) / (COLS * WC), (rows + 32 * WR - 1) / (32 * WR)));
     hipLaunchKernelGGL(kernel, grid, dim3(64 * WR * WC), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
   };
-  constexpr bool FP16 = sizeof(T) == 2;
+  constexpr int G = B / 32;
   const int64_t tiles = (int64_t)((cols + 127) / 128) * ((rows + 127) / 128);
   with_store_policy(rows, ldq, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
     if (qT) return launch(quantize_kernel<T, B, true, 4, 1, 128, SP>, 4, 1, 128);
     if constexpr (SP == kStoreThrough) {
-      constexpr int G = B / 32;
-      if constexpr (B == 32 || FP16)
-        if (tiles <= (B == 32 ? 64 : 256)) return launch(quantize_kernel<T, B, false, G, G, 32, SP>, G, G, 32);
-      if (tiles <= (FP16 ? 768 : 256)) return launch(quantize_kernel<T, B, false, G, (B + 63) / 64, 64, SP>, G, (B + 63) / 64, 64);
+      if constexpr (B == 32 && sizeof(T) == 4)
+        if (tiles <= 64) return launch(quantize_kernel<T, B, false, 1, 1, 32, SP>, 1, 1, 32);
+      if (tiles <= 256) return launch(quantize_kernel<T, B, false, G, (B + 63) / 64, 64, SP>, G, (B + 63) / 64, 64);
     }
-    launch(quantize_kernel<T, B, false, 4, 1, 128, SP>, 4, 1, 128);
+    launch(quantize_kernel<T, B, false, G, 1, 128, SP>, G, 1, 128);
   });
 }
 
