@@ -83,9 +83,9 @@ struct Strip {
 typedef Strip<32> Strip32;
 
 // Block max-abs, over the lanes of a strip that share a block column and over the waves that share the block through `exchange`
-// (up to four values per wave), then Eq. 1's scale.  At block sizes 64 and 128 every wave of the workgroup has to get here.
+// (up to four values per wave).  At block sizes 64 and 128 every wave of the workgroup has to get here.
 template <int B, int WAVES, int RW>
-__device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES, RW>& t, float (*exchange)[4], float& scale, double& inv) {
+__device__ __forceinline__ float strip_block_max(float m, const Strip<B, WAVES, RW>& t, float (*exchange)[4]) {
   m = wave_group_max<56 | (B / 16 - 1)>(m);
   if constexpr (B > RW) {
     if ((t.lane & (56 | (B / 16 - 1))) == 0) exchange[t.wave][t.ch / (B / 16)] = m;
@@ -93,7 +93,12 @@ __device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES,
 #pragma unroll
     for (int k = 0; k < t.BT; ++k) m = fmaxf(m, exchange[t.wave / t.BT * t.BT + k][t.ch / (B / 16)]);
   }
-  block_scale(m, scale, inv);
+  return m;
+}
+// the same and Eq. 1's scale
+template <int B, int WAVES, int RW>
+__device__ __forceinline__ void strip_block_scale(float m, const Strip<B, WAVES, RW>& t, float (*exchange)[4], float& scale, double& inv) {
+  block_scale(strip_block_max(m, t, exchange), scale, inv);
 }
 // at block size 32: the 16 lanes of a strip that share a block column (same ch / 2)
 __device__ __forceinline__ void strip32_block_scale(float m, float& scale, double& inv) { block_scale(wave_group_max<56 | 1>(m), scale, inv); }
