@@ -53,21 +53,23 @@ __device__ __forceinline__ void gelu_table_entries(float a, float& pos, float& n
   }
 }
 
-template <bool BWD>
-__device__ __forceinline__ void gelu_build_half_table(float* tab, float sx, int i) {
+// Entries of lane `i` of a half table: those of the codes i and -i (i = 64 half + lane).
+// code 0: GELU(0) = 0 comes out exactly; GELU'(0) = 1/2 is set, because the fit is only good to 4e-7 there and a
+// derivative of 0.49999997 would push every halved gradient code off its rounding tie.  Entry 128 (code -128,
+// which no quantizer output holds) is 0.
+struct TablePair {
   float pos, neg;
-  gelu_table_entries<BWD>((float)i * sx, pos, neg);
-  // code 0: GELU(0) = 0 comes out exactly; GELU'(0) = 1/2 is set, because the fit is only good to 4e-7 there and a
-  // derivative of 0.49999997 would push every halved gradient code off its rounding tie.  Entry 128 (code -128,
-  // which no quantizer output holds) is 0.
-  tab[i] = (BWD && i == 0) ? 0.5f : pos;
-  tab[i == 0 ? 128 : 256 - i] = i == 0 ? 0.0f : neg;
-}
+};
 template <bool BWD>
-__device__ __forceinline__ void gelu_build_table(float* tab, float sx, int lane) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) gelu_build_half_table<BWD>(tab, sx, lane + 64 * h);
+__device__ __forceinline__ TablePair gelu_table_pair(float sx, int i) {
+  TablePair e;
+  gelu_table_entries<BWD>((float)i * sx, e.pos, e.neg);
+  if (BWD && i == 0) e.pos = 0.5f;
+  if (i == 0) e.neg = 0.0f;
+  return e;
 }
+__device__ __forceinline__ int table_pos(int i) { return i; }
+__device__ __forceinline__ int table_neg(int i) { return i == 0 ? 128 : 256 - i; }
 
 // Between LDS accesses of one wave, which LDS serves in program order: keeps the compiler from moving one past the other.
 __device__ __forceinline__ void wave_lds_order() {
@@ -76,18 +78,42 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The largest (smallest) signed code of a lane's 16 P codes.
+template <bool LARGEST, int P>
+__device__ __forceinline__ int extreme_code(const uint4 (&v)[P]) {
+  typedef short v2s __attribute__((ext_vector_type(2)));   // two codes, each the upper byte
+  const auto both = [](v2s a, v2s b) __attribute__((always_inline)) { return LARGEST ? __builtin_elementwise_max(a, b) : __builtin_elementwise_min(a, b); };
+  v2s m = __builtin_bit_cast(v2s, v[0].x);
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const v2s odd = __builtin_bit_cast(v2s, d == 0 ? v[p].x : d == 1 ? v[p].y : d == 2 ? v[p].z : v[p].w);
+      m = both(both(m, odd), odd << 8);
+    }
+  const int a = m[0] >> 8, b = m[1] >> 8;
+  return LARGEST ? max(a, b) : min(a, b);
+}
+
 // GELU forward and backward (BWD: dx = g GELU'(x)) on strips: a table per block and wave, or, with waves of 16 rows, per block of a
 // strip, built by the waves that share it.
+//
+// Forward, a block's results are a function of the code alone, and so are their codes: the table is quantized, 256 entries for the 1024 elements
+// of a block, and an element is one byte looked up.  That takes the block's max-abs before the first lookup.  GELU grows with x > 0, and -GELU(-a)
+// grows with a up to 0.75 and stays below 0.17.  So it is GELU of the largest code if that is more than 0.17, else the larger of it and of the
+// smallest code's, unless that lies below -0.7.  Such blocks, and those without an ordinary scale, take FP32 tables, and Eq. 1 for each element.
+// (Forward, us: 262144 x 3072 303 -> 271, of which the memory takes 270 at the rate of Add; 8192 x 5120 from the last-level cache 18 -> 14.3, 8192 x 1280 5.9 -> 5.6,
+// 1024 x 1024 3.3 -> 3.15.  With the max-abs found by looking FP32 values up first the chain is longer: 8192 x 1280 13 % slower than without.)
 template <bool BWD, int B, int WAVES, int RW, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX, const int8_t* __restrict__ G,
                                                          const float* __restrict__ SG, int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
   constexpr int NBC = 128 / B;   // blocks of a strip
   constexpr int SHARED = RW < 32 ? Strip<B, WAVES, RW>::BT : 1;   // waves that share a strip's tables
-  __shared__ float s_tabs[WAVES / SHARED][NBC][256];
-  __shared__ float s_amax[WAVES][4];
+  __shared__ __align__(1024) float s_tabs[WAVES / SHARED][NBC][256];
+  __shared__ float s_amax[WAVES][4], s_amin[WAVES][4];
   const Strip<B, WAVES, RW> t(rows, cols);
-  constexpr int P = Strip<B, WAVES, RW>::PASSES;
-  if (t.BT == 1 && !t.inside) return;   // a whole wave; there is no workgroup barrier
+  constexpr int P = Strip<B, WAVES, RW>::PASSES, BT = Strip<B, WAVES, RW>::BT;
+  if (BT == 1 && !t.inside) return;   // a whole wave; there is no workgroup barrier
   const int64_t pass = (int64_t)8 * cols;
   uint4 px[P], pg[BWD ? P : 1];   // requested first: their latency runs beside the table build
 #pragma unroll
@@ -98,54 +124,160 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
   // the strip's block scales are the same for all lanes: scalar loads (the grids are not written by this kernel before the
   // barrier, and at block size 32 by nobody else)
   typedef const __attribute__((address_space(4))) float* const_f32_ptr;
-  const const_f32_ptr sx_row = (const_f32_ptr)SX + (int64_t)(t.bi / t.BT) * t.lc + t.c0 / B;
+  const const_f32_ptr sx_row = (const_f32_ptr)SX + (int64_t)(t.bi / BT) * t.lc + t.c0 / B;
   const int nblk = min(NBC, t.lc - t.c0 / B);
-  if constexpr (SHARED == 1) {
+  // this wave's part of the strip's tables: half tables, in turn with the waves that share them
+  constexpr int HALVES = (2 * NBC + SHARED - 1) / SHARED;   // (at block size 128 two of eight waves have one)
+  const auto half_of = [&](int u) __attribute__((always_inline)) { return u * SHARED + (SHARED == 1 ? 0 : t.wave % SHARED); };
+  const auto code_of = [&](int h) __attribute__((always_inline)) { return t.lane + 64 * (h & 1); };
+  TablePair entry[HALVES];
 #pragma unroll
-    for (int k = 0; k < NBC; ++k)
-      if (k < nblk) gelu_build_table<BWD>(s_tabs[t.wave][k], sx_row[k], t.lane);
-    wave_lds_order();
-  } else {   // half a table at a time, in turn
-#pragma unroll
-    for (int u = 0; u < 2 * NBC; u += SHARED) {
-      const int h = u + t.wave % SHARED;
-      if (h < 2 * nblk) gelu_build_half_table<BWD>(s_tabs[t.wave / SHARED][h / 2], sx_row[h / 2], t.lane + 64 * (h & 1));
-    }
-    __syncthreads();
+  for (int u = 0; u < HALVES; ++u) {
+    const int h = half_of(u);
+    entry[u] = gelu_table_pair<BWD>(sx_row[min(h / 2, nblk - 1)], code_of(h));
   }
-  const float* const tab = s_tabs[t.wave / SHARED][t.ch / (B / 16)];   // lanes outside the matrix may read a table nobody built: see Strip::base
-  float sg = 0.0f, sg128 = 0.0f;
-  if (BWD) {
-    sg = SG[t.block_index()];
-    sg128 = -128.0f * sg;
-  }
-  float y[P][16];
-  float m = 0.0f;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const uint32_t w[4] = {px[p].x, px[p].y, px[p].z, px[p].w};
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      y[p][4 * d + 0] = tab[w[d] & 0xffu];
-      y[p][4 * d + 1] = tab[(w[d] >> 8) & 0xffu];
-      y[p][4 * d + 2] = tab[(w[d] >> 16) & 0xffu];
-      y[p][4 * d + 3] = tab[w[d] >> 24];
-    }
-    if (BWD) {
-      float ug[16];
-      unpack16_biased(pg[p], ug);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) y[p][e] = __builtin_fmaf(ug[e], sg, sg128) * y[p][e];
-    }
-    m = amax16(m, y[p]);
-  }
+  const int own_table = t.ch / (B / 16);
+  const auto tables_built = [&]() __attribute__((always_inline)) {
+    if constexpr (SHARED == 1) wave_lds_order();
+    else __syncthreads();
+  };
+
   float scale;
-  double inv;
-  strip_block_scale(m, t, s_amax, scale, inv);
+  uint4 o[P];
+  bool quantized = false;
+  if constexpr (!BWD) {
+    // ---- the table quantized
+    // Maximum of `v` over a block; `all`: f(maximum) for every block of the wave or, where a strip has several, of the workgroup
+    const auto block_max = [&](float v, float (*exchange)[4], bool& all, auto f) __attribute__((always_inline)) {
+      v = wave_group_max<56 | (B / 16 - 1)>(v);
+      bool mine = f(v);
+      if constexpr (BT > 1) {
+        if ((t.lane & (56 | (B / 16 - 1))) == 0) exchange[t.wave][own_table] = v;
+        __syncthreads();
+        const int first = min(t.lane / NBC, WAVES / BT - 1) * BT;
+        float other = 0.0f;
+#pragma unroll
+        for (int k = 0; k < BT; ++k) {
+          v = fmaxf(v, exchange[t.wave / BT * BT + k][own_table]);
+          other = fmaxf(other, exchange[first + k][t.lane % NBC]);
+        }
+        mine = f(other);
+      }
+      all = !__any(!mine);
+      return v;
+    };
+    const float sx = sx_row[min(own_table, nblk - 1)];
+    const auto result_of = [&](int code) __attribute__((always_inline)) {   // |GELU| of a code's input
+      float pos, neg;
+      const float a = fabsf((float)code) * sx;
+      gelu_table_entries<false>(a, pos, neg);
+      return code > 0 ? pos : -neg;
+    };
+    constexpr float kEnough = 0.1701f, kMonotone = 0.7f, kHuge = 3.0e38f;
+    const int most = extreme_code<true>(px);
+    float amax = most > 0 && sx > 0.0f ? result_of(most) : 0.0f;
+    amax = block_max(amax < kHuge ? amax : 0.0f, s_amax, quantized, [](float v) { return v >= kEnough; });
+    if (__builtin_expect(!quantized, 0)) {
+      const int least = extreme_code<false>(px);
+      const float a = (float)(least < 0 ? -least : 0) * sx;
+      const float other = sx >= 0.0f && a <= kMonotone && least > -128 ? (least < 0 ? result_of(least) : 0.0f) : kHuge;
+      amax = block_max(fmaxf(other, amax), s_amin, quantized, [](float v) { return v < kHuge; });
+    }
+    if (__builtin_expect(quantized, 1)) {
+      double inv;
+      block_scale(amax, scale, inv);
+      int8_t* const codes = reinterpret_cast<int8_t*>(s_tabs[t.wave / SHARED]);   // 256 of each block
+#pragma unroll
+      for (int u = 0; u < HALVES; ++u) {
+        const int h = half_of(u), i = code_of(h);
+        if (h >= 2 * NBC) break;
+        const double k = read_lane_f64(inv, h / 2 * (B / 16));
+        codes[h / 2 * 256 + table_pos(i)] = (int8_t)code_bits(entry[u].pos, k);
+        codes[h / 2 * 256 + table_neg(i)] = (int8_t)code_bits(entry[u].neg, k);
+      }
+      tables_built();
+      typedef __attribute__((address_space(3))) uint8_t* lds_u8;
+      const uint32_t base = (uint32_t)(uintptr_t)(lds_ptr)(codes) + 256 * own_table;   // a multiple of 256, below 65536
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const uint32_t w[4] = {px[p].x, px[p].y, px[p].z, px[p].w};
+        uint32_t r[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          uint32_t c[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) c[e] = *(lds_u8)(uintptr_t)__builtin_amdgcn_perm(w[d], base, 0x0c0c0104u + e);   // the code below the base's second byte
+          r[d] = (c[0] | c[1] << 8) | (c[2] | c[3] << 8) << 16;
+        }
+        o[p] = make_uint4(r[0], r[1], r[2], r[3]);
+      }
+    }
+  }
+  if (!quantized) {
+    // ---- FP32 tables
+#pragma unroll
+    for (int u = 0; u < HALVES; ++u) {
+      const int h = half_of(u), i = code_of(h);
+      if (h >= 2 * NBC) break;
+      s_tabs[t.wave / SHARED][h / 2][table_pos(i)] = entry[u].pos;
+      s_tabs[t.wave / SHARED][h / 2][table_neg(i)] = entry[u].neg;
+    }
+    tables_built();
+    const float* const tab = s_tabs[t.wave / SHARED][own_table];
+    float sg = 0.0f, sg128 = 0.0f;
+    if (BWD) {
+      sg = SG[t.block_index()];
+      sg128 = -128.0f * sg;
+    }
+    const auto results = [&](int p, float (&y)[16]) __attribute__((always_inline)) {
+      const uint32_t w[4] = {px[p].x, px[p].y, px[p].z, px[p].w};
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        y[4 * d + 0] = tab[w[d] & 0xffu];
+        y[4 * d + 1] = tab[(w[d] >> 8) & 0xffu];
+        y[4 * d + 2] = tab[(w[d] >> 16) & 0xffu];
+        y[4 * d + 3] = tab[w[d] >> 24];
+      }
+      if (BWD) {
+        float ug[16];
+        unpack16_biased(pg[p], ug);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) y[e] = __builtin_fmaf(ug[e], sg, sg128) * y[e];
+      }
+    };
+    float m = 0.0f;
+    double inv;
+    if constexpr (BWD) {
+      float y[P][16];
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        results(p, y[p]);
+        m = amax16(m, y[p]);
+      }
+      strip_block_scale(m, t, s_amax, scale, inv);
+#pragma unroll
+      for (int p = 0; p < P; ++p) o[p] = quantize16(y[p], inv);
+    } else {   // looked up twice: kept, the results would take the registers of a wave on every SIMD
+      float y[16];
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        results(p, y);
+        m = amax16(m, y);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      strip_block_scale(m, t, s_amax, scale, inv);
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        results(p, y);
+        o[p] = quantize16(y, inv);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
   if (!t.ok) return;
   if (t.owns_scale()) store_scale<SP>(&SY[t.block_index()], scale);
 #pragma unroll
-  for (int p = 0; p < P; ++p) store_as<SP>(Y + t.base + p * pass, quantize16(y[p], inv));
+  for (int p = 0; p < P; ++p) store_as<SP>(Y + t.base + p * pass, o[p]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -321,14 +453,17 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
 // 16 rows has half the serial chain.  From a few million elements on it matters how the waves come out on 1024 SIMDs: 32-row waves fill
 // rounds of 4 M elements, half waves round a rest less up, and cost twice the scales, reductions and exchanges.  The lines lie where the
 // gain over sizes and widths ends, alone and in the paths of a training step (profiles/strip_heights.txt).  32 -> 16 rows in us:
-//   GELU, forward and backward one after the other: block 32 4 M elements 10.8 -> 9.5, 13 M 16.3 -> 14.8, 17 M 19.1 -> 18.2, 20 M 21.5 -> 22.0
-//     (beyond 21 M up to 5 % faster again, 40 M 40.8 -> 40.3); block 64 10 M 13.1 -> 12.0, 17 M 18.4 -> 17.0, 20 M 21.0 -> 21.6, 36 M 35.8 -> 34.7;
-//     block 128 only backward, alone 1 M 4.8 -> 4.2, 12 M 10.5 -> 10.1 (forward 12 M 7.7 -> 7.6, from the cache 28 M 10.1 -> 11.2: eight waves to a table)
+//   GELU forward, from memory and from the last-level cache: block 32 1 M elements 3.7 -> 3.15 and 3.7 -> 3.15, 6 M 5.25 -> 4.85 and 4.7 -> 4.5, 10 M 6.35 -> 6.1
+//     and 5.65 -> 5.55, 12 M 7.5 -> 7.2 and 5.9 -> 6.05 (MLP step 4096 x 768 -> 3072 0.3 less), 16 M 8.25 -> 8.5 and 6.85 -> 7.25, 40 M 19.7 -> 19.5 and 14.3 -> 15.9; block 64 1 M 3.45 -> 3.0, 10 M 6.1 -> 5.55
+//     and 5.0 -> 4.75, 12 M 7.15 -> 7.55 and 5.15 -> 5.2, 16 M 8.0 -> 9.4 and 5.85 -> 6.1; block 128 10 M 5.7 -> 5.55 and 4.85 -> 5.2 (eight waves to a table)
+//   GELU backward, alone: block 128 1 M 4.8 -> 4.2, 12 M 10.5 -> 10.1; at block 32 and 64, one after the other with a forward that took waves as low: block 32
+//     4 M elements 10.8 -> 9.5, 13 M 16.3 -> 14.8, 17 M 19.1 -> 18.2, 20 M 21.5 -> 22.0; block 64 17 M 18.4 -> 17.0, 36 M 35.8 -> 34.7
 //   Add, alone 1 M 3.8 -> 3.3, block 64 and 128 3.9 -> 3.2 and 4.1 -> 3.6; in the residual path at block 32 10 M 53.7 -> 53.8, 12 M 63.8 -> 63.4, 16 M
 //     76.5 -> 75.7, 20 M 86.7 -> 86.0, by up to 2 % the one or the other way from width to width; block 128 16 M 83.8 -> 82.7
 //   Dropout, alone 1 M 3.5 -> 3.1, 4 M 4.1 -> 4.4; in the residual path 8 M 48.4 -> 49.0, 12 M 63.4 -> 63.4, 20 M 86.0 -> 86.5
 static bool low_gelu(bool backward, int block, int64_t rows, int64_t cols) {
-  if (block == 128) return backward && rows * cols <= 16 << 20;
+  if (!backward) return block != 128 && rows * cols <= (block == 32 ? 13 : 11) << 20;
+  if (block == 128) return rows * cols <= 16 << 20;
   return block == 64 || rows * cols <= 18 << 20;
 }
 static bool low_add(int block, int64_t rows, int64_t cols) { return rows * cols <= (block == 128 ? 32 : block == 64 ? 12 : 11) << 20; }

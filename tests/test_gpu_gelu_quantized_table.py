@@ -1,0 +1,97 @@
+"""GELU forward looks quantized codes up wherever a block's largest result follows from its largest or smallest code, and takes FP32 tables where one block of
+the strip (of the workgroup, where its waves share blocks) does not let it.  Blocks of every kind, beside ordinary ones and beside one that forces
+the general way: codes and scales have to be the same both ways, and within the bound of the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2403_12422_amd as jf
+from paper_2403_12422_amd import workloads
+from test_gpu_parity import dev, host, say
+
+pytestmark = pytest.mark.gpu
+
+# (scale, smallest code, largest code)
+KINDS = {
+    "both signs": (2.0 / 127, -127, 127),
+    "positive decides just": (0.295 / 127, -127, 127),         # GELU(0.295) = 0.1817
+    "small": (0.25 / 127, -127, 127),                          # the smallest code is within the monotone part
+    "negative alone, small": (0.69 / 127, -127, -1),
+    "negative alone, large": (3.0 / 127, -127, -60),           # general
+    "small positive, large negative": (2.0 / 127, -127, 8),    # general
+    "far tail": (13.0 / 127, -127, -100),                      # general
+    "tiny": (1e-30, -127, 127),
+    "subnormal": (1e-42, -127, 127),
+    "zero scale": (0.0, -127, 127),
+    "zero codes": (1.0, 0, 0),
+    "one code": (0.01, 5, 5),
+    "huge": (1e30, -127, 127),
+}
+
+
+def _block(g, kind, block):
+    s, lo, hi = KINDS[kind]
+    q = g.integers(lo, hi + 1, size=(block, block))
+    q[0, 0], q[block - 1, block - 1] = lo, hi
+    return q.astype(np.int8), np.float32(s)
+
+
+def _tensor(g, block, rows, cols):
+    names = list(KINDS)
+    X, S, which = np.zeros((rows * block, cols * block), np.int8), np.zeros((rows, cols), np.float32), np.zeros((rows, cols), int)
+    for i in range(rows):
+        for j in range(cols):
+            # ordinary blocks mostly, so that strips and workgroups of all quantized tables occur
+            k = names[0] if g.random() < 0.5 and (i * cols + j) % 3 else names[(i * cols + j) // 3 % len(names)]
+            which[i, j] = names.index(k)
+            X[i * block:(i + 1) * block, j * block:(j + 1) * block], S[i, j] = _block(g, k, block)
+    return X, S, which
+
+
+# 32: strips of four blocks, ragged; small tensors are on waves of 16 rows, the widest on waves of 32
+@pytest.mark.parametrize("block,rows,cols", [(32, 16, 13), (32, 3, 1), (32, 120, 97), (64, 9, 5), (64, 40, 72), (128, 5, 3), (128, 14, 9)])
+def test_blocks_of_every_kind(block, rows, cols):
+    say(f"GELU tables block={block} {rows}x{cols} blocks")
+    g = workloads.rng(9700 + block + rows)
+    X, S, which = _tensor(g, block, rows, cols)
+    Y, SY = jf.jf_gelu_q(dev(X), dev(S), block)
+    y, sy = host(Y), host(SY)
+    oY, oSY, of = oracle.gelu_q(X, S, block)
+    ordinary = np.isin(which, [list(KINDS).index(k) for k in KINDS if k not in ("tiny", "subnormal", "huge", "far tail")])
+    o = np.repeat(np.repeat(ordinary, block, 0), block, 1)
+    np.testing.assert_allclose(sy[ordinary], oSY[ordinary], rtol=1e-5)
+    d = np.abs(y.astype(int) - oY.astype(int))[o]
+    assert d.max() <= 1 and np.count_nonzero(d) <= 1e-3 * d.size
+    # the same blocks with the general way forced in each strip by its first block (code -128 beside all negative ones)
+    X2, S2 = X.copy(), S.copy()
+    X2.reshape(rows, block, cols * block)[:, :, :block] = -100
+    X2[::block, 0] = -128
+    first = np.zeros((rows, cols), bool)
+    for c in range(0, cols, 128 // block):
+        first[:, c] = True
+        X2[:, c * block:(c + 1) * block] = -100
+        X2[::block, c * block] = -128
+        S2[:, c] = 0.02
+    Y2, SY2 = jf.jf_gelu_q(dev(X2), dev(S2), block)
+    keep = ~first
+    k = np.repeat(np.repeat(keep, block, 0), block, 1)
+    np.testing.assert_array_equal(host(SY2)[keep], sy[keep])
+    np.testing.assert_array_equal(host(Y2)[k], y[k])
+
+
+@pytest.mark.parametrize("block", [32, 64, 128])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, -0.5])
+def test_scales_that_are_none(block, bad):
+    """A block with such a scale leaves the others of its strip and workgroup what they are without it."""
+    say(f"GELU tables block={block} scale {bad}")
+    g = workloads.rng(9750 + block)
+    X, S, _ = _tensor(g, block, 8, 8)
+    y, sy = (host(t) for t in jf.jf_gelu_q(dev(X), dev(S), block))
+    S2 = S.copy()
+    S2[3, 2] = bad
+    y2, sy2 = (host(t) for t in jf.jf_gelu_q(dev(X), dev(S2), block))
+    keep = np.ones(S.shape, bool)
+    keep[3, 2] = False
+    k = np.repeat(np.repeat(keep, block, 0), block, 1)
+    np.testing.assert_array_equal(sy2[keep], sy[keep])
+    np.testing.assert_array_equal(y2[k], y[k])
