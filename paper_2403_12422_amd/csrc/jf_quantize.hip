@@ -227,26 +227,30 @@ static void dispatch_quantize(int block, const T* x, int64_t ldx, int rows, int 
 
 // Dequantizer Q^-1 of Eq. 1: out = code * scale as FP32 or FP16 (the hand-over to a floating-point operator
 // such as the FP16 attention core of Sec. 7.1).  HBM-bound: 1 byte in, 2 or 4 out per element.  A thread writes 16 bytes
-// (8 FP16 or 4 FP32 values) at a time, so that a wave fills whole lines, and takes DQ_CHUNKS such chunks 256 apart, whose
+// (8 FP16 or 4 FP32 values) at a time, so that a wave fills whole lines, and takes CHUNKS such chunks 256 apart, whose
 // codes and scales are requested before the first is used; rows follow each other without a gap, so that no lane idles at
 // their ends.  The quotient chunk / (chunks per row) is formed once per workgroup in 64 bits and per chunk in 32.
-static constexpr int DQ_CHUNKS = 4;
-template <typename T, StorePolicy SP>
+// CHUNKS: two.  More of them have more requests in flight a lane, but their addresses, 36 instructions each, stand in front of them one after the other,
+// and waves of fewer come and go more evenly.  FP16 with one, two, three and four chunks, us: 8192 x 3840 18.9, 17.6, 18.0, 18.6, from the last-level
+// cache 13.2, 12.6, 12.9, 12.4; 8192 x 1280 8.0, 7.8, 8.3, 8.0; 8192 x 2048 11.1, 11.2, 11.4, 12.0; 1024 x 1024 2.4, 2.3, 2.4, 2.65; 65536 x 4096
+// 137, 128, 129, 130; FP32 with two and four 8192 x 1280 9.0 and 9.25, 65536 x 4096 206.8 and 207.8.  Four where two would make a grid of 2^32
+// threads, which cannot be launched.
+template <typename T, StorePolicy SP, int CHUNKS>
 __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restrict__ q, const float* __restrict__ s, int rows,
                                                           int cols, int block_log2, T* __restrict__ out, int64_t ldo) {
   constexpr int VEC = 16 / sizeof(T);
   typedef typename std::conditional<VEC == 8, uint2, uint32_t>::type packed_t;
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   const uint32_t chunks = cols / VEC;
-  const int64_t first = (int64_t)blockIdx.x * (256 * DQ_CHUNKS), total = (int64_t)rows * chunks;
+  const int64_t first = (int64_t)blockIdx.x * (256 * CHUNKS), total = (int64_t)rows * chunks;
   const int row0 = (int)(first / chunks);
   const uint32_t rem = (uint32_t)(first - (int64_t)row0 * chunks);
   const int lc = cols >> block_log2;
-  packed_t p[DQ_CHUNKS];
-  float sc[DQ_CHUNKS];
-  int row[DQ_CHUNKS], col[DQ_CHUNKS];
+  packed_t p[CHUNKS];
+  float sc[CHUNKS];
+  int row[CHUNKS], col[CHUNKS];
 #pragma unroll
-  for (int u = 0; u < DQ_CHUNKS; ++u) {
+  for (int u = 0; u < CHUNKS; ++u) {
     const uint32_t i = rem + u * 256 + threadIdx.x, r = i / chunks;
     row[u] = row0 + (int)r;
     col[u] = VEC * (int)(i - r * chunks);
@@ -256,7 +260,7 @@ __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restric
     }
   }
 #pragma unroll
-  for (int u = 0; u < DQ_CHUNKS; ++u) {
+  for (int u = 0; u < CHUNKS; ++u) {
     if (first + u * 256 + threadIdx.x >= total) break;
     vec_t v;
 #pragma unroll
@@ -281,16 +285,20 @@ extern "C" int32_t jf_dequantize_block(const int8_t* q, const float* s, int64_t 
   if (!valid_dim(rows, block) || !valid_dim(cols, block) || !valid_size(rows, cols) || ldo < cols) return JF_ERR_SHAPE;
   if (!aligned16(q) || !aligned4(s) || !aligned16(out) || (ldo % 8)) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const int64_t per_wg = 256 * DQ_CHUNKS * (out_dtype == 0 ? 4 : 8);
-  const unsigned grid = (unsigned)((rows * cols + per_wg - 1) / per_wg);
   with_store_policy(rows, ldo * (out_dtype == 0 ? 4 : 2), [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
-    if (out_dtype == 0)
-      hipLaunchKernelGGL((dequantize_kernel<float, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, block_log2(block),
-                         static_cast<float*>(out), ldo);
-    else
-      hipLaunchKernelGGL((dequantize_kernel<_Float16, SP>), dim3(grid), dim3(256), 0, st, q, s, (int)rows, (int)cols, block_log2(block),
-                         static_cast<_Float16*>(out), ldo);
+    const auto launch = [&](auto kernel, auto* to, int chunks) {
+      const int64_t per_wg = 256 * chunks * (int64_t)(16 / sizeof(*to));
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((rows * cols + per_wg - 1) / per_wg)), dim3(256), 0, st, q, s, (int)rows, (int)cols, block_log2(block), to, ldo);
+    };
+    const auto launch_as = [&](auto* to) {
+      typedef std::remove_pointer_t<decltype(to)> T;
+      constexpr int64_t VEC = 16 / sizeof(T);
+      if (rows * cols < (int64_t(1) << 32) * 2 * VEC - 4096) launch(dequantize_kernel<T, SP, 2>, to, 2);
+      else launch(dequantize_kernel<T, SP, 4>, to, 4);
+    };
+    if (out_dtype == 0) launch_as(static_cast<float*>(out));
+    else launch_as(static_cast<_Float16*>(out));
   });
   return launch_status();
 }
