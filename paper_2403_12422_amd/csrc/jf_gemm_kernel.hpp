@@ -161,6 +161,15 @@ __device__ __forceinline__ void fold(float (&acc)[N], const V& v, float t) {
     asm("v_fmac_f32 %0, %1, %2" : "+v"(acc[r]) : "s"(t), "v"(c));
   }
 }
+// The same in two halves, for loops that keep them apart.
+__device__ __forceinline__ void fold_convert(float (&c)[16], const v16i& v) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) c[r] = (float)v[r];
+}
+__device__ __forceinline__ void fold_add(float (&acc)[16], const float (&c)[16], float t) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) asm("v_fmac_f32 %0, %1, %2" : "+v"(acc[r]) : "s"(t), "v"(c[r]));
+}
 
 // First row and column of the tile that a workgroup takes.  Workgroups are dealt round-robin to the 8 XCDs (each with its own
 // L2).  Renumber them so that every XCD works on one contiguous run of tiles, and order the tiles in groups of GROUP_M tile rows,

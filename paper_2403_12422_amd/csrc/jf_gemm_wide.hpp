@@ -235,6 +235,8 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
     }
   };
   constexpr int PARTS = QUARTERS ? 2 : 1;   // MFMAs of a step; each has its share of the fold behind it
+  constexpr bool PHASES = B == 64;          // but here all of it stands behind the last (see run_stage)
+  static_assert(!PHASES || PARTS == 1, "whole sub-blocks");
   auto zero_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int a = 0; a < WM; ++a)
@@ -262,7 +264,14 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
       // The arbiter favours the older of a SIMD's two waves, which then waits at the barrier while the other, alone, leaves the pipes
       // idle.  Between two barriers the wave that is behind goes first (16384 x 4096 -> 11008 at B = 128 759 / 732 / 749 -> 741 / 715 /
       // 734 us forward / dgrad / wgrad, both gradients 1488 -> 1450; 4096^3 at B = 64 93.2 / 92.5 / 91.9 -> 92.8 / 91.4 / 89.7).
-      if constexpr (i % 2 == 0) __builtin_amdgcn_s_setprio(3 - ((i - SYNC + NT) % NT) / 2);
+      // PHASES (B = 64, where the vector ALU bounds the loop): conversions issue at 4.3 cycles and FMAs at 2.3, and those of two waves run beside each
+      // other.  Left alone both waves convert and then both add.  So all of a unit's conversions stand before its FMAs, and a wave in its FMAs and the
+      // next chain goes before one in its conversions: bare chains of 2 MFMAs with their folds, two waves, random codes 33.4 -> 31.0 ns
+      // per MFMA, small numbers 29.9 -> 23.9; 8192^3 683 / 670 / 665 -> 671 / 649 / 644 us, 4096^3 91.2 -> 90.0, both gradients 177.6 -> 172.5.
+      // (At B = 128 the fold is too short for it: 16384 x 4096 -> 11008 1390 -> 1400.  At B = 32, four waves of two workgroups to a SIMD, bare chains
+      // gain 10 %, the kernels lose 1-2: there the power limit and the fragments' way into the registers bound the loop.)
+      constexpr int since = (i - SYNC + NT) % NT, LOW = since < NT / 2 ? 2 : 0;
+      if constexpr (!PHASES && i % 2 == 0) __builtin_amdgcn_s_setprio(3 - since / 2);
       if constexpr (i == SYNC) {
         if (NBUF > 2 && !after_store) wait_loads(std::integral_constant<int, LOADS * (NBUF - 2)>());
         else wait_loads(std::integral_constant<int, 0>());
@@ -274,6 +283,10 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
         constexpr int js = decltype(js_tag)::value;
         chain_step((i + 1) % NT, js, 0, nxt);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PHASES && js == KPB - 1) {
+          __builtin_amdgcn_s_setprio(LOW);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         if constexpr (PARTS == 1 && i == WN - 2) read_a(slot, 1, js);
         if constexpr (PARTS == 1 && i == 2 * WN - 2) read_a(nslot, 0, js);
         if constexpr (i >= SYNC) {
@@ -285,7 +298,16 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
           });
         }
         constexpr int R0 = 16 * js / KPB, R1 = 16 * (js + 1) / KPB, RM = QUARTERS ? (R0 + R1) / 2 : R1;
-        fold<R0, RM>(acc[a][b], cur, scale[b * NSB / WN]);
+        if constexpr (!PHASES) {
+          fold<R0, RM>(acc[a][b], cur, scale[b * NSB / WN]);
+        } else if constexpr (js == KPB - 1) {
+          float c[16];
+          fold_convert(c, cur);
+          __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_s_setprio(LOW + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          fold_add(acc[a][b], c, scale[b * NSB / WN]);
+        }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (PARTS == 2) {
           chain_step((i + 1) % NT, js, 1, nxt);
