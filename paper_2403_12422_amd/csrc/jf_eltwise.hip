@@ -455,14 +455,16 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
 // gain over sizes and widths ends, alone and in the paths of a training step (profiles/strip_heights.txt).  32 -> 16 rows in us:
 //   GELU forward, from memory and from the last-level cache: block 32 1 M elements 3.7 -> 3.15 and 3.7 -> 3.15, 6 M 5.25 -> 4.85 and 4.7 -> 4.5, 10 M 6.35 -> 6.1
 //     and 5.65 -> 5.55, 12 M 7.5 -> 7.2 and 5.9 -> 6.05 (MLP step 4096 x 768 -> 3072 0.3 less), 16 M 8.25 -> 8.5 and 6.85 -> 7.25, 40 M 19.7 -> 19.5 and 14.3 -> 15.9; block 64 1 M 3.45 -> 3.0, 10 M 6.1 -> 5.55
-//     and 5.0 -> 4.75, 12 M 7.15 -> 7.55 and 5.15 -> 5.2, 16 M 8.0 -> 9.4 and 5.85 -> 6.1; block 128 10 M 5.7 -> 5.55 and 4.85 -> 5.2 (eight waves to a table)
+//     and 5.0 -> 4.75, 12 M 7.15 -> 7.55 and 5.15 -> 5.2, 16 M 8.0 -> 9.4 and 5.85 -> 6.1; block 128 10 M 5.7 -> 5.55 and 4.85 -> 5.2 (eight waves to a table);
+//     rows that share lines, which from memory cost the waves of 32 rows more: 11264 x 1504 12.45 -> 11.75 and 7.9 -> 8.25, 9024 x 3104 17.7 -> 17.2, 16000 x 2080 19.65 ->
+//     18.95, 36992 x 864 18.8 -> 18.6 and 13.0 -> 14.8, at block 64 30016 x 1088 16.8 -> 16.1
 //   GELU backward, alone: block 128 1 M 4.8 -> 4.2, 12 M 10.5 -> 10.1; at block 32 and 64, one after the other with a forward that took waves as low: block 32
 //     4 M elements 10.8 -> 9.5, 13 M 16.3 -> 14.8, 17 M 19.1 -> 18.2, 20 M 21.5 -> 22.0; block 64 17 M 18.4 -> 17.0, 36 M 35.8 -> 34.7
 //   Add, alone 1 M 3.8 -> 3.3, block 64 and 128 3.9 -> 3.2 and 4.1 -> 3.6; in the residual path at block 32 10 M 53.7 -> 53.8, 12 M 63.8 -> 63.4, 16 M
 //     76.5 -> 75.7, 20 M 86.7 -> 86.0, by up to 2 % the one or the other way from width to width; block 128 16 M 83.8 -> 82.7
 //   Dropout, alone 1 M 3.5 -> 3.1, 4 M 4.1 -> 4.4; in the residual path 8 M 48.4 -> 49.0, 12 M 63.4 -> 63.4, 20 M 86.0 -> 86.5
 static bool low_gelu(bool backward, int block, int64_t rows, int64_t cols) {
-  if (!backward) return block != 128 && rows * cols <= (block == 32 ? 13 : 11) << 20;
+  if (!backward) return block != 128 && (cols % 128 || rows * cols <= (block == 32 ? 13 : 11) << 20);
   if (block == 128) return rows * cols <= 16 << 20;
   return block == 64 || rows * cols <= 18 << 20;
 }
