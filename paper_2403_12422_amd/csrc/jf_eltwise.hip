@@ -102,7 +102,7 @@ __device__ __forceinline__ int extreme_code(const uint4 (&v)[P]) {
 // of a block, and an element is one byte looked up.  That takes the block's max-abs before the first lookup.  GELU grows with x > 0, and -GELU(-a)
 // grows with a up to 0.75 and stays below 0.17.  So it is GELU of the largest code if that is more than 0.17, else the larger of it and of the
 // smallest code's, unless that lies below -0.7.  Such blocks, and those without an ordinary scale, take FP32 tables, and Eq. 1 for each element.
-// (Forward, us: 262144 x 3072 303 -> 271, of which the memory takes 270 at the rate of Add; 8192 x 5120 from the last-level cache 18 -> 14.3, 8192 x 1280 5.9 -> 5.6,
+// (Forward, us: 32768 x 4096 51.5 -> 43.0, 262144 x 3072 in turn with its backward 721 -> 697 for both, back to back 297 and 299; 8192 x 5120 from the last-level cache 18 -> 14.3, 8192 x 1280 5.9 -> 5.6,
 // 1024 x 1024 3.3 -> 3.15.  With the max-abs found by looking FP32 values up first the chain is longer: 8192 x 1280 13 % slower than without.)
 template <bool BWD, int B, int WAVES, int RW, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX, const int8_t* __restrict__ G,
