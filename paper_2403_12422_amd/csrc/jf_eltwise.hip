@@ -175,8 +175,9 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
     };
     constexpr float kEnough = 0.1701f, kMonotone = 0.7f, kHuge = 3.0e38f;
     const int most = extreme_code<true>(px);
+    // a lane's result beyond kHuge (or infinite, or none) has to stay in the block's maximum, where both tests refuse it
     float amax = most > 0 && sx > 0.0f ? result_of(most) : 0.0f;
-    amax = block_max(amax < kHuge ? amax : 0.0f, s_amax, quantized, [](float v) { return v >= kEnough; });
+    amax = block_max(amax < kHuge ? amax : __builtin_inff(), s_amax, quantized, [](float v) { return v >= kEnough && v < kHuge; });
     if (__builtin_expect(!quantized, 0)) {
       const int least = extreme_code<false>(px);
       const float a = (float)(least < 0 ? -least : 0) * sx;

@@ -26,6 +26,10 @@ KINDS = {
     "zero codes": (1.0, 0, 0),
     "one code": (0.01, 5, 5),
     "huge": (1e30, -127, 127),
+    # results up to 3.05e38 and 3.3e38, of at most 3.4e38, that some lanes of the block have and others do not; and that all have
+    "largest numbers": (2.4e36, -127, 127),
+    "largest numbers, higher": (2.6e36, -127, 127),
+    "largest numbers alone": (2.6e36, 118, 127),
 }
 
 
