@@ -78,21 +78,38 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The largest (smallest) signed code of a lane's 16 P codes.
-template <bool LARGEST, int P>
-__device__ __forceinline__ int extreme_code(const uint4 (&v)[P]) {
-  typedef short v2s __attribute__((ext_vector_type(2)));   // two codes, each the upper byte
-  const auto both = [](v2s a, v2s b) __attribute__((always_inline)) { return LARGEST ? __builtin_elementwise_max(a, b) : __builtin_elementwise_min(a, b); };
+// The largest signed code of a lane's 16 P codes.  (Two at a time, each the upper byte of 16 bits: what stands below it does not decide.)
+template <int P>
+__device__ __forceinline__ int largest_code(const uint4 (&v)[P]) {
+  typedef short v2s __attribute__((ext_vector_type(2)));
   v2s m = __builtin_bit_cast(v2s, v[0].x);
 #pragma unroll
   for (int p = 0; p < P; ++p)
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
       const v2s odd = __builtin_bit_cast(v2s, d == 0 ? v[p].x : d == 1 ? v[p].y : d == 2 ? v[p].z : v[p].w);
-      m = both(both(m, odd), odd << 8);
+      m = __builtin_elementwise_max(__builtin_elementwise_max(m, odd), (v2s)(odd << 8));
     }
-  const int a = m[0] >> 8, b = m[1] >> 8;
-  return LARGEST ? max(a, b) : min(a, b);
+  return max(m[0] >> 8, m[1] >> 8);
+}
+// Of the same codes the smallest that is not below `at`, and the largest below it; above 127 and below -128: there is none.  Differences modulo
+// 256 put the codes from `at` up first and those below it last, the next one at the very end.
+template <int P>
+__device__ __forceinline__ void codes_around(const uint4 (&v)[P], int at, int& from, int& below) {
+  typedef unsigned short v2u __attribute__((ext_vector_type(2)));
+  const v2u origin = (v2u)(unsigned short)(at << 8);
+  v2u first = (v2u)(unsigned short)0xffff, last = (v2u)(unsigned short)0;
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const v2u two = __builtin_bit_cast(v2u, d == 0 ? v[p].x : d == 1 ? v[p].y : d == 2 ? v[p].z : v[p].w);
+      const v2u odd = two - origin, even = (v2u)(two << 8) - origin;
+      first = __builtin_elementwise_min(__builtin_elementwise_min(first, odd), even);
+      last = __builtin_elementwise_max(__builtin_elementwise_max(last, odd), even);
+    }
+  from = at + (min(first[0], first[1]) >> 8);
+  below = at + (max(last[0], last[1]) >> 8) - 256;
 }
 
 // GELU forward and backward (BWD: dx = g GELU'(x)) on strips: a table per block and wave, or, with waves of 16 rows, per block of a
@@ -100,17 +117,21 @@ __device__ __forceinline__ int extreme_code(const uint4 (&v)[P]) {
 //
 // Forward, a block's results are a function of the code alone, and so are their codes: the table is quantized, 256 entries for the 1024 elements
 // of a block, and an element is one byte looked up.  That takes the block's max-abs before the first lookup.  GELU grows with x > 0, and -GELU(-a)
-// grows with a up to 0.75 and stays below 0.17.  So it is GELU of the largest code if that is more than 0.17, else the larger of it and of the
-// smallest code's, unless that lies below -0.7.  Such blocks, and those without an ordinary scale, take FP32 tables, and Eq. 1 for each element.
-// (Forward, us: 32768 x 4096 51.5 -> 43.0, 262144 x 3072 in turn with its backward 721 -> 697 for both, back to back 297 and 299; 8192 x 5120 from the last-level cache 18 -> 14.3, 8192 x 1280 5.9 -> 5.6,
-// 1024 x 1024 3.3 -> 3.15.  With the max-abs found by looking FP32 values up first the chain is longer: 8192 x 1280 13 % slower than without.)
+// grows with a up to 0.7518, where it is 0.17, and falls beyond.  So the max-abs is GELU of the largest code if that stands for 0.3 or more, else the
+// largest of it and of the two codes next to -0.7518 on either side.  (Between neighbouring codes GELU changes by 4e-5 of itself or more, there too,
+// and FP32 evaluates it to 1e-6, so that the order of the codes is that of the table's entries.)  Blocks without an ordinary scale, and those whose
+// results are next to none, where that is not so, take FP32 tables, and Eq. 1 for each element.
+// (Forward, us, FP32 tables -> quantized, ordinary activations: 32768 x 4096 from memory 51.5 -> 44, 8192 x 5120 from the last-level cache 18 -> 14.5,
+// 8192 x 1280 6.0 -> 5.75, 1024 x 1024 3.3 -> 3.15.  Where every block is below -0.3 so that the smaller codes decide: 32768 x 4096 50 -> 48, 8192 x 5120
+// 17.4 -> 17, 8192 x 1280 5.75 -> 6.6, 1024 x 1024 3.3 -> 3.4; in 1 % of the blocks 8192 x 1280 6.0 -> 6.0.  With the max-abs found by looking
+// FP32 values up first 8192 x 1280 took 13 % longer than without quantized tables.)
 template <bool BWD, int B, int WAVES, int RW, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restrict__ X, const float* __restrict__ SX, const int8_t* __restrict__ G,
                                                          const float* __restrict__ SG, int rows, int cols, int8_t* __restrict__ Y, float* __restrict__ SY) {
   constexpr int NBC = 128 / B;   // blocks of a strip
   constexpr int SHARED = RW < 32 ? Strip<B, WAVES, RW>::BT : 1;   // waves that share a strip's tables
   __shared__ __align__(1024) float s_tabs[WAVES / SHARED][NBC][256];
-  __shared__ float s_amax[WAVES][4], s_amin[WAVES][4];
+  __shared__ float s_amax[WAVES][4], s_amax32[WAVES][4];
   const Strip<B, WAVES, RW> t(rows, cols);
   constexpr int P = Strip<B, WAVES, RW>::PASSES, BT = Strip<B, WAVES, RW>::BT;
   if (BT == 1 && !t.inside) return;   // a whole wave; there is no workgroup barrier
@@ -147,25 +168,6 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
   bool quantized = false;
   if constexpr (!BWD) {
     // ---- the table quantized
-    // Maximum of `v` over a block; `all`: f(maximum) for every block of the wave or, where a strip has several, of the workgroup
-    const auto block_max = [&](float v, float (*exchange)[4], bool& all, auto f) __attribute__((always_inline)) {
-      v = wave_group_max<56 | (B / 16 - 1)>(v);
-      bool mine = f(v);
-      if constexpr (BT > 1) {
-        if ((t.lane & (56 | (B / 16 - 1))) == 0) exchange[t.wave][own_table] = v;
-        __syncthreads();
-        const int first = min(t.lane / NBC, WAVES / BT - 1) * BT;
-        float other = 0.0f;
-#pragma unroll
-        for (int k = 0; k < BT; ++k) {
-          v = fmaxf(v, exchange[t.wave / BT * BT + k][own_table]);
-          other = fmaxf(other, exchange[first + k][t.lane % NBC]);
-        }
-        mine = f(other);
-      }
-      all = !__any(!mine);
-      return v;
-    };
     const float sx = sx_row[min(own_table, nblk - 1)];
     const auto result_of = [&](int code) __attribute__((always_inline)) {   // |GELU| of a code's input
       float pos, neg;
@@ -173,17 +175,42 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
       gelu_table_entries<false>(a, pos, neg);
       return code > 0 ? pos : -neg;
     };
-    constexpr float kEnough = 0.1701f, kMonotone = 0.7f, kHuge = 3.0e38f;
-    const int most = extreme_code<true>(px);
-    // a lane's result beyond kHuge (or infinite, or none) has to stay in the block's maximum, where both tests refuse it
-    float amax = most > 0 && sx > 0.0f ? result_of(most) : 0.0f;
-    amax = block_max(amax < kHuge ? amax : __builtin_inff(), s_amax, quantized, [](float v) { return v >= kEnough && v < kHuge; });
-    if (__builtin_expect(!quantized, 0)) {
-      const int least = extreme_code<false>(px);
-      const float a = (float)(least < 0 ? -least : 0) * sx;
-      const float other = sx >= 0.0f && a <= kMonotone && least > -128 ? (least < 0 ? result_of(least) : 0.0f) : kHuge;
-      amax = block_max(fmaxf(other, amax), s_amin, quantized, [](float v) { return v < kHuge; });
+    constexpr float kEnough = 0.3f, kLowest = 0.7517915f, kHuge = 3.0e38f, kLeast = 0x1p-100f;
+    int code = max(largest_code(px), 0);   // whose result this lane brings
+    float amax = result_of(code);
+    bool ordinary = true;
+    if (__builtin_expect(__any(!((float)code * sx >= kEnough)), 0)) {
+      // Four lanes of a block at a time put their codes together, and each brings the result of one.
+      int from, below;
+      codes_around(px, -(int)__builtin_amdgcn_fmed3f(kLowest * __builtin_amdgcn_rcpf(sx), 0.0f, 127.0f), from, below);
+      const auto over4 = [](int v, auto op) __attribute__((always_inline)) {
+        return wave_group_reduce<9>(v, op, [](int x, auto bit) { return lane_xor_i32<decltype(bit)::value>(x); });
+      };
+      const auto larger = [](int a, int b) { return max(a, b); };
+      code = over4(code, larger);
+      from = over4(from, [](int a, int b) { return min(a, b); });
+      below = over4(below, larger);
+      const int turn = t.lane & 9;
+      if (turn == 1) code = min(from, 0);
+      if (turn == 8) code = below > -128 ? below : 0;   // (code -128 has entry 0)
+      ordinary = sx >= 0.0f && 128.0f * sx < kHuge;
+      amax = result_of(code);
     }
+    // a result beyond kHuge (or infinite, or none) has to stay in the block's maximum, which is refused then
+    amax = wave_group_max<56 | (B / 16 - 1)>(ordinary && amax < kHuge ? amax : kHuge);
+    float voted = amax;   // where a strip has several waves: a block of the workgroup for each lane, so that all of them come to the same
+    if constexpr (BT > 1) {
+      if ((t.lane & (56 | (B / 16 - 1))) == 0) s_amax[t.wave][own_table] = amax;
+      __syncthreads();
+      const int first = min(t.lane / NBC, WAVES / BT - 1) * BT;
+      voted = 0.0f;
+#pragma unroll
+      for (int k = 0; k < BT; ++k) {
+        amax = fmaxf(amax, s_amax[t.wave / BT * BT + k][own_table]);
+        voted = fmaxf(voted, s_amax[first + k][t.lane % NBC]);
+      }
+    }
+    quantized = !__any(!(voted == 0.0f || (voted >= kLeast && voted < kHuge)));
     if (__builtin_expect(quantized, 1)) {
       double inv;
       block_scale(amax, scale, inv);
@@ -255,7 +282,7 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
         results(p, y[p]);
         m = amax16(m, y[p]);
       }
-      strip_block_scale(m, t, s_amax, scale, inv);
+      strip_block_scale(m, t, s_amax32, scale, inv);
 #pragma unroll
       for (int p = 0; p < P; ++p) o[p] = quantize16(y[p], inv);
     } else {   // looked up twice: kept, the results would take the registers of a wave on every SIMD
@@ -266,7 +293,7 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
         m = amax16(m, y);
         __builtin_amdgcn_sched_barrier(0);
       }
-      strip_block_scale(m, t, s_amax, scale, inv);
+      strip_block_scale(m, t, s_amax32, scale, inv);
 #pragma unroll
       for (int p = 0; p < P; ++p) {
         results(p, y);

@@ -1,6 +1,6 @@
-"""GELU forward looks quantized codes up wherever a block's largest result follows from its largest or smallest code, and takes FP32 tables where one block of
-the strip (of the workgroup, where its waves share blocks) does not let it.  Blocks of every kind, beside ordinary ones and beside one that forces
-the general way: codes and scales have to be the same both ways, and within the bound of the oracle."""
+"""GELU forward looks quantized codes up: a block's largest result follows from its largest code, or from the two next to the lowest point of GELU.  It takes
+FP32 tables where one block of the strip (of the workgroup, where its waves share blocks) has no ordinary scale or results next to none.  Blocks of every kind,
+beside ordinary ones and beside one that forces the general way: codes and scales have to be the same both ways, and within the bound of the oracle."""
 import numpy as np
 import pytest
 
@@ -15,13 +15,18 @@ pytestmark = pytest.mark.gpu
 KINDS = {
     "both signs": (2.0 / 127, -127, 127),
     "positive decides just": (0.295 / 127, -127, 127),         # GELU(0.295) = 0.1817
-    "small": (0.25 / 127, -127, 127),                          # the smallest code is within the monotone part
+    "small": (0.25 / 127, -127, 127),                          # the smallest code decides
     "negative alone, small": (0.69 / 127, -127, -1),
-    "negative alone, large": (3.0 / 127, -127, -60),           # general
-    "small positive, large negative": (2.0 / 127, -127, 8),    # general
-    "far tail": (13.0 / 127, -127, -100),                      # general
-    "tiny": (1e-30, -127, 127),
-    "subnormal": (1e-42, -127, 127),
+    "negative alone": (1.6 / 127, -127, -1),                   # the lowest point is in the middle
+    "negative alone, large": (3.0 / 127, -127, -60),           # and here above the largest code
+    "negative alone, lowest point at the end": (0.7517915 / 127, -127, -100),
+    "negative alone, coarse": (2.5, -127, -1),
+    "minus one": (1e-3, -1, 0),
+    "small positive, large negative": (2.0 / 127, -127, 8),
+    "far tail": (13.0 / 127, -127, -100),
+    "beyond the tail": (0.16, -127, -80),                      # general: results from 1e-36 down to none
+    "tiny": (1e-29, -127, 127),
+    "subnormal": (1e-42, -127, 127),                           # general
     "zero scale": (0.0, -127, 127),
     "zero codes": (1.0, 0, 0),
     "one code": (0.01, 5, 5),
@@ -61,24 +66,48 @@ def test_blocks_of_every_kind(block, rows, cols):
     Y, SY = jf.jf_gelu_q(dev(X), dev(S), block)
     y, sy = host(Y), host(SY)
     oY, oSY, of = oracle.gelu_q(X, S, block)
-    ordinary = np.isin(which, [list(KINDS).index(k) for k in KINDS if k not in ("tiny", "subnormal", "huge", "far tail")])
+    ordinary = np.isin(which, [list(KINDS).index(k) for k in KINDS if k not in ("tiny", "subnormal", "huge", "far tail", "beyond the tail")])
     o = np.repeat(np.repeat(ordinary, block, 0), block, 1)
     np.testing.assert_allclose(sy[ordinary], oSY[ordinary], rtol=1e-5)
     d = np.abs(y.astype(int) - oY.astype(int))[o]
     assert d.max() <= 1 and np.count_nonzero(d) <= 1e-3 * d.size
-    # the same blocks with the general way forced in each strip by its first block (code -128 beside all negative ones)
+    _same_the_general_way(X, S, block, y, sy)
+
+
+def _same_the_general_way(X, S, block, y, sy):
+    """The same blocks beside one of a negative scale in each strip, which forces it the general way, have the results y and sy."""
     X2, S2 = X.copy(), S.copy()
-    first = np.zeros((rows, cols), bool)
-    for c in range(0, cols, 128 // block):
+    first = np.zeros(S.shape, bool)
+    for c in range(0, S.shape[1], 128 // block):
         first[:, c] = True
         X2[:, c * block:(c + 1) * block] = -100
-        X2[::block, c * block] = -128
-        S2[:, c] = 0.02
+        S2[:, c] = -0.02
     Y2, SY2 = jf.jf_gelu_q(dev(X2), dev(S2), block)
     keep = ~first
     k = np.repeat(np.repeat(keep, block, 0), block, 1)
     np.testing.assert_array_equal(host(SY2)[keep], sy[keep])
     np.testing.assert_array_equal(host(Y2)[k], y[k])
+
+
+@pytest.mark.parametrize("block,rows,cols", [(32, 96, 128), (64, 64, 34)])
+def test_blocks_without_a_large_code(block, rows, cols):
+    """The codes about the lowest point of GELU at -0.75 decide: of every scale and range of codes, with gaps, some also in the far tail."""
+    say(f"GELU negative blocks block={block} {rows}x{cols} blocks")
+    g = workloads.rng(9800 + block)
+    S = np.exp(g.uniform(np.log(1e-4), np.log(0.2), size=(rows, cols))).astype(np.float32)
+    lo = g.integers(-127, 1, size=S.shape)
+    hi = np.minimum(lo + g.integers(0, 128, size=S.shape), (0.28 / S).astype(int))
+    up = lambda a: np.repeat(np.repeat(a, block, 0), block, 1)
+    X = g.integers(up(lo), up(hi) + 1)
+    X = np.where((X % 16 < 12) | up(g.random(S.shape) < 0.5), X, up(lo)).astype(np.int8)
+    y, sy = (host(t) for t in jf.jf_gelu_q(dev(X), dev(S), block))
+    oY, oSY, _ = oracle.gelu_q(X, S, block)
+    # The oracle's 1 + erf(x / sqrt 2) is off by up to 2^-53 and an input reaches 25: 25 * 2^-54 / 127 = 1.1e-17 of a scale, 1e-6 of one of 1e-11.
+    near = oSY > 1e-11
+    np.testing.assert_allclose(sy[near], oSY[near], rtol=1e-5)
+    d = np.abs(y.astype(int) - oY.astype(int))[up(near)]
+    assert d.max() <= 1 and np.count_nonzero(d) <= 1e-3 * d.size
+    _same_the_general_way(X, S, block, y, sy)
 
 
 @pytest.mark.parametrize("block", [32, 64, 128])
