@@ -408,7 +408,8 @@ __device__ __forceinline__ uint32_t kept_codes(uint32_t codes, uint32_t nibble) 
 // only (127 is prime).  So one FP32 FMA with 127 / m rounds every other code; and at m / 2, where fl(m k) = 2 fl(m k / 2), it is beyond 63.5 or
 // not as the scale fl(amax / 127) lies below amax / 127 or above it: the factor is moved by 2^-20 of itself to that side (a scale that is
 // amax / 127 exactly makes a tie, which goes to 64).  The moved factor takes no other code past a tie: 127 * 2^-20 < 1 / 256.
-// That holds while k and amax are no subnormals and finite; a wave with other blocks takes the general rounding.
+// That holds while k and amax are no subnormals and finite; a wave with other blocks takes the general rounding, but for blocks of k = 0 (padding,
+// dead channels), whose codes are all 0.
 // (Vector instructions per element 8.9 -> 5.8.  8192 x 1280 from the last-level cache 5.0 -> 4.0 us, from memory 6.6 -> 6.25, at block 64 and 128 6.6 -> 6.3
 // and 7.0 -> 6.6; 16384 x 2560 19.3 -> 18.2; 262144 x 3072 307, as before: the memory.  Residual path of 8192 x 1280 46.8 -> 45.6.)
 template <int B, int WAVES, int RW, StorePolicy SP>
@@ -448,10 +449,10 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
   const float amax = fmaxf(fabsf(__builtin_fmaf(m + 128.0f, k, k128)), 0.0f);
   uint4 o[P];
   float scale;
-  if (__builtin_expect(!__any(!(k >= 0x1p-100f && k <= 0x1p100f)), 1)) {
+  if (__builtin_expect(!__any(!(k == 0.0f || (k >= 0x1p-100f && k <= 0x1p100f))), 1)) {
     scale = amax / 127.0f;
     const float over = __builtin_fmaf(scale, 127.0f, -amax);   // exact in sign: of scale - amax / 127
-    const float f = m > 0.0f ? 127.0f * __builtin_amdgcn_rcpf(m) * (over > 0.0f ? 1.0f - 0x1p-20f : 1.0f + 0x1p-20f) : 0.0f;
+    const float f = amax > 0.0f ? 127.0f * __builtin_amdgcn_rcpf(m) * (over > 0.0f ? 1.0f - 0x1p-20f : 1.0f + 0x1p-20f) : 0.0f;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       uint32_t r[16];
