@@ -193,6 +193,7 @@ __device__ __forceinline__ double read_lane_f64(double v, int lane) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+constexpr unsigned kLdsBytes = 160 * 1024;   // of a compute unit
 typedef __attribute__((address_space(3))) void* lds_ptr;
 // One direct-to-LDS load of 16 bytes per lane: lane l's bytes from ubase + voff go to LDS address lds + 16*l.
 // Written out because the compiler only selects the 64-bit per-lane address form for the builtin; the form with

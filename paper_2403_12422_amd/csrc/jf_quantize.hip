@@ -102,6 +102,8 @@ struct Row16<_Float16> {
   }
 };
 
+static constexpr int kTransposeBytes = 128 * 132;   // LDS of a transposed copy's tile
+
 // B = quantization block; a workgroup's tile is WR x WC waves of 32 rows and COLS columns each.
 template <typename T, int B, bool TRANSPOSED_COPY, int WR, int WC, int COLS, StorePolicy SP>
 __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restrict__ x, int64_t ldx, int rows, int cols,
@@ -111,7 +113,7 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
   static_assert(TR >= B || B == 32, "a block lies inside one workgroup's tile");
   static_assert(TC >= B && (!TRANSPOSED_COPY || (TR == 128 && COLS == 128 && WC == 1)), "whole blocks; the transposed copy goes by 128 x 128");
   __shared__ float s_amax[WR][TC / 32];                // [32-row strip][32-col group]
-  __shared__ __align__(16) uint8_t s_codes[TRANSPOSED_COPY ? 128 * 132 : 16];
+  __shared__ __align__(16) uint8_t s_codes[TRANSPOSED_COPY ? kTransposeBytes : 16];
   const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % WR, across = WC == 1 ? 0 : (threadIdx.x >> 6) / WR;
   const TileIndex wg = tile_of_workgroup((cols + TC - 1) / TC);
   const int r0 = __builtin_amdgcn_readfirstlane((wg.y * WR + wave) * 32);   // first row of this wave's strip
@@ -195,23 +197,38 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
 // 64 and 128 alike.  Strips of 32 columns gain in FP32 from the cache only (block 32, 64 and 32 columns: 48 tiles 3.1, 2.9, from memory 2.9, 3.2; the MLP
 // step 1056 x 800 -> 2080, 63 tiles for the activation, 51.5, 51.1), and in FP16 nowhere.  (Four block rows to a workgroup: FP16 8192 x 3840 20.4 for
 // 19.7, FP32 4096 x 3072 14.1 for 13.9.)
+//
+// Results that are streamed, 64 MB and more: eight waves on a compute unit (six of FP32, which have twice the bytes in flight), where their registers
+// would allow 20 to 32.  16 to 24 MB in flight are enough for the memory, and what is in flight beyond lies further apart in it.  FP16 takes two strips
+// across, so that a workgroup reads 512 bytes of a row, unless the strips are few and the last workgroup's second one is none.  As many as fit -> these, us:
+// FP16 1048576 x 768 440 -> 400, 262144 x 3072 443 -> 412, 32768 x 4096 74.5 -> 67, at block 128 1048576 x 768 447 -> 414; FP32 262144 x 3072 708 -> 660,
+// 1048576 x 768 722 -> 690, 32768 x 4096 120 -> 115, at block 64 262144 x 3072 713 -> 682; with the transposed copy FP32 262144 x 3072 896 -> 846, FP16 621 ->
+// 612, at block 64 and 128 622 -> 596.  (FP16 1048576 x 768 by one strip 416; 1048576 x 128 by two 83, by one 68.)
 template <typename T, int B>
 static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t* q, int64_t ldq, float* s, int8_t* qT,
                             int64_t ldqT, float* sT, hipStream_t st) {
-  // the kernel for tiles of WR x WC strips of COLS columns
-  const auto launch = [&](auto kernel, int WR, int WC, int COLS) {
+  // the kernel for tiles of WR x WC strips of COLS columns; `waves`: at most so many on a compute unit, kept to by the LDS that a workgroup asks for
+  const auto launch = [&](auto kernel, int WR, int WC, int COLS, int waves = 0) {
     const dim3 grid(tile_grid((cols + COLS * WC - 1) / (COLS * WC), (rows + 32 * WR - 1) / (32 * WR)));
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * WR * WC), 0, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
+    const unsigned own = 2048 + (qT ? kTransposeBytes : 0);   // the kernel's own, with a margin
+    const unsigned lds = waves ? kLdsBytes / (waves / (WR * WC)) - own : 0;
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * WR * WC), lds, st, x, ldx, rows, cols, q, ldq, s, qT, ldqT, sT);
   };
   constexpr int G = B / 32;
   const int64_t tiles = (int64_t)((cols + 127) / 128) * ((rows + 127) / 128);
   with_store_policy(rows, ldq, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
-    if (qT) return launch(quantize_kernel<T, B, true, 4, 1, 128, SP>, 4, 1, 128);
+    if (qT) return launch(quantize_kernel<T, B, true, 4, 1, 128, SP>, 4, 1, 128, SP == kStoreStream ? 8 : 0);
     if constexpr (SP == kStoreThrough) {
       if constexpr (B == 32 && sizeof(T) == 4)
         if (tiles <= 64) return launch(quantize_kernel<T, B, false, 1, 1, 32, SP>, 1, 1, 32);
       if (tiles <= 256) return launch(quantize_kernel<T, B, false, G, (B + 63) / 64, 64, SP>, G, (B + 63) / 64, 64);
+    }
+    if constexpr (SP == kStoreStream) {
+      const int strips = (cols + 127) / 128;
+      if constexpr (sizeof(T) == 2 && B <= 64)
+        if (strips % 2 == 0 || strips > 8) return launch(quantize_kernel<T, B, false, G, 2, 128, SP>, G, 2, 128, 8);
+      return launch(quantize_kernel<T, B, false, G, 1, 128, SP>, G, 1, 128, sizeof(T) == 4 && B <= 64 ? 6 : 8);
     }
     launch(quantize_kernel<T, B, false, G, 1, 128, SP>, G, 1, 128);
   });

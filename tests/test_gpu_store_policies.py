@@ -44,3 +44,25 @@ def test_large_results_equal_those_of_small_calls(block, N, C):
             assert torch.equal(got[1][brows], want[1]), name
             for a, b in zip(got[2:], want[2:]):   # row partials: block column by block column
                 assert torch.equal(a[:, rows], b), name
+
+
+# 5, 6 and 9 strips of 128 columns: FP16 by one, by two, and by two with none in the last place; rows that end amid a tile of 128
+@pytest.mark.parametrize("block", [32, 64, 128])
+@pytest.mark.parametrize("N,C", [(104960, 640), (87424, 768), (58368, 1152)])
+def test_streamed_quantizer(block, N, C):
+    if block == 32:
+        N += 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + C + block)
+    x32 = torch.randn((N, C), device="cuda", generator=g)
+    for x in (x32, x32.half()):
+        say(f"streamed quantizer {x.dtype} block={block} {N} x {C}")
+        q, s = jf.jf_quantize_block(x, block)
+        qt = jf.jf_quantize_block(x, block, transposed_copy=True)
+        assert torch.equal(qt[0], q) and torch.equal(qt[1], s)
+        assert torch.equal(qt[2], q.t()) and torch.equal(qt[3], s.t())
+        part = 12800
+        for first in range(0, N, part):
+            rows, brows = slice(first, min(first + part, N)), slice(first // block, min(first + part, N) // block)
+            want = jf.jf_quantize_block(x[rows], block)
+            assert torch.equal(q[rows], want[0]) and torch.equal(s[brows], want[1])
