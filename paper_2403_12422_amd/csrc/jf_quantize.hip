@@ -250,8 +250,9 @@ static void dispatch_quantize(int block, const T* x, int64_t ldx, int rows, int 
 // CHUNKS: two.  More of them have more requests in flight a lane, but their addresses, 36 instructions each, stand in front of them one after the other,
 // and waves of fewer come and go more evenly.  FP16 with one, two, three and four chunks, us: 8192 x 3840 18.9, 17.6, 18.0, 18.6, from the last-level
 // cache 13.2, 12.6, 12.9, 12.4; 8192 x 1280 8.0, 7.8, 8.3, 8.0; 8192 x 2048 11.1, 11.2, 11.4, 12.0; 1024 x 1024 2.4, 2.3, 2.4, 2.65; 65536 x 4096
-// 137, 128, 129, 130; FP32 with two and four 8192 x 1280 9.0 and 9.25, 65536 x 4096 206.8 and 207.8.  Four where two would make a grid of 2^32
-// threads, which cannot be launched.
+// 137, 128, 129, 130; FP32 with two and four 8192 x 1280 11.2 and 12.1, 65536 x 4096 205.5 and 206.5.  Four for FP32 from 335 M elements on, where
+// it is the other way round: 131072 x 3072 311 and 308, 262144 x 3072 631 and 614, 524288 x 3072 1275 and 1239 (FP16 384 and 393, 773 and 800); and
+// where two would make a grid of 2^32 threads, which cannot be launched.
 template <typename T, StorePolicy SP, int CHUNKS>
 __global__ void __launch_bounds__(256) dequantize_kernel(const int8_t* __restrict__ q, const float* __restrict__ s, int rows,
                                                           int cols, int block_log2, T* __restrict__ out, int64_t ldo) {
@@ -311,8 +312,9 @@ extern "C" int32_t jf_dequantize_block(const int8_t* q, const float* s, int64_t 
     const auto launch_as = [&](auto* to) {
       typedef std::remove_pointer_t<decltype(to)> T;
       constexpr int64_t VEC = 16 / sizeof(T);
-      if (rows * cols < (int64_t(1) << 32) * 2 * VEC - 4096) launch(dequantize_kernel<T, SP, 2>, to, 2);
-      else launch(dequantize_kernel<T, SP, 4>, to, 4);
+      if constexpr (SP != kStoreThrough)
+        if (rows * cols >= (sizeof(T) == 4 ? int64_t(320) << 20 : (int64_t(1) << 32) * 2 * VEC - 4096)) return launch(dequantize_kernel<T, SP, 4>, to, 4);
+      launch(dequantize_kernel<T, SP, 2>, to, 2);
     };
     if (out_dtype == 0) launch_as(static_cast<float*>(out));
     else launch_as(static_cast<_Float16*>(out));

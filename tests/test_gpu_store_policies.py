@@ -66,3 +66,18 @@ def test_streamed_quantizer(block, N, C):
             rows, brows = slice(first, min(first + part, N)), slice(first // block, min(first + part, N) // block)
             want = jf.jf_quantize_block(x[rows], block)
             assert torch.equal(q[rows], want[0]) and torch.equal(s[brows], want[1])
+
+
+# FP32 from 335 M elements on, in whole lines and in rows that share them: another number of chunks a thread
+@pytest.mark.parametrize("block,N,C", [(32, 87392, 3840), (64, 419456, 800 + 32), (128, 65664, 5120)])
+def test_large_dequantizer(block, N, C):
+    say(f"large dequantizer block={block} {N} x {C}")
+    assert N * C >= 320 << 20
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + C)
+    X, SX = _tensor(g, N, C, block)
+    got = jf.jf_dequantize_block(X, SX, block, torch.float32)
+    part = N // 16 // 128 * 128
+    for first in range(0, N, part):
+        rows, brows = slice(first, min(first + part, N)), slice(first // block, min(first + part, N) // block)
+        assert torch.equal(got[rows], jf.jf_dequantize_block(X[rows], SX[brows], block, torch.float32))
