@@ -194,8 +194,8 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
 // (at block size 128 two, one block): half the serial chain of a wave, and more waves than the chip has SIMDs from 64 tiles on.  Beyond, the waves
 // fill it as they are, and half lines of codes cost more.  With 128 and 64 columns from memory, us: FP16 at block 32 48 tiles 3.5, 3.0, 128 tiles
 // 4.0, 3.3, 256 tiles 4.7, 4.7, 384 tiles 6.0, 6.2, 1920 tiles 19.7, 21.0; FP32 48 tiles 3.7, 2.9, 256 tiles 6.2, 6.1, 768 tiles 13.9, 14.0; block
-// 64 and 128 alike.  Strips of 32 columns gain in FP32 from the cache only (block 32, 64 and 32 columns: 48 tiles 3.1, 2.9, from memory 2.9, 3.2; the MLP
-// step 1056 x 800 -> 2080, 63 tiles for the activation, 51.5, 51.1), and in FP16 nowhere.  (Four block rows to a workgroup: FP16 8192 x 3840 20.4 for
+// 64 and 128 alike.  (Strips of 32 columns are slower at all sizes: FP32 at block 32 4 tiles 2.55 for 2.35, 48 tiles 3.25 for 2.95, from the cache 2.95
+// for 2.45.  Four block rows to a workgroup: FP16 8192 x 3840 20.4 for
 // 19.7, FP32 4096 x 3072 14.1 for 13.9.)
 //
 // Results that are streamed, 64 MB and more: eight waves on a compute unit (six of FP32, which have twice the bytes in flight), where their registers
@@ -220,8 +220,6 @@ static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t*
     constexpr StorePolicy SP = decltype(sp)::value;
     if (qT) return launch(quantize_kernel<T, B, true, 4, 1, 128, SP>, 4, 1, 128, SP == kStoreStream ? 8 : 0);
     if constexpr (SP == kStoreThrough) {
-      if constexpr (B == 32 && sizeof(T) == 4)
-        if (tiles <= 64) return launch(quantize_kernel<T, B, false, 1, 1, 32, SP>, 1, 1, 32);
       if (tiles <= 256) return launch(quantize_kernel<T, B, false, G, (B + 63) / 64, 64, SP>, G, (B + 63) / 64, 64);
     }
     if constexpr (SP == kStoreStream) {

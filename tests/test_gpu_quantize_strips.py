@@ -1,4 +1,4 @@
-"""The quantizer on strips of 32, 64 and 128 columns: sizes on both sides of the lines between them, with ragged last tiles, against
+"""The quantizer on strips of 64 and 128 columns: sizes on both sides of the line between them, with ragged last tiles, against
 the oracle (codes and scales are exact)."""
 import numpy as np
 import pytest
