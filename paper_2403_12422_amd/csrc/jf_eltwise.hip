@@ -217,8 +217,8 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
       int8_t* const codes = reinterpret_cast<int8_t*>(s_tabs[t.wave / SHARED]);   // 256 of each block
 #pragma unroll
       for (int u = 0; u < HALVES; ++u) {
+        static_assert(BWD || 2 * NBC % SHARED == 0, "a wave has whole half tables to do");
         const int h = half_of(u), i = code_of(h);
-        if (h >= 2 * NBC) break;
         const double k = read_lane_f64(inv, h / 2 * (B / 16));
         codes[h / 2 * 256 + table_pos(i)] = (int8_t)code_bits(entry[u].pos, k);
         codes[h / 2 * 256 + table_neg(i)] = (int8_t)code_bits(entry[u].neg, k);
@@ -481,29 +481,29 @@ __global__ void __launch_bounds__(64 * WAVES) dropout_kernel(const int8_t* __res
 // Whether an operator takes waves of 16 rows (for results that are written through).  Small tensors give a SIMD a wave or two, and a wave of
 // 16 rows has half the serial chain.  From a few million elements on it matters how the waves come out on 1024 SIMDs: 32-row waves fill
 // rounds of 4 M elements, half waves round a rest less up, and cost twice the scales, reductions and exchanges.  The lines lie where the
-// gain over sizes and widths ends, alone and in the paths of a training step (profiles/strip_heights.txt).  32 -> 16 rows in us:
-//   GELU forward, from memory and from the last-level cache: block 32 1 M elements 3.7 -> 3.15 and 3.7 -> 3.15, 6 M 5.25 -> 4.85 and 4.7 -> 4.5, 10 M 6.35 -> 6.1
-//     and 5.65 -> 5.55, 12 M 7.5 -> 7.2 and 5.9 -> 6.05 (MLP step 4096 x 768 -> 3072 0.3 less), 16 M 8.25 -> 8.5 and 6.85 -> 7.25, 40 M 19.7 -> 19.5 and 14.3 -> 15.9; block 64 1 M 3.45 -> 3.0, 10 M 6.1 -> 5.55
-//     and 5.0 -> 4.75, 12 M 7.15 -> 7.55 and 5.15 -> 5.2, 16 M 8.0 -> 9.4 and 5.85 -> 6.1; block 128 10 M 5.7 -> 5.55 and 4.85 -> 5.2 (eight waves to a table);
-//     rows that share lines, which from memory cost the waves of 32 rows more: 11264 x 1504 12.45 -> 11.75 and 7.9 -> 8.25, 9024 x 3104 17.7 -> 17.2, 16000 x 2080 19.65 ->
-//     18.95, 36992 x 864 18.8 -> 18.6 and 13.0 -> 14.8, at block 64 30016 x 1088 16.8 -> 16.1
-//   GELU backward, alone: block 128 1 M 4.8 -> 4.2, 12 M 10.5 -> 10.1; at block 32 and 64, one after the other with a forward that took waves as low: block 32
-//     4 M elements 10.8 -> 9.5, 13 M 16.3 -> 14.8, 17 M 19.1 -> 18.2, 20 M 21.5 -> 22.0; block 64 17 M 18.4 -> 17.0, 36 M 35.8 -> 34.7
+// gain ends in the paths of a training step, or before, where an operator alone on operands from memory begins to lose; all figures are in
+// profiles/strip_heights.txt.  32 -> 16 rows in us, alone from memory | from the last-level cache | in its path:
+//   GELU forward, block 32   1 M elements 3.7 -> 3.1 | 3.7 -> 3.1   14 M 8.35 -> 8.0 | 6.7 -> 6.85 | 132.8 -> 131.7   15 M 8.75 -> 9.75 | 6.8 -> 7.45 | 137.1 -> 136.0
+//     block 64   11 M 6.3 -> 5.9 | 5.1 -> 5.1 | 102.6 -> 100.2   12 M 7.2 -> 8.0 | 5.25 -> 5.2 | 104.4 -> 102.4      block 128: eight waves to a table, nowhere
+//     rows that share lines   27 M 17.3 -> 16.9 | 10.8 -> 12.1 | 250.7 -> 249.0   31 M 18.4 -> 19.1 | 13.15 -> 13.95 | 226.9 -> 225.6
+//   GELU backward, block 32   13 M 11.55 -> 11.0 | 8.15 -> 7.95 | 131.5 -> 129.8   14 M 11.9 -> 11.1 | 8.3 -> 8.1 | 135.0 -> 135.1   16 M 12.8 -> 12.7 | 8.45 -> 9.05 |
+//     140.2 -> 141.2; rows that share lines 17 M 16.85 -> 16.45 | 11.65 -> 13.0 | 166.5 -> 166.3   block 64   11 M 9.6 -> 9.5 | 6.85 -> 6.45 | 102.2 -> 100.3   12 M
+//     9.85 -> 11.1 | 7.0 -> 6.5 | 103.4 -> 104.6
 //   Add, alone 1 M 3.8 -> 3.3, block 64 and 128 3.9 -> 3.2 and 4.1 -> 3.6; in the residual path at block 32 10 M 53.7 -> 53.8, 12 M 63.8 -> 63.4, 16 M
 //     76.5 -> 75.7, 20 M 86.7 -> 86.0, by up to 2 % the one or the other way from width to width; block 128 16 M 83.8 -> 82.7
-//   Dropout, alone 1 M 3.5 -> 3.1, 4 M 4.1 -> 4.4; in the residual path 8 M 48.4 -> 49.0, 12 M 63.4 -> 63.4, 20 M 86.0 -> 86.5
+//   Dropout, block 32   1 M 2.7 -> 2.65 | 2.7 -> 2.5 | 23.9 -> 22.8   4 M 3.6 -> 3.7 | 3.05 -> 3.0 | 30.5 -> 30.0   8 M, path only, 38.3 -> 39.3
 static bool low_gelu(bool backward, int block, int64_t rows, int64_t cols) {
-  if (!backward) return block != 128 && (cols % 128 || rows * cols <= (block == 32 ? 13 : 11) << 20);
-  if (block == 128) return rows * cols <= 16 << 20;
-  return block == 64 || rows * cols <= 18 << 20;
+  const bool shared = cols % 128;   // rows that share lines
+  const int most = backward ? (block == 128 ? 16 : block == 64 ? (shared ? 12 : 11) : shared ? 18 : 13) : block == 64 ? 11 : 14;   // in 2^20 elements
+  return (!backward && shared) || rows * cols <= int64_t(most) << 20;
 }
 static bool low_add(int block, int64_t rows, int64_t cols) { return rows * cols <= (block == 128 ? 32 : block == 64 ? 12 : 11) << 20; }
-static bool low_dropout(int block, int64_t rows, int64_t cols) { return block <= 64 && rows * cols <= 2 << 20; }
+static bool low_dropout(int64_t rows, int64_t cols) { return rows * cols <= 4 << 20; }
 
 template <bool BWD>
 static void launch_gelu(int block, const int8_t* X, const float* SX, const int8_t* G, const float* SG, int rows, int cols, int8_t* Y, float* SY,
                         hipStream_t st) {
-  with_instance(block, rows, cols, low_gelu(BWD, block, rows, cols), [&](auto b, auto w, auto r, auto sp) {
+  with_instance<BWD>(block, rows, cols, low_gelu(BWD, block, rows, cols), [&](auto b, auto w, auto r, auto sp) {
     constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, RW = decltype(r)::value;
     constexpr StorePolicy SP = decltype(sp)::value;
     hipLaunchKernelGGL((gelu_kernel<BWD, B, WAVES, RW, SP>), (strip_grid<B, WAVES, RW>(rows, cols)), dim3(64 * WAVES), 0, st, X, SX, G, SG, rows, cols, Y, SY);
@@ -542,7 +542,7 @@ extern "C" int32_t jf_dropout_q(const int8_t* X, const float* SX, const uint8_t*
   if (reinterpret_cast<uintptr_t>(mask_bits) & 1u) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const float keep_scale = (float)(1.0 / (1.0 - (double)p));
-  with_instance(block, N, C, low_dropout(block, N, C), [&](auto b, auto w, auto r, auto sp) {
+  with_instance<false>(block, N, C, low_dropout(N, C), [&](auto b, auto w, auto r, auto sp) {
     constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, RW = decltype(r)::value;
     hipLaunchKernelGGL((dropout_kernel<B, WAVES, RW, decltype(sp)::value>), (strip_grid<B, WAVES, RW>(N, C)), dim3(64 * WAVES), 0, st, X, SX, mask_bits,
                        keep_scale, (int)N, (int)C, Y, SY);
@@ -559,7 +559,7 @@ extern "C" int32_t jf_add_q(const int8_t* X1, const float* S1, const int8_t* X2,
   if ((row_mean == nullptr) != (row_sumsq == nullptr)) return JF_ERR_NULL;
   if (!aligned16(X2) || !aligned4(S2) || (row_mean && (!aligned4(row_mean) || !aligned4(row_sumsq)))) return JF_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  with_instance(block, N, C, low_add(block, N, C), [&](auto b, auto w, auto r, auto sp) {
+  with_instance<true>(block, N, C, low_add(block, N, C), [&](auto b, auto w, auto r, auto sp) {
     constexpr int B = decltype(b)::value, WAVES = decltype(w)::value, RW = decltype(r)::value;
     constexpr StorePolicy SP = decltype(sp)::value;
     const auto launch = [&](auto kernel) {

@@ -127,14 +127,14 @@ static inline void with_block(int block, F&& f) {
 }
 
 // f(block size, waves per workgroup, rows of a wave, store policy) as integral constants: 16 rows instead of 32 if `low`, for results
-// that are written through
-template <class F>
+// that are written through; at block size 128 only for an operator that has such waves there (LOW128)
+template <bool LOW128, class F>
 static void with_instance(int block, int64_t rows, int64_t cols, bool low, F&& f) {
   with_block(block, [&](auto b) {
     with_store_policy(rows, cols, [&](auto sp) {
       constexpr int B = decltype(b)::value;
       constexpr StorePolicy SP = decltype(sp)::value;
-      if constexpr (SP == kStoreThrough)
+      if constexpr (SP == kStoreThrough && (B < 128 || LOW128))
         if (low) return f(b, std::integral_constant<int, B == 128 ? 8 : 4>(), std::integral_constant<int, 16>(), sp);
       f(b, std::integral_constant<int, strip_waves(B, SP)>(), std::integral_constant<int, 32>(), sp);
     });

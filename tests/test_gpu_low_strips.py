@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("block,N,C", [(32, 2176, 992), (32, 9856, 1280), (64, 2176, 1024), (64, 9856, 1280), (128, 13184, 1280), (128, 26368, 1280),
-                                       (32, 14720, 1280), (32, 14752, 1280), (64, 10944, 1152), (64, 40256, 832)])
+                                       (32, 14720, 1280), (32, 14752, 1280), (64, 10944, 1152), (64, 40256, 832),
+                                       (32, 3296, 1280), (32, 10656, 1280), (32, 11520, 1280), (64, 9088, 1280)])
 def test_behind_the_lines(block, N, C):
     policies.test_large_results_equal_those_of_small_calls(block, N, C)
 
