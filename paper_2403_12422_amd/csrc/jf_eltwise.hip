@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(64 * WAVES) add_kernel(const int8_t* __restric
 }
 
 // ------------------------------------------------------------------------------------------------
-// The codes of a packed dword whose keep bits, the low four of `bits`, are set; 0 for the others (bits above the four are ignored).  The
+// The codes of a packed dword whose keep bits are set, the four bits of `nibble`, which is less than 16; 0 for the others.  The
 // multiplication puts bit j at bit 8 j + 2 (and copies elsewhere), where it makes the byte selector j + 4, byte j of `codes`, instead of
 // j, a byte of zero.
 __device__ __forceinline__ uint32_t kept_codes(uint32_t codes, uint32_t nibble) {

@@ -1,13 +1,14 @@
 """Dropout rounds with one FP32 FMA: the code times 127 / max|code|, that factor moved to one side by 2^-20 of itself.  The rule against the exact
-quotient of the FP32 numbers, for every code and every maximum, at scales of all significands and of the binades at the rule's ends."""
+quotient of the FP32 numbers: for every code and every maximum at a sample of the scales, the binades at the rule's ends among them, and for the codes
+at and beside half an even maximum, the only tie there is, at every significand of the scale."""
 import numpy as np
 
 F32 = np.float32
 
 
-def _codes(k, m):
-    """k (n,) float32, m the largest |code|: codes by the rule and round-half-even of the exact quotient, both (n, 2 m + 1)."""
-    c = np.arange(-m, m + 1)
+def _codes(k, m, c=None):
+    """k (n,) float32, m the largest |code|: codes c, or all, by the rule and by round-half-even of the exact quotient."""
+    c = np.arange(-m, m + 1) if c is None else c
     amax = (F32(m) * k).astype(F32)
     s = amax / F32(127)
     over = np.sign(s.astype(np.float64) * 127 - amax)                                # exact: 24 bits times 7
@@ -27,7 +28,12 @@ def test_every_code_and_maximum():
         _codes(k.astype(F32), m)
 
 
-def test_every_significand_at_an_even_maximum():
-    k = np.arange(1 << 23, 1 << 24, 131).astype(F32)
-    for m in (2, 64, 126, 128):
-        _codes(k, m)
+def test_significands_at_every_even_maximum():
+    for m in range(2, 129, 2):
+        _codes(np.arange((1 << 23) + m, 1 << 24, 4099).astype(F32), m)
+
+
+def test_ties_at_every_significand():
+    for m in (2, 64, 126):
+        for first in range(1 << 23, 1 << 24, 1 << 20):
+            _codes(np.arange(first, first + (1 << 20)).astype(F32), m, np.arange(m // 2 - 1, m // 2 + 2))

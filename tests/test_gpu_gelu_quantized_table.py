@@ -57,7 +57,7 @@ def _tensor(g, block, rows, cols):
     return X, S, which
 
 
-# 32: strips of four blocks, ragged; small tensors are on waves of 16 rows, the widest on waves of 32
+# strips of four, two and one blocks, ragged; at block 32 and, but for the widest, at 64 on waves of 16 rows
 @pytest.mark.parametrize("block,rows,cols", [(32, 16, 13), (32, 3, 1), (32, 120, 97), (64, 9, 5), (64, 40, 72), (128, 5, 3), (128, 14, 9)])
 def test_blocks_of_every_kind(block, rows, cols):
     say(f"GELU tables block={block} {rows}x{cols} blocks")
@@ -72,6 +72,31 @@ def test_blocks_of_every_kind(block, rows, cols):
     d = np.abs(y.astype(int) - oY.astype(int))[o]
     assert d.max() <= 1 and np.count_nonzero(d) <= 1e-3 * d.size
     _same_the_general_way(X, S, block, y, sy)
+
+
+def _large(g, block, rows, cols):
+    """Such a tensor from copies of its first 37 rows of blocks."""
+    X, S, _ = _tensor(g, block, 37, cols)
+    return np.tile(X, (rows // 37 + 1, 1))[:rows * block], np.tile(S, (rows // 37 + 1, 1))[:rows]
+
+
+# Waves of 32 rows, results written through, streamed and written back.  At block 32 each wave has its tables to itself and decides by itself.
+LARGE = [(32, 480, 128), (32, 544, 128), (32, 352, 97), (64, 200, 64), (64, 272, 64), (64, 176, 49), (128, 120, 32), (128, 144, 32)]
+
+
+@pytest.mark.parametrize("block,rows,cols", LARGE)
+def test_large_tensors_of_every_kind(block, rows, cols):
+    """The results of calls on parts that are small enough for waves of 16 rows (at block 128: for results that are written through)."""
+    say(f"GELU tables, large, block={block} {rows}x{cols} blocks")
+    X, S = _large(workloads.rng(9850 + block + rows), block, rows, cols)
+    X, S = dev(X), dev(S)
+    y, sy = jf.jf_gelu_q(X, S, block)
+    part = 10_000_000 // (cols * block * block)
+    for first in range(0, rows, part):
+        r = slice(first, min(first + part, rows))
+        py, psy = jf.jf_gelu_q(X[r.start * block:r.stop * block].contiguous(), S[r].contiguous(), block)
+        np.testing.assert_array_equal(host(sy[r]), host(psy))
+        np.testing.assert_array_equal(host(y[r.start * block:r.stop * block]), host(py))
 
 
 def _same_the_general_way(X, S, block, y, sy):
@@ -110,13 +135,13 @@ def test_blocks_without_a_large_code(block, rows, cols):
     _same_the_general_way(X, S, block, y, sy)
 
 
-@pytest.mark.parametrize("block", [32, 64, 128])
+@pytest.mark.parametrize("block,rows,cols", [(32, 8, 8), (64, 8, 8), (128, 8, 8), (32, 480, 128), (32, 352, 97)])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, -0.5])
-def test_scales_that_are_none(block, bad):
+def test_scales_that_are_none(block, rows, cols, bad):
     """A block with such a scale leaves the others of its strip and workgroup what they are without it."""
-    say(f"GELU tables block={block} scale {bad}")
+    say(f"GELU tables block={block} {rows}x{cols} blocks, scale {bad}")
     g = workloads.rng(9750 + block)
-    X, S, _ = _tensor(g, block, 8, 8)
+    X, S = _large(g, block, rows, cols)
     y, sy = (host(t) for t in jf.jf_gelu_q(dev(X), dev(S), block))
     S2 = S.copy()
     S2[3, 2] = bad
