@@ -253,7 +253,7 @@ def microbench():
             "  that no MFMA writes; '1 mfma + 16 cvt + 16 fmac' / '+ 8 cvt + 8 fmac' / '+ 4 cvt + 4 fmac' are block size 32 / 64 / 128;",
             "  'MFMA rate' = 65536 ops x 1024 SIMDs / that time.  fold_chain_rate: the same mixes with the real data flow (the fold reads the",
             "  tile the previous MFMA chain wrote, tiles in VGPRs), with operands of a few small numbers and with random codes, which draw more",
-            "  power and so run at a lower clock.  kloop_overheads: the block-32 pattern of fold_chain_rate plus, one kind at a",
+            "  power and so run at a lower clock; 'by halves': all conversions of a fold, then all its FMAs, with priorities.  kloop_overheads: the block-32 pattern of fold_chain_rate plus, one kind at a",
             "  time, the other instructions of a K loop (variant 1: one ds_read_b128 per unit; 2: + stage barrier; 3: + direct-to-LDS",
             "  loads with 64-bit lane addresses; 4: + scalar scale loads and their product; 5: loads with scalar base + 32-bit lane offset,",
             "  the form the GEMM kernel uses; 6: 5 with a stage's eight fragment reads issued at once).  kloop_model: a whole K loop",
@@ -266,12 +266,12 @@ def microbench():
     write("microbench_machine_limits.txt", head + text)
     bare, codes = {}, {}
     for l in text:
-        m = re.match(r"block\s+(\d+) \(chain of \d\), tiles in VGPRs, (random codes, )?(\d) waves/SIMD:\s+[\d.]+ ns per MFMA ->\s+(\d+) TOP/s", l)
+        m = re.match(r"block\s+(\d+) \(chain of \d\), tiles in VGPRs, (random codes, )?(by halves, )?(\d) waves/SIMD:\s+[\d.]+ ns per MFMA ->\s+(\d+) TOP/s", l)
         if m:
             best = codes if m.group(2) else bare
-            best[m.group(1)] = max(best.get(m.group(1), 0.0), float(m.group(4)))
+            best[m.group(1)] = max(best.get(m.group(1), 0.0), float(m.group(5)))
     json.dump({"bare_fold_TOPS": bare, "random_codes_fold_TOPS": codes, "peak_TOPS": 5000.0,
-               "note": "best over 2-4 waves per SIMD; MFMA chain + fold with no memory traffic (fold_chain_rate): operands of a few small numbers, "
+               "note": "best over 2-4 waves per SIMD and both orders of the fold; MFMA chain + fold with no memory traffic (fold_chain_rate): operands of a few small numbers, "
                        "and random codes, under which the power limit lowers the clock",
                "source": "profiles/microbench_machine_limits.txt"}, open(os.path.join(OUT, "microbench_fold_ceilings.json"), "w"), indent=1)
     print("wrote profiles/microbench_fold_ceilings.json")
