@@ -266,10 +266,10 @@ __device__ __forceinline__ void gemm_wide(const KernelArgs args, const int wave,
       // 734 us forward / dgrad / wgrad, both gradients 1488 -> 1450; 4096^3 at B = 64 93.2 / 92.5 / 91.9 -> 92.8 / 91.4 / 89.7).
       // PHASES (B = 64, where the vector ALU bounds the loop): conversions issue at 4.3 cycles and FMAs at 2.3, and those of two waves run beside each
       // other.  Left alone both waves convert and then both add.  So all of a unit's conversions stand before its FMAs, and a wave in its FMAs and the
-      // next chain goes before one in its conversions: bare chains of 2 MFMAs with their folds, two waves, random codes 33.4 -> 31.0 ns
-      // per MFMA, small numbers 29.9 -> 23.9; 8192^3 683 / 670 / 665 -> 671 / 649 / 644 us, 4096^3 91.2 -> 90.0, both gradients 177.6 -> 172.5.
+      // next chain goes before one in its conversions: bare chains of 2 MFMAs with their folds, two waves, random codes 36.6 -> 29.5 ns
+      // per MFMA, small numbers 31.3 -> 25.0; 8192^3 683 / 670 / 665 -> 671 / 649 / 644 us, 4096^3 91.2 -> 90.0, both gradients 177.6 -> 172.5.
       // (At B = 128 the fold is too short for it: 16384 x 4096 -> 11008 1390 -> 1400.  At B = 32, four waves of two workgroups to a SIMD, bare chains
-      // gain 10 %, the kernels lose 1-2: there the power limit and the fragments' way into the registers bound the loop.)
+      // gain 10-20 %, the kernels lose 1-2: there the power limit and the fragments' way into the registers bound the loop.)
       constexpr int since = (i - SYNC + NT) % NT, LOW = since < NT / 2 ? 2 : 0;
       if constexpr (!PHASES && i % 2 == 0) __builtin_amdgcn_s_setprio(3 - since / 2);
       if constexpr (i == SYNC) {
