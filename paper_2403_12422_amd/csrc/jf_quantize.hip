@@ -204,6 +204,9 @@ __global__ void __launch_bounds__(64 * WR * WC) quantize_kernel(const T* __restr
 // FP16 1048576 x 768 440 -> 400, 262144 x 3072 443 -> 412, 32768 x 4096 74.5 -> 67, at block 128 1048576 x 768 447 -> 414; FP32 262144 x 3072 708 -> 660,
 // 1048576 x 768 722 -> 690, 32768 x 4096 120 -> 115, at block 64 262144 x 3072 713 -> 682; with the transposed copy FP32 262144 x 3072 896 -> 846, FP16 621 ->
 // 612, at block 64 and 128 622 -> 596.  (FP16 1048576 x 768 by one strip 416; 1048576 x 128 by two 83, by one 68.)
+// FP32 with the transposed copy, from 22 M elements on: twelve waves, sixteen where rows share lines.  Without a bound the loads without branches had cost
+// it 1 to 3 % from memory: 12288 x 4096 65.2 with them, 67.0, now 62.2 us; 4096 x 5632 29.4, 30.4, 29.2, from the last-level cache 22.8 each; 32768 x 1024 42.7, 43.5,
+// 41.4, from the cache 31.6 each; 16384 x 2080 50.5, 51.1, 50.2; smaller ones lose 1 to 3 % from the cache by it (20480 x 1024 20.6 -> 21.25).
 template <typename T, int B>
 static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t* q, int64_t ldq, float* s, int8_t* qT,
                             int64_t ldqT, float* sT, hipStream_t st) {
@@ -218,7 +221,10 @@ static void launch_quantize(const T* x, int64_t ldx, int rows, int cols, int8_t*
   const int64_t tiles = (int64_t)((cols + 127) / 128) * ((rows + 127) / 128);
   with_store_policy(rows, ldq, [&](auto sp) {
     constexpr StorePolicy SP = decltype(sp)::value;
-    if (qT) return launch(quantize_kernel<T, B, true, 4, 1, 128, SP>, 4, 1, 128, SP == kStoreStream ? 8 : 0);
+    if (qT) {
+      const int waves = SP == kStoreStream ? 8 : sizeof(T) == 2 || int64_t(rows) * cols < 21 << 20 ? 0 : SP == kStoreThrough ? 12 : 16;
+      return launch(quantize_kernel<T, B, true, 4, 1, 128, SP>, 4, 1, 128, waves);
+    }
     if constexpr (SP == kStoreThrough) {
       if (tiles <= 256) return launch(quantize_kernel<T, B, false, G, (B + 63) / 64, 64, SP>, G, (B + 63) / 64, 64);
     }

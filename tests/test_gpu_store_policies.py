@@ -68,6 +68,23 @@ def test_streamed_quantizer(block, N, C):
             assert torch.equal(q[rows], want[0]) and torch.equal(s[brows], want[1])
 
 
+# FP32 with the transposed copy from 22 M elements on, written through, written back, written through: fewer workgroups on a compute unit
+@pytest.mark.parametrize("block,N,C", [(32, 22112, 1024), (64, 16448, 2112), (128, 32896, 768)])
+def test_large_transposed_copy(block, N, C):
+    say(f"large transposed copy block={block} {N} x {C}")
+    assert N * C >= 21 << 20
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + C + block)
+    x = torch.randn((N, C), device="cuda", generator=g)
+    q, s, qT, sT = jf.jf_quantize_block(x, block, transposed_copy=True)
+    assert torch.equal(qT, q.t()) and torch.equal(sT, s.t())
+    part = 4096
+    for first in range(0, N, part):
+        rows, brows = slice(first, min(first + part, N)), slice(first // block, min(first + part, N) // block)
+        want = jf.jf_quantize_block(x[rows], block)
+        assert torch.equal(q[rows], want[0]) and torch.equal(s[brows], want[1])
+
+
 # FP32 from 335 M elements on, in whole lines and in rows that share them: another number of chunks a thread
 @pytest.mark.parametrize("block,N,C", [(32, 87392, 3840), (64, 419456, 800 + 32), (128, 65664, 5120)])
 def test_large_dequantizer(block, N, C):
