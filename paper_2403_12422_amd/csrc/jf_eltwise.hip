@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(64 * WAVES) gelu_kernel(const int8_t* __restri
       float pos, neg;
       const float a = fabsf((float)code) * sx;
       gelu_table_entries<false>(a, pos, neg);
-      return code > 0 ? pos : -neg;
+      return fabsf(code > 0 ? pos : neg);   // (no -0: a scale is 0 or more)
     };
     constexpr float kEnough = 0.3f, kLowest = 0.7517915f, kHuge = 3.0e38f, kLeast = 0x1p-100f;
     int code = max(largest_code(px), 0);   // whose result this lane brings

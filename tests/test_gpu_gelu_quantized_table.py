@@ -151,3 +151,19 @@ def test_scales_that_are_none(block, rows, cols, bad):
     k = np.repeat(np.repeat(keep, block, 0), block, 1)
     np.testing.assert_array_equal(sy2[keep], sy[keep])
     np.testing.assert_array_equal(y2[k], y[k])
+
+
+@pytest.mark.parametrize("block", [32, 64, 128])
+def test_scales_of_blocks_without_results(block):
+    """Codes or scales of 0, or inputs so far below 0 that GELU is 0: the scale is 0 and not -0, beside ordinary blocks and alone."""
+    say(f"GELU blocks without results, block={block}")
+    g = workloads.rng(9950 + block)
+    S = np.tile(np.array([0.02, 0.0, 1.0, 2.0], np.float32), (6, 2))
+    X = g.integers(-127, 128, size=(6 * block, 8 * block))
+    X[:, 2 * block:3 * block] = X[:, 6 * block:7 * block] = 0
+    X[:, 3 * block:4 * block] = X[:, 7 * block:] = -100
+    X[2 * block:], S[2:] = -100, 2.0
+    sy = host(jf.jf_gelu_q(dev(X.astype(np.int8)), dev(S), block)[1])
+    ordinary = np.zeros(S.shape, bool)
+    ordinary[:2, ::4] = True
+    assert (sy[ordinary] > 0).all() and not sy[~ordinary].any() and not np.signbit(sy).any()
